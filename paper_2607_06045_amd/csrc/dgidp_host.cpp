@@ -1,6 +1,7 @@
 // Host side of dgidp: context, quadtree mesh and connectivity, state transfer,
 // and the C-ABI entry points declared in include/dgidp.h.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -185,20 +186,29 @@ double host_pressure(const double* u, double g)
 
 int sync_stats(dgidp_ctx* ctx, dgidp_stats* s, int nstages)
 {
-    DevStats h;
-    HIPCHK(hipMemcpyAsync(&h, ctx->stats, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
+    std::array<DevStats, kStatSpread> h;
+    HIPCHK(hipMemcpyAsync(h.data(), ctx->stats, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
-    s->fv_inadmissible = (int64_t)h.fv_inadmissible;
-    s->violations = (int64_t)h.violations;
-    double tv, tm;
-    std::memcpy(&tv, &h.theta_vol_min_bits, 8);
-    std::memcpy(&tm, &h.theta_mort_min_bits, 8);
-    s->theta_vol_min = tv;
-    s->theta_mort_min = tm;
-    s->alpha_vol_mean = h.nfaces ? h.alpha_vol_sum / (double)h.nfaces : 0.0;
-    s->alpha_mort_mean = h.nmortars ? h.alpha_mort_sum / (double)h.nmortars : 0.0;
-    s->dt = h.dt;
-    (void)nstages;
+    *s = dgidp_stats();
+    s->theta_vol_min = s->theta_mort_min = 1.0;
+    double av = 0.0, am = 0.0;
+    for (const DevStats& d : h) {
+        s->fv_inadmissible += (int64_t)d.fv_inadmissible;
+        s->violations += (int64_t)d.violations;
+        double tv, tm;
+        std::memcpy(&tv, &d.theta_vol_min_bits, 8);
+        std::memcpy(&tm, &d.theta_mort_min_bits, 8);
+        s->theta_vol_min = std::min(s->theta_vol_min, tv);
+        s->theta_mort_min = std::min(s->theta_mort_min, tm);
+        av += d.alpha_vol_sum;
+        am += d.alpha_mort_sum;
+    }
+    // interior subcell faces (2 N (N+1) per element) and mortars of all stages
+    const double nf = (double)nstages * (double)ctx->E * 2.0 * ctx->p.N * (ctx->p.N + 1);
+    const double nm = (double)nstages * (double)ctx->M;
+    s->alpha_vol_mean = nf > 0.0 ? av / nf : 0.0;
+    s->alpha_mort_mean = nm > 0.0 ? am / nm : 0.0;
+    s->dt = h[0].dt;
     return 0;
 }
 
@@ -591,10 +601,10 @@ int dgidp_create(const dgidp_params* p, void* stream, dgidp_ctx** out)
     (void)noalloc_scratch_setup();
     if (hipMalloc((void**)&ctx->dt_dev, sizeof(double)) != hipSuccess ||
         hipMalloc((void**)&ctx->acc, 2 * kDtWords * sizeof(unsigned long long)) != hipSuccess ||
-        hipMalloc((void**)&ctx->stats, sizeof(DevStats)) != hipSuccess ||
+        hipMalloc((void**)&ctx->stats, kStatSpread * sizeof(DevStats)) != hipSuccess ||
         hipMalloc((void**)&ctx->bad, sizeof(unsigned long long)) != hipSuccess ||
         hipMemset(ctx->acc, 0, 2 * kDtWords * sizeof(unsigned long long)) != hipSuccess ||
-        hipMemset(ctx->stats, 0, sizeof(DevStats)) != hipSuccess) {
+        hipMemset(ctx->stats, 0, kStatSpread * sizeof(DevStats)) != hipSuccess) {
         dgidp_destroy(ctx);
         return DGIDP_E_DEVICE;
     }

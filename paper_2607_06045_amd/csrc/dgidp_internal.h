@@ -42,18 +42,19 @@ struct Tab {
     double Vinv[n][n];            // nodal -> modal, orthonormal Legendre: m_i = sum_a Vinv[i][a] q_a
 };
 
-// Device-side statistics accumulator.
-struct DevStats {
+// Device-side statistics accumulator.  A context holds kStatSpread of them, one
+// cache line each; block b adds to entry b % kStatSpread and the host merges
+// them (the dt of a step is stored in the first).
+struct alignas(128) DevStats {
     unsigned long long fv_inadmissible;
     unsigned long long violations;
     unsigned long long theta_vol_min_bits;   // min over positive doubles as bit patterns
     unsigned long long theta_mort_min_bits;
     double alpha_vol_sum;
     double alpha_mort_sum;
-    unsigned long long nfaces;
-    unsigned long long nmortars;
     double dt;
 };
+constexpr int kStatSpread = 64;
 
 struct DevMesh {
     int E = 0, M = 0;
