@@ -86,51 +86,36 @@ struct Geo {
     static constexpr int NF = 2 * N * n;           // interior subcell faces per element
     // LDS variable stride of the primitive array: unpadded.  At N = 3 padding
     // to an odd element stride cost blocks per compute unit, more than the
-    // bank conflicts it saved; at N = 4 a pad of one made no difference
-    // (288.7 against 289.8 us per stage on the 246,736-leaf workload).
+    // bank conflicts it saved; at N = 4 a pad of one made no difference.
     static constexpr int PR = NN;  // sR variable stride
     // x and y pairs in two passes where the x pairs fill whole thread rounds
-    // (N = 4); the pair buffer then needs the larger of the mortar staging
-    // (12 n) and half the pairs with the x lines' telescoped fluxes.  The
-    // low-order subcell fluxes go to the primitive rows once those are read,
-    // so the pair buffer no longer holds them.
+    // (N = 4): the pair buffer then holds half the pairs.  Between the passes
+    // the lanes that telescoped an x line keep its sums in registers; after the
+    // second pass both sums of line L go to its slots, y to 0 .. N-1 and x to
+    // N .. 2N-1.  In one pass (N = 3) every line's sums replace its first N
+    // slots, the y lines following the x lines.
     static constexpr bool SPLIT = (n * NPL) % NN == 0;
-    static constexpr int XH = n * NPL;  // SPLIT: the x lines' telescoped fluxes follow the pair slots
-    // (one pad slot at N = 4: an odd stride keeps the elements sharing a wave
-    // out of step with the 256-byte bank period)
-    static constexpr int PP = SPLIT ? (XH + n * N > 12 * n ? XH + n * N : 12 * n) + 1 : NP;  // sPair variable stride
-    // free pair slots after the telescoping (the slots N..NPL-1 of every line
-    // whose first N slots hold its telescoped fluxes) carry the surface terms
-    // of the face nodes: face f, position k in line f L + k / FR, slot N + k % FR
-    static constexpr int FR = NPL - N;
-    static constexpr int FL = (n + FR - 1) / FR;
-    static_assert(FR >= 1 && FL <= 2 && 4 * FL <= (SPLIT ? n : 2 * n), "surface-term slots");
-    static __device__ __forceinline__ int fslot(int f, int k)
+    static constexpr int PS = SPLIT ? n * NPL : NP;  // pair slots per variable
+    // sPair variable stride: the pair slots; the mortar variant stages the
+    // mortar traces there (12 n).  At N = 4 the conforming variant then takes
+    // 16,280 B per block, ten blocks and five waves per SIMD.
+    static constexpr int pp(bool mort) { return mort && 12 * n >= PS ? 12 * n + 1 : PS; }
+    static __device__ __forceinline__ int hx_slot(int b, int pos) { return b * NPL + (SPLIT ? N : 0) + pos; }
+    static __device__ __forceinline__ int hy_slot(int a, int pos) { return (SPLIT ? a : n + a) * NPL + pos; }
+    // free slots after the telescoping: the surface terms of the y faces at the
+    // element's corners c = a corner + 2 b corner
+    static __device__ __forceinline__ int corner_slot(int c)
     {
-        if constexpr (FL == 1) return f * NPL + N + k;
-        else return (f * 2 + (k >= FR ? 1 : 0)) * NPL + N + (k >= FR ? k - FR : k);
+        return SPLIT ? (c >> 1) * NPL + 2 * N + (c & 1) : c * NPL + N;
     }
+    static_assert(SPLIT ? NPL >= 2 * N + 2 : NPL > N, "corner slots");
 };
-
-// (l, k) of the node pairs l < k of a line, 6 bits per pair in line order
-template <int N>
-constexpr unsigned long long pair_code()
-{
-    unsigned long long c = 0;
-    int i = 0;
-    for (int l = 0; l <= N; ++l)
-        for (int k = l + 1; k <= N; ++k) {
-            c |= (unsigned long long)(l | (k << 3)) << (6 * i);
-            ++i;
-        }
-    return c;
-}
 
 // The node pairs of an element, N per thread: thread q evaluates the pairs
 // q + i NN (i < N) of the list "x lines, then y lines; in each line the pairs
 // (l, k), l < k, in order" (N NN pairs in all, 2 n n(n-1)/2).  Entry
-// ql | qk << 5 | d << 10 | l << 11 | k << 14: the two nodes (element-local
-// indices), the direction and their positions along the line.
+// ql | qk << 8 | (l n + k) << 16 | d << 24: the two nodes (element-local
+// indices), their entry of Sbar and the direction, a byte each.
 template <int N>
 struct PairMap {
     static constexpr int n = N + 1, NN = n * n, NPL = n * (n - 1) / 2;
@@ -149,10 +134,47 @@ struct PairMap {
                 const int k = l + 1 + r;
                 const int ql = d == 0 ? line * n + l : l * n + line;
                 const int qk = d == 0 ? line * n + k : k * n + line;
-                code[q][i] = (unsigned)(ql | qk << 5 | d << 10 | l << 11 | k << 14);
+                code[q][i] = (unsigned)(ql | qk << 8 | (l * n + k) << 16 | d << 24);
             }
     }
 };
+// The face node that the thread of node q = (a, b) evaluates: a node of an x
+// face its own x face, an inner node of a y face its own y face; the y faces at
+// the four corners go to the four interior nodes next to them.  So all but those
+// four hold a face's surface term on the thread that adds it.  Entry
+// f | k << 2 | qo << 5 | qn << 10 | own << 15 | corner << 16: the face, the
+// position along it, its node and the node across a conforming face; own: the
+// face's node is q; corner: the term goes to a corner node.  Neither is set for
+// the threads without a face (N = 4: the middle cross), which repeat another's.
+template <int N>
+struct FaceMap {
+    static constexpr int n = N + 1, NN = n * n;
+    unsigned int code[NN];
+    static constexpr int node(int f, int k)
+    {
+        return f < 2 ? k * n + (f & 1) * N : k + (f & 1) * N * n;
+    }
+    constexpr FaceMap() : code()
+    {
+        for (int q = 0; q < NN; ++q) {
+            const int a = q % n, b = q / n;
+            const bool xf = a == 0 || a == N, yf = b == 0 || b == N;
+            const bool corner = !xf && !yf && (a == 1 || a == N - 1) && (b == 1 || b == N - 1);
+            const int f = xf ? (a == N ? 1 : 0) : yf ? (b == N ? 3 : 2) : corner ? (b == N - 1 ? 3 : 2) : 0;
+            const int k = xf ? b : yf ? a : corner ? (a == N - 1 ? N : 0) : b;
+            code[q] = (unsigned)(f | k << 2 | node(f, k) << 5 | node(f ^ 1, k) << 10 | (xf || yf ? 1 : 0) << 15 |
+                                 (corner ? 1 : 0) << 16);
+        }
+    }
+};
+__constant__ FaceMap<3> c_fm3 = FaceMap<3>();
+__constant__ FaceMap<4> c_fm4 = FaceMap<4>();
+template <int N>
+__device__ __forceinline__ unsigned face_entry(int q);
+template <>
+__device__ __forceinline__ unsigned face_entry<3>(int q) { return c_fm3.code[q]; }
+template <>
+__device__ __forceinline__ unsigned face_entry<4>(int q) { return c_fm4.code[q]; }
 __constant__ PairMap<3> c_pm3 = PairMap<3>();
 __constant__ PairMap<4> c_pm4 = PairMap<4>();
 template <int N>
@@ -165,15 +187,14 @@ __device__ __forceinline__ unsigned pair_entry<4>(int q, int i) { return c_pm4.c
 // ---------------------------------------------------------------------------
 // arithmetic helpers
 // ---------------------------------------------------------------------------
-// 1/y from the hardware estimate and two Newton steps (about 1 ulp); used on
-// the paths every node takes, where y > 0
+// 1/y from the hardware estimate r (relative error e = 1 - y r of about 2^-23)
+// and the third-order step r (1 + e + e^2), whose own error is e^3 (about 1 ulp
+// after rounding); used on the paths every node takes, where y > 0
 __device__ __forceinline__ double frcp(double y)
 {
-    double r = __builtin_amdgcn_rcp(y);
-    double e = fma(-y, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-y, r, 1.0);
-    return fma(r, e, r);
+    const double r = __builtin_amdgcn_rcp(y);
+    const double e = fma(-y, r, 1.0);
+    return fma(r, fma(e, e, e), r);
 }
 
 // sqrt(y) for y >= 0 (normal or zero): the hardware reciprocal square root,
@@ -302,63 +323,81 @@ __device__ __forceinline__ void mortar_flux(int d, bool large_low, const NodeP& 
     llf_face(d, large_low, ui, us, F);
 }
 
-// logarithmic mean x^ln = (x - y) / (ln x - ln y) from the logarithms lx, ly.
-// Where |f| = |x - y| / (x + y) < 1e-2 (f^2 < 1e-4) the series
-// x^ln = (x + y)/2 f / atanh f = (x + y)/2 (1 - f^2/3 - 4 f^4/45 - 44 f^6/945 - ...)
-// (from the series of 2 atanh, as in Ismail & Roe 2009), whose next term is
-// below 4e-18 relative there.  Branch free: one reciprocal serves whichever
-// form applies.
-__device__ __forceinline__ double lnmean(double x, double y, double lx, double ly)
+// Half the logarithmic mean, x^ln / 2 with x^ln = (x - y) / (ln x - ln y), and
+// the inverse one, 1 / x^ln.  With s = x + y, d = x - y, f = d / s, where
+// |f| < 1e-2 (f^2 < 1e-4) the series
+//   x^ln / 2 = (s/4) f / atanh f = s (1/4 - (11/945) f^2 (945/132 + f^2 (21/11 + f^2)))
+//   1 / x^ln = (2 atanh f) / d   = (2 + (2/7) f^2 (7/3 + f^2 (7/5 + f^2))) / s
+// (from the series of 2 atanh, as in Ismail & Roe 2009; the next terms are below
+// 4e-18 relative there; monic, so that an instruction has one literal at most),
+// otherwise the quotient of the differences.  r is 1/s or, off the series, 1 / (lx - ly)
+// and 1/d.
+__device__ __forceinline__ bool lnmean_series(double s, double d) { return fabs(d) < 1e-2 * s; }
+__device__ __forceinline__ double half_lnmean_series(double s, double f)
 {
-    const double s = x + y, d = x - y;
-    const bool ser = fabs(d) < 1e-2 * s;
-    const double r = frcp(ser ? s : lx - ly);
-    const double f = d * r, f2 = f * f;
-    // 1/3 + f2 (4/45 + f2 44/945) = 44/945 (945/132 + f2 (21/11 + f2)): one
-    // literal per instruction
+    const double f2 = f * f;
     const double t = fma(f2, f2 + 21.0 / 11.0, 945.0 / 132.0) * f2;
-    const double sv = 0.5 * s * fma(-44.0 / 945.0, t, 1.0);
-    return ser ? sv : f;
+    return s * fma(-11.0 / 945.0, t, 0.25);
 }
-
-// 1 / x^ln = (ln x - ln y) / (x - y); series (2 + f^2 (2/3 + f^2 (2/5 + f^2 2/7))) / (x + y)
-__device__ __forceinline__ double inv_lnmean(double x, double y, double lx, double ly)
+__device__ __forceinline__ double inv_lnmean_series(double r, double f)
 {
-    const double s = x + y, d = x - y;
-    const bool ser = fabs(d) < 1e-2 * s;
-    const double r = frcp(ser ? s : d);
-    const double f = d * r, f2 = f * f;
-    // 2/3 + f2 (2/5 + f2 2/7) = 2/7 (7/3 + f2 (7/5 + f2))
+    const double f2 = f * f;
     const double t = fma(f2, f2 + 7.0 / 5.0, 7.0 / 3.0) * f2;
-    const double sv = fma(2.0 / 7.0, t, 2.0) * r;
-    return ser ? sv : (lx - ly) * r;
+    return fma(2.0 / 7.0, t, 2.0) * r;
+}
+// either form, branch free: one reciprocal serves whichever applies
+__device__ __forceinline__ double half_lnmean(double s, double d, double lx, double ly)
+{
+    const bool ser = lnmean_series(s, d);
+    const double f = d * frcp(ser ? s : lx - ly);
+    return ser ? half_lnmean_series(s, f) : 0.5 * f;
+}
+__device__ __forceinline__ double inv_lnmean(double s, double d, double lx, double ly)
+{
+    const bool ser = lnmean_series(s, d);
+    const double r = frcp(ser ? s : d);
+    return ser ? inv_lnmean_series(r, d * r) : (lx - ly) * r;
 }
 
-// Natural logarithm for x > 0 normal (NaN for x <= 0 or NaN): x = m 2^k with
-// m in [sqrt(1/2), sqrt(2)), f = m - 1 (exact), s = f / (2 + f), so that
-// ln m = 2 atanh s = 2 s + T, T = 2 s^3/3 + 2 s^5/5 + ... (|s| < 0.172, the
-// series to s^21 leaves less than 2^-56 of ln m), and 2 s = f - s f gives
-// ln m = f - s (f - T / s) with T / s a polynomial in s^2; ln x = k ln 2 +
-// ln m with ln 2 split into a head whose product with k is exact and a tail.
-// About 1 ulp, thirty instructions (the run-time library's logarithm takes
-// about eighty).
-__device__ __forceinline__ double flog(double x)
+// Natural logarithms of x and y, both normal (NaN for an argument <= 0 or NaN):
+// x = m 2^k with m in [sqrt(1/2), sqrt(2)), f = m - 1 (exact), s = f / (2 + f), so
+// that ln m = 2 atanh s = 2 s + T, T = 2 s^3/3 + 2 s^5/5 + ..., and 2 s = f - s f
+// gives ln m = f - s (f - T / s) with T / s = z (2/3 + 2 z/5 + ...) in z = s^2 < 0.0295
+// (here the polynomial of seven coefficients with the least largest error, 2^-59
+// of ln m); ln x = k ln 2 + ln m with ln 2 split into a head whose product
+// with k is exact and a tail.  About 1 ulp; the two share one reciprocal, of
+// (2 + f_x)(2 + f_y) between 2.9 and 5.9.
+struct LogParts {
+    double f, k;
+};
+__device__ __forceinline__ LogParts log_split(double x)
 {
-    double m = __builtin_amdgcn_frexp_mant(x);  // [0.5, 1)
-    int k = __builtin_amdgcn_frexp_exp(x);
-    if (m < 0x1.6a09e667f3bcdp-1) {
-        m *= 2.0;
-        k -= 1;
-    }
-    const double f = m - 1.0;
-    const double sf = f * frcp(2.0 + f);
+    const double m = __builtin_amdgcn_frexp_mant(x);  // [0.5, 1)
+    const int k = __builtin_amdgcn_frexp_exp(x);
+    const bool low = m < 0x1.6a09e667f3bcdp-1;
+    return LogParts{low ? fma(2.0, m, -1.0) : m - 1.0, (double)(low ? k - 1 : k)};
+}
+__device__ __forceinline__ double log_join(const LogParts& p, double r, double x)
+{
+    const double sf = p.f * r;
     const double z = sf * sf;
-    const double t = z * (2.0 / 3.0 + z * (2.0 / 5.0 + z * (2.0 / 7.0 + z * (2.0 / 9.0 + z * (2.0 / 11.0 +
-                     z * (2.0 / 13.0 + z * (2.0 / 15.0 + z * (2.0 / 17.0 + z * (2.0 / 19.0 + z * (2.0 / 21.0))))))))));
-    const double lm = f - sf * (f - t);
-    const double kd = (double)k;
-    const double r = fma(kd, 0x1.62e42fefp-1, fma(kd, 0x1.473de6af278edp-34, lm));
-    return x > 0.0 ? r : __builtin_nan("");
+    double t = fma(z, 0x1.2f056395f5a67p-3, 0x1.39a1bab2e7e3cp-3);
+    t = fma(z, t, 0x1.74663ee8bc916p-3);
+    t = fma(z, t, 0x1.c71c52095abb5p-3);
+    t = fma(z, t, 0x1.24924941f1295p-2);
+    t = fma(z, t, 0x1.999999997fdb7p-2);
+    t = fma(z, t, 0x1.5555555555592p-1);
+    const double lm = fma(-sf, fma(-z, t, p.f), p.f);
+    const double l = fma(p.k, 0x1.62e42fefp-1, fma(p.k, 0x1.473de6af278edp-34, lm));
+    return x > 0.0 ? l : __builtin_nan("");
+}
+__device__ __forceinline__ void flog2(double x, double y, double& lx, double& ly)
+{
+    const LogParts px = log_split(x), py = log_split(y);
+    const double dx = 2.0 + px.f, dy = 2.0 + py.f;
+    const double r = frcp(dx * dy);
+    lx = log_join(px, dy * r, x);
+    ly = log_join(py, dx * r, y);
 }
 
 __device__ __forceinline__ float lnmeanf(float x, float y, float lx, float ly)
@@ -581,9 +620,26 @@ __device__ __forceinline__ double volume_factor(const double* uFV, const double 
     if (P < 0.0) th = fmax(fmin((rt - uFV[0]) * frcp(P), 1.0), 0.0);
     if (LOCB && Pp > 0.0) th = fmin(th, fmax((rce * kMarginHi - uFV[0]) / Pp, 0.0));
     // pressure: each face's increment scaled by Gamma = 2d = 4 (a zero
-    // increment, as on a missing face, admits theta = 1 at an admissible uFV)
+    // increment, as on a missing face, admits theta = 1 at an admissible uFV).
+    // All four full steps are tested first, without a branch; only a wave with a
+    // node that fails one runs the roots
+    bool full = true;
+    {
+        const double e0 = uFV[3] - pt * ig1;
+        const double g0 = uFV[0] * e0 - 0.5 * (uFV[1] * uFV[1] + uFV[2] * uFV[2]);
+        full = g0 > 0.0 && uFV[0] > 0.0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) th = fmin(th, theta_p<4>(uFV, cf[j], pt, ig1));
+        for (int j = 0; j < 4; ++j) {
+            const double r1 = fma(4.0, cf[j][0], uFV[0]);
+            const double m1 = fma(4.0, cf[j][1], uFV[1]), m2 = fma(4.0, cf[j][2], uFV[2]);
+            const double g1v = fma(4.0, cf[j][3], e0) * r1 - 0.5 * (m1 * m1 + m2 * m2);
+            full = full && r1 > 0.0 && g1v >= 0.0;
+        }
+    }
+    if (!full) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) th = fmin(th, theta_p<4>(uFV, cf[j], pt, ig1));
+    }
     // specific entropy: per face on [0, th].  The target ln(s_min (1 + 2^-40))
     // is capped at lsi lowered by 2^-41: with bounds from the low-order solution
     // lsi is the node's own low-order log entropy (where the node itself is the
@@ -741,20 +797,6 @@ __device__ __forceinline__ void load_node(const double* u, int e, int q, NodeP& 
     make_node(s, g);
 }
 
-// pair (l, k), l < k, number i of a line
-template <int N>
-__device__ __forceinline__ void pair_lk(int i, int& l, int& k)
-{
-    constexpr int n = N + 1;
-    int r = i;
-    l = 0;
-    while (r >= n - 1 - l) {
-        r -= n - 1 - l;
-        ++l;
-    }
-    k = l + 1 + r;
-}
-
 // node qq of the block's element le from its LDS primitives; the conserved
 // state is formed again from them (rho v = rho * v, E = p / (gamma - 1) +
 // (rho v . v) / 2: within a few ulp of the stored state, the same for every
@@ -780,6 +822,14 @@ __device__ __forceinline__ void pair_lk(int i, int& l, int& k)
 // surface phase with Kopriva's mortar and the sparse low-order mortar flux,
 // mortar slot records); the batches without one run the MORT = false variant,
 // which has no mortar code, fewer registers and four waves per SIMD.
+// Bound: FP64 and other vector instructions and, nearly as busy, LDS accesses
+// (both about two thirds of the time; the HBM floor is a third).  So the
+// variants save instructions: the conforming launch of the 246,736-leaf N = 4
+// mesh runs 895 vector, 169 scalar and 106 LDS instructions per wave (1,119, 229
+// and 112 before) through the short form of smooth pairs, fluxes in their face's
+// frame with the weight folded into the wave speeds, one reciprocal for several
+// quotients, the faces' roles from a table, and lanes that repeat a node
+// instead of being switched off; its step went from 904 to 805 us.
 template <int N, int MODE, bool MIXED, int LIMK, bool MORT>
 // at least three waves per SIMD: the local-limiting variant would otherwise
 // take 172 registers and run two (63.3 against 67.7 us on the 22,156-leaf
@@ -795,24 +845,23 @@ void k_stage(StageArgs A)
     constexpr bool LOC = LIMK >= 1, COMB = LIMK == 2, BAR = LIMK == 1 || LIMK == 2;
     constexpr bool PURE = LIMK == 1 || LIMK == 3;
     constexpr int n = G::n, NN = G::NN, EPB = G::EPB, NT = G::NT, NFN = G::NFN;
-    constexpr int NPL = G::NPL, NP = G::NP, NF = G::NF, PPT = NP / NN, PP = G::PP;
+    constexpr int NPL = G::NPL, NP = G::NP, NF = G::NF, PPT = NP / NN, PP = G::pp(MORT);
     static_assert(NP % NN == 0, "pair split");
-    constexpr bool DSTAT = (n * NPL) % NN == 0, SPLIT = G::SPLIT;
-    constexpr int XH = n * NPL;  // SPLIT: the x lines' telescoped fluxes follow the pair slots
-    static_assert(!SPLIT || (DSTAT && XH + n * N <= G::PP), "two-pass pair buffer");
-    static_assert(G::PP >= 12 * n, "mortar buffers reuse the pair buffer");
+    constexpr bool SPLIT = G::SPLIT;
+    static_assert(!MORT || PP >= 12 * n, "mortar buffers reuse the pair buffer");
     static_assert(G::PR == NN && 4 * NF + NN <= 8 * NN, "subcell fluxes and node factors reuse sR");
     constexpr int MB = 4 * n;  // offset of the mortar-node fluxes in the pair buffer
 
     // variable-major (see Geo)
     __shared__ double sR[EPB][8][G::PR];     // rho, v1, v2, p, c, ln rho, z = rho/p, ln z
-    __shared__ double sPair[EPB][4][G::PP];  // pair fluxes, then telescoped fluxes and surface terms
+    __shared__ double sPair[EPB][4][PP];     // pair fluxes, then antidiffusive fluxes and corner terms
     // bar states of local limiting: rows 0-3 the subcell faces owned by a node
     // (x: density, log entropy; y: the same), rows 4-6 the face lanes' range
-    // across the element face; row 0 later the local node factors of the blend
+    // (face f, position k at f n + k) across the element face; row 0 later the
+    // local node factors of the blend
     __shared__ double sB[BAR ? EPB : 1][7][BAR ? NN : 1];
     __shared__ double sTw[2][n];              // LGL weights and their reciprocals, read per lane
-    __shared__ double sS[n][n];               // Sbar, read per pair
+    __shared__ double sS[n][n];               // Sbar / 2, read per pair
     // After phase 5b the primitive rows of sR are read no more: they take the
     // low-order subcell fluxes, variable-major over the NF faces (x faces
     // b N + a, y faces N n + a N + b), and after them the node factors.
@@ -821,36 +870,51 @@ void k_stage(StageArgs A)
 
     const Tab<N>& tb = T<N>();
     const double g = A.gamma, ig1 = A.ig1;
+    // every lane runs every phase: the lanes past the block's nodes repeat
+    // nodes of their own wave, those past the mesh's last element repeat it in
+    // LDS rows of their own; act masks what goes to memory
+    static_assert(NT <= G::BS && G::BS - NT <= NN && (G::BS - NT == 0 || NT - NN >= G::BS - 64),
+                  "the last lanes repeat nodes of their own wave");
     const int tid = threadIdx.x;
-    const int le = tid / NN, q = tid - le * NN, a = q % n, b = q / n;
+    const int tl = tid < NT ? tid : tid - NN;
+    const int le = tl / NN, q = tl - le * NN, a = q % n, b = q / n;
     const int xb = !MORT && A.rev ? xcd_batch_rev(blockIdx.x, gridDim.x) : xcd_batch(blockIdx.x, gridDim.x);
-    const int e = (A.blist ? A.blist[A.boff + xb] : xb) * EPB + le;
+    const int e0 = (A.blist ? A.blist[A.boff + xb] : xb) * EPB;
+    const bool act = tid < NT && e0 + le < A.E;
+    const int e = e0 + le < A.E ? e0 + le : A.E - 1;
     double* const sRe = &sR[0][0][0] + le * 8 * NN;  // element le's rows, flat
     double* const sPe = &sPair[0][0][0] + le * 4 * PP;  // element le's pair buffer, flat
-    const bool act = tid < NT && e < A.E;
+    const unsigned role = face_entry<N>(q);
+    // this thread's node pairs (the pair map)
+    unsigned pcode[PPT];
+#pragma unroll
+    for (int i = 0; i < PPT; ++i) pcode[i] = pair_entry<N>(q, i);
     if (tid < n) {
         sTw[0][tid] = tb.w[tid];
         sTw[1][tid] = tb.winv[tid];
     }
-    if (tid < NN) (&sS[0][0])[tid] = (&tb.S[0][0])[tid];
+    if (tid < NN) (&sS[0][0])[tid] = 0.5 * (&tb.S[0][0])[tid];
 
     // ---- phase 1: own node into LDS; face-node role and its remote loads ----
-    double hx = 1.0, hy = 1.0;
-    int fcode[4] = {-1, -1, -1, -1};
-    const bool fnode = act && q < NFN;       // this lane also evaluates one face node
-    const int ff = q / n, fk = q - (q / n) * n;  // its face and position
-    const int qfo = face_q<N>(ff, fk), qfn = face_q<N>(ff ^ 1, fk);  // the face node, its neighbour's
-    int fcode_f = -1, fnb = 0, fnb2 = -1, bk = 0;
-    double onb[4];  // conforming neighbour state (boundary: exterior state) across face ff at fk
+    // the face node this lane also evaluates: its face, position, node, the node across
+    const int ff = role & 3, fk = (role >> 2) & 7, qfo = (role >> 5) & 31, qfn = (role >> 10) & 31;
+    const bool fown = (role >> 15) & 1, fcor = (role >> 16) & 1;
+    const int dff = ff >> 1;
+    const bool lowf = ff & 1;                    // element on the low side of face ff
+    // issue the independent global loads first
+    const int fcode_f = A.fmort[e * 4 + ff];
+    const int fnb = A.fnbr[e * 4 + ff];
+    int fcode[4];  // the element's face codes (local bounds and mortar slots)
+    if (LOC || MORT)
+#pragma unroll
+        for (int f = 0; f < 4; ++f) fcode[f] = A.fmort[e * 4 + f];
+    const int fnb2 = MORT ? A.fnbr2[e * 4 + ff] : -1;
+    // conforming neighbour state (boundary: exterior state) across face ff at fk
+    // in the face's frame: density, normal and tangential momentum, energy
+    // (large side: the first small element's trace in the x, y frame)
+    double onb[4];
     double us1[4];  // large side: the second small element's trace at position fk
-    // u^n of this node for the SSP combination, loaded where it is needed (so
-    // that it occupies no registers through the flux phases), and this node's
-    // state (uin)
-    double un4[4] = {0, 0, 0, 0};
-    double u0[4] = {0, 0, 0, 0};
-    // the low-order surface term of this lane's face node, kept in registers
-    // until phase 5 frees pair slots, which then carry it to the node's own thread
-    double fterm[4] = {0, 0, 0, 0};
+    int bk = 0;
     // local bounds: own log entropy; for face lanes the density range and the
     // smallest log entropy of the bar states across this lane's face node
     double ls_own = 0.0;
@@ -859,22 +923,10 @@ void k_stage(StageArgs A)
     double fb_lo = __builtin_inf(), fb_hi = -__builtin_inf(), fb_ls = __builtin_inf();
     const double dtpart =
         A.dtmax ? __longlong_as_double((long long)A.dtmax[(tid & 63) * kDtStride]) : 0.0;
-    // this thread's node pairs (the pair map), loaded with the state
-    unsigned pcode[PPT];
-#pragma unroll
-    for (int i = 0; i < PPT; ++i) pcode[i] = act ? pair_entry<N>(q, i) : 0u;
-    if (act) {
-        // issue the independent global loads first
-#pragma unroll
-        for (int f = 0; f < 4; ++f) fcode[f] = A.fmort[e * 4 + f];
-        if (fnode) {
-            fnb = A.fnbr[e * 4 + ff];
-            fnb2 = A.fnbr2[e * 4 + ff];
-        }
+    double u0[4];  // this node's state
+    {
         NodeP me;
         load_node<N>(A.uin, e, q, me, g);
-        hx = A.h[2 * e];
-        hy = A.h[2 * e + 1];
         if (COMB) w_e = A.ind[e];
 #pragma unroll
         for (int v = 0; v < 4; ++v) u0[v] = me.u[v];
@@ -896,8 +948,7 @@ void k_stage(StageArgs A)
             sR[le][6][q] = pack2(lrf, (float)z);
             sR[le][7][q] = pack2(lzf, 0.0f);
         } else {
-            lr = flog(me.r);
-            lz = flog(z);
+            flog2(me.r, z, lr, lz);
             sR[le][5][q] = lr;
             sR[le][6][q] = z;
             sR[le][7][q] = lz;
@@ -908,34 +959,40 @@ void k_stage(StageArgs A)
                            fcode[3] >= 0);
         // ln(p rho^-gamma) of the node itself, the bar state (i, i)
         if (need_loc) ls_own = MIXED ? log(me.p) - g * log(me.r) : (1.0 - g) * lr - lz;
-        if (fnode) {
-            fcode_f = fcode[ff];
-            if (fcode_f == -1) {
-                load_u<N>(A.uin, fnb, qfn, onb);
-            } else if (fcode_f < -1) {
-                const int j = (-2 - fcode_f) * n + fk;
-                bk = A.bkind[j];
+    }
+    const double hx = A.h[2 * e], hy = A.h[2 * e + 1];
+    if (MORT && fcode_f >= 0) {
+        if (!fm_small(fcode_f)) {
+            // large side: both small traces at position fk, kept in
+            // registers for the mortar-node fluxes and staged for the
+            // sparse low-order pairs of the other positions
+            load_u<N>(A.uin, fnb, qfn, onb);
+            load_u<N>(A.uin, fnb2, qfn, us1);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) onb[v] = A.bext[(size_t)j * 4 + v];
-            } else if (MORT && !fm_small(fcode_f)) {
-                // large side: both small traces at position fk, kept in
-                // registers for the mortar-node fluxes and staged for the
-                // sparse low-order pairs of the other positions
-                load_u<N>(A.uin, fnb, qfn, onb);
-                load_u<N>(A.uin, fnb2, qfn, us1);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    sPair[le][v][MB + (ff * 2 + 0) * n + fk] = onb[v];
-                    sPair[le][v][MB + (ff * 2 + 1) * n + fk] = us1[v];
-                }
-            } else if (MORT) {
-                // small side: stage the large face trace for the interpolation
-                double w[4];
-                load_u<N>(A.uin, fnb, qfn, w);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) sPair[le][v][ff * n + fk] = w[v];
+            for (int v = 0; v < 4; ++v) {
+                sPair[le][v][MB + (ff * 2 + 0) * n + fk] = onb[v];
+                sPair[le][v][MB + (ff * 2 + 1) * n + fk] = us1[v];
             }
+        } else {
+            // small side: stage the large face trace for the interpolation
+            double w[4];
+            load_u<N>(A.uin, fnb, qfn, w);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) sPair[le][v][ff * n + fk] = w[v];
         }
+    } else if (fcode_f < -1) {
+        const int j = (-2 - fcode_f) * n + fk;
+        bk = A.bkind[j];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) onb[v] = A.bext[(size_t)j * 4 + v];
+    } else {
+        const double* p = A.uin + ((unsigned)fnb * 4u * NN + (unsigned)qfn);
+        const double* pn = p + (1 + dff) * NN;
+        const double* pt = p + (2 - dff) * NN;
+        onb[0] = p[0];
+        onb[1] = pn[0];
+        onb[2] = pt[0];
+        onb[3] = p[3 * NN];
     }
     __syncthreads();
     double dt;
@@ -950,32 +1007,61 @@ void k_stage(StageArgs A)
         dt = A.dt ? *A.dt : 0.0;
     }
 
-    // ---- phase 2: one surface flux per face node ----
-    const int dff = ff >> 1;
-    const bool lowf = ff & 1;                    // element on the low side of face ff
+    // ---- phase 2: one surface flux per face node: the low-order surface term ----
     const double sgf = lowf ? -1.0 : 1.0;
     const double hff = ff < 2 ? hy : hx;
-    if (fnode) {
-        NodeP own;  // the face node's state
-        LDS_NODE(own, qfo);
+    double fterm[4];
+    {
+        NodeP own;  // the face node's state (mortars; boundaries; bar states)
+        if (MORT || BAR) LDS_NODE(own, qfo);
         if (fcode_f < 0) {
-            NodeP o;
-            if (fcode_f == -1) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) o.u[v] = onb[v];
-            } else {
-                boundary_ghost(bk, onb, own, ff, g, o.u);
+            if (fcode_f < -1) {
+                NodeP me;
+                LDS_NODE(me, qfo);
+                double gu[4];
+                boundary_ghost(bk, onb, me, ff, g, gu);
+                onb[0] = gu[0];
+                onb[1] = dff == 0 ? gu[1] : gu[2];
+                onb[2] = dff == 0 ? gu[2] : gu[1];
+                onb[3] = gu[3];
             }
-            make_node(o, g);
+            // LLF in the face's frame, the face node from its LDS rows (the
+            // arithmetic of LDS_NODE).  With W = +-w h / 2 (minus on the low side),
+            // W F = W/2 (f_own + f_o) + |W|/2 lambda (u_o - u_own) on either side
+            const double r = sR[le][0][qfo], vn = sR[le][1 + dff][qfo], vt = sR[le][2 - dff][qfo];
+            const double p = sR[le][3][qfo], c = sR[le][4][qfo];
+            const double mn = r * vn, mt = r * vt, E = fma(p, ig1, 0.5 * fma(mn, vn, mt * vt));
+            const double ir = frcp(onb[0]);
+            const double on = onb[1] * ir, ot = onb[2] * ir;
+            const double op = (g - 1.0) * (onb[3] - 0.5 * fma(onb[1], on, onb[2] * ot));
+            const double oc = fsqrt(g * op * ir);
+            const double W = 0.25 * hff * sTw[0][fk];
+            const double K = W * fmax(fabs(vn) + c, fabs(on) + oc);
+            const double Ws = sgf * W, wa = Ws * vn, wb = Ws * on;
             double F[4];
-            llf_face(dff, lowf, own, o, F);
+            F[0] = fma(K, onb[0] - r, fma(onb[0], wb, r * wa));
+            F[1] = fma(K, onb[1] - mn, fma(onb[1], wb, mn * wa));
+            F[2] = fma(K, onb[2] - mt, fma(onb[2], wb, mt * wa));
+            F[3] = fma(K, onb[3] - E, fma(onb[3], wb, E * wa));
+            F[1] = fma(Ws, p + op, F[1]);
+            F[3] += fma(op, wb, p * wa);
             if (BAR && need_loc) {
+                NodeP o;
+                o.u[0] = o.r = onb[0];
+                o.u[1] = dff == 0 ? onb[1] : onb[2];
+                o.u[2] = dff == 0 ? onb[2] : onb[1];
+                o.u[3] = onb[3];
+                o.v1 = dff == 0 ? on : ot;
+                o.v2 = dff == 0 ? ot : on;
+                o.p = op;
+                o.c = oc;
                 bar_bounds(dff, lowf, own, o, g, fb_lo, fb_ls);
                 fb_hi = fb_lo;
             }
-            const double W = sgf * sTw[0][fk] * hff * 0.5;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) fterm[v] = W * F[v];
+            fterm[0] = F[0];
+            fterm[1] = dff == 0 ? F[1] : F[2];
+            fterm[2] = dff == 0 ? F[2] : F[1];
+            fterm[3] = F[3];
         } else if (MORT && !fm_small(fcode_f)) {
             // large side: mortar-node fluxes at position fk of both halves
             // (kept in registers until every lane has read the staged small
@@ -1085,7 +1171,7 @@ void k_stage(StageArgs A)
             }
 #pragma unroll
             for (int v = 0; v < 4; ++v) fterm[v] = lo[v];
-            {
+            if (act && (fown || fcor)) {
                 const int S = fm_mortar(fcode_f);
                 double* R = A.slot + (size_t)(S * 3 * n + n + fm_half(fcode_f) * n + fk) * kSlotW;
 #pragma unroll
@@ -1096,7 +1182,7 @@ void k_stage(StageArgs A)
     if constexpr (MORT) {  // (every batch of the mortar launch holds a mortar element)
         __syncthreads();
         // ---- phase 3: large sides publish and project the mortar fluxes ----
-        const bool large = fnode && fcode_f >= 0 && !fm_small(fcode_f);
+        const bool large = fcode_f >= 0 && !fm_small(fcode_f);
         if (large) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -1129,8 +1215,9 @@ void k_stage(StageArgs A)
                 ho[v] = sgf * sTw[0][fk] * hff * 0.5 * acc;
             }
             double* R = A.slot + (size_t)(S * 3 * n + fk) * kSlotW;
+            if (act && (fown || fcor))
 #pragma unroll
-            for (int v = 0; v < 4; ++v) R[4 + v] = ho[v] - fterm[v];
+                for (int v = 0; v < 4; ++v) R[4 + v] = ho[v] - fterm[v];
         }
         __syncthreads();
     }
@@ -1145,45 +1232,60 @@ void k_stage(StageArgs A)
     // are evaluated in two passes (SPLIT): the x lines are telescoped into the
     // slots after the x pairs, then the y pairs take the x pairs' slots, so the
     // pair buffer holds half the pairs at a time.
-    const double hhx = 0.5 * hy, hhy = 0.5 * hx;  // pair scale of x and y lines
+    // The pair values carry Sbar only, the density's half of it (the line's
+    // factor w h is applied to the telescoped sums, twice for the density).
+    // Where both logarithmic means of every lane's pair are on their series, as in
+    // smooth flow and in most waves beside a shock, the round takes the short form
+    // without the logarithms' rows and selects, and one reciprocal for both sums;
+    // the test costs a wave that is not six instructions.
     auto pair_rounds = [&](auto i0c, auto i1c, int slot_off) {
         constexpr int i0 = decltype(i0c)::value, i1 = decltype(i1c)::value;
-        if (!act) return;
 #pragma unroll
         for (int i = i0; i < i1; ++i) {
             const unsigned c = pcode[i];
-            const int ql = c & 31, qk = (c >> 5) & 31;
+            const int ql = c & 255, qk = (c >> 8) & 255;
             // a round wholly below or above the x pairs' n NPL slots has a constant
             // direction; only a round that straddles them (N = 3: the second) decodes it
-            const int d = (i + 1) * NN <= n * NPL ? 0 : (i * NN >= n * NPL ? 1 : (int)((c >> 10) & 1));
+            const int d = (i + 1) * NN <= n * NPL ? 0 : (i * NN >= n * NPL ? 1 : (int)(c >> 24));
             const int p = q + i * NN - slot_off;
             const int rn = 1 + d, rt = 2 - d;
-            const double scale = sS[(c >> 11) & 7][(c >> 14) & 7] * (d ? hhy : hhx);
+            const double hS = (&sS[0][0])[(c >> 16) & 255];  // Sbar / 2
             const double Ln = sR[le][rn][ql], Lt = sR[le][rt][ql];
             const double Rn = sR[le][rn][qk], Rt = sR[le][rt][qk];
-            double f0, fn, ft, f3;
             if (!MIXED) {
-                const double L0 = sR[le][0][ql], L3 = sR[le][3][ql];
-                const double L5 = sR[le][5][ql], L6 = sR[le][6][ql], L7 = sR[le][7][ql];
-                const double R0 = sR[le][0][qk], R3 = sR[le][3][qk];
-                const double R5 = sR[le][5][qk], R6 = sR[le][6][qk], R7 = sR[le][7][qk];
-                const double iz_ln = inv_lnmean(L6, R6, L7, R7);
-                const double vna = 0.5 * (Ln + Rn), vta = 0.5 * (Lt + Rt);
-                const double fr = lnmean(L0, R0, L5, R5) * vna;
-                f0 = fr;
+                const double L0 = sR[le][0][ql], L3 = sR[le][3][ql], L6 = sR[le][6][ql];
+                const double R0 = sR[le][0][qk], R3 = sR[le][3][qk], R6 = sR[le][6][qk];
+                const double s0 = L0 + R0, d0 = L0 - R0, s6 = L6 + R6, d6 = L6 - R6;
+                double hl, iz;  // rho^ln / 2 and 1 / z^ln
+                if (__all(lnmean_series(s0, d0) && lnmean_series(s6, d6))) {
+                    const double r = frcp(s0 * s6);
+                    const double r6 = s0 * r;
+                    hl = half_lnmean_series(s0, d0 * (s6 * r));
+                    iz = inv_lnmean_series(r6, d6 * r6);
+                } else {
+                    hl = half_lnmean(s0, d0, sR[le][5][ql], sR[le][5][qk]);
+                    iz = inv_lnmean(s6, d6, sR[le][7][ql], sR[le][7][qk]);
+                }
+                const double sn = Ln + Rn, st = Lt + Rt;
+                const double h = hS * (hl * sn);  // Sbar rho^ln {{vn}} / 2
+                const double ig2 = 2.0 * ig1;
                 if (A.vflux == DGIDP_FLUX_CHANDRASHEKAR) {
                     // Chandrashekar: beta = z / 2, so p~ = rho-bar / (2 beta-bar) =
                     // (rho_L + rho_R) / (z_L + z_R) and 1 / (2 beta^ln) = 1 / z^ln
-                    const double pt = (L0 + R0) * frcp(L6 + R6);
-                    fn = fr * vna + pt;
-                    ft = fr * vta;
-                    f3 = fr * (ig1 * iz_ln - 0.25 * (Ln * Ln + Lt * Lt + Rn * Rn + Rt * Rt)) + vna * fn + vta * ft;
+                    const double fn = fma(h, sn, 2.0 * hS * (s0 * frcp(s6))), ft = h * st;
+                    const double k2 = Ln * Ln + Lt * Lt + Rn * Rn + Rt * Rt;
+                    sPair[le][rn][p] = fn;
+                    sPair[le][rt][p] = ft;
+                    sPair[le][3][p] = fma(h, fma(ig2, iz, -0.5 * k2), 0.5 * fma(sn, fn, st * ft));
                 } else {
-                    fn = fr * vna + 0.5 * (L3 + R3);
-                    ft = fr * vta;
-                    f3 = fr * (0.5 * (Ln * Rn + Lt * Rt) + ig1 * iz_ln) + 0.5 * (L3 * Rn + R3 * Ln);
+                    const double kin = fma(Lt, Rt, Ln * Rn);
+                    sPair[le][rn][p] = fma(h, sn, hS * (L3 + R3));
+                    sPair[le][rt][p] = h * st;
+                    sPair[le][3][p] = fma(h, fma(ig2, iz, kin), hS * fma(R3, Ln, L3 * Rn));
                 }
+                sPair[le][0][p] = h;
             } else {
+                const double scale = 2.0 * hS;
                 const F2 L5 = unpack2(sR[le][5][ql]), L6 = unpack2(sR[le][6][ql]);
                 const F2 R5 = unpack2(sR[le][5][qk]), R6 = unpack2(sR[le][6][qk]);
                 const float L7 = unpack2(sR[le][7][ql]).x, R7 = unpack2(sR[le][7][qk]).x;
@@ -1192,32 +1294,30 @@ void k_stage(StageArgs A)
                 const float vnL = (float)Ln, vnR = (float)Rn, vtL = (float)Lt, vtR = (float)Rt;
                 const float vna = 0.5f * (vnL + vnR), vta = 0.5f * (vtL + vtR);
                 const float fr = lnmeanf(rL, rR, L6.x, R6.x) * vna;
-                f0 = fr;
+                float fn, ft, f3;
                 if (A.vflux == DGIDP_FLUX_CHANDRASHEKAR) {
                     const float pt = (rL + rR) / (zL + zR);
-                    const float fnf = fr * vna + pt, ftf = fr * vta;
-                    fn = fnf;
-                    ft = ftf;
+                    fn = fr * vna + pt;
+                    ft = fr * vta;
                     f3 = fr * ((float)ig1 * iz_ln - 0.25f * (vnL * vnL + vtL * vtL + vnR * vnR + vtR * vtR)) +
-                         vna * fnf + vta * ftf;
+                         vna * fn + vta * ft;
                 } else {
                     fn = fr * vna + 0.5f * (pL + pR);
                     ft = fr * vta;
                     f3 = fr * (0.5f * (vnL * vnR + vtL * vtR) + (float)ig1 * iz_ln) + 0.5f * (pL * vnR + pR * vnL);
                 }
+                sPair[le][0][p] = hS * fr;
+                sPair[le][rn][p] = scale * fn;
+                sPair[le][rt][p] = scale * ft;
+                sPair[le][3][p] = scale * f3;
             }
-            sPair[le][0][p] = scale * f0;
-            sPair[le][rn][p] = scale * fn;
-            sPair[le][rt][p] = scale * ft;
-            sPair[le][3][p] = scale * f3;
         }
     };
     // telescoped high-order subcell fluxes of one line and variable: the flux
     // through the subcell face after position pos is the sum of the line's pair
     // fluxes (l, k) with l <= pos < k; with the position a loop constant every
-    // pair index is static.  P: the line's pair slots; the N sums go to H.
-    auto telescope = [&](const double* P, double* H) {
-        double hof[N];
+    // pair index is static.  P: the line's pair slots.
+    auto telescope = [&](const double* P, double (&hof)[N]) {
 #pragma unroll
         for (int pos = 0; pos < N; ++pos) {
             double acc = 0.0;
@@ -1227,80 +1327,106 @@ void k_stage(StageArgs A)
                 for (int k = pos + 1; k < n; ++k) acc += P[l * (2 * n - l - 1) / 2 + (k - l - 1)];
             hof[pos] = acc;
         }
-#pragma unroll
-        for (int pos = 0; pos < N; ++pos) H[pos] = hof[pos];
     };
+    // ---- phase 4 and 5a: pair fluxes and telescoped high-order subcell fluxes,
+    // one telescoping task per line and variable (task t: line t / 4, variable t % 4) ----
     if constexpr (SPLIT) {
-        // ---- phase 4 and 5a in two passes: one task per line and variable ----
+        const bool tele = q < 4 * n;
+        double* const P = &sPair[le][q & 3][(q >> 2) * NPL];
+        double xs[N], ys[N];
         pair_rounds(std::integral_constant<int, 0>(), std::integral_constant<int, PPT / 2>(), 0);
         __syncthreads();
-        if (act && q < 4 * n) telescope(&sPair[le][q & 3][(q >> 2) * NPL], &sPair[le][q & 3][XH + (q >> 2) * N]);
+        if (tele) telescope(P, xs);
         __syncthreads();
         pair_rounds(std::integral_constant<int, PPT / 2>(), std::integral_constant<int, PPT>(), n * NPL);
         __syncthreads();
-        if (act && q < 4 * n) {
-            double* P = &sPair[le][q & 3][(q >> 2) * NPL];
-            telescope(P, P);
+        if (tele) {
+            telescope(P, ys);
+#pragma unroll
+            for (int pos = 0; pos < N; ++pos) {
+                P[pos] = ys[pos];
+                P[N + pos] = xs[pos];
+            }
         }
     } else {
         pair_rounds(std::integral_constant<int, 0>(), std::integral_constant<int, PPT>(), 0);
         __syncthreads();
-
-        // ---- phase 5a: telescoped high-order subcell fluxes ----
-        // One task per line and variable (x lines first, then y lines; 8n tasks,
-        // task t = q + j NN for j = 0, 1).  The N sums replace the line's first N
-        // pair slots of that variable, which no other task reads.
+        // the N sums replace the line's first N pair slots of that variable,
+        // which no other task reads (x lines first, then y lines; 8n tasks,
+        // task t = q + j NN for j = 0, 1)
         static_assert(8 * n <= 2 * NN, "two telescoping tasks per lane at most");
-        if (act) {
+        {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int t = q + j * NN;
                 if (t < 8 * n) {
-                    double* P = &sPair[le][t & 3][(t >> 2) * NPL];
-                    telescope(P, P);
+                    double* const P = &sPair[le][t & 3][(t >> 2) * NPL];
+                    double hof[N];
+                    telescope(P, hof);
+#pragma unroll
+                    for (int pos = 0; pos < N; ++pos) P[pos] = hof[pos];
                 }
             }
         }
     }
     // ---- phase 5b: low-order subcell fluxes of the faces owned by this node,
-    // x (a|a+1) and y (b|b+1) ----
+    // x (a|a+1) and y (b|b+1), times the line's weight: w_b h_y / 2 and w_a h_x / 2.
+    // With F = (f_L + f_R) / 2 - lambda (u_R - u_L) / 2 and f = u v_n + pressure terms,
+    // four instructions per variable; equal states still leave the dissipation
+    // exactly zero ----
+    // (a node on the upper element boundary owns no face in that direction: it
+    // takes itself as the neighbour with weight 0)
+    const double whx = a < N ? 0.5 * hy * sTw[0][b] : 0.0, why = b < N ? 0.5 * hx * sTw[0][a] : 0.0;
     double FVo[2][4];
     double brb[2] = {0.0, 0.0}, bls[2] = {0.0, 0.0};  // bar state of each owned subcell face
-    if (act) {
+    {
         NodeP me;
         LDS_NODE(me, q);
 #pragma unroll
         for (int d = 0; d < 2; ++d) {
-            const int pos = d == 0 ? a : b;
-            if (pos >= N) continue;
-            const int qn = d == 0 ? q + 1 : q + n;
+            const int qo = d == 0 ? (a < N ? q + 1 : q) : (b < N ? q + n : q);
             NodeP o;
-            LDS_NODE(o, qn);
-            double F[4];
-            llf_face(d, true, me, o, F);
-            if (BAR && need_loc) bar_bounds(d, true, me, o, g, brb[d], bls[d]);
-            const double hs = 0.5 * (d == 0 ? hy : hx);
+            LDS_NODE(o, qo);
+            const double hw = 0.5 * (d == 0 ? whx : why);
+            const double va = d == 0 ? me.v1 : me.v2, vb = d == 0 ? o.v1 : o.v2;
+            const double hl = hw * fmax(fabs(va) + me.c, fabs(vb) + o.c);
+            const double wa = hw * va, wb = hw * vb;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) FVo[d][v] = hs * F[v];
+            for (int v = 0; v < 4; ++v)
+                FVo[d][v] = fma(-hl, o.u[v] - me.u[v], fma(o.u[v], wb, me.u[v] * wa));
+            FVo[d][1 + d] = fma(hw, me.p + o.p, FVo[d][1 + d]);
+            FVo[d][3] += fma(o.p, wb, me.p * wa);
+            if (BAR && need_loc) bar_bounds(d, true, me, o, g, brb[d], bls[d]);
         }
     }
     // every read of the primitives (and of the pairs, by the telescoping) is done
     __syncthreads();
-    if (act) {
-        if (a < N) {
+    // the owner of a subcell face forms its antidiffusive flux w (f^HO - f^FV),
+    // keeps both fluxes (ADo, FVo) and leaves them for the face's other node:
+    // the low-order one in the freed primitive rows, the antidiffusive one in
+    // the slot of the telescoped flux
+    double ADo[2][4];
+    const int ax = a < N ? a : N - 1, by = b < N ? b : N - 1;  // (clamped; not stored there)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) sFV(v, b * N + a) = FVo[0][v];
-        }
-        if (b < N) {
+    for (int d = 0; d < 2; ++d) {
+        const int hs = d == 0 ? G::hx_slot(b, ax) : G::hy_slot(a, by);
+        const double wh = d == 0 ? whx : why;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) sFV(v, N * n + a * N + b) = FVo[1][v];
+        for (int v = 0; v < 4; ++v) ADo[d][v] = fma(v == 0 ? 2.0 * wh : wh, sPe[v * PP + hs], -FVo[d][v]);
+        if (d == 0 ? a < N : b < N) {
+            const int fi = d == 0 ? b * N + a : N * n + a * N + b;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                sPe[v * PP + hs] = ADo[d][v];
+                sFV(v, fi) = FVo[d][v];
+            }
         }
     }
-    // the face lanes' surface terms go to the free pair slots
-    if (fnode) {
-        const int fs = G::fslot(ff, fk);
+    // the y faces' surface terms at the element's corners
+    if (fcor) {
+        const int cs = G::corner_slot((fk ? 1 : 0) + (ff & 1 ? 2 : 0));
 #pragma unroll
-        for (int v = 0; v < 4; ++v) sPair[le][v][fs] = fterm[v];
+        for (int v = 0; v < 4; ++v) sPe[v * PP + cs] = fterm[v];
     }
     if (BAR && need_loc) {
         if (a < N) {
@@ -1311,58 +1437,43 @@ void k_stage(StageArgs A)
             sB[le][2][q] = brb[1];
             sB[le][3][q] = bls[1];
         }
-        if (fnode) {
-            sB[le][4][q] = fb_lo;
-            sB[le][5][q] = fb_hi;
-            sB[le][6][q] = fb_ls;
+        if (fown || fcor) {
+            sB[le][4][ff * n + fk] = fb_lo;
+            sB[le][5][ff * n + fk] = fb_hi;
+            sB[le][6][ff * n + fk] = fb_ls;
         }
     }
     __syncthreads();
 
     // ---- phase 6: low-order residual, bounds, node factors ----
-    if (act && MODE == MODE_STAGE && A.a != 0.0) load_u<N>(A.un, e, q, un4);
+    // u^n of this node for the SSP combination, loaded where it is needed (so
+    // that it occupies no registers through the flux phases)
+    double un4[4] = {0, 0, 0, 0};
+    if (MODE == MODE_STAGE && A.a != 0.0) load_u<N>(A.un, e, q, un4);
     const bool onf[4] = {a == 0, a == N, b == 0, b == N};
-    // the four subcell faces j of the node (left, right, below, above), each
-    // taken at a clamped in-range position of the node's own line; a missing
-    // face (on the element boundary) has weight 0.  Face index (x faces
-    // b N + pos, y faces N n + a N + pos), slot of the telescoped high-order
-    // flux (x faces on line b, y faces on line a) and signed weight (+w on the
-    // left / lower face, -w on the right / upper one), formed where used.
-    auto fpos = [&](int j) {
-        return j == 0 ? (a > 0 ? a - 1 : 0) : j == 1 ? (a < N ? a : N - 1) : j == 2 ? (b > 0 ? b - 1 : 0)
-                                                                             : (b < N ? b : N - 1);
-    };
-    auto fidx = [&](int j) { return j < 2 ? b * N + fpos(j) : N * n + a * N + fpos(j); };
-    auto hslot = [&](int j) {
-        if (SPLIT) return j < 2 ? XH + b * N + fpos(j) : a * NPL + fpos(j);
-        return j < 2 ? b * NPL + fpos(j) : (n + a) * NPL + fpos(j);
-    };
-    auto fweight = [&](int j) {
-        const double w = sTw[0][j < 2 ? b : a];
-        const bool has = j == 0 ? a > 0 : j == 1 ? a < N : j == 2 ? b > 0 : b < N;
-        return has ? ((j & 1) ? -w : w) : 0.0;
-    };
-    double RLO[4], dS0[4] = {0, 0, 0, 0}, dS1[4] = {0, 0, 0, 0};
+    // the subcell faces to the left of and below the node, read at a clamped
+    // in-range position of its own line; a missing face (on the element
+    // boundary) has weight 0
+    const double hasl = a > 0 ? 1.0 : 0.0, hasb = b > 0 ? 1.0 : 0.0;
+    const int al = a > 0 ? a - 1 : 0, bl = b > 0 ? b - 1 : 0;
+    double RLO[4], ADl[4], ADb[4], dS0[4] = {0, 0, 0, 0}, dS1[4] = {0, 0, 0, 0};
     int slot0 = -1, slot1 = -1, nmf = 0;
-    double im = 1.0;  // 1 / m_i
-    // antidiffusive flux w (f^HO - f^FV) of face j, signed as its weight, variable v
-    auto antidiff = [&](int j, int v) { return fweight(j) * (sPe[v * PP + hslot(j)] - sFV(v, fidx(j))); };
-    if (act) {
-        im = 4.0 * frcp(hx * hy) * sTw[1][a] * sTw[1][b];
-        const double cw[4] = {fweight(0), fweight(1), fweight(2), fweight(3)};
-        const int fi[4] = {fidx(0), fidx(1), fidx(2), fidx(3)};
-        // the surface terms of the element faces the node lies on: at most one
-        // x face (0 or 1) and one y face (2 or 3), weight 0 where it lies on none
-        const double csx = onf[0] || onf[1] ? 1.0 : 0.0, csy = onf[2] || onf[3] ? 1.0 : 0.0;
-        const int fsx = G::fslot(a == 0 ? 0 : 1, b), fsy = G::fslot(b == 0 ? 2 : 3, a);
+    const double im = 4.0 * frcp(hx * hy) * sTw[1][a] * sTw[1][b];  // 1 / m_i
+    {
+        const int fl = b * N + al, fb = N * n + a * N + bl;
+        const int hl = G::hx_slot(b, al), hb = G::hy_slot(a, bl);
+        // the node's surface terms: its own lane's, and at the corners the y
+        // face's from its slot
+        const double own = fown ? 1.0 : 0.0;
+        const double cor = (onf[0] || onf[1]) && (onf[2] || onf[3]) ? 1.0 : 0.0;
+        const int cs = G::corner_slot((2 * a > N ? 1 : 0) + (2 * b > N ? 2 : 0));
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            double r = 0.0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) r = fma(cw[j], sFV(v, fi[j]), r);
-            r = fma(csx, sPe[v * PP + fsx], r);
-            r = fma(csy, sPe[v * PP + fsy], r);
-            RLO[v] = r;
+            ADl[v] = sPe[v * PP + hl];
+            ADb[v] = sPe[v * PP + hb];
+            double r = fma(hasl, sFV(v, fl), -FVo[0][v]) + fma(hasb, sFV(v, fb), -FVo[1][v]);
+            r = fma(own, fterm[v], r);
+            RLO[v] = fma(cor, sPe[v * PP + cs], r);
         }
         if constexpr (MORT) {
             // a node lies on at most one x face (a = 0 or N) and one y face (b = 0 or
@@ -1392,7 +1503,7 @@ void k_stage(StageArgs A)
             for (int v = 0; v < 4; ++v) {
                 double r = RLO[v];
                 if (MODE == MODE_RHS_HIGH) {
-                    r += antidiff(0, v) + antidiff(1, v) + antidiff(2, v) + antidiff(3, v);
+                    r += fma(hasl, ADl[v], -ADo[0][v]) + fma(hasb, ADb[v], -ADo[1][v]);
                     r += dS0[v] + dS1[v];
                 }
                 A.uout[((unsigned)e * 4u + v) * NN + q] = r * im;
@@ -1409,11 +1520,11 @@ void k_stage(StageArgs A)
     double rlf = 0.0, rhi = 0.0, lsm = 0.0, thl = 1.0;
     double lsi = 0.0;  // local bounds: the node's own low-order log entropy (cap of the entropy target)
     unsigned long long inad = 0;
-    if (act) {
+    {
 #pragma unroll
         for (int v = 0; v < 4; ++v) uFV[v] = u0[v] + dtm * RLO[v];
         const double pFV = pressure(uFV, g);
-        if (!(uFV[0] > 0.0) || !(pFV > 0.0)) inad = 1;
+        if (act && (!(uFV[0] > 0.0) || !(pFV > 0.0))) inad = 1;
         rmin = A.beta * uFV[0];
         pmin = A.beta * pFV;
         if (need_loc && !BAR) {
@@ -1454,7 +1565,7 @@ void k_stage(StageArgs A)
                 rhi = fmax(rhi, sB[le][2][q]);
                 lsm = fmin(lsm, sB[le][3][q]);
             }
-            const int fnq[4] = {0 * n + b, 1 * n + b, 2 * n + a, 3 * n + a};  // face lane of each face
+            const int fnq[4] = {0 * n + b, 1 * n + b, 2 * n + a, 3 * n + a};
 #pragma unroll
             for (int f = 0; f < 4; ++f) {
                 if (!onf[f]) continue;
@@ -1465,12 +1576,15 @@ void k_stage(StageArgs A)
             // the positivity floor stays: the density floor is the larger one
             rlf = fmax(rmin, rlo);
         }
-        // the faces' increments dt / m_i w (f^HO - f^FV), signed (zero for missing faces)
+        // the faces' increments dt / m_i w (f^HO - f^FV) (left, right, below,
+        // above), signed (zero for missing faces)
+        const double dl = dtm * hasl, db = dtm * hasb;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const double wd = dtm * fweight(j);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) cf[j][v] = wd * (sPe[v * PP + hslot(j)] - sFV(v, fidx(j)));
+        for (int v = 0; v < 4; ++v) {
+            cf[0][v] = dl * ADl[v];
+            cf[1][v] = -dtm * ADo[0][v];
+            cf[2][v] = db * ADb[v];
+            cf[3][v] = -dtm * ADo[1][v];
         }
         if (A.limiter != DGIDP_LIMIT_NONE) {
             if (PURE) {
@@ -1484,10 +1598,8 @@ void k_stage(StageArgs A)
     // the blend keeps its local node factors in the first bar-state row, read
     // above for the bounds
     if (COMB) __syncthreads();
-    if (act) {
-        sTh(q) = th;
-        if (COMB) sB[le][0][q] = thl;
-    }
+    sTh(q) = th;
+    if (COMB) sB[le][0][q] = thl;
     __syncthreads();
 
     // ---- phase 7: limited volume update, SSP combination, mortar slots ----
