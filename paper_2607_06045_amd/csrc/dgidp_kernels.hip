@@ -6,7 +6,7 @@
 //             evaluates the surface fluxes with one lane per face node
 //             (conforming LLF, Kopriva's L2 mortar, the sparse IDP mortar flux
 //             of eq. interfaceflux_local), the Ranocha two-point fluxes once per
-//             node pair of every line, telescopes them into high-order subcell
+//             node pair of every line, sums them to high-order subcell
 //             fluxes (eq. fluxdifferencingform), evaluates the LLF subcell
 //             fluxes (eq. FVmethod), forms the low-order update and the
 //             positivity bounds (eq. Bounds_Positivity), limits the volume
@@ -81,63 +81,55 @@ struct Geo {
     static_assert(EPB == stage_block_elems(N), "host element order assumes this block size");
     static constexpr int NT = EPB * NN;            // active threads
     static constexpr int NFN = 4 * n;              // face nodes per element
-    static constexpr int NPL = n * (n - 1) / 2;    // node pairs per line
-    static constexpr int NP = 2 * n * NPL;         // node pairs per element
-    static constexpr int NF = 2 * N * n;           // interior subcell faces per element
-    // LDS variable stride of the primitive array: unpadded.  At N = 3 padding
-    // to an odd element stride cost blocks per compute unit, more than the
-    // bank conflicts it saved; at N = 4 a pad of one made no difference.
-    static constexpr int PR = NN;  // sR variable stride
-    // x and y pairs in two passes where the x pairs fill whole thread rounds
-    // (N = 4): the pair buffer then holds half the pairs.  Between the passes
-    // the lanes that telescoped an x line keep its sums in registers; after the
-    // second pass both sums of line L go to its slots, y to 0 .. N-1 and x to
-    // N .. 2N-1.  In one pass (N = 3) every line's sums replace its first N
-    // slots, the y lines following the x lines.
-    static constexpr bool SPLIT = (n * NPL) % NN == 0;
-    static constexpr int PS = SPLIT ? n * NPL : NP;  // pair slots per variable
-    // sPair variable stride: the pair slots; the mortar variant stages the
-    // mortar traces there (12 n).  At N = 4 the conforming variant then takes
-    // 16,280 B per block, ten blocks and five waves per SIMD.
-    static constexpr int pp(bool mort) { return mort && 12 * n >= PS ? 12 * n + 1 : PS; }
-    static __device__ __forceinline__ int hx_slot(int b, int pos) { return b * NPL + (SPLIT ? N : 0) + pos; }
-    static __device__ __forceinline__ int hy_slot(int a, int pos) { return (SPLIT ? a : n + a) * NPL + pos; }
-    // free slots after the telescoping: the surface terms of the y faces at the
-    // element's corners c = a corner + 2 b corner
-    static __device__ __forceinline__ int corner_slot(int c)
-    {
-        return SPLIT ? (c >> 1) * NPL + 2 * N + (c & 1) : c * NPL + N;
-    }
-    static_assert(SPLIT ? NPL >= 2 * N + 2 : NPL > N, "corner slots");
+    // LDS per element: 8 rows of primitives, one value per node, and per variable
+    // the pair buffer.  It takes the pair fluxes that other threads need (see
+    // the pair phase), then the antidiffusive fluxes of the x faces at the node
+    // on their left and of the y faces at the node below (rounds of NN); the
+    // mortar variant first stages the mortar traces there (12 n).  A LDS access
+    // serves 16 lanes a cycle where their doubles differ modulo 16, so the
+    // element strides are 9 modulo 16 at N = 4: consecutive threads, 25 to an
+    // element, then meet no conflict.
+    static constexpr int PV = N == 4 ? 2 * NN + 2 * n : 2 * NN;  // sPair variable stride
+    static constexpr int pp(bool mort) { return mort && 12 * n > PV ? 12 * n : PV; }
+    static constexpr int pad9(int x) { return N == 4 ? x + (25 - x % 16) % 16 : x; }
+    static constexpr int ES = pad9(8 * NN);                        // sR element stride
+    static constexpr int es(bool mort) { return pad9(4 * pp(mort)); }  // sPair element stride
 };
 
-// The node pairs of an element, N per thread: thread q evaluates the pairs
-// q + i NN (i < N) of the list "x lines, then y lines; in each line the pairs
-// (l, k), l < k, in order" (N NN pairs in all, 2 n n(n-1)/2).  Entry
-// ql | qk << 8 | (l n + k) << 16 | d << 24: the two nodes (element-local
-// indices), their entry of Sbar and the direction, a byte each.
+// The node pairs of an element, N per thread: each of thread (a, b)'s pairs holds
+// its own node, whose primitives it then reads once per pass.  At N = 4 the
+// partners are a + 1 and a + 2 (modulo n) on its x line, then the same on its y
+// line; at N = 3 a + 1, b + 1 and, in a last round, a + 2 where a / 2 + b / 2 is
+// even and b + 2 where it is odd.  Every pair of every line occurs once.  Entry,
+// 16 bits: the partner's node | (l n + k) << 5 | d << 10 | own << 11 with l < k
+// the positions along the line (the entry of Sbar), d the direction, own = 1
+// where this thread's node is k.
 template <int N>
 struct PairMap {
-    static constexpr int n = N + 1, NN = n * n, NPL = n * (n - 1) / 2;
-    unsigned int code[NN][N];
+    static constexpr int n = N + 1, NN = n * n;
+    unsigned int code[NN][(N + 1) / 2];
     constexpr PairMap() : code()
     {
         for (int q = 0; q < NN; ++q)
             for (int i = 0; i < N; ++i) {
-                const int p = q + i * NN;
-                const int d = p / (n * NPL), rem = p % (n * NPL), line = rem / NPL;
-                int l = 0, r = rem % NPL;
-                while (r >= n - 1 - l) {
-                    r -= n - 1 - l;
-                    ++l;
+                const int a = q % n, b = q / n;
+                int d = 0, step = 0;
+                if (N == 4) {
+                    d = i / 2;
+                    step = 1 + i % 2;
+                } else {
+                    d = i < 2 ? i : (a / 2 + b / 2) % 2;
+                    step = i < 2 ? 1 : 2;
                 }
-                const int k = l + 1 + r;
-                const int ql = d == 0 ? line * n + l : l * n + line;
-                const int qk = d == 0 ? line * n + k : k * n + line;
-                code[q][i] = (unsigned)(ql | qk << 8 | (l * n + k) << 16 | d << 24);
+                const int me = d == 0 ? a : b, other = (me + step) % n;
+                const int qo = d == 0 ? b * n + other : other * n + a;
+                const int l = me < other ? me : other, k = me < other ? other : me;
+                code[q][i / 2] |= (unsigned)(qo | (l * n + k) << 5 | d << 10 | (me == k ? 1 : 0) << 11)
+                                  << (16 * (i % 2));
             }
     }
 };
+
 // The face node that the thread of node q = (a, b) evaluates: a node of an x
 // face its own x face, an inner node of a y face its own y face; the y faces at
 // the four corners go to the four interior nodes next to them.  So all but those
@@ -178,7 +170,7 @@ __device__ __forceinline__ unsigned face_entry<4>(int q) { return c_fm4.code[q];
 __constant__ PairMap<3> c_pm3 = PairMap<3>();
 __constant__ PairMap<4> c_pm4 = PairMap<4>();
 template <int N>
-__device__ __forceinline__ unsigned pair_entry(int q, int i);
+__device__ __forceinline__ unsigned pair_entry(int q, int i);  // pairs 2 i and 2 i + 1
 template <>
 __device__ __forceinline__ unsigned pair_entry<3>(int q, int i) { return c_pm3.code[q][i]; }
 template <>
@@ -324,40 +316,50 @@ __device__ __forceinline__ void mortar_flux(int d, bool large_low, const NodeP& 
 }
 
 // Half the logarithmic mean, x^ln / 2 with x^ln = (x - y) / (ln x - ln y), and
-// the inverse one, 1 / x^ln.  With s = x + y, d = x - y, f = d / s, where
-// |f| < 1e-2 (f^2 < 1e-4) the series
-//   x^ln / 2 = (s/4) f / atanh f = s (1/4 - (11/945) f^2 (945/132 + f^2 (21/11 + f^2)))
-//   1 / x^ln = (2 atanh f) / d   = (2 + (2/7) f^2 (7/3 + f^2 (7/5 + f^2))) / s
-// (from the series of 2 atanh, as in Ismail & Roe 2009; the next terms are below
-// 4e-18 relative there; monic, so that an instruction has one literal at most),
-// otherwise the quotient of the differences.  r is 1/s or, off the series, 1 / (lx - ly)
-// and 1/d.
-__device__ __forceinline__ bool lnmean_series(double s, double d) { return fabs(d) < 1e-2 * s; }
-__device__ __forceinline__ double half_lnmean_series(double s, double f)
+// the inverse one, 1 / x^ln.  With s = x + y, d = x - y, f = d / s, z = f^2
+//   x^ln / 2 = (s/4) f / atanh f,   1 / x^ln = (2 / s) atanh f / f
+// (ln x - ln y = 2 atanh f, as in Ismail & Roe 2009), both analytic in z:
+//   z < 1e-4: the series
+//     s (1/4 - (11/945) z (945/132 + z (21/11 + z))) and (2 + (2/7) z (7/3 + z (7/5 + z))) / s
+//     (the next terms are below 4e-18 relative there; monic, so that an
+//     instruction has one literal at most)
+//   z < kLnPoly, x / y between 0.71 and 1.41: polynomials of seven coefficients with the least
+//     largest error (2.4e-19 and 1.3e-18 relative), so that a pair needs no logarithms of its
+//     nodes
+//   beyond: the logarithm of the ratio.
+constexpr double kLnSeries = 1e-4;
+constexpr double kLnPoly = 0.0294;
+__device__ __forceinline__ double half_lnmean_series(double s, double z)
 {
-    const double f2 = f * f;
-    const double t = fma(f2, f2 + 21.0 / 11.0, 945.0 / 132.0) * f2;
+    const double t = fma(z, z + 21.0 / 11.0, 945.0 / 132.0) * z;
     return s * fma(-11.0 / 945.0, t, 0.25);
 }
-__device__ __forceinline__ double inv_lnmean_series(double r, double f)
+__device__ __forceinline__ double inv_lnmean_series(double r, double z)
 {
-    const double f2 = f * f;
-    const double t = fma(f2, f2 + 7.0 / 5.0, 7.0 / 3.0) * f2;
+    const double t = fma(z, z + 7.0 / 5.0, 7.0 / 3.0) * z;
     return fma(2.0 / 7.0, t, 2.0) * r;
 }
-// either form, branch free: one reciprocal serves whichever applies
-__device__ __forceinline__ double half_lnmean(double s, double d, double lx, double ly)
+__device__ __forceinline__ double half_lnmean_poly(double s, double z)
 {
-    const bool ser = lnmean_series(s, d);
-    const double f = d * frcp(ser ? s : lx - ly);
-    return ser ? half_lnmean_series(s, f) : 0.5 * f;
+    double t = fma(z, -0x1.e7f35bc2ef6bbp-9, -0x1.11f376d9b629ap-8);
+    t = fma(z, t, -0x1.65255cdd70460p-8);
+    t = fma(z, t, -0x1.eeb2bc5db1c99p-8);
+    t = fma(z, t, -0x1.7d6d2c3e58a33p-7);
+    t = fma(z, t, -0x1.6c16c16c0d016p-6);
+    t = fma(z, t, -0x1.5555555555561p-4);
+    return s * fma(z, t, 0.25);
 }
-__device__ __forceinline__ double inv_lnmean(double s, double d, double lx, double ly)
+// (2 atanh f / f - 2) / z, |f| < 0.1716: also the logarithm's polynomial
+__device__ __forceinline__ double atanh_poly(double z)
 {
-    const bool ser = lnmean_series(s, d);
-    const double r = frcp(ser ? s : d);
-    return ser ? inv_lnmean_series(r, d * r) : (lx - ly) * r;
+    double t = fma(z, 0x1.2f056395f5a67p-3, 0x1.39a1bab2e7e3cp-3);
+    t = fma(z, t, 0x1.74663ee8bc916p-3);
+    t = fma(z, t, 0x1.c71c52095abb5p-3);
+    t = fma(z, t, 0x1.24924941f1295p-2);
+    t = fma(z, t, 0x1.999999997fdb7p-2);
+    return fma(z, t, 0x1.5555555555592p-1);
 }
+__device__ __forceinline__ double inv_lnmean_poly(double r, double z) { return fma(z, atanh_poly(z), 2.0) * r; }
 
 // Natural logarithms of x and y, both normal (NaN for an argument <= 0 or NaN):
 // x = m 2^k with m in [sqrt(1/2), sqrt(2)), f = m - 1 (exact), s = f / (2 + f), so
@@ -381,13 +383,7 @@ __device__ __forceinline__ double log_join(const LogParts& p, double r, double x
 {
     const double sf = p.f * r;
     const double z = sf * sf;
-    double t = fma(z, 0x1.2f056395f5a67p-3, 0x1.39a1bab2e7e3cp-3);
-    t = fma(z, t, 0x1.74663ee8bc916p-3);
-    t = fma(z, t, 0x1.c71c52095abb5p-3);
-    t = fma(z, t, 0x1.24924941f1295p-2);
-    t = fma(z, t, 0x1.999999997fdb7p-2);
-    t = fma(z, t, 0x1.5555555555592p-1);
-    const double lm = fma(-sf, fma(-z, t, p.f), p.f);
+    const double lm = fma(-sf, fma(-z, atanh_poly(z), p.f), p.f);
     const double l = fma(p.k, 0x1.62e42fefp-1, fma(p.k, 0x1.473de6af278edp-34, lm));
     return x > 0.0 ? l : __builtin_nan("");
 }
@@ -797,21 +793,22 @@ __device__ __forceinline__ void load_node(const double* u, int e, int q, NodeP& 
     make_node(s, g);
 }
 
-// node qq of the block's element le from its LDS primitives; the conserved
-// state is formed again from them (rho v = rho * v, E = p / (gamma - 1) +
-// (rho v . v) / 2: within a few ulp of the stored state, the same for every
-// reader of a node, so that equal states still meet in a zero flux difference)
+// node qq of the block's element le from its LDS rows; the momenta are formed
+// again from the primitives (rho v = rho * v: within an ulp of the stored
+// state, the same for every reader of a node, so that equal states still meet
+// in a zero flux difference), in the mixed mode also the energy
+// (E = p / (gamma - 1) + (rho v . v) / 2)
 #define LDS_NODE(X, qq)                                                    \
     do {                                                                   \
-        X.r = sR[le][0][qq];                                               \
-        X.v1 = sR[le][1][qq];                                              \
-        X.v2 = sR[le][2][qq];                                              \
-        X.p = sR[le][3][qq];                                               \
-        X.c = sR[le][4][qq];                                               \
+        X.r = sRe[0 * NN + (qq)];                                           \
+        X.v1 = sRe[1 * NN + (qq)];                                          \
+        X.v2 = sRe[2 * NN + (qq)];                                          \
+        X.p = sRe[3 * NN + (qq)];                                           \
+        X.c = sRe[4 * NN + (qq)];                                           \
         X.u[0] = X.r;                                                      \
         X.u[1] = X.r * X.v1;                                               \
         X.u[2] = X.r * X.v2;                                               \
-        X.u[3] = fma(X.p, ig1, 0.5 * (X.u[1] * X.v1 + X.u[2] * X.v2));     \
+        X.u[3] = MIXED ? fma(X.p, ig1, 0.5 * (X.u[1] * X.v1 + X.u[2] * X.v2)) : sRe[5 * NN + (qq)]; \
     } while (0)
 
 // LIMK: 0 positivity (or none, at run time), 1 local bounds from bar states,
@@ -822,14 +819,18 @@ __device__ __forceinline__ void load_node(const double* u, int e, int q, NodeP& 
 // surface phase with Kopriva's mortar and the sparse low-order mortar flux,
 // mortar slot records); the batches without one run the MORT = false variant,
 // which has no mortar code, fewer registers and four waves per SIMD.
-// Bound: FP64 and other vector instructions and, nearly as busy, LDS accesses
-// (both about two thirds of the time; the HBM floor is a third).  So the
-// variants save instructions: the conforming launch of the 246,736-leaf N = 4
-// mesh runs 895 vector, 169 scalar and 106 LDS instructions per wave (1,119, 229
-// and 112 before) through the short form of smooth pairs, fluxes in their face's
-// frame with the weight folded into the wave speeds, one reciprocal for several
-// quotients, the faces' roles from a table, and lanes that repeat a node
-// instead of being switched off; its step went from 904 to 805 us.
+// Bound: vector instructions and LDS accesses, each busy for about two thirds of
+// the time (the HBM floor is a third), so every phase is written for few of both:
+// pairs on their series or polynomial without logarithms, fluxes in their
+// face's frame with the weight folded into the wave speeds, one reciprocal for
+// several quotients, the faces' roles from a table, lanes that repeat a node
+// instead of being switched off, a thread's pairs around its own node with
+// its share of the face sums in registers, and strides without bank conflicts.
+// Conforming launch of the 246,736-leaf N = 4 mesh, per wave: 799 vector and 92
+// LDS instructions (748 LDS cycles, 186 of them conflicts), from 1,119 and 112
+// (1,121, 393); five steps of that mesh take 3.80 ms, from 4.51.  More waves do not
+// help: at 92 registers and 16.3 KB of LDS per block, five per SIMD
+// instead of four, the same instructions took the same time.
 template <int N, int MODE, bool MIXED, int LIMK, bool MORT>
 // at least three waves per SIMD: the local-limiting variant would otherwise
 // take 172 registers and run two (63.3 against 67.7 us on the 22,156-leaf
@@ -844,17 +845,14 @@ void k_stage(StageArgs A)
     // solution (read from A.lob); PURE: local factors only
     constexpr bool LOC = LIMK >= 1, COMB = LIMK == 2, BAR = LIMK == 1 || LIMK == 2;
     constexpr bool PURE = LIMK == 1 || LIMK == 3;
-    constexpr int n = G::n, NN = G::NN, EPB = G::EPB, NT = G::NT, NFN = G::NFN;
-    constexpr int NPL = G::NPL, NP = G::NP, NF = G::NF, PPT = NP / NN, PP = G::pp(MORT);
-    static_assert(NP % NN == 0, "pair split");
-    constexpr bool SPLIT = G::SPLIT;
-    static_assert(!MORT || PP >= 12 * n, "mortar buffers reuse the pair buffer");
-    static_assert(G::PR == NN && 4 * NF + NN <= 8 * NN, "subcell fluxes and node factors reuse sR");
+    constexpr int n = G::n, NN = G::NN, EPB = G::EPB, NT = G::NT;
+    constexpr int PP = G::pp(MORT);
+    static_assert(N == 3 || N == 4, "pair map and face sums");
     constexpr int MB = 4 * n;  // offset of the mortar-node fluxes in the pair buffer
 
-    // variable-major (see Geo)
-    __shared__ double sR[EPB][8][G::PR];     // rho, v1, v2, p, c, ln rho, z = rho/p, ln z
-    __shared__ double sPair[EPB][4][PP];     // pair fluxes, then antidiffusive fluxes and corner terms
+    // per node: rho, v1, v2, p, c, E, z = rho / p (mixed: FP32 pairs in rows 5-7)
+    __shared__ double sR[EPB * G::ES];
+    __shared__ double sPair[EPB * G::es(MORT)];  // pair fluxes, then antidiffusive fluxes and corner terms
     // bar states of local limiting: rows 0-3 the subcell faces owned by a node
     // (x: density, log entropy; y: the same), rows 4-6 the face lanes' range
     // (face f, position k at f n + k) across the element face; row 0 later the
@@ -863,10 +861,10 @@ void k_stage(StageArgs A)
     __shared__ double sTw[2][n];              // LGL weights and their reciprocals, read per lane
     __shared__ double sS[n][n];               // Sbar / 2, read per pair
     // After phase 5b the primitive rows of sR are read no more: they take the
-    // low-order subcell fluxes, variable-major over the NF faces (x faces
-    // b N + a, y faces N n + a N + b), and after them the node factors.
-#define sFV(v, fi) sRe[(v) * NF + (fi)]
-#define sTh(qq) sRe[4 * NF + (qq)]
+    // low-order subcell fluxes, rows of N n (the x faces b N + a in rows 0-3, the
+    // y faces b n + a in rows 4-7), and after them the node factors.
+    constexpr int NFH = N * n;
+    static_assert(8 * NFH + NN <= 8 * NN, "subcell fluxes and node factors reuse sR");
 
     const Tab<N>& tb = T<N>();
     const double g = A.gamma, ig1 = A.ig1;
@@ -882,13 +880,13 @@ void k_stage(StageArgs A)
     const int e0 = (A.blist ? A.blist[A.boff + xb] : xb) * EPB;
     const bool act = tid < NT && e0 + le < A.E;
     const int e = e0 + le < A.E ? e0 + le : A.E - 1;
-    double* const sRe = &sR[0][0][0] + le * 8 * NN;  // element le's rows, flat
-    double* const sPe = &sPair[0][0][0] + le * 4 * PP;  // element le's pair buffer, flat
+    double* const sRe = sR + le * G::ES;           // the element's rows
+    double* const sPe = sPair + le * G::es(MORT);  // and its pair buffer
+    double* const sT = sRe + 8 * NFH;      // node factors
     const unsigned role = face_entry<N>(q);
-    // this thread's node pairs (the pair map)
-    unsigned pcode[PPT];
+    unsigned pcode[(N + 1) / 2];  // this thread's node pairs (the pair map)
 #pragma unroll
-    for (int i = 0; i < PPT; ++i) pcode[i] = pair_entry<N>(q, i);
+    for (int i = 0; i < (N + 1) / 2; ++i) pcode[i] = pair_entry<N>(q, i);
     if (tid < n) {
         sTw[0][tid] = tb.w[tid];
         sTw[1][tid] = tb.winv[tid];
@@ -930,35 +928,34 @@ void k_stage(StageArgs A)
         if (COMB) w_e = A.ind[e];
 #pragma unroll
         for (int v = 0; v < 4; ++v) u0[v] = me.u[v];
-        // the logarithms feed only the two-point volume fluxes: FP32 in the
-        // mixed mode, where rows 5-7 hold the FP32 operands of those fluxes in
-        // pairs (rho, p), (ln rho, z), (ln z, 0)
+        // mixed mode: rows 5-7 hold the FP32 operands of the two-point volume
+        // fluxes in pairs (rho, p), (ln rho, z), (ln z, 0)
         const double z = me.r * frcp(me.p);
-        sR[le][0][q] = me.r;
-        sR[le][1][q] = me.v1;
-        sR[le][2][q] = me.v2;
-        sR[le][3][q] = me.p;
-        sR[le][4][q] = me.c;
-        double lr, lz;
+        sRe[(0) * NN + q] = me.r;
+        sRe[(1) * NN + q] = me.v1;
+        sRe[(2) * NN + q] = me.v2;
+        sRe[(3) * NN + q] = me.p;
+        sRe[(4) * NN + q] = me.c;
         if (MIXED) {
-            const float lrf = __logf((float)me.r), lzf = __logf((float)z);
-            lr = lrf;
-            lz = lzf;
-            sR[le][5][q] = pack2((float)me.r, (float)me.p);
-            sR[le][6][q] = pack2(lrf, (float)z);
-            sR[le][7][q] = pack2(lzf, 0.0f);
+            sRe[5 * NN + q] = pack2((float)me.r, (float)me.p);
+            sRe[6 * NN + q] = pack2(__logf((float)me.r), (float)z);
+            sRe[7 * NN + q] = pack2(__logf((float)z), 0.0f);
         } else {
-            flog2(me.r, z, lr, lz);
-            sR[le][5][q] = lr;
-            sR[le][6][q] = z;
-            sR[le][7][q] = lz;
+            sRe[5 * NN + q] = me.u[3];
+            // (a negative density, which only the unlimited scheme can reach, leaves
+            // its pair fluxes undefined)
+            sRe[6 * NN + q] = me.r > 0.0 ? z : __builtin_nan("");
         }
         // the blend needs local factors only where the indicator fires, and at
         // mortar nodes (their mortar may blend with another element's weight)
         need_loc = LOC && (!COMB || w_e > 0.0 || fcode[0] >= 0 || fcode[1] >= 0 || fcode[2] >= 0 ||
                            fcode[3] >= 0);
         // ln(p rho^-gamma) of the node itself, the bar state (i, i)
-        if (need_loc) ls_own = MIXED ? log(me.p) - g * log(me.r) : (1.0 - g) * lr - lz;
+        if (need_loc) {
+            double lr, lp;
+            flog2(me.r, me.p, lr, lp);
+            ls_own = lp - g * lr;
+        }
     }
     const double hx = A.h[2 * e], hy = A.h[2 * e + 1];
     if (MORT && fcode_f >= 0) {
@@ -970,15 +967,15 @@ void k_stage(StageArgs A)
             load_u<N>(A.uin, fnb2, qfn, us1);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                sPair[le][v][MB + (ff * 2 + 0) * n + fk] = onb[v];
-                sPair[le][v][MB + (ff * 2 + 1) * n + fk] = us1[v];
+                sPe[v * PP + MB + (ff * 2 + 0) * n + fk] = onb[v];
+                sPe[v * PP + MB + (ff * 2 + 1) * n + fk] = us1[v];
             }
         } else {
             // small side: stage the large face trace for the interpolation
             double w[4];
             load_u<N>(A.uin, fnb, qfn, w);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) sPair[le][v][ff * n + fk] = w[v];
+            for (int v = 0; v < 4; ++v) sPe[v * PP + ff * n + fk] = w[v];
         }
     } else if (fcode_f < -1) {
         const int j = (-2 - fcode_f) * n + fk;
@@ -1028,9 +1025,10 @@ void k_stage(StageArgs A)
             // LLF in the face's frame, the face node from its LDS rows (the
             // arithmetic of LDS_NODE).  With W = +-w h / 2 (minus on the low side),
             // W F = W/2 (f_own + f_o) + |W|/2 lambda (u_o - u_own) on either side
-            const double r = sR[le][0][qfo], vn = sR[le][1 + dff][qfo], vt = sR[le][2 - dff][qfo];
-            const double p = sR[le][3][qfo], c = sR[le][4][qfo];
-            const double mn = r * vn, mt = r * vt, E = fma(p, ig1, 0.5 * fma(mn, vn, mt * vt));
+            const double r = sRe[(0) * NN + qfo], vn = sRe[(1 + dff) * NN + qfo], vt = sRe[(2 - dff) * NN + qfo];
+            const double p = sRe[(3) * NN + qfo], c = sRe[(4) * NN + qfo];
+            const double mn = r * vn, mt = r * vt;
+            const double E = MIXED ? fma(p, ig1, 0.5 * fma(mn, vn, mt * vt)) : sRe[5 * NN + qfo];
             const double ir = frcp(onb[0]);
             const double on = onb[1] * ir, ot = onb[2] * ir;
             const double op = (g - 1.0) * (onb[3] - 0.5 * fma(onb[1], on, onb[2] * ot));
@@ -1077,9 +1075,9 @@ void k_stage(StageArgs A)
 #pragma unroll
                 for (int j = 0; j < n; ++j) {
                     const int qj = face_q<N>(ff, j);
-                    const double r = sR[le][0][qj], v1 = sR[le][1][qj], v2 = sR[le][2][qj];
+                    const double r = sRe[0 * NN + qj], v1 = sRe[1 * NN + qj], v2 = sRe[2 * NN + qj];
                     const double m1 = r * v1, m2 = r * v2;
-                    const double uj[4] = {r, m1, m2, fma(sR[le][3][qj], ig1, 0.5 * (m1 * v1 + m2 * v2))};
+                    const double uj[4] = {r, m1, m2, fma(sRe[3 * NN + qj], ig1, 0.5 * (m1 * v1 + m2 * v2))};
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         if (MIXED) ia[v] = (float)ia[v] + tb.If[hh][fk][j] * (float)uj[v];
@@ -1107,7 +1105,7 @@ void k_stage(StageArgs A)
                 const double wt = tb.Wt[fk][col];
                 NodeP us;
 #pragma unroll
-                for (int v = 0; v < 4; ++v) us.u[v] = sPair[le][v][MB + ff * 2 * n + col];
+                for (int v = 0; v < 4; ++v) us.u[v] = sPe[v * PP + MB + ff * 2 * n + col];
                 make_node(us, g);
                 double Gf[4];
                 llf_face(dff, lowf, own, us, Gf);
@@ -1133,12 +1131,12 @@ void k_stage(StageArgs A)
                 if (MIXED) {
                     float acc = 0.0f;
 #pragma unroll
-                    for (int j = 0; j < n; ++j) acc += tb.If[hh][fk][j] * (float)sPair[le][v][ff * n + j];
+                    for (int j = 0; j < n; ++j) acc += tb.If[hh][fk][j] * (float)sPe[v * PP + ff * n + j];
                     ui.u[v] = acc;
                 } else {
                     double acc = 0.0;
 #pragma unroll
-                    for (int j = 0; j < n; ++j) acc += tb.I[hh][fk][j] * sPair[le][v][ff * n + j];
+                    for (int j = 0; j < n; ++j) acc += tb.I[hh][fk][j] * sPe[v * PP + ff * n + j];
                     ui.u[v] = acc;
                 }
             }
@@ -1154,7 +1152,7 @@ void k_stage(StageArgs A)
                 const double wt = tb.Wt[j][hh * n + fk];
                 NodeP uj;
 #pragma unroll
-                for (int v = 0; v < 4; ++v) uj.u[v] = sPair[le][v][ff * n + j];
+                for (int v = 0; v < 4; ++v) uj.u[v] = sPe[v * PP + ff * n + j];
                 make_node(uj, g);
                 double Gf[4];
                 llf_face(dff, lowf, own, uj, Gf);
@@ -1186,8 +1184,8 @@ void k_stage(StageArgs A)
         if (large) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                sPair[le][v][MB + (ff * 2 + 0) * n + fk] = onb[v];
-                sPair[le][v][MB + (ff * 2 + 1) * n + fk] = us1[v];
+                sPe[v * PP + MB + (ff * 2 + 0) * n + fk] = onb[v];
+                sPe[v * PP + MB + (ff * 2 + 1) * n + fk] = us1[v];
             }
         }
         __syncthreads();
@@ -1203,14 +1201,14 @@ void k_stage(StageArgs A)
                     for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
                         for (int l = 0; l < n; ++l)
-                            accf += tb.Pf[hh][fk][l] * (float)sPair[le][v][MB + (ff * 2 + hh) * n + l];
+                            accf += tb.Pf[hh][fk][l] * (float)sPe[v * PP + MB + (ff * 2 + hh) * n + l];
                     acc = accf;
                 } else {
 #pragma unroll
                     for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
                         for (int l = 0; l < n; ++l)
-                            acc += tb.P[hh][fk][l] * sPair[le][v][MB + (ff * 2 + hh) * n + l];
+                            acc += tb.P[hh][fk][l] * sPe[v * PP + MB + (ff * 2 + hh) * n + l];
                 }
                 ho[v] = sgf * sTw[0][fk] * hff * 0.5 * acc;
             }
@@ -1227,44 +1225,62 @@ void k_stage(StageArgs A)
     // velocity is read from LDS row 1 + d and the tangential one from row 2 - d,
     // and the two momentum components are stored back to rows 1 + d and 2 - d,
     // so that lanes holding x and y pairs run the same instructions.
-    // pair p = q + i NN: the x pairs are slots below n NPL.  Where NN divides that
-    // count (N = 4) the direction of round i is a constant, and the x and y pairs
-    // are evaluated in two passes (SPLIT): the x lines are telescoped into the
-    // slots after the x pairs, then the y pairs take the x pairs' slots, so the
-    // pair buffer holds half the pairs at a time.
+    //
+    // The high-order flux through the subcell face after position pos of a line
+    // is the sum of the line's pair fluxes (l, k) with l <= pos < k.  Each thread
+    // holds pairs of its own node (the pair map), so it keeps its share of the
+    // face it owns in registers (Hown) and only publishes what others need:
+    //  N = 4, s1(a) = (a, a + 1) and s2(a) = (a, a + 2) modulo 5: the faces sum
+    //    0: s1(0) + s2(0) + s2(3) + s1(4)
+    //    1: s1(1) + s2(1) + s2(0) + s2(3) + s1(4) + s2(4)
+    //    2: s1(2) + s2(2) + s2(1) + s2(3) + s1(4) + s2(4)
+    //    3: s1(3) + s2(2) + s1(4) + s2(4)
+    //    so entry a of the line takes s2(a), entry 4 s1(4) + s2(4), and s1(4) has
+    //    one of its own;
+    //  N = 3: 0: (01) + (03) + (02), 1: (12) + (03) + (02) + (13), 2: (23) + (03) + (13);
+    //    (03), (02) and (13) are published.
     // The pair values carry Sbar only, the density's half of it (the line's
-    // factor w h is applied to the telescoped sums, twice for the density).
-    // Where both logarithmic means of every lane's pair are on their series, as in
-    // smooth flow and in most waves beside a shock, the round takes the short form
-    // without the logarithms' rows and selects, and one reciprocal for both sums;
-    // the test costs a wave that is not six instructions.
-    auto pair_rounds = [&](auto i0c, auto i1c, int slot_off) {
-        constexpr int i0 = decltype(i0c)::value, i1 = decltype(i1c)::value;
+    // factor w h is applied to the faces' sums, twice for the density).
+    // A node needs no logarithms: smooth pairs, and most pairs beside a shock, take
+    // a series or polynomial of their own, and only a round with a pair of states
+    // further apart than a factor of 1.41 the logarithms of its pairs' ratios.
+    double Hown[2][4];
+    const double last_a = a == N ? 1.0 : 0.0, last_b = b == N ? 1.0 : 0.0;  // (N = 4)
+    const double in_a = a < 3 ? 1.0 : 0.0, in_b = b < 3 ? 1.0 : 0.0;
+    {
 #pragma unroll
-        for (int i = i0; i < i1; ++i) {
-            const unsigned c = pcode[i];
-            const int ql = c & 255, qk = (c >> 8) & 255;
-            // a round wholly below or above the x pairs' n NPL slots has a constant
-            // direction; only a round that straddles them (N = 3: the second) decodes it
-            const int d = (i + 1) * NN <= n * NPL ? 0 : (i * NN >= n * NPL ? 1 : (int)(c >> 24));
-            const int p = q + i * NN - slot_off;
+        for (int i = 0; i < N; ++i) {
+            const unsigned c = pcode[i / 2] >> (16 * (i % 2));
+            const int qo = (int)(c & 31);  // the partner's node
+            const int d = N == 4 ? i / 2 : i < 2 ? i : (int)((c >> 10) & 1);
             const int rn = 1 + d, rt = 2 - d;
-            const double hS = (&sS[0][0])[(c >> 16) & 255];  // Sbar / 2
-            const double Ln = sR[le][rn][ql], Lt = sR[le][rt][ql];
-            const double Rn = sR[le][rn][qk], Rt = sR[le][rt][qk];
+            const double hS = (&sS[0][0])[(c >> 5) & 31];  // Sbar / 2
+            double f[4];  // density, normal and tangential momentum, energy
+            const double Ln = sRe[(rn) * NN + q], Lt = sRe[(rt) * NN + q];
+            const double Rn = sRe[(rn) * NN + qo], Rt = sRe[(rt) * NN + qo];
             if (!MIXED) {
-                const double L0 = sR[le][0][ql], L3 = sR[le][3][ql], L6 = sR[le][6][ql];
-                const double R0 = sR[le][0][qk], R3 = sR[le][3][qk], R6 = sR[le][6][qk];
+                const double L0 = sRe[(0) * NN + q], L3 = sRe[(3) * NN + q], L6 = sRe[(6) * NN + q];
+                const double R0 = sRe[(0) * NN + qo], R3 = sRe[(3) * NN + qo], R6 = sRe[(6) * NN + qo];
                 const double s0 = L0 + R0, d0 = L0 - R0, s6 = L6 + R6, d6 = L6 - R6;
+                // one reciprocal for both sums; the round takes the shortest form
+                // that serves all its lanes
+                const double r = frcp(s0 * s6), r6 = s0 * r;
+                const double f0 = d0 * (s6 * r), f6 = d6 * r6;
+                const double z0 = f0 * f0, z6 = f6 * f6, zm = fmax(z0, z6);
                 double hl, iz;  // rho^ln / 2 and 1 / z^ln
-                if (__all(lnmean_series(s0, d0) && lnmean_series(s6, d6))) {
-                    const double r = frcp(s0 * s6);
-                    const double r6 = s0 * r;
-                    hl = half_lnmean_series(s0, d0 * (s6 * r));
-                    iz = inv_lnmean_series(r6, d6 * r6);
+                if (__all(zm < kLnSeries)) {
+                    hl = half_lnmean_series(s0, z0);
+                    iz = inv_lnmean_series(r6, z6);
                 } else {
-                    hl = half_lnmean(s0, d0, sR[le][5][ql], sR[le][5][qk]);
-                    iz = inv_lnmean(s6, d6, sR[le][7][ql], sR[le][7][qk]);
+                    hl = half_lnmean_poly(s0, z0);
+                    iz = inv_lnmean_poly(r6, z6);
+                    if (!__all(zm < kLnPoly)) {
+                        const double rr = frcp(R0 * R6);
+                        double l0, l6;
+                        flog2(L0 * (R6 * rr), L6 * (R0 * rr), l0, l6);
+                        if (!(z0 < kLnPoly)) hl = 0.5 * d0 * frcp(l0);
+                        if (!(z6 < kLnPoly)) iz = l6 * frcp(d6);
+                    }
                 }
                 const double sn = Ln + Rn, st = Lt + Rt;
                 const double h = hS * (hl * sn);  // Sbar rho^ln {{vn}} / 2
@@ -1274,24 +1290,29 @@ void k_stage(StageArgs A)
                     // (rho_L + rho_R) / (z_L + z_R) and 1 / (2 beta^ln) = 1 / z^ln
                     const double fn = fma(h, sn, 2.0 * hS * (s0 * frcp(s6))), ft = h * st;
                     const double k2 = Ln * Ln + Lt * Lt + Rn * Rn + Rt * Rt;
-                    sPair[le][rn][p] = fn;
-                    sPair[le][rt][p] = ft;
-                    sPair[le][3][p] = fma(h, fma(ig2, iz, -0.5 * k2), 0.5 * fma(sn, fn, st * ft));
+                    f[1] = fn;
+                    f[2] = ft;
+                    f[3] = fma(h, fma(ig2, iz, -0.5 * k2), 0.5 * fma(sn, fn, st * ft));
                 } else {
                     const double kin = fma(Lt, Rt, Ln * Rn);
-                    sPair[le][rn][p] = fma(h, sn, hS * (L3 + R3));
-                    sPair[le][rt][p] = h * st;
-                    sPair[le][3][p] = fma(h, fma(ig2, iz, kin), hS * fma(R3, Ln, L3 * Rn));
+                    f[1] = fma(h, sn, hS * (L3 + R3));
+                    f[2] = h * st;
+                    f[3] = fma(h, fma(ig2, iz, kin), hS * fma(R3, Ln, L3 * Rn));
                 }
-                sPair[le][0][p] = h;
+                f[0] = h;
             } else {
                 const double scale = 2.0 * hS;
-                const F2 L5 = unpack2(sR[le][5][ql]), L6 = unpack2(sR[le][6][ql]);
-                const F2 R5 = unpack2(sR[le][5][qk]), R6 = unpack2(sR[le][6][qk]);
-                const float L7 = unpack2(sR[le][7][ql]).x, R7 = unpack2(sR[le][7][qk]).x;
-                const float rL = L5.x, rR = R5.x, pL = L5.y, pR = R5.y, zL = L6.y, zR = R6.y;
+                const F2 L5 = unpack2(sRe[(5) * NN + q]), L6 = unpack2(sRe[(6) * NN + q]);
+                const F2 R5 = unpack2(sRe[(5) * NN + qo]), R6 = unpack2(sRe[(6) * NN + qo]);
+                const float L7 = unpack2(sRe[(7) * NN + q]).x, R7 = unpack2(sRe[(7) * NN + qo]).x;
+                const float rL = L5.x, rR = R5.x, zL = L6.y, zR = R6.y;
                 const float iz_ln = inv_lnmeanf(zL, zR, L7, R7);
-                const float vnL = (float)Ln, vnR = (float)Rn, vtL = (float)Lt, vtR = (float)Rt;
+                // (pressures and velocities in the order of the positions along the line,
+                // so that the single precision result does not depend on who holds the pair)
+                const bool own = (c >> 11) & 1;
+                const float pL = own ? R5.y : L5.y, pR = own ? L5.y : R5.y;
+                const float vnL = (float)(own ? Rn : Ln), vnR = (float)(own ? Ln : Rn);
+                const float vtL = (float)(own ? Rt : Lt), vtR = (float)(own ? Lt : Rt);
                 const float vna = 0.5f * (vnL + vnR), vta = 0.5f * (vtL + vtR);
                 const float fr = lnmeanf(rL, rR, L6.x, R6.x) * vna;
                 float fn, ft, f3;
@@ -1306,69 +1327,42 @@ void k_stage(StageArgs A)
                     ft = fr * vta;
                     f3 = fr * (0.5f * (vnL * vnR + vtL * vtR) + (float)ig1 * iz_ln) + 0.5f * (pL * vnR + pR * vnL);
                 }
-                sPair[le][0][p] = hS * fr;
-                sPair[le][rn][p] = scale * fn;
-                sPair[le][rt][p] = scale * ft;
-                sPair[le][3][p] = scale * f3;
+                f[0] = hS * fr;
+                f[1] = scale * fn;
+                f[2] = scale * ft;
+                f[3] = scale * f3;
             }
-        }
-    };
-    // telescoped high-order subcell fluxes of one line and variable: the flux
-    // through the subcell face after position pos is the sum of the line's pair
-    // fluxes (l, k) with l <= pos < k; with the position a loop constant every
-    // pair index is static.  P: the line's pair slots.
-    auto telescope = [&](const double* P, double (&hof)[N]) {
+            const int vi[4] = {0, rn, rt, 3};  // rows of the four components
+            if constexpr (N == 4) {
+                const int line = 2 * NN + d * n + (d == 0 ? b : a);
+                const double last = d == 0 ? last_a : last_b, in = d == 0 ? in_a : in_b;
 #pragma unroll
-        for (int pos = 0; pos < N; ++pos) {
-            double acc = 0.0;
+                for (int j = 0; j < 4; ++j) {
+                    if (i % 2 == 0) {
+                        Hown[d][vi[j]] = f[j];
+                        if (last != 0.0) sPe[vi[j] * PP + line] = f[j];
+                    } else {
+                        sPe[vi[j] * PP + d * NN + q] = fma(last, Hown[d][vi[j]], f[j]);
+                        Hown[d][vi[j]] = fma(in, f[j], Hown[d][vi[j]]);
+                    }
+                }
+            } else {
+                // entries of a direction: (03), (02) and (13) of the four lines
+                if (i < 2) {
 #pragma unroll
-            for (int l = 0; l <= pos; ++l)
+                    for (int j = 0; j < 4; ++j) {
+                        Hown[i][vi[j]] = f[j];
+                        if (i == 0 ? a == N : b == N) sPe[vi[j] * PP + 3 * n * i + (i == 0 ? b : a)] = f[j];
+                    }
+                } else {
+                    const int at = d * 3 * n + n + n * ((d == 0 ? a : b) & 1) + (d == 0 ? b : a);
 #pragma unroll
-                for (int k = pos + 1; k < n; ++k) acc += P[l * (2 * n - l - 1) / 2 + (k - l - 1)];
-            hof[pos] = acc;
-        }
-    };
-    // ---- phase 4 and 5a: pair fluxes and telescoped high-order subcell fluxes,
-    // one telescoping task per line and variable (task t: line t / 4, variable t % 4) ----
-    if constexpr (SPLIT) {
-        const bool tele = q < 4 * n;
-        double* const P = &sPair[le][q & 3][(q >> 2) * NPL];
-        double xs[N], ys[N];
-        pair_rounds(std::integral_constant<int, 0>(), std::integral_constant<int, PPT / 2>(), 0);
-        __syncthreads();
-        if (tele) telescope(P, xs);
-        __syncthreads();
-        pair_rounds(std::integral_constant<int, PPT / 2>(), std::integral_constant<int, PPT>(), n * NPL);
-        __syncthreads();
-        if (tele) {
-            telescope(P, ys);
-#pragma unroll
-            for (int pos = 0; pos < N; ++pos) {
-                P[pos] = ys[pos];
-                P[N + pos] = xs[pos];
-            }
-        }
-    } else {
-        pair_rounds(std::integral_constant<int, 0>(), std::integral_constant<int, PPT>(), 0);
-        __syncthreads();
-        // the N sums replace the line's first N pair slots of that variable,
-        // which no other task reads (x lines first, then y lines; 8n tasks,
-        // task t = q + j NN for j = 0, 1)
-        static_assert(8 * n <= 2 * NN, "two telescoping tasks per lane at most");
-        {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int t = q + j * NN;
-                if (t < 8 * n) {
-                    double* const P = &sPair[le][t & 3][(t >> 2) * NPL];
-                    double hof[N];
-                    telescope(P, hof);
-#pragma unroll
-                    for (int pos = 0; pos < N; ++pos) P[pos] = hof[pos];
+                    for (int j = 0; j < 4; ++j) sPe[vi[j] * PP + at] = f[j];
                 }
             }
         }
     }
+    __syncthreads();
     // ---- phase 5b: low-order subcell fluxes of the faces owned by this node,
     // x (a|a+1) and y (b|b+1), times the line's weight: w_b h_y / 2 and w_a h_x / 2.
     // With F = (f_L + f_R) / 2 - lambda (u_R - u_L) / 2 and f = u v_n + pressure terms,
@@ -1399,32 +1393,60 @@ void k_stage(StageArgs A)
             if (BAR && need_loc) bar_bounds(d, true, me, o, g, brb[d], bls[d]);
         }
     }
-    // every read of the primitives (and of the pairs, by the telescoping) is done
-    __syncthreads();
+    // the node's low-order residual so far: its surface term and the faces it owns
+    double RLO[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) RLO[v] = (fown ? fterm[v] : 0.0) - FVo[0][v] - FVo[1][v];
     // the owner of a subcell face forms its antidiffusive flux w (f^HO - f^FV),
     // keeps both fluxes (ADo, FVo) and leaves them for the face's other node:
     // the low-order one in the freed primitive rows, the antidiffusive one in
-    // the slot of the telescoped flux
+    // the pair buffer
+    const double hasl = a > 0 ? 1.0 : 0.0, hasb = b > 0 ? 1.0 : 0.0;
     double ADo[2][4];
-    const int ax = a < N ? a : N - 1, by = b < N ? b : N - 1;  // (clamped; not stored there)
 #pragma unroll
     for (int d = 0; d < 2; ++d) {
-        const int hs = d == 0 ? G::hx_slot(b, ax) : G::hy_slot(a, by);
         const double wh = d == 0 ? whx : why;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) ADo[d][v] = fma(v == 0 ? 2.0 * wh : wh, sPe[v * PP + hs], -FVo[d][v]);
-        if (d == 0 ? a < N : b < N) {
-            const int fi = d == 0 ? b * N + a : N * n + a * N + b;
+        const int pos = d == 0 ? a : b, line = d == 0 ? b : a;
+        const double has = d == 0 ? hasl : hasb;
+        if constexpr (N == 4) {
+            // s2 of the node before (from position 1 on), s2(3) (up to face 2), and
+            // s1(4) + s2(4), at face 0 s1(4) alone
+            const int e0i = d * NN + (d == 0 ? line * n : line), st = d == 0 ? 1 : n;
+            const int i1 = d * NN + (pos > 0 ? q - st : q), i2 = e0i + 3 * st;
+            const int i3 = pos > 0 ? e0i + N * st : 2 * NN + d * n + line;
+            const double in = d == 0 ? in_a : in_b;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                sPe[v * PP + hs] = ADo[d][v];
-                sFV(v, fi) = FVo[d][v];
+                const double H = fma(has, sPe[v * PP + i1], fma(in, sPe[v * PP + i2], Hown[d][v] + sPe[v * PP + i3]));
+                ADo[d][v] = fma(v == 0 ? 2.0 * wh : wh, H, -FVo[d][v]);
+            }
+        } else {
+            const double low = pos < 2 ? 1.0 : 0.0;
+            const int e0i = d * 3 * n + line;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const double H = fma(has, sPe[v * PP + e0i + 2 * n],
+                                     fma(low, sPe[v * PP + e0i + n], Hown[d][v] + sPe[v * PP + e0i]));
+                ADo[d][v] = fma(v == 0 ? 2.0 * wh : wh, H, -FVo[d][v]);
             }
         }
     }
-    // the y faces' surface terms at the element's corners
+    // every read of the primitives and of the pair fluxes is done
+    __syncthreads();
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+        if (d == 0 ? a < N : b < N) {
+            const int fi = d == 0 ? q - b : q;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                sPe[v * PP + d * NN + q] = ADo[d][v];
+                sRe[(d * 4 + v) * NFH + fi] = FVo[d][v];
+            }
+        }
+    // the y faces' surface terms at the element's corners, in the x entries that
+    // hold no face (a = N)
     if (fcor) {
-        const int cs = G::corner_slot((fk ? 1 : 0) + (ff & 1 ? 2 : 0));
+        const int cs = N + n * ((fk ? 1 : 0) + (ff & 1 ? 2 : 0));
 #pragma unroll
         for (int v = 0; v < 4; ++v) sPe[v * PP + cs] = fterm[v];
     }
@@ -1453,27 +1475,22 @@ void k_stage(StageArgs A)
     const bool onf[4] = {a == 0, a == N, b == 0, b == N};
     // the subcell faces to the left of and below the node, read at a clamped
     // in-range position of its own line; a missing face (on the element
-    // boundary) has weight 0
-    const double hasl = a > 0 ? 1.0 : 0.0, hasb = b > 0 ? 1.0 : 0.0;
-    const int al = a > 0 ? a - 1 : 0, bl = b > 0 ? b - 1 : 0;
-    double RLO[4], ADl[4], ADb[4], dS0[4] = {0, 0, 0, 0}, dS1[4] = {0, 0, 0, 0};
+    // boundary) has weight 0 (hasl, hasb)
+    double ADl[4], ADb[4], dS0[4] = {0, 0, 0, 0}, dS1[4] = {0, 0, 0, 0};
     int slot0 = -1, slot1 = -1, nmf = 0;
     const double im = 4.0 * frcp(hx * hy) * sTw[1][a] * sTw[1][b];  // 1 / m_i
     {
-        const int fl = b * N + al, fb = N * n + a * N + bl;
-        const int hl = G::hx_slot(b, al), hb = G::hy_slot(a, bl);
-        // the node's surface terms: its own lane's, and at the corners the y
-        // face's from its slot
-        const double own = fown ? 1.0 : 0.0;
+        const int hl = a > 0 ? q - 1 : q, hb = NN + (b > 0 ? q - n : q);
+        const int fl = a > 0 ? q - b - 1 : b * N, fb = b > 0 ? q - n : q;
+        // at the corners the y face's surface term from its slot
         const double cor = (onf[0] || onf[1]) && (onf[2] || onf[3]) ? 1.0 : 0.0;
-        const int cs = G::corner_slot((2 * a > N ? 1 : 0) + (2 * b > N ? 2 : 0));
+        const int cs = N + n * ((2 * a > N ? 1 : 0) + (2 * b > N ? 2 : 0));
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             ADl[v] = sPe[v * PP + hl];
             ADb[v] = sPe[v * PP + hb];
-            double r = fma(hasl, sFV(v, fl), -FVo[0][v]) + fma(hasb, sFV(v, fb), -FVo[1][v]);
-            r = fma(own, fterm[v], r);
-            RLO[v] = fma(cor, sPe[v * PP + cs], r);
+            const double Fl = sRe[v * NFH + fl], Fb = sRe[(4 + v) * NFH + fb];
+            RLO[v] = fma(cor, sPe[v * PP + cs], fma(hasb, Fb, fma(hasl, Fl, RLO[v])));
         }
         if constexpr (MORT) {
             // a node lies on at most one x face (a = 0 or N) and one y face (b = 0 or
@@ -1598,7 +1615,7 @@ void k_stage(StageArgs A)
     // the blend keeps its local node factors in the first bar-state row, read
     // above for the bounds
     if (COMB) __syncthreads();
-    sTh(q) = th;
+    sT[q] = th;
     if (COMB) sB[le][0][q] = thl;
     __syncthreads();
 
@@ -1614,8 +1631,8 @@ void k_stage(StageArgs A)
         const int qn4[4] = {a > 0 ? q - 1 : q, a < N ? q + 1 : q, b > 0 ? q - n : q, b < N ? q + n : q};
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            tf[j] = COMB ? (1.0 - w_e) * fmin(th, sTh(qn4[j])) + w_e * fmin(thl, sB[le][0][qn4[j]])
-                         : fmin(th, sTh(qn4[j]));
+            tf[j] = COMB ? (1.0 - w_e) * fmin(th, sT[qn4[j]]) + w_e * fmin(thl, sB[le][0][qn4[j]])
+                         : fmin(th, sT[qn4[j]]);
 #pragma unroll
         for (int v = 0; v < 4; ++v)
             uvol[v] = uFV[v] + tf[0] * cf[0][v] + tf[1] * cf[1][v] + tf[2] * cf[2][v] + tf[3] * cf[3][v];

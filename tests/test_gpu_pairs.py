@@ -1,10 +1,11 @@
-"""The two-point volume fluxes in both forms of the logarithmic means, through the
+"""The two-point volume fluxes in every form of the logarithmic means, through the
 high-order residual and one limited step against the oracle.
 
-A wave takes the short form where every lane's pair is on the series, |f| < 1e-2
-with f = (x - y) / (x + y).  The amplitudes put all pairs of random states inside
-it (1e-4), all states around its edge, so that most waves hold both kinds (1e-2,
-2e-2), and nearly all pairs outside (0.6); the scales shift the logarithms' range
+A wave takes the series where all its pairs have |f| < 1e-2, f = (x - y) / (x + y),
+the polynomials where they have |f| < 0.171, and logarithms beyond.  The amplitudes
+put all pairs of random states on the series (1e-4), around its edge, so that most
+waves hold both kinds (1e-2, 2e-2), on the polynomials (0.08), around their edge
+(0.17) and mostly beyond (0.6); the scales shift the logarithms' range
 (a density and a pressure in other units).  Element counts of 1, 5 and 24 leave
 the last block partly filled (blocks of 4 elements at N = 3, 5 at N = 4).
 Tolerance 1e-12 in the metrics of parity.py, the bound of every other parity
@@ -31,7 +32,7 @@ def noisy(x, amp, rs, ps):
 
 @pytest.mark.parametrize("N", [3, 4])
 @pytest.mark.parametrize("flux", ["ranocha", "chandrashekar"])
-@pytest.mark.parametrize("amp", [1e-4, 1e-2, 2e-2, 0.6])
+@pytest.mark.parametrize("amp", [1e-4, 1e-2, 2e-2, 0.08, 0.17, 0.6])
 @pytest.mark.parametrize("rs,ps", [(1.0, 1.0), (1e-9, 3e4), (7e8, 2e-7)])
 def test_pair_flux_forms(oracle, rs, ps, amp, flux, N):
     import paper_2607_06045_amd as P
