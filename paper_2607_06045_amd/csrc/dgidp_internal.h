@@ -68,9 +68,7 @@ struct DevMesh {
     double* slot = nullptr;     // [M*3n*kSlotW]
     int* perm = nullptr;        // [E] external index of internal element e
     double* shock_ind = nullptr;  // [E] shock indicator of combined limiting (internal order)
-    double* dlo = nullptr;      // [E*4*NN] R_LO / m of a stage's input (low-order-solution bounds)
-    double* lob = nullptr;      // [E*3*NN] rho min, rho max, ln s min from the low-order solution
-    double* lsv = nullptr;      // [E*2*NN] low-order density and ln s per node
+    double* lsv = nullptr;      // [E*2*NN] density and ln s of the low-order solution (its bounds)
     // [ceil(E / stage_block_elems(N))] stage-kernel element batches: the nbm
     // batches holding an element with a mortar face first, then the others,
     // each part in ascending order
@@ -162,10 +160,10 @@ int launch_mortar(int N, const DevMesh& m, double* uout, double b, DevStats* st,
                   double gamma, int limiter);
 // per-element shock indicator on the pressure of u into m.shock_ind (combined limiting)
 int launch_shock_indicator(int N, const DevMesh& m, const double* u, double gamma, hipStream_t s);
-// local bounds from the low-order solution u + dt * dlo into lob (eq. Bounds_LowOrder);
-// lsv [E*2*NN] holds the per-node low-order density and log entropy between the passes
-int launch_lowbounds(int N, const DevMesh& m, double gamma, const double* u, const double* dlo,
-                     const DtSource& dt, double* lsv, double* lob, hipStream_t s);
+// density and log entropy of the low-order solution u + dt R_LO / m into m.lsv
+// (bounds of eq. Bounds_LowOrder); st only receives the dt it takes from dtmax
+int launch_lowsol(int N, const DevMesh& m, const KernelParams& kp, const double* u, const DtSource& dt,
+                  DevStats* st, hipStream_t s);
 // max over nodes of the dt denominator, atomically merged into the accumulator
 // set acc (all zero on entry); the set other is cleared for the next step
 int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, int mode,

@@ -773,7 +773,13 @@ __device__ __forceinline__ void push_stats(DevStats* st, unsigned long long inad
 // ---------------------------------------------------------------------------
 // element kernel
 // ---------------------------------------------------------------------------
-enum { MODE_STAGE = 0, MODE_RHS_HIGH = 1, MODE_RHS_LOW = 2 };
+// MODE_LOWSOL: the low-order solution u + dt R_LO / m of every node, its density
+// and log entropy (+inf where density or pressure is not positive), for the
+// bounds of eq. Bounds_LowOrder, which the stage itself gathers through LDS and
+// its face lanes.  The low-order modes skip the pair fluxes.  On the 22,156-leaf
+// blast a stage's bounds cost a residual with pair fluxes (15.9 us), a pass over
+// it (6.4 us) and a gather (11.7 us) before, 10.8 us now; five steps 1,124 and 825 us.
+enum { MODE_STAGE = 0, MODE_RHS_HIGH = 1, MODE_RHS_LOW = 2, MODE_LOWSOL = 3 };
 
 struct StageArgs {
     const double* uin;
@@ -782,7 +788,7 @@ struct StageArgs {
     double a, b;
     const double* dt;
     const double* ind;  // combined limiting: shock indicator per element, in [0, 1]
-    const double* lob;  // bounds from the low-order solution: [E][3][NN] rho min, rho max, ln s min
+    const double* lsv;  // bounds from the low-order solution: [E][2][NN] its density and log entropy
     // when set, dt = cfl / max over the accumulator set dtmax (bits of
     // non-negative doubles); block 0 stores it in dt_out
     const unsigned long long* dtmax;
@@ -858,7 +864,7 @@ __device__ __forceinline__ void load_node(const double* u, int e, int q, NodeP& 
 // LIMK: 0 positivity (or none, at run time), 1 local bounds from bar states,
 // 2 the blend of positivity and bar-state local factors by the per-element
 // shock indicator A.ind (eq. combination_posLim_local), 3 local bounds from the
-// low-order solution (eq. Bounds_LowOrder), read from A.lob
+// low-order solution (eq. Bounds_LowOrder), read from A.lsv
 // MORT: the launch over the element batches that hold a mortar element (the
 // surface phase with Kopriva's mortar and the sparse low-order mortar flux,
 // mortar slot records); the batches without one run the MORT = false variant,
@@ -886,9 +892,11 @@ void k_stage(StageArgs A)
     using G = Geo<N>;
     // LOC: local bounds enforced; COMB: blended with positivity; BAR: the bounds
     // come from bar states (computed here), otherwise from the low-order
-    // solution (read from A.lob); PURE: local factors only
+    // solution (read from A.lsv); PURE: local factors only
+    // PAIRS: the pair fluxes and antidiffusive fluxes are needed
     constexpr bool LOC = LIMK >= 1, COMB = LIMK == 2, BAR = LIMK == 1 || LIMK == 2;
     constexpr bool PURE = LIMK == 1 || LIMK == 3;
+    constexpr bool PAIRS = MODE == MODE_STAGE || MODE == MODE_RHS_HIGH;
     constexpr int n = G::n, NN = G::NN, EPB = G::EPB, NT = G::NT;
     constexpr int PP = G::pp(MORT);
     static_assert(N == 3 || N == 4, "pair map and face sums");
@@ -897,11 +905,12 @@ void k_stage(StageArgs A)
     // per node: rho, v1, v2, p, c, E, z = rho / p (mixed: FP32 pairs in rows 5-7)
     __shared__ double sR[EPB * G::ES];
     __shared__ double sPair[EPB * G::es(MORT)];  // pair fluxes, then antidiffusive fluxes and corner terms
-    // bar states of local limiting: rows 0-3 the subcell faces owned by a node
+    // local bounds from the low-order solution: rows 0 and 1 its density and log
+    // entropy per node; from bar states: rows 0-3 the subcell faces owned by a node
     // (x: density, log entropy; y: the same), rows 4-6 the face lanes' range
     // (face f, position k at f n + k) across the element face; row 0 later the
     // local node factors of the blend
-    __shared__ double sB[BAR ? EPB : 1][7][BAR ? NN : 1];
+    __shared__ double sB[LOC ? EPB : 1][7][LOC ? NN : 1];
     __shared__ double sTw[2][n];              // LGL weights and their reciprocals, read per lane
     __shared__ double sS[n][n];               // Sbar / 2, read per pair
     // After phase 5b the primitive rows of sR are read no more: they take the
@@ -974,7 +983,7 @@ void k_stage(StageArgs A)
         for (int v = 0; v < 4; ++v) u0[v] = me.u[v];
         // mixed mode: rows 5-7 hold the FP32 operands of the two-point volume
         // fluxes in pairs (rho, p), (ln rho, z), (ln z, 0)
-        const double z = me.r * frcp(me.p);
+        const double z = PAIRS ? me.r * frcp(me.p) : 0.0;
         sRe[(0) * NN + q] = me.r;
         sRe[(1) * NN + q] = me.v1;
         sRe[(2) * NN + q] = me.v2;
@@ -988,7 +997,7 @@ void k_stage(StageArgs A)
             sRe[5 * NN + q] = me.u[3];
             // (a negative density, which only the unlimited scheme can reach, leaves
             // its pair fluxes undefined)
-            sRe[6 * NN + q] = me.r > 0.0 ? z : __builtin_nan("");
+            if (PAIRS) sRe[6 * NN + q] = me.r > 0.0 ? z : __builtin_nan("");
         }
         // the blend needs local factors only where the indicator fires, and at
         // mortar nodes (their mortar may blend with another element's weight)
@@ -998,6 +1007,37 @@ void k_stage(StageArgs A)
         if (need_loc) ls_own = log_entropy(me.r, me.p, g);
     }
     const double hx = A.h[2 * e], hy = A.h[2 * e + 1];
+    if (LIMK == 3) {
+        // the low-order solution at the node and across this lane's face node (the
+        // matching node of a conforming face, the nodes with a nonzero sparse
+        // weight across a mortar, none across a boundary)
+        const double* own = A.lsv + ((unsigned)e * 2u * NN + (unsigned)q);
+        sB[le][0][q] = own[0];
+        sB[le][1][q] = own[NN];
+        auto gather = [&](int el, int node) {
+            const double* o = A.lsv + ((unsigned)el * 2u * NN + (unsigned)node);
+            fb_lo = fmin(fb_lo, o[0]);
+            fb_hi = fmax(fb_hi, o[0]);
+            fb_ls = fmin(fb_ls, o[NN]);
+        };
+        if (fcode_f == -1) {
+            gather(fnb, qfn);
+        } else if (MORT && fcode_f >= 0) {
+            const bool small = fm_small(fcode_f);
+            const int hh = fm_half(fcode_f);
+            const int nz = small ? tb.snc[hh][fk] : tb.lnc[fk];
+#pragma unroll 1
+            for (int i = 0; i < nz; ++i) {
+                const int col = small ? tb.snz[hh][fk][i] : tb.lnz[fk][i];  // large side: h n + l
+                gather(small || col < n ? fnb : fnb2, face_q<N>(ff ^ 1, col < n ? col : col - n));
+            }
+        }
+        if (fown || fcor) {
+            sB[le][4][ff * n + fk] = fb_lo;
+            sB[le][5][ff * n + fk] = fb_hi;
+            sB[le][6][ff * n + fk] = fb_ls;
+        }
+    }
     if (MORT && fcode_f >= 0) {
         if (!fm_small(fcode_f)) {
             // large side: both small traces at position fk, kept in
@@ -1289,7 +1329,7 @@ void k_stage(StageArgs A)
     const double in_a = a < 3 ? 1.0 : 0.0, in_b = b < 3 ? 1.0 : 0.0;
     {
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
+        for (int i = 0; i < (PAIRS ? N : 0); ++i) {
             const unsigned c = pcode[i / 2] >> (16 * (i % 2));
             const int qo = (int)(c & 31);  // the partner's node
             const int d = N == 4 ? i / 2 : i < 2 ? i : (int)((c >> 10) & 1);
@@ -1402,7 +1442,7 @@ void k_stage(StageArgs A)
             }
         }
     }
-    __syncthreads();
+    if constexpr (PAIRS) __syncthreads();
     // ---- phase 5b: low-order subcell fluxes of the faces owned by this node,
     // x (a|a+1) and y (b|b+1), times the line's weight: w_b h_y / 2 and w_a h_x / 2.
     // With F = (f_L + f_R) / 2 - lambda (u_R - u_L) / 2 and f = u v_n + pressure terms,
@@ -1444,7 +1484,7 @@ void k_stage(StageArgs A)
     const double hasl = a > 0 ? 1.0 : 0.0, hasb = b > 0 ? 1.0 : 0.0;
     double ADo[2][4];
 #pragma unroll
-    for (int d = 0; d < 2; ++d) {
+    for (int d = 0; d < (PAIRS ? 2 : 0); ++d) {
         const double wh = d == 0 ? whx : why;
         const int pos = d == 0 ? a : b, line = d == 0 ? b : a;
         const double has = d == 0 ? hasl : hasb;
@@ -1479,7 +1519,7 @@ void k_stage(StageArgs A)
             const int fi = d == 0 ? q - b : q;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                sPe[v * PP + d * NN + q] = ADo[d][v];
+                if (PAIRS) sPe[v * PP + d * NN + q] = ADo[d][v];
                 sRe[(d * 4 + v) * NFH + fi] = FVo[d][v];
             }
         }
@@ -1527,12 +1567,14 @@ void k_stage(StageArgs A)
         const int cs = N + n * ((2 * a > N ? 1 : 0) + (2 * b > N ? 2 : 0));
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            ADl[v] = sPe[v * PP + hl];
-            ADb[v] = sPe[v * PP + hb];
+            if (PAIRS) {
+                ADl[v] = sPe[v * PP + hl];
+                ADb[v] = sPe[v * PP + hb];
+            }
             const double Fl = sRe[v * NFH + fl], Fb = sRe[(4 + v) * NFH + fb];
             RLO[v] = fma(cor, sPe[v * PP + cs], fma(hasb, Fb, fma(hasl, Fl, RLO[v])));
         }
-        if constexpr (MORT) {
+        if constexpr (MORT && PAIRS) {
             // a node lies on at most one x face (a = 0 or N) and one y face (b = 0 or
             // N): slot 0 takes the mortar of its x face, slot 1 that of its y face
             const int cx = onf[0] ? fcode[0] : (onf[1] ? fcode[1] : -1);
@@ -1553,6 +1595,18 @@ void k_stage(StageArgs A)
             }
             nmf = (cx >= 0) + (cy >= 0);
         }
+    }
+    if (MODE == MODE_LOWSOL) {
+        double w[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) w[v] = u0[v] + dt * (RLO[v] * im);
+        const double p = pressure(w, g);
+        if (act) {
+            double* o = A.uout + ((unsigned)e * 2u * NN + (unsigned)q);
+            o[0] = w[0];
+            o[NN] = w[0] > 0.0 && p > 0.0 ? log_entropy(w[0], p, g) : __builtin_inf();
+        }
+        return;
     }
     if (MODE == MODE_RHS_LOW || MODE == MODE_RHS_HIGH) {
         if (act) {
@@ -1585,15 +1639,30 @@ void k_stage(StageArgs A)
         rmin = A.beta * uFV[0];
         pmin = A.beta * pFV;
         if (need_loc && !BAR) {
-            // bounds from the low-order solution; the node's own low-order
-            // state, as computed here, is inside them by definition (the
-            // bounds kernel's copy of it may differ in the last bit)
-            const size_t bi = (size_t)e * 3 * NN + q;
-            double rlo = fmin(A.lob[bi], uFV[0]);
-            rhi = fmax(A.lob[bi + NN], uFV[0]);
-            lsm = A.lob[bi + 2 * NN];
+            // bounds from the low-order solution over the node and its low-order
+            // neighbours; the node's own low-order state, as computed here, is inside
+            // them by definition (its stored copy may differ in the last bit)
+            double rlo = uFV[0];
+            rhi = uFV[0];
             lsi = uFV[0] > 0.0 && pFV > 0.0 ? log_entropy(uFV[0], pFV, g) : -__builtin_inf();
-            lsm = fmin(lsm, lsi);
+            lsm = lsi;
+            auto take = [&](double lo, double hi, double ls) {
+                rlo = fmin(rlo, lo);
+                rhi = fmax(rhi, hi);
+                lsm = fmin(lsm, ls);
+            };
+            // (at the element's edge the node itself once more, and its faces)
+            const int nq[5] = {q, a > 0 ? q - 1 : q, a < N ? q + 1 : q, b > 0 ? q - n : q, b < N ? q + n : q};
+#pragma unroll
+            for (int j = 0; j < 5; ++j) take(sB[le][0][nq[j]], sB[le][0][nq[j]], sB[le][1][nq[j]]);
+            if (onf[0] || onf[1]) {
+                const int i = (onf[0] ? 0 : n) + b;
+                take(sB[le][4][i], sB[le][5][i], sB[le][6][i]);
+            }
+            if (onf[2] || onf[3]) {
+                const int i = (onf[2] ? 2 * n : 3 * n) + a;
+                take(sB[le][4][i], sB[le][5][i], sB[le][6][i]);
+            }
             rlf = fmax(rmin, rlo);
         } else if (need_loc) {
             // bounds over the node and the bar states of its low-order neighbours
@@ -1838,145 +1907,6 @@ __global__ __launch_bounds__(256) void k_mortar(const double* __restrict__ slot,
         }
     }
     if (st) push_stats(st, 0, viol, thmin, asum, true);
-}
-
-// ---------------------------------------------------------------------------
-// local bounds from the low-order solution (eq. Bounds_LowOrder): per node the
-// density range over u^FV = u + dt R_LO / m of the node and its low-order
-// neighbours (subcell neighbours; the matching node across a conforming face;
-// the nodes with a nonzero sparse weight across a mortar; none across a
-// boundary), and the smallest ln(p rho^-gamma) among those with rho, p > 0.
-// Two passes: k_lowsol forms each node's low-order density and log entropy
-// once (two logarithms per node, coalesced), k_lowbounds gathers them.
-// ---------------------------------------------------------------------------
-struct LoBoundsArgs {
-    const double* u;
-    const double* dlo;  // R_LO / m, [E][4][NN] (internal order)
-    const double* dt;   // dt source as for the stage kernel: dt, or cfl / max(dtmax)
-    const unsigned long long* dtmax;
-    double cfl;
-    const int* fnbr;
-    const int* fnbr2;
-    const int* fmort;
-    int E;
-    double gamma;
-    double* lsv;  // [E][2][NN] low-order density, ln s (+inf where rho or p <= 0)
-    double* lob;  // [E][3][NN] rho min, rho max, ln s min
-};
-
-template <int N>
-__global__ __launch_bounds__(256) void k_lowsol(LoBoundsArgs A)
-{
-    constexpr int NN = (N + 1) * (N + 1);
-    double dt;
-    if (A.dtmax) {  // the same value the stage kernel derives (every lane takes part)
-        const double part = __longlong_as_double((long long)A.dtmax[(threadIdx.x & 63) * kDtStride]);
-        dt = A.cfl / wave_max(part);
-    } else {
-        dt = *A.dt;
-    }
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (size_t)A.E * NN) return;
-    const size_t e = i / NN, q = i - e * NN;
-    double w[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const size_t k = (e * 4 + v) * NN + q;
-        w[v] = A.u[k] + dt * A.dlo[k];
-    }
-    const double p = pressure(w, A.gamma);
-    A.lsv[e * 2 * NN + q] = w[0];
-    A.lsv[e * 2 * NN + NN + q] =
-        w[0] > 0.0 && p > 0.0 ? log_entropy(w[0], p, A.gamma) : __builtin_inf();
-}
-
-template <int N>
-__device__ __forceinline__ void lo_gather(const double* __restrict__ lsv, int e, int q, double& lo,
-                                          double& hi, double& ls)
-{
-    constexpr int NN = (N + 1) * (N + 1);
-    const double r = lsv[(size_t)e * 2 * NN + q];
-    lo = fmin(lo, r);
-    hi = fmax(hi, r);
-    ls = fmin(ls, lsv[(size_t)e * 2 * NN + NN + q]);
-}
-
-// one thread per node
-template <int N>
-__global__ __launch_bounds__(256) void k_lowbounds(LoBoundsArgs A)
-{
-    constexpr int n = N + 1, NN = n * n;
-    const Tab<N>& tb = T<N>();
-    // (contiguous node ranges per XCD: the neighbours' values mostly in the same L2)
-    const size_t i = (size_t)xcd_batch(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    if (i >= (size_t)A.E * NN) return;
-    const int e = (int)(i / NN), q = (int)(i - (size_t)e * NN), a = q % n, b = q / n;
-    double lo = __builtin_inf(), hi = -__builtin_inf(), ls = __builtin_inf();
-    lo_gather<N>(A.lsv, e, q, lo, hi, ls);
-    if (a > 0) lo_gather<N>(A.lsv, e, q - 1, lo, hi, ls);
-    if (a < N) lo_gather<N>(A.lsv, e, q + 1, lo, hi, ls);
-    if (b > 0) lo_gather<N>(A.lsv, e, q - n, lo, hi, ls);
-    if (b < N) lo_gather<N>(A.lsv, e, q + n, lo, hi, ls);
-    const bool on[4] = {a == 0, a == N, b == 0, b == N};
-#pragma unroll
-    for (int f = 0; f < 4; ++f) {
-        if (!on[f]) continue;
-        const int code = A.fmort[e * 4 + f];
-        if (code < -1) continue;  // boundary
-        const int k = f < 2 ? b : a;
-        const int nb = A.fnbr[e * 4 + f];
-        if (code == -1) {
-            lo_gather<N>(A.lsv, nb, face_q<N>(f ^ 1, k), lo, hi, ls);
-        } else if (!fm_small(code)) {
-            const int nb2 = A.fnbr2[e * 4 + f];
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int l = 0; l < n; ++l)
-                    if (tb.Wt[k][hh * n + l] != 0.0)
-                        lo_gather<N>(A.lsv, hh == 0 ? nb : nb2, face_q<N>(f ^ 1, l), lo, hi, ls);
-        } else {
-            const int hh = fm_half(code);
-#pragma unroll
-            for (int kk = 0; kk < n; ++kk)
-                if (tb.Wt[kk][hh * n + k] != 0.0) lo_gather<N>(A.lsv, nb, face_q<N>(f ^ 1, kk), lo, hi, ls);
-        }
-    }
-    const size_t bi = (size_t)e * 3 * NN + q;
-    A.lob[bi] = lo;
-    A.lob[bi + NN] = hi;
-    A.lob[bi + 2 * NN] = ls;
-}
-
-int launch_lowbounds(int N, const DevMesh& m, double gamma, const double* u, const double* dlo,
-                     const DtSource& dt, double* lsv, double* lob, hipStream_t s)
-{
-    if (m.E == 0) return 0;
-    LoBoundsArgs A;
-    A.u = u;
-    A.dlo = dlo;
-    A.dt = dt.dt;
-    A.dtmax = dt.dtmax;
-    A.cfl = dt.cfl;
-    A.fnbr = m.fnbr;
-    A.fnbr2 = m.fnbr2;
-    A.fmort = m.fmort;
-    A.E = m.E;
-    A.gamma = gamma;
-    A.lsv = lsv;
-    A.lob = lob;
-    const size_t nodes = (size_t)m.E * (N + 1) * (N + 1);
-    const dim3 grid((unsigned)((nodes + 255) / 256));
-    if (N == 3) {
-        hipLaunchKernelGGL(k_lowsol<3>, grid, dim3(256), 0, s, A);
-        hipLaunchKernelGGL(k_lowbounds<3>, grid, dim3(256), 0, s, A);
-    } else if (N == 4) {
-        hipLaunchKernelGGL(k_lowsol<4>, grid, dim3(256), 0, s, A);
-        hipLaunchKernelGGL(k_lowbounds<4>, grid, dim3(256), 0, s, A);
-    } else {
-        return -1;
-    }
-    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 // ---------------------------------------------------------------------------
@@ -2698,7 +2628,7 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     A.b = b;
     A.dt = dt.dt;
     A.ind = m.shock_ind;
-    A.lob = m.lob;
+    A.lsv = m.lsv;
     A.dtmax = dt.dtmax;
     A.cfl = dt.cfl;
     A.dt_out = dt.dt_out;
@@ -2706,7 +2636,7 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     // it; on a small one (fewer than kFinalMin batches) the extra launch costs
     // more than the stage's own per-wave reduction
     constexpr int kFinalMin = 16384;
-    if (dt.dtmax && dt.dt_out && mode == MODE_STAGE && (m.E + G::EPB - 1) / G::EPB >= kFinalMin) {
+    if (dt.dtmax && dt.dt_out && (mode == MODE_STAGE || mode == MODE_LOWSOL) && (m.E + G::EPB - 1) / G::EPB >= kFinalMin) {
         static_assert(kDtSpread == 64, "one wave reduces the dt accumulators");
         hipLaunchKernelGGL(k_dt_final, dim3(1), dim3(64), 0, s, dt.dtmax, dt.cfl, dt.dt_out, st);
         A.dt = dt.dt_out;
@@ -2789,8 +2719,10 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
         using MH = std::integral_constant<int, MODE_RHS_HIGH>;
         if (mixed) go(MH(), BT(), I0());
         else go(MH(), BF(), I0());
-    } else {
+    } else if (mode == MODE_RHS_LOW) {
         go(std::integral_constant<int, MODE_RHS_LOW>(), BF(), I0());
+    } else {
+        go(std::integral_constant<int, MODE_LOWSOL>(), BF(), I0());
     }
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -2802,6 +2734,15 @@ int launch_stage(int N, const DevMesh& m, const KernelParams& kp, const double* 
     if (m.E == 0) return 0;
     if (N == 3) return stage_N<3>(m, kp, uin, un, uout, a, b, dt, st, MODE_STAGE, s, rev);
     if (N == 4) return stage_N<4>(m, kp, uin, un, uout, a, b, dt, st, MODE_STAGE, s, rev);
+    return -1;
+}
+
+int launch_lowsol(int N, const DevMesh& m, const KernelParams& kp, const double* u, const DtSource& dt,
+                  DevStats* st, hipStream_t s)
+{
+    if (m.E == 0) return 0;
+    if (N == 3) return stage_N<3>(m, kp, u, nullptr, m.lsv, 0.0, 1.0, dt, st, MODE_LOWSOL, s);
+    if (N == 4) return stage_N<4>(m, kp, u, nullptr, m.lsv, 0.0, 1.0, dt, st, MODE_LOWSOL, s);
     return -1;
 }
 
