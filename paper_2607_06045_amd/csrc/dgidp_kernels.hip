@@ -886,7 +886,7 @@ template <int N, int MODE, bool MIXED, int LIMK, bool MORT>
 // take 172 registers and run two (63.3 against 67.7 us on the 22,156-leaf
 // blast with a few spilled registers; the other variants fit anyway); the
 // conforming positivity variant fits 128 registers, four waves
-__global__ __launch_bounds__(Geo<N>::BS) __attribute__((amdgpu_waves_per_eu((!MORT && LIMK == 0) ? 4 : 3)))
+__global__ __launch_bounds__(Geo<N>::BS) __attribute__((amdgpu_waves_per_eu((LIMK == 0 && (!MORT || N == 4 || MIXED)) ? 4 : 3)))
 void k_stage(StageArgs A)
 {
     using G = Geo<N>;
@@ -901,6 +901,16 @@ void k_stage(StageArgs A)
     constexpr int PP = G::pp(MORT);
     static_assert(N == 3 || N == 4, "pair map and face sums");
     constexpr int MB = 4 * n;  // offset of the mortar-node fluxes in the pair buffer
+    // LATE: the large sides form their high-order mortar fluxes after every lane
+    // has read the staged traces, in place of them, and u^n, the state and the mortar
+    // increments are read where they are used: 128 registers instead of 148,
+    // four waves per SIMD, with positivity limiting, no spills with local bounds.  The
+    // FP64 N = 3 variant runs on the small meshes, where a block's chain counts
+    // more than waves: it forms those fluxes beside the low-order pairs and holds
+    // them over the barrier.  Five steps of the 14,871-leaf N = 4 blast took 402 us late and
+    // 414 early, of the mixed shear layer 659 and 670, three of the blended jet 669 and
+    // 711; but of the 22,156-leaf N = 3 blast 353 late and 346 early.
+    constexpr bool LATE = MORT && (N == 4 || LIMK != 0 || MIXED);
 
     // per node: rho, v1, v2, p, c, E, z = rho / p (mixed: FP32 pairs in rows 5-7)
     __shared__ double sR[EPB * G::ES];
@@ -1040,9 +1050,7 @@ void k_stage(StageArgs A)
     }
     if (MORT && fcode_f >= 0) {
         if (!fm_small(fcode_f)) {
-            // large side: both small traces at position fk, kept in
-            // registers for the mortar-node fluxes and staged for the
-            // sparse low-order pairs of the other positions
+            // large side: stage both small traces at position fk
             load_u<N>(A.uin, fnb, qfn, onb);
             load_u<N>(A.uin, fnb2, qfn, us1);
 #pragma unroll
@@ -1084,6 +1092,33 @@ void k_stage(StageArgs A)
         dt = A.dt ? *A.dt : 0.0;
     }
 
+    // high-order flux on the mortar of a large side, at position fk of half hh, between
+    // the face interpolated to it (its nodes' conserved states formed as
+    // LDS_NODE does) and the small side's trace u, which the flux replaces
+    auto mortar_ho = [&](int hh, double (&u)[4]) {
+        NodeP ui, us;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) us.u[v] = u[v];
+        make_node(us, g);
+        double ia[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < n; ++j) {
+            const int qj = face_q<N>(ff, j);
+            const double r = sRe[0 * NN + qj], v1 = sRe[1 * NN + qj], v2 = sRe[2 * NN + qj];
+            const double m1 = r * v1, m2 = r * v2;
+            const double E = MIXED ? fma(sRe[3 * NN + qj], ig1, 0.5 * (m1 * v1 + m2 * v2)) : sRe[5 * NN + qj];
+            const double uj[4] = {r, m1, m2, E};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                if (MIXED) ia[v] = (float)ia[v] + tb.If[hh][fk][j] * (float)uj[v];
+                else ia[v] += tb.I[hh][fk][j] * uj[v];
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) ui.u[v] = ia[v];
+        make_node(ui, g);
+        mortar_flux(dff, lowf, ui, us, u);
+    };
     // ---- phase 2: one surface flux per face node: the low-order surface term ----
     const double sgf = lowf ? -1.0 : 1.0;
     const double hff = ff < 2 ? hy : hx;
@@ -1141,39 +1176,11 @@ void k_stage(StageArgs A)
             fterm[2] = dff == 0 ? F[2] : F[1];
             fterm[3] = F[3];
         } else if (MORT && !fm_small(fcode_f)) {
-            // large side: mortar-node fluxes at position fk of both halves
-            // (kept in registers until every lane has read the staged small
-            // traces), and the sparse low-order pairs of this node
-            for (int hh = 0; hh < 2; ++hh) {
-                NodeP ui, us;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) us.u[v] = hh == 0 ? onb[v] : us1[v];
-                make_node(us, g);
-                // the large face interpolated to half hh, from the face nodes'
-                // conserved states formed as LDS_NODE does
-                double ia[4] = {0, 0, 0, 0};
-#pragma unroll
-                for (int j = 0; j < n; ++j) {
-                    const int qj = face_q<N>(ff, j);
-                    const double r = sRe[0 * NN + qj], v1 = sRe[1 * NN + qj], v2 = sRe[2 * NN + qj];
-                    const double m1 = r * v1, m2 = r * v2;
-                    const double uj[4] = {r, m1, m2, fma(sRe[3 * NN + qj], ig1, 0.5 * (m1 * v1 + m2 * v2))};
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        if (MIXED) ia[v] = (float)ia[v] + tb.If[hh][fk][j] * (float)uj[v];
-                        else ia[v] += tb.I[hh][fk][j] * uj[v];
-                    }
-                }
-#pragma unroll
-                for (int v = 0; v < 4; ++v) ui.u[v] = ia[v];
-                make_node(ui, g);
-                double F[4];
-                mortar_flux(dff, lowf, ui, us, F);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    if (hh == 0) onb[v] = F[v];
-                    else us1[v] = F[v];
-                }
+            // large side: the high-order mortar fluxes (LATE: in phase 3), then the
+            // sparse low-order pairs of this node with the staged traces
+            if (PAIRS && !LATE) {
+                mortar_ho(0, onb);
+                mortar_ho(1, us1);
             }
             // (over this node's nonzero weights only: a wave runs as many
             // rounds as its busiest lane)
@@ -1249,7 +1256,7 @@ void k_stage(StageArgs A)
             }
 #pragma unroll
             for (int v = 0; v < 4; ++v) fterm[v] = lo[v];
-            if (act && (fown || fcor)) {
+            if (PAIRS && act && (fown || fcor)) {
                 const int S = fm_mortar(fcode_f);
                 double* R = A.slot + (size_t)(S * 3 * n + n + fm_half(fcode_f) * n + fk) * kSlotW;
 #pragma unroll
@@ -1259,13 +1266,29 @@ void k_stage(StageArgs A)
     }
     if constexpr (MORT) {  // (every batch of the mortar launch holds a mortar element)
         __syncthreads();
-        // ---- phase 3: large sides publish and project the mortar fluxes ----
-        const bool large = fcode_f >= 0 && !fm_small(fcode_f);
+        // ---- phase 3: high-order mortar fluxes of the large sides in place of this
+        // lane's staged small traces (which every lane has read), then their
+        // projection ----
+        // (updated in place: lanes that repeat another's face node stay out)
+        const bool large = PAIRS && tid < NT && (fown || fcor) && fcode_f >= 0 && !fm_small(fcode_f);
         if (large) {
+            if constexpr (LATE) {
+#pragma unroll 1
+                for (int hh = 0; hh < 2; ++hh) {
+                    double* const tr = &sPe[MB + (ff * 2 + hh) * n + fk];
+                    double F[4];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                sPe[v * PP + MB + (ff * 2 + 0) * n + fk] = onb[v];
-                sPe[v * PP + MB + (ff * 2 + 1) * n + fk] = us1[v];
+                    for (int v = 0; v < 4; ++v) F[v] = tr[v * PP];
+                    mortar_ho(hh, F);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) tr[v * PP] = F[v];
+                }
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    sPe[v * PP + MB + (ff * 2 + 0) * n + fk] = onb[v];
+                    sPe[v * PP + MB + (ff * 2 + 1) * n + fk] = us1[v];
+                }
             }
         }
         __syncthreads();
@@ -1293,7 +1316,7 @@ void k_stage(StageArgs A)
                 ho[v] = sgf * sTw[0][fk] * hff * 0.5 * acc;
             }
             double* R = A.slot + (size_t)(S * 3 * n + fk) * kSlotW;
-            if (act && (fown || fcor))
+            if (act)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) R[4 + v] = ho[v] - fterm[v];
         }
@@ -1551,12 +1574,13 @@ void k_stage(StageArgs A)
     // u^n of this node for the SSP combination, loaded where it is needed (so
     // that it occupies no registers through the flux phases)
     double un4[4] = {0, 0, 0, 0};
-    if (MODE == MODE_STAGE && A.a != 0.0) load_u<N>(A.un, e, q, un4);
+    if (MODE == MODE_STAGE && !LATE && A.a != 0.0) load_u<N>(A.un, e, q, un4);
+    if (LATE) load_u<N>(A.uin, e, q, u0);
     const bool onf[4] = {a == 0, a == N, b == 0, b == N};
     // the subcell faces to the left of and below the node, read at a clamped
     // in-range position of its own line; a missing face (on the element
     // boundary) has weight 0 (hasl, hasb)
-    double ADl[4], ADb[4], dS0[4] = {0, 0, 0, 0}, dS1[4] = {0, 0, 0, 0};
+    double ADl[4], ADb[4], dS0[4], dS1[4];
     int slot0 = -1, slot1 = -1, nmf = 0;
     const double im = 4.0 * frcp(hx * hy) * sTw[1][a] * sTw[1][b];  // 1 / m_i
     {
@@ -1583,16 +1607,14 @@ void k_stage(StageArgs A)
                 const int S3 = fm_mortar(code) * 3 * n;
                 return fm_small(code) ? S3 + n + fm_half(code) * n + k : S3 + k;
             };
-            if (cx >= 0) {
-                slot0 = slot_of(cx, b);
+            if (cx >= 0) slot0 = slot_of(cx, b);
+            if (cy >= 0) slot1 = slot_of(cy, a);
+            if (!LATE && slot0 >= 0)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) dS0[v] = A.slot[(size_t)slot0 * kSlotW + 4 + v];
-            }
-            if (cy >= 0) {
-                slot1 = slot_of(cy, a);
+            if (!LATE && slot1 >= 0)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) dS1[v] = A.slot[(size_t)slot1 * kSlotW + 4 + v];
-            }
             nmf = (cx >= 0) + (cy >= 0);
         }
     }
@@ -1615,7 +1637,8 @@ void k_stage(StageArgs A)
                 double r = RLO[v];
                 if (MODE == MODE_RHS_HIGH) {
                     r += fma(hasl, ADl[v], -ADo[0][v]) + fma(hasb, ADb[v], -ADo[1][v]);
-                    r += dS0[v] + dS1[v];
+                    const double* dS = A.slot + 4 + v;
+                    r += (slot0 >= 0 ? dS[(size_t)slot0 * kSlotW] : 0.0) + (slot1 >= 0 ? dS[(size_t)slot1 * kSlotW] : 0.0);
                 }
                 A.uout[((unsigned)e * 4u + v) * NN + q] = r * im;
             }
@@ -1721,6 +1744,7 @@ void k_stage(StageArgs A)
             }
         }
     }
+    if (LATE && A.a != 0.0) load_u<N>(A.un, e, q, un4);
     // the blend keeps its local node factors in the first bar-state row, read
     // above for the bounds
     if (COMB) __syncthreads();
@@ -1773,13 +1797,14 @@ void k_stage(StageArgs A)
         } else {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                if ((j == 0 ? slot0 : slot1) < 0) continue;
-                const double* dS = j == 0 ? dS0 : dS1;
+                const int slot = j == 0 ? slot0 : slot1;
+                if (slot < 0) continue;
+                double* S = A.slot + (size_t)slot * kSlotW;
                 double c[4], dc[4];
                 bool fin = true;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    c[v] = dtm * dS[v];
+                    c[v] = dtm * (LATE ? S[4 + v] : j == 0 ? dS0[v] : dS1[v]);  // (high-order minus low-order flux terms, phases 2 and 3)
                     dc[v] = nmf * c[v];
                     fin = fin && isfinite(dc[v]);
                 }
@@ -1795,7 +1820,6 @@ void k_stage(StageArgs A)
                         if (COMB) tsl = mortar_factor<true>(uvol, dc, rlf, pmin, rhi, lsm, lsi, g, ig1);
                     }
                 }
-                double* S = A.slot + (size_t)(j == 0 ? slot0 : slot1) * kSlotW;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     S[v] = uvol[v];
