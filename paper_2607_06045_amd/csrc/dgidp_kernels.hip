@@ -21,6 +21,7 @@
 // stage kernel of the step reduces those and takes dt = cfl / max.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <type_traits>
 
 #include "dgidp_internal.h"
@@ -2102,193 +2103,248 @@ __global__ __launch_bounds__(kDtBlock) void k_dt(DtArgs A)
 }
 
 // ---------------------------------------------------------------------------
-// modal indicator (k_indicator), features and the learned indicator
-// (k_features).  Squared orthonormal-Legendre coefficients of a staged nodal
-// quantity q[b'][a'], one thread per mode (i, j) = (a, b) of an element, in
-// two sum-factorised passes through LDS:
+// modal sensors: the indicators (k_indicator), the features and the learned
+// indicator (k_features).  All start from the squared orthonormal-Legendre
+// coefficients of a nodal quantity q[b'][a'], in two sum-factorised passes:
 //   r[b'][i] = sum_a' Vinv[i][a'] q[b'][a'],   m[j][i] = sum_b' Vinv[j][b'] r[b'][i]
-// (n reads per thread and pass instead of n^2).
-//  Hennemann indicator on rho p: energy = max of the energy fractions of the
-//  highest and the second-highest mode shells, alpha = logistic with threshold
-//  T = 0.5 10^(-1.8 (N+1)^(1/4)) and sharpness ln(9999), zero below 1e-3,
-//  capped at 0.5.
+//  Hennemann indicator: energy = max of the energy fractions of the highest and
+//  the second-highest mode shells, alpha = logistic with threshold
+//  T = 0.5 10^(-1.8 (N+1)^(1/4)) and sharpness ln(9999), zero below 1e-3.  On rho p,
+//  capped at 0.5 (FP32, external element order); or, for combined limiting
+//  (Sec. 3.5), on p and not capped (FP64, internal order).
 //  Features: x- and y-shell energy fractions of rho and of p for the shells
-//  N-3 .. N (16 values), one lane per feature.
-// Outputs (FP32) go to the external element order through perm.
+//  N-3 .. N (16 values; FP32, external order).
+//
+// Every wave works alone on 64 / (N+1) elements: it loads their nodes in order
+// (all loads first), then takes one row of nodes per lane for the first pass and one
+// column for the second, in place in LDS, so the matrix rows are scalar operands
+// and a pass takes n reads and n^2 products for n modes; the reductions run
+// over columns and rows in the same way, and no lane waits for another wave.
+// Bound: memory (32 B per node read; what the last-level cache still holds of the state
+// comes faster than the 5.2 TB/s of a large copy).  On 246,736 elements of N = 4 (198 MB),
+// the form with one lane per mode, block barriers and one lane per element for the
+// whole reduction against this one: modal indicator 51 -> 30 us, features 50 -> 33,
+// learned indicator 62 -> 43.
 // ---------------------------------------------------------------------------
 template <int N>
-__device__ __forceinline__ double modal_x(const Tab<N>& tb, const double* Q, int a, int b)
-{
-    constexpr int n = N + 1;
-    double r = 0.0;
-#pragma unroll
-    for (int aa = 0; aa < n; ++aa) r += tb.Vinv[a][aa] * Q[b * n + aa];
-    return r;
-}
-
-template <int N>
-__device__ __forceinline__ double modal_y_sq(const Tab<N>& tb, const double* Rx, int a, int b)
-{
-    constexpr int n = N + 1;
-    double m = 0.0;
-#pragma unroll
-    for (int bb = 0; bb < n; ++bb) m += tb.Vinv[b][bb] * Rx[bb * n + a];
-    return m * m;
-}
-
-template <int N>
-__global__ __launch_bounds__(128) void k_indicator(const double* __restrict__ u, int E,
-                                                   const int* __restrict__ perm, double gamma,
-                                                   float* __restrict__ alpha)
-{
-    constexpr int n = N + 1, NN = n * n, EPB = 128 / NN;
-    __shared__ double sQ[EPB][NN];
-    __shared__ double sR[EPB][NN];
-    const Tab<N>& tb = T<N>();
-    const int tid = threadIdx.x;
-    const int le = tid / NN, q = tid - le * NN, a = q % n, b = q / n;
-    const int e = blockIdx.x * EPB + le;
-    const bool act = tid < EPB * NN && e < E;
-    if (act) {
-        double w[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) w[v] = u[((size_t)e * 4 + v) * NN + q];
-        sQ[le][q] = w[0] * (gamma - 1.0) * (w[3] - 0.5 * (w[1] * w[1] + w[2] * w[2]) / w[0]);
-    }
-    __syncthreads();
-    if (act) sR[le][q] = modal_x<N>(tb, sQ[le], a, b);
-    __syncthreads();
-    if (act) sQ[le][q] = modal_y_sq<N>(tb, sR[le], a, b);  // sQ now holds m^2
-    __syncthreads();
-    if (!act || q != 0) return;
-    double all = 0.0, low1 = 0.0, low2 = 0.0;
-    for (int j = 0; j < n; ++j)
-        for (int i = 0; i < n; ++i) {
-            const double m2 = sQ[le][j * n + i];
-            all += m2;
-            if (i < N && j < N) low1 += m2;
-            if (i < N - 1 && j < N - 1) low2 += m2;
-        }
-    const double en = fmax((all - low1) / all, (low1 - low2) / low1);
-    const double T = 0.5 * pow(10.0, -1.8 * sqrt(sqrt((double)(N + 1))));
-    const double s = log((1.0 - 1e-4) / 1e-4);
-    double al = 1.0 / (1.0 + exp(-(s / T) * (en - T)));
-    if (al < 1e-3) al = 0.0;
-    alpha[perm[e]] = (float)fmin(al, 0.5);
-}
-
-// Features of a tile of TE elements per 256-thread block, in rounds of
-// 256 / (N+1)^2 elements (one thread per node); the tile's state is loaded
-// before its first round.  Each feature takes one lane: its shell sum of n
-// squared modes; the 16 lanes of an element are consecutive lanes of one wave
-// and form the total energy of each quantity from the x-shell sums with three
-// butterfly steps.  NET = false writes the features; NET = true keeps them in
-// LDS and wave 0 runs the network on the tile (the matrix-core pass of
-// mlp::forward32: features rounded to FP32, then to BF16; weights staged once
-// per block in LDS).
-template <int N>
-struct FeatGeom {
-    static constexpr int NN = (N + 1) * (N + 1), CH = 256 / NN;
-    static constexpr int R = (32 / CH) < 1 ? 1 : 32 / CH;  // rounds: 3 at N = 4, 2 at N = 3
-    static constexpr int TE = R * CH;                       // 30 at N = 4, 32 at N = 3
+struct ModalGeo {
+    static constexpr int n = N + 1, NN = n * n;
+    static constexpr int WE = 64 / n;                     // elements per wave: 16 at N = 3, 12 at N = 4
+    static constexpr int L = WE * n;                      // lanes with a row or column
+    static constexpr int PER = (WE * NN + 63) / 64;       // nodes per lane when loading
+    // LDS strides: rows 5 doubles apart and elements 20 (N = 3) or 25 apart: the 16
+    // lanes of an access differ modulo 16 (but for two pairs at N = 4 by columns)
+    static constexpr int RS = 5, ES = RS * n;
+    static constexpr int kWaves = 4;                      // per block
 };
 
-template <int N, bool NET>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7), amdgpu_num_vgpr(64))) void k_features(
-    const double* __restrict__ u, int E, const int* __restrict__ perm, double gamma,
-    const uint16_t* __restrict__ wb, float* __restrict__ out)
+// orders the LDS accesses of one wave (which the hardware keeps in order) for the
+// compiler; no wave waits for another
+__device__ __forceinline__ void wave_sync()
 {
-    using G = FeatGeom<N>;
-    constexpr int n = N + 1, NN = G::NN, CH = G::CH, R = G::R, TE = G::TE;
-    static_assert(TE <= 32 && N >= 3, "one wave of the network pass per tile; shells N-3 .. N");
-    __shared__ double sQ[2][CH][NN];  // nodal values, then squared modes
-    __shared__ double sR[2][CH][NN];  // x pass
-    __shared__ __align__(16) float sX[NET ? 32 : 1][mlp::kNin + 4];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// density and pressure of the wave's nodes lane + 64 i of elements e0 .. e0 + WE - 1
+// (elements past the last repeat it)
+template <int N>
+__device__ __forceinline__ void modal_load(const double* __restrict__ u, int e0, int E, double gamma, int lane,
+                                           double (&r)[ModalGeo<N>::PER], double (&p)[ModalGeo<N>::PER])
+{
+    using G = ModalGeo<N>;
+    double w[G::PER][4];
+#pragma unroll
+    for (int i = 0; i < G::PER; ++i) {
+        const int k = lane + 64 * i, el = k / G::NN, q = k - el * G::NN;
+        const double* pu = u + ((size_t)min(e0 + el, E - 1) * 4 * G::NN + q);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) w[i][v] = pu[v * G::NN];
+    }
+#pragma unroll
+    for (int i = 0; i < G::PER; ++i) {
+        r[i] = w[i][0];
+        p[i] = (gamma - 1.0) * (w[i][3] - 0.5 * (w[i][1] * w[i][1] + w[i][2] * w[i][2]) / w[i][0]);
+    }
+}
+
+// Squared modes m[j] = m2[j][c] of column c of element t / n, where lane t < L is
+// (element, c); x holds the nodal values in modal_load's order, Q is the wave's
+// WE * ES doubles.  Q's column c of the element may be overwritten by its lane
+// afterwards.
+template <int N>
+__device__ __forceinline__ void modal_modes(const Tab<N>& tb, double* Q, const double (&x)[ModalGeo<N>::PER],
+                                            int lane, int t, double (&m)[N + 1])
+{
+    using G = ModalGeo<N>;
+    constexpr int n = G::n;
+#pragma unroll
+    for (int i = 0; i < G::PER; ++i) {
+        const int k = lane + 64 * i, el = k / G::NN, q = k - el * G::NN;
+        if (G::WE * G::NN % 64 == 0 || i + 1 < G::PER || el < G::WE)
+            Q[el * G::ES + (q / n) * G::RS + q % n] = x[i];
+    }
+    wave_sync();
+    double y[n];
+    double* row = Q + t * G::RS;  // (ES = RS n: the rows of all elements are RS apart)
+#pragma unroll
+    for (int k = 0; k < n; ++k) y[k] = row[k];
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < n; ++k) s += tb.Vinv[i][k] * y[k];
+        row[i] = s;
+    }
+    wave_sync();
+    const double* col = Q + (t / n) * G::ES + t % n;
+#pragma unroll
+    for (int k = 0; k < n; ++k) y[k] = col[k * G::RS];
+#pragma unroll
+    for (int j = 0; j < n; ++j) {
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < n; ++k) s += tb.Vinv[j][k] * y[k];
+        m[j] = s * s;
+    }
+}
+
+// SHOCK: the pressure, FP64 result in internal order
+template <int N, bool SHOCK, typename OUT>
+__global__ __launch_bounds__(256) void k_indicator(const double* __restrict__ u, int E,
+                                                   const int* __restrict__ perm, double gamma, double thresh,
+                                                   double sharp, OUT* __restrict__ alpha)
+{
+    using G = ModalGeo<N>;
+    constexpr int n = G::n;
+    __shared__ double sQ[G::kWaves][G::WE * G::ES];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int e0 = (blockIdx.x * G::kWaves + wv) * G::WE;
+    if (e0 >= E) return;
+    double* Q = sQ[wv];
+    double r[G::PER], p[G::PER], m[n];
+    modal_load<N>(u, e0, E, gamma, lane, r, p);
+    if (!SHOCK) {
+#pragma unroll
+        for (int i = 0; i < G::PER; ++i) p[i] *= r[i];
+    }
+    const int t = min(lane, G::L - 1), c = t % n;
+    modal_modes<N>(T<N>(), Q, p, lane, t, m);
+    // this column's part of the highest shell, the second-highest and the rest
+    double s = 0.0;
+#pragma unroll
+    for (int j = 0; j < N - 1; ++j) s += m[j];
+    double* col = Q + (t / n) * G::ES + c;
+    col[0] = c == N ? s + m[N - 1] + m[N] : m[N];
+    col[G::RS] = c == N ? 0.0 : c == N - 1 ? s + m[N - 1] : m[N - 1];
+    col[2 * G::RS] = c < N - 1 ? s : 0.0;
+    wave_sync();
+    if (lane >= G::WE || e0 + lane >= E) return;
+    double top1 = 0.0, top2 = 0.0, low2 = 0.0;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        top1 += Q[lane * G::ES + i];
+        top2 += Q[lane * G::ES + G::RS + i];
+        low2 += Q[lane * G::ES + 2 * G::RS + i];
+    }
+    const double low1 = low2 + top2, en = fmax(top1 / (low1 + top1), top2 / low1);
+    const double al = 1.0 / (1.0 + exp(-(sharp / thresh) * (en - thresh)));
+    if (SHOCK) alpha[e0 + lane] = al < 1e-3 ? 0.0 : al;
+    else alpha[perm[e0 + lane]] = al < 1e-3 ? 0.0f : (OUT)fmin(al, 0.5);
+}
+
+template <int N, bool SHOCK, typename OUT>
+static void launch_modal(int E, const double* u, const int* perm, double gamma, OUT* alpha, hipStream_t s)
+{
+    using G = ModalGeo<N>;
+    const double thresh = 0.5 * std::pow(10.0, -1.8 * std::pow((double)(N + 1), 0.25));
+    const double sharp = std::log((1.0 - 1e-4) / 1e-4);
+    hipLaunchKernelGGL((k_indicator<N, SHOCK, OUT>), dim3((E - 1) / (G::kWaves * G::WE) + 1), dim3(256), 0, s, u, E,
+                       perm, gamma, thresh, sharp, alpha);
+}
+
+// NET = false writes the features, one group of elements per wave.  NET = true
+// keeps those of NT groups (32 elements at N = 3, 24 at N = 4) in LDS and runs the
+// network on them (the matrix-core pass of mlp::forward32: features rounded to FP32,
+// then to BF16; the weights are staged in LDS once per block).
+template <int N, bool NET>
+__global__ __launch_bounds__(256) void k_features(const double* __restrict__ u, int E,
+                                                  const int* __restrict__ perm, double gamma,
+                                                  const uint16_t* __restrict__ wb, float* __restrict__ out)
+{
+    using G = ModalGeo<N>;
+    constexpr int n = G::n, NT = NET ? 2 : 1;
+    static_assert(NT * G::WE <= 32 && N >= 3, "one network pass per wave; shells N-3 .. N");
+    static_assert(G::WE * 16 % 64 == 0, "whole waves of features");
+    __shared__ double sQ[G::kWaves][G::WE * G::ES];
+    __shared__ double sS[G::kWaves][2][2][G::L];  // shell sums: quantity, direction
+    __shared__ __align__(16) float sX[NET ? G::kWaves : 1][32][mlp::kNin + 4];
     __shared__ __align__(16) mlp::LdsWeights sW[1];  // not allocated when NET is false (unused)
-    const Tab<N>& tb = T<N>();
-    const int tid = threadIdx.x;
-    const int le = tid / NN, q = tid - le * NN, a = q % n, b = q / n;
-    const int fe = tid >> 4, f = tid & 15;
-    // feature f of element fe: quantity f / 8 (rho, p), direction (f / 4) % 2
-    // (x shells: sums over the y modes, y shells: over the x modes), shell N - 3 + f % 4
-    const int fk = f >> 3, kk = N - 3 + (f & 3);
-    const bool ydir = (f >> 2) & 1;
-    const int e0 = blockIdx.x * TE;
-    // the weights are staged first (their loads are issued before the state's);
-    // the rounds' barriers order the staging before the network pass
-    if (NET) mlp::stage_weights(sW[0], wb, tid, 256);
-    double w[R][4];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int e = e0 + r * CH + le;
-        if (tid < CH * NN && e < E) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) w[r][v] = u[((size_t)e * 4 + v) * NN + q];
-        }
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int tile0 = (blockIdx.x * G::kWaves + wv) * NT * G::WE;
+    if (NET) {
+        mlp::stage_weights(sW[0], wb, threadIdx.x, 256);
+        __syncthreads();
     }
+    double* Q = sQ[wv];
+    const int t = min(lane, G::L - 1);
+#pragma unroll 1
+    for (int g = 0; g < NT; ++g) {
+        const int e0 = tile0 + g * G::WE;
+        if (e0 >= E) break;
+        double x[2][G::PER];
+        modal_load<N>(u, e0, E, gamma, lane, x[0], x[1]);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const bool act = tid < CH * NN && e0 + r * CH + le < E;
-        if (act) {
-            const double p = (gamma - 1.0) * (w[r][3] - 0.5 * (w[r][1] * w[r][1] + w[r][2] * w[r][2]) / w[r][0]);
-            sQ[0][le][q] = w[r][0];
-            sQ[1][le][q] = p;
-        }
-        __syncthreads();
-        if (act) {
-            sR[0][le][q] = modal_x<N>(tb, sQ[0][le], a, b);
-            sR[1][le][q] = modal_x<N>(tb, sQ[1][le], a, b);
-        }
-        __syncthreads();
-        if (act) {  // sQ now holds m^2
-            sQ[0][le][q] = modal_y_sq<N>(tb, sR[0][le], a, b);
-            sQ[1][le][q] = modal_y_sq<N>(tb, sR[1][le], a, b);
-        }
-        __syncthreads();
-        if (fe < CH) {  // whole 16-lane groups
-            const int e = e0 + r * CH + fe;
-            const bool ok = e < E;
-            double sh = 0.0, part = 0.0;
-            if (ok) {
-                const double* m2 = sQ[fk][fe];
+        for (int k = 0; k < 2; ++k) {
+            double m[n], s = 0.0;
+            modal_modes<N>(T<N>(), Q, x[k], lane, t, m);
+            double* col = Q + (t / n) * G::ES + t % n;
 #pragma unroll
-                for (int j = 0; j < n; ++j) sh += ydir ? m2[kk * n + j] : m2[j * n + kk];
-                if (!ydir) {
-                    part = sh;
-                    // the x shells below N - 3 (one at N = 4) enter the total by lane N - 3
-                    if ((f & 3) == 0)
-#pragma unroll
-                        for (int c0 = 0; c0 < N - 3; ++c0)
-#pragma unroll
-                            for (int j = 0; j < n; ++j) part += m2[j * n + c0];
-                }
+            for (int j = 0; j < n; ++j) {
+                s += m[j];
+                col[j * G::RS] = m[j];
             }
-            part += __shfl_xor(part, 1, 64);
-            part += __shfl_xor(part, 2, 64);
-            part += __shfl_xor(part, 4, 64);
-            const float v = ok ? (float)(sh / part) : 0.0f;
-            if (!NET && ok) out[(size_t)perm[e] * 16 + f] = v;
-            if (NET) sX[r * CH + fe][f] = v;
+            sS[wv][k][0][t] = s;
+            wave_sync();
+            s = 0.0;
+#pragma unroll
+            for (int i = 0; i < n; ++i) s += Q[t * G::RS + i];
+            sS[wv][k][1][t] = s;
+            wave_sync();
         }
-        // the next round's staging overwrites sQ (and the network pass reads sX):
-        // the reads and writes above are done
-        if (NET || r + 1 < R) __syncthreads();
+        // feature f of an element: quantity f / 8 (rho, p), direction (f / 4) % 2
+        // (x shells: sums over the y modes, y shells: over the x modes), shell N - 3 + f % 4
+        const int f = lane & 15;
+#pragma unroll
+        for (int i = 0; i < G::WE / 4; ++i) {
+            const int el = (lane >> 4) + 4 * i;
+            const double* S = &sS[wv][f >> 3][0][el * n];
+            double all = 0.0;
+#pragma unroll
+            for (int j = 0; j < n; ++j) all += S[j];
+            const float v = (float)(sS[wv][f >> 3][(f >> 2) & 1][el * n + N - 3 + (f & 3)] / all);
+            if (NET) sX[wv][g * G::WE + el][f] = v;
+            else if (e0 + el < E) out[(size_t)perm[e0 + el] * 16 + f] = v;
+        }
+        wave_sync();
     }
-    if (!NET || tid >= 64) return;
-    const int c = tid & 31, hf = tid >> 5;
+    if (!NET || tile0 >= E) return;
+    const int c = lane & 31, hf = lane >> 5;
+    const bool ok = c < NT * G::WE && tile0 + c < E;
     float xv[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) xv[t] = c < TE ? sX[c][hf * 8 + t] : 0.0f;
-    const float y = mlp::forward32(sW[0], mlp::pack_bf16x8(xv), tid);
-    if (hf == 0 && c < TE && e0 + c < E) out[perm[e0 + c]] = y;
+    for (int j = 0; j < 8; ++j) xv[j] = ok ? sX[wv][c][hf * 8 + j] : 0.0f;
+    const float y = mlp::forward32(sW[0], mlp::pack_bf16x8(xv), lane);
+    if (hf == 0 && ok) out[perm[tile0 + c]] = y;
 }
 
 template <int N, bool NET>
 static void launch_features(int E, const double* u, const int* perm, double gamma, const uint16_t* wb, float* out,
                             hipStream_t s)
 {
-    const int ntiles = (E + FeatGeom<N>::TE - 1) / FeatGeom<N>::TE;
-    hipLaunchKernelGGL((k_features<N, NET>), dim3(ntiles), dim3(256), 0, s, u, E, perm, gamma, wb, out);
+    constexpr int per = ModalGeo<N>::kWaves * ModalGeo<N>::WE * (NET ? 2 : 1);
+    hipLaunchKernelGGL((k_features<N, NET>), dim3((E - 1) / per + 1), dim3(256), 0, s, u, E, perm, gamma, wb, out);
 }
 
 int launch_indicator(int N, int E, const double* u, const int* perm, double gamma, float* alpha,
@@ -2297,10 +2353,8 @@ int launch_indicator(int N, int E, const double* u, const int* perm, double gamm
     if (E <= 0) return 0;
     if (N != 3 && N != 4) return -1;
     if (alpha) {
-        const int EPB = 128 / ((N + 1) * (N + 1));
-        const int grid = (E + EPB - 1) / EPB;
-        if (N == 3) hipLaunchKernelGGL(k_indicator<3>, dim3(grid), dim3(128), 0, s, u, E, perm, gamma, alpha);
-        else hipLaunchKernelGGL(k_indicator<4>, dim3(grid), dim3(128), 0, s, u, E, perm, gamma, alpha);
+        if (N == 3) launch_modal<3, false>(E, u, perm, gamma, alpha, s);
+        else launch_modal<4, false>(E, u, perm, gamma, alpha, s);
     }
     if (feat) {
         if (N == 3) launch_features<3, false>(E, u, perm, gamma, nullptr, feat, s);
@@ -2319,59 +2373,11 @@ int launch_learned_indicator(int N, int E, const double* u, const int* perm, dou
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// ---------------------------------------------------------------------------
-// shock indicator of combined limiting (Sec. 3.5): the Hennemann indicator on
-// the pressure, not capped, FP64, one value per element in internal order.
-// One thread per node stages p, one thread per mode (i, j) forms its squared
-// orthonormal-Legendre coefficient (the two passes of modal_x and modal_y_sq),
-// thread 0 of the element reduces.
-// ---------------------------------------------------------------------------
-template <int N>
-__global__ __launch_bounds__(128) void k_shock_indicator(const double* __restrict__ u, int E, double gamma,
-                                                         double* __restrict__ ind)
-{
-    constexpr int n = N + 1, NN = n * n, EPB = 128 / NN;
-    __shared__ double sP[EPB][NN];
-    __shared__ double sR[EPB][NN];
-    const Tab<N>& tb = T<N>();
-    const int tid = threadIdx.x;
-    const int le = tid / NN, q = tid - le * NN, a = q % n, b = q / n;
-    const int e = blockIdx.x * EPB + le;
-    const bool act = tid < EPB * NN && e < E;
-    if (act) {
-        double w[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) w[v] = u[((size_t)e * 4 + v) * NN + q];
-        sP[le][q] = (gamma - 1.0) * (w[3] - 0.5 * (w[1] * w[1] + w[2] * w[2]) / w[0]);
-    }
-    __syncthreads();
-    if (act) sR[le][q] = modal_x<N>(tb, sP[le], a, b);
-    __syncthreads();
-    if (act) sP[le][q] = modal_y_sq<N>(tb, sR[le], a, b);  // sP now holds m^2
-    __syncthreads();
-    if (!act || q != 0) return;
-    double all = 0.0, low1 = 0.0, low2 = 0.0;
-    for (int j = 0; j < n; ++j)
-        for (int i = 0; i < n; ++i) {
-            const double m2 = sP[le][j * n + i];
-            all += m2;
-            if (i < N && j < N) low1 += m2;
-            if (i < N - 1 && j < N - 1) low2 += m2;
-        }
-    const double en = fmax((all - low1) / all, (low1 - low2) / low1);
-    const double T = 0.5 * pow(10.0, -1.8 * sqrt(sqrt((double)(N + 1))));
-    const double s = log((1.0 - 1e-4) / 1e-4);
-    const double al = 1.0 / (1.0 + exp(-(s / T) * (en - T)));
-    ind[e] = al < 1e-3 ? 0.0 : al;
-}
-
 int launch_shock_indicator(int N, const DevMesh& m, const double* u, double gamma, hipStream_t s)
 {
     if (m.E <= 0) return 0;
-    const int EPB = 128 / ((N + 1) * (N + 1));
-    const int grid = (m.E + EPB - 1) / EPB;
-    if (N == 3) hipLaunchKernelGGL(k_shock_indicator<3>, dim3(grid), dim3(128), 0, s, u, m.E, gamma, m.shock_ind);
-    else if (N == 4) hipLaunchKernelGGL(k_shock_indicator<4>, dim3(grid), dim3(128), 0, s, u, m.E, gamma, m.shock_ind);
+    if (N == 3) launch_modal<3, true>(m.E, u, nullptr, gamma, m.shock_ind, s);
+    else if (N == 4) launch_modal<4, true>(m.E, u, nullptr, gamma, m.shock_ind, s);
     else return -1;
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
