@@ -562,10 +562,8 @@ int stage_on(dgidp_ctx* ctx, const DevMesh& dm, const double* uin, const double*
             dt.dtmax = nullptr;
         }
     }
-    if (launch_stage(ctx->p.N, dm, kp, uin, un, uout, a, b, dt, st, ctx->stream, rev))
+    if (launch_stage(ctx->p.N, dm, kp, uin, un, uout, a, b, dt, st, ctx->stream, rev, true))
         return fail(ctx, DGIDP_E_DEVICE, "stage kernel launch failed");
-    if (launch_mortar(ctx->p.N, dm, uout, b, st, ctx->stream, kp.gamma, kp.limiter))
-        return fail(ctx, DGIDP_E_DEVICE, "mortar kernel launch failed");
     return 0;
 }
 

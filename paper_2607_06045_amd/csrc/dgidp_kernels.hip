@@ -772,6 +772,119 @@ __device__ __forceinline__ void push_stats(DevStats* st, unsigned long long inad
 }
 
 // ---------------------------------------------------------------------------
+// mortar corrections: one thread per slot, after the stage's mortar elements are
+// written.  Where the stage is one launch they are a launch of their own (k_mortar);
+// where it is two, the conforming elements' launch starts with them: neither reads
+// what the other writes, and most of a launch of little work is hidden.  On the
+// 246,736-leaf mesh they take 8.6 to 10.5 us in a launch of their own and lengthen the
+// conforming launch by 4 us; five steps 3,780 us before, 3,729 now (with the time step
+// taken by the mortar elements' launch).
+// ---------------------------------------------------------------------------
+struct MortarArgs {
+    const double* slot;
+    const int* snode;
+    const int* spart;
+    int M;
+    double* uout;
+    double b;
+    double gamma;
+    int limiter;
+    DevStats* st;
+};
+
+// factor of mortar S: the minimum of its slots' node factors; combined
+// limiting blends the positivity and the local minimum with the largest
+// indicator of the mortar's three elements
+template <int N>
+__device__ __forceinline__ double mortar_theta(const double* __restrict__ slot, int S, int limiter)
+{
+    constexpr int NS = 3 * (N + 1);
+    double t = 1.0, tl = 1.0, w = 0.0;
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        const double* R = slot + ((size_t)S * NS + j) * kSlotW;
+        t = fmin(t, R[8]);
+        if (limiter == DGIDP_LIMIT_COMBINED) {
+            tl = fmin(tl, R[13]);
+            w = fmax(w, R[14]);
+        }
+    }
+    return limiter == DGIDP_LIMIT_COMBINED ? (1.0 - w) * t + w * tl : t;
+}
+
+// correction of slot s (past the last slot: none); all lanes of a wave call it
+template <int N>
+__device__ __forceinline__ void mortar_slot(const MortarArgs& A, int s)
+{
+    constexpr int n = N + 1, NN = n * n, NS = 3 * n;
+    const double* __restrict__ slot = A.slot;
+    double* uout = A.uout;
+    unsigned long long viol = 0;
+    double asum = 0.0, thmin = 1.0;
+    if (s < A.M * NS) {
+        const int S = s / NS;
+        // every load that needs no other load first: slot factors of the
+        // mortar, this slot's record, its node and its partner
+        const double* R = slot + (size_t)s * kSlotW;
+        const int part = A.spart[s];
+        const int node = A.snode[s];
+        double rec[11];
+#pragma unroll
+        for (int i = 0; i < 11; ++i) rec[i] = R[i];
+        double t = mortar_theta<N>(slot, S, A.limiter);
+        const int e = node / NN, q = node - e * NN;
+        double uo[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) uo[v] = uout[((size_t)e * 4 + v) * NN + q];
+        if (s == S * NS) {
+            asum = 1.0 - t;
+            thmin = t;
+        }
+        bool apply = true;
+        double corr[4] = {0, 0, 0, 0};
+        if (t != 0.0)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) corr[v] = t * rec[4 + v];
+        if (part >= 0) {
+            const int S2 = part / NS;
+            if (S2 < S) {
+                apply = false;  // the lower-numbered mortar applies both corrections
+            } else {
+                const double t2 = mortar_theta<N>(slot, S2, A.limiter);
+                if (t2 != 0.0)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) corr[v] += t2 * slot[(size_t)part * kSlotW + 4 + v];
+            }
+        }
+        if (apply) {
+            double w[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                uout[((size_t)e * 4 + v) * NN + q] = uo[v] + A.b * corr[v];
+                w[v] = rec[v] + corr[v];
+            }
+            if (A.limiter == DGIDP_LIMIT_LOCAL || A.limiter == DGIDP_LIMIT_LOCAL_LOWORDER) {
+                const double rhi = R[11], lsm = R[12];
+                const double pw = pressure(w, A.gamma);
+                if (!(w[0] >= rec[9] * (1.0 - kLocalTol)) || w[0] > rhi * (1.0 + kLocalTol) ||
+                    pw < rec[10] || !(log_entropy(w[0], pw, A.gamma) >= lsm - kLocalTol))
+                    viol = 1;
+            } else if (A.limiter != DGIDP_LIMIT_NONE &&
+                       (w[0] < rec[9] || pressure(w, A.gamma) < rec[10] || w[0] != w[0])) {
+                viol = 1;
+            }
+        }
+    }
+    if (A.st) push_stats(A.st, 0, viol, thmin, asum, true);
+}
+
+template <int N>
+__global__ __launch_bounds__(256) void k_mortar(MortarArgs A)
+{
+    mortar_slot<N>(A, blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+// ---------------------------------------------------------------------------
 // element kernel
 // ---------------------------------------------------------------------------
 // MODE_LOWSOL: the low-order solution u + dt R_LO / m of every node, its density
@@ -814,6 +927,10 @@ struct StageArgs {
     int limiter;
     int vflux;  // two-point volume flux: DGIDP_FLUX_RANOCHA or DGIDP_FLUX_CHANDRASHEKAR
     DevStats* st;
+    // the first mblocks blocks of a conforming launch, a multiple of 8, correct the
+    // mortars of the launch before it instead
+    int mblocks;
+    MortarArgs mo;
 };
 
 // node (a, b) at position k along face f
@@ -938,9 +1055,18 @@ void k_stage(StageArgs A)
     static_assert(NT <= G::BS && G::BS - NT <= NN && (G::BS - NT == 0 || NT - NN >= G::BS - 64),
                   "the last lanes repeat nodes of their own wave");
     const int tid = threadIdx.x;
+    int bid = blockIdx.x, nblk = gridDim.x;
+    if constexpr (!MORT && LIMK == 0 && MODE == MODE_STAGE) {
+        if (bid < A.mblocks) {
+            mortar_slot<N>(A.mo, bid * G::BS + tid);
+            return;
+        }
+        bid -= A.mblocks;
+        nblk -= A.mblocks;
+    }
     const int tl = tid < NT ? tid : tid - NN;
     const int le = tl / NN, q = tl - le * NN, a = q % n, b = q / n;
-    const int xb = !MORT && A.rev ? xcd_batch_rev(blockIdx.x, gridDim.x) : xcd_batch(blockIdx.x, gridDim.x);
+    const int xb = !MORT && A.rev ? xcd_batch_rev(bid, nblk) : xcd_batch(bid, nblk);
     const int e0 = (A.blist ? A.blist[A.boff + xb] : xb) * EPB;
     const bool act = tid < NT && e0 + le < A.E;
     const int e = e0 + le < A.E ? e0 + le : A.E - 1;
@@ -1085,7 +1211,7 @@ void k_stage(StageArgs A)
     if (A.dtmax) {
         const double m = wave_max(dtpart);
         dt = A.cfl / m;
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (bid == 0 && threadIdx.x == 0) {
             *A.dt_out = dt;
             if (A.st) A.st->dt = dt;
         }
@@ -1844,97 +1970,6 @@ void k_stage(StageArgs A)
 }
 
 // ---------------------------------------------------------------------------
-// mortar kernel: one thread per slot
-// ---------------------------------------------------------------------------
-// factor of mortar S: the minimum of its slots' node factors; combined
-// limiting blends the positivity and the local minimum with the largest
-// indicator of the mortar's three elements
-template <int N>
-__device__ __forceinline__ double mortar_theta(const double* __restrict__ slot, int S, int limiter)
-{
-    constexpr int NS = 3 * (N + 1);
-    double t = 1.0, tl = 1.0, w = 0.0;
-#pragma unroll
-    for (int j = 0; j < NS; ++j) {
-        const double* R = slot + ((size_t)S * NS + j) * kSlotW;
-        t = fmin(t, R[8]);
-        if (limiter == DGIDP_LIMIT_COMBINED) {
-            tl = fmin(tl, R[13]);
-            w = fmax(w, R[14]);
-        }
-    }
-    return limiter == DGIDP_LIMIT_COMBINED ? (1.0 - w) * t + w * tl : t;
-}
-
-template <int N>
-__global__ __launch_bounds__(256) void k_mortar(const double* __restrict__ slot,
-                                                const int* __restrict__ snode,
-                                                const int* __restrict__ spart, int M,
-                                                double* uout, double bcoef, double gamma,
-                                                int limiter, DevStats* st)
-{
-    constexpr int n = N + 1, NN = n * n, NS = 3 * n;
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    unsigned long long viol = 0;
-    double asum = 0.0, thmin = 1.0;
-    if (s < M * NS) {
-        const int S = s / NS;
-        // every load that needs no other load first: slot factors of the
-        // mortar, this slot's record, its node and its partner
-        const double* R = slot + (size_t)s * kSlotW;
-        const int part = spart[s];
-        const int node = snode[s];
-        double rec[11];
-#pragma unroll
-        for (int i = 0; i < 11; ++i) rec[i] = R[i];
-        double t = mortar_theta<N>(slot, S, limiter);
-        const int e = node / NN, q = node - e * NN;
-        double uo[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) uo[v] = uout[((size_t)e * 4 + v) * NN + q];
-        if (s == S * NS) {
-            asum = 1.0 - t;
-            thmin = t;
-        }
-        bool apply = true;
-        double corr[4] = {0, 0, 0, 0};
-        if (t != 0.0)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) corr[v] = t * rec[4 + v];
-        if (part >= 0) {
-            const int S2 = part / NS;
-            if (S2 < S) {
-                apply = false;  // the lower-numbered mortar applies both corrections
-            } else {
-                const double t2 = mortar_theta<N>(slot, S2, limiter);
-                if (t2 != 0.0)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) corr[v] += t2 * slot[(size_t)part * kSlotW + 4 + v];
-            }
-        }
-        if (apply) {
-            double w[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                uout[((size_t)e * 4 + v) * NN + q] = uo[v] + bcoef * corr[v];
-                w[v] = rec[v] + corr[v];
-            }
-            if (limiter == DGIDP_LIMIT_LOCAL || limiter == DGIDP_LIMIT_LOCAL_LOWORDER) {
-                const double rhi = R[11], lsm = R[12];
-                const double pw = pressure(w, gamma);
-                if (!(w[0] >= rec[9] * (1.0 - kLocalTol)) || w[0] > rhi * (1.0 + kLocalTol) ||
-                    pw < rec[10] || !(log_entropy(w[0], pw, gamma) >= lsm - kLocalTol))
-                    viol = 1;
-            } else if (limiter != DGIDP_LIMIT_NONE &&
-                       (w[0] < rec[9] || pressure(w, gamma) < rec[10] || w[0] != w[0])) {
-                viol = 1;
-            }
-        }
-    }
-    if (st) push_stats(st, 0, viol, thmin, asum, true);
-}
-
-// ---------------------------------------------------------------------------
 // time step: per node sum_j 2 d_ij / m_i (or the low-order estimate), block max
 // ---------------------------------------------------------------------------
 struct DtArgs {
@@ -2647,7 +2682,7 @@ __global__ __launch_bounds__(64) void k_dt_final(const unsigned long long* dtmax
 template <int N>
 static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, const double* un,
                    double* uout, double a, double b, const DtSource& dt, DevStats* st, int mode,
-                   hipStream_t s, bool rev = false)
+                   hipStream_t s, bool rev = false, bool mortars = false)
 {
     using G = Geo<N>;
     StageArgs A;
@@ -2662,16 +2697,6 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     A.dtmax = dt.dtmax;
     A.cfl = dt.cfl;
     A.dt_out = dt.dt_out;
-    // on a large mesh dt is reduced once, by k_dt_final, and the stage reads
-    // it; on a small one (fewer than kFinalMin batches) the extra launch costs
-    // more than the stage's own per-wave reduction
-    constexpr int kFinalMin = 16384;
-    if (dt.dtmax && dt.dt_out && (mode == MODE_STAGE || mode == MODE_LOWSOL) && (m.E + G::EPB - 1) / G::EPB >= kFinalMin) {
-        static_assert(kDtSpread == 64, "one wave reduces the dt accumulators");
-        hipLaunchKernelGGL(k_dt_final, dim3(1), dim3(64), 0, s, dt.dtmax, dt.cfl, dt.dt_out, st);
-        A.dt = dt.dt_out;
-        A.dtmax = nullptr;
-    }
     A.fnbr = m.fnbr;
     A.fnbr2 = m.fnbr2;
     A.fmort = m.fmort;
@@ -2696,14 +2721,31 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
                    : kp.limiter == DGIDP_LIMIT_LOCAL_LOWORDER ? 3 : 0;
     // Positivity limiting on a large mesh: the batches with a mortar element
     // (the first m.nbm entries of the batch list) in one launch, the others in
-    // a second one without mortar code (four waves per SIMD instead of three).
-    // The mortar launch ends with a partly idle GPU, so a mesh of fewer than
-    // kSplitMin batches, or with a larger mortar share, runs as one launch of
-    // the mortar variant; so do the local-limiting modes, whose conforming
-    // variant keeps three waves per SIMD.  A mesh without mortars runs the
-    // conforming variant alone.
+    // a second one without mortar code, in which the first launch's mortars are
+    // corrected.  The first ends with a partly idle GPU, so a mesh of fewer than
+    // kSplitMin batches, or with a larger mortar share, runs as one launch of the
+    // mortar variant: five steps of the 22,156-leaf blast (5,539 batches, N = 3) take
+    // 348 us in one launch and 478 in two, of the 246,736-leaf quadrants (49,348,
+    // N = 4) 3,851 and 3,748.  So do the local-limiting modes (three steps of the
+    // 22,156-leaf blast 714 and 979).  A mesh without mortars runs the conforming
+    // variant alone.
     constexpr int kSplitMin = 16384;
     const bool split = m.nbm == 0 || (lk == 0 && nb >= kSplitMin && 8LL * m.nbm <= nb);
+    const bool two = split && m.nbm > 0;
+    // dt from the accumulators: in a stage of two launches the first reduces them
+    // per wave, stores dt, and the second reads it.  In one launch over a large mesh
+    // k_dt_final reduces them once; with fewer than kFinalMin batches the extra launch
+    // costs more than the stage's own per-wave reduction.
+    constexpr int kFinalMin = 16384;
+    if (dt.dtmax && dt.dt_out && !two && nb >= kFinalMin) {
+        static_assert(kDtSpread == 64, "one wave reduces the dt accumulators");
+        hipLaunchKernelGGL(k_dt_final, dim3(1), dim3(64), 0, s, dt.dtmax, dt.cfl, dt.dt_out, st);
+        A.dt = dt.dt_out;
+        A.dtmax = nullptr;
+    }
+    // the mortar corrections of this stage
+    A.mo = {m.slot, m.slot_node, m.slot_partner, mortars ? m.M : 0, uout, b, kp.gamma, kp.limiter, st};
+    A.mblocks = 0;
     auto go = [&](auto modec, auto mixc, auto lkc) {
         constexpr int MD = decltype(modec)::value, LK = decltype(lkc)::value;
         constexpr bool MX = decltype(mixc)::value;
@@ -2717,6 +2759,12 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
         if (m.nbm > 0) {
             A.boff = 0;
             hipLaunchKernelGGL((k_stage<N, MD, MX, LK, true>), dim3(m.nbm), dim3(G::BS), 0, s, A);
+            if (A.dtmax) {
+                A.dt = dt.dt_out;
+                A.dtmax = nullptr;
+            }
+            // whole rounds over the XCDs, so that the batch ranges keep their XCD
+            A.mblocks = ((A.mo.M * 3 * (N + 1) + G::BS - 1) / G::BS + 7) / 8 * 8;
         }
         if (nb > m.nbm) {
             // (only this launch may walk its ranges backwards: its blocks cost
@@ -2724,7 +2772,7 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
             // costlier mortar batches first on purpose)
             A.boff = m.nbm;
             A.rev = rev ? 1 : 0;
-            hipLaunchKernelGGL((k_stage<N, MD, MX, LK, false>), dim3(nb - m.nbm), dim3(G::BS), 0, s, A);
+            hipLaunchKernelGGL((k_stage<N, MD, MX, LK, false>), dim3(A.mblocks + nb - m.nbm), dim3(G::BS), 0, s, A);
         }
     };
     using I0 = std::integral_constant<int, 0>;
@@ -2754,16 +2802,18 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     } else {
         go(std::integral_constant<int, MODE_LOWSOL>(), BF(), I0());
     }
+    if (A.mo.M > 0 && !two)
+        hipLaunchKernelGGL(k_mortar<N>, dim3((A.mo.M * 3 * (N + 1) + 255) / 256), dim3(256), 0, s, A.mo);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 int launch_stage(int N, const DevMesh& m, const KernelParams& kp, const double* uin,
                  const double* un, double* uout, double a, double b, const DtSource& dt,
-                 DevStats* st, hipStream_t s, bool rev)
+                 DevStats* st, hipStream_t s, bool rev, bool mortars)
 {
     if (m.E == 0) return 0;
-    if (N == 3) return stage_N<3>(m, kp, uin, un, uout, a, b, dt, st, MODE_STAGE, s, rev);
-    if (N == 4) return stage_N<4>(m, kp, uin, un, uout, a, b, dt, st, MODE_STAGE, s, rev);
+    if (N == 3) return stage_N<3>(m, kp, uin, un, uout, a, b, dt, st, MODE_STAGE, s, rev, mortars);
+    if (N == 4) return stage_N<4>(m, kp, uin, un, uout, a, b, dt, st, MODE_STAGE, s, rev, mortars);
     return -1;
 }
 
@@ -2791,17 +2841,11 @@ int launch_mortar(int N, const DevMesh& m, double* uout, double b, DevStats* st,
                   double gamma, int limiter)
 {
     if (m.M == 0) return 0;
-    const int NS = 3 * (N + 1);
-    const int total = m.M * NS;
-    const int grid = (total + 255) / 256;
-    if (N == 3)
-        hipLaunchKernelGGL(k_mortar<3>, dim3(grid), dim3(256), 0, s, m.slot, m.slot_node,
-                           m.slot_partner, m.M, uout, b, gamma, limiter, st);
-    else if (N == 4)
-        hipLaunchKernelGGL(k_mortar<4>, dim3(grid), dim3(256), 0, s, m.slot, m.slot_node,
-                           m.slot_partner, m.M, uout, b, gamma, limiter, st);
-    else
-        return -1;
+    const MortarArgs A = {m.slot, m.slot_node, m.slot_partner, m.M, uout, b, gamma, limiter, st};
+    const dim3 grid((m.M * 3 * (N + 1) + 255) / 256);
+    if (N == 3) hipLaunchKernelGGL(k_mortar<3>, grid, dim3(256), 0, s, A);
+    else if (N == 4) hipLaunchKernelGGL(k_mortar<4>, grid, dim3(256), 0, s, A);
+    else return -1;
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
