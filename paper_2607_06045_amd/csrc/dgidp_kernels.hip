@@ -1970,6 +1970,31 @@ void k_stage(StageArgs A)
 }
 
 // ---------------------------------------------------------------------------
+// kernels of a row or column of nodes per lane (large meshes' time step, sensors): every
+// wave works alone on 64 / (N+1) elements
+// ---------------------------------------------------------------------------
+template <int N>
+struct RowGeo {
+    static constexpr int n = N + 1, NN = n * n;
+    static constexpr int WE = 64 / n;                     // elements per wave: 16 at N = 3, 12 at N = 4
+    static constexpr int L = WE * n;                      // lanes with a row or column
+    static constexpr int PER = (WE * NN + 63) / 64;       // nodes per lane when loading
+    // LDS strides: rows 5 doubles apart and elements 20 (N = 3) or 25 apart: the 16
+    // lanes of an access differ modulo 16 (but for two pairs at N = 4 by columns)
+    static constexpr int RS = 5, ES = RS * n;
+    static constexpr int kWaves = 4;                      // per block
+};
+
+// orders the LDS accesses of one wave (which the hardware keeps in order) for the
+// compiler; no wave waits for another
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// ---------------------------------------------------------------------------
 // time step: per node sum_j 2 d_ij / m_i (or the low-order estimate), block max
 // ---------------------------------------------------------------------------
 struct DtArgs {
@@ -1991,6 +2016,23 @@ struct DtArgs {
 __device__ __forceinline__ double wave_speed(const NodeP& s, int d)
 {
     return fabs(d == 0 ? s.v1 : s.v2) + s.c;
+}
+
+// the block's maximum (of its waves' in red) into one of the accumulators
+template <int NW>
+__device__ __forceinline__ void dt_merge(const DtArgs& A, const double* red)
+{
+    if (threadIdx.x == 0) {
+        // non-negative doubles order like their bit patterns; NaN and zero
+        // maxima are left out, as fmax would
+        double m = red[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) m = fmax(m, red[w]);
+        if (m > 0.0)
+            atomicMax(A.acc + (blockIdx.x % kDtSpread) * kDtStride,
+                      (unsigned long long)__double_as_longlong(m));
+    }
+    if (blockIdx.x == 0 && threadIdx.x < kDtSpread) A.other[threadIdx.x * kDtStride] = 0ull;
 }
 
 // the dt kernel: kDtBlock = 256-thread blocks (16 elements at N = 3, 10 at N = 4), fewer
@@ -2124,17 +2166,178 @@ __global__ __launch_bounds__(kDtBlock) void k_dt(DtArgs A)
     s = wave_max(s);
     if ((tid & 63) == 0) sRed[tid >> 6] = s;
     __syncthreads();
-    if (tid == 0) {
-        // non-negative doubles order like their bit patterns; NaN and zero
-        // maxima are left out, as fmax would
-        double m = sRed[0];
+    dt_merge<NW>(A, sRed);
+}
+
+// The same maximum on a large mesh, by waves of 64 / (N+1) elements: the nodes' wave
+// speeds once per node, then one row of nodes per lane with the element's x faces at its
+// ends, then one column with the y faces.  Bound: memory; besides the 32 B per node the
+// face nodes' gathers, whose lines hold some five times the element's own bytes, so
+// the wave speeds across a face of one of the block's 64 or 48 consecutive elements
+// (of some 85% of the faces) come from LDS.  On 246,736 elements of N = 4 (198 MB) one
+// thread per node takes 63.4 us, rows without the shared faces 59.9, this 44.8.
+template <int N>
+__global__ __launch_bounds__(256) void k_dt_rows(DtArgs A)
+{
+    using G = RowGeo<N>;
+    constexpr int n = G::n, NN = G::NN;
+    __shared__ double sL[G::kWaves][2][G::WE * G::ES];
+    __shared__ double sM[G::kWaves][2][64];  // wave speeds across a mortar, by position
+    __shared__ double sWt[n][2 * n];          // mortar weights, read per lane
+    __shared__ double sRed[G::kWaves];
+    const Tab<N>& tb = T<N>();
+    const double g = A.gamma;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    // (contiguous element ranges per XCD from their ends, as in k_dt; elements past the
+    // last repeat it)
+    const int eb = xcd_batch_rev(blockIdx.x, gridDim.x) * (G::kWaves * G::WE), e0 = eb + wv * G::WE;
+    const int t = min(lane, G::L - 1), el = t / n, k = t - el * n;
+    const int e = min(e0 + el, A.E - 1);
+    const bool idp = A.mode != DGIDP_DT_LOWORDER;
+    double* const lx = sL[wv][0];
+    double* const ly = sL[wv][1];
+    if (threadIdx.x < 2 * NN) (&sWt[0][0])[threadIdx.x] = (&tb.Wt[0][0])[threadIdx.x];
+    const double hx = A.h[2 * e], hy = A.h[2 * e + 1], wk = tb.w[k];
+    int code[4] = {-1, -1, -1, -1}, nb[4] = {0, 0, 0, 0};
+    double fu[4][4];  // the states across the faces at position k, or the boundary node's own
+    if (idp) {
+        __builtin_memcpy(code, __builtin_assume_aligned(A.fmort + 4 * (size_t)e, 16), 16);
+        __builtin_memcpy(nb, __builtin_assume_aligned(A.fnbr + 4 * (size_t)e, 16), 16);
 #pragma unroll
-        for (int w = 1; w < NW; ++w) m = fmax(m, sRed[w]);
-        if (m > 0.0)
-            atomicMax(A.acc + (blockIdx.x % kDtSpread) * kDtStride,
-                      (unsigned long long)__double_as_longlong(m));
+        for (int f = 0; f < 4; ++f) {
+            nb[f] -= eb;
+            if (code[f] != -1 || (unsigned)nb[f] >= (unsigned)(G::kWaves * G::WE))
+                load_u<N>(A.u, code[f] < -1 ? e : nb[f] + eb, face_q<N>(code[f] < -1 ? f : f ^ 1, k), fu[f]);
+        }
     }
-    if (blockIdx.x == 0 && tid < kDtSpread) A.other[tid * kDtStride] = 0ull;
+#pragma unroll
+    for (int i = 0; i < G::PER; ++i) {
+        const int j = lane + 64 * i, ej = j / NN, q = j - ej * NN;
+        NodeP o;
+        load_node<N>(A.u, min(e0 + ej, A.E - 1), q, o, g);
+        if (G::WE * NN % 64 == 0 || i + 1 < G::PER || ej < G::WE) {
+            const int at = ej * G::ES + (q / n) * G::RS + q % n;
+            lx[at] = wave_speed(o, 0);
+            ly[at] = wave_speed(o, 1);
+        }
+    }
+    // wave speeds across the faces at position k: of an element of another block from its
+    // state, of one of this block from LDS
+    // (lo2: of the second small element of a large side)
+    double lo[4] = {0.0, 0.0, 0.0, 0.0}, lo2[4] = {0.0, 0.0, 0.0, 0.0};
+    auto inside = [&](int f) { return code[f] == -1 && (unsigned)nb[f] < (unsigned)(G::kWaves * G::WE); };
+    if (idp) {
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            if (inside(f)) continue;
+            NodeP o;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) o.u[v] = fu[f][v];
+            make_node(o, g);
+            if (code[f] < -1) {  // boundary: the ghost state of the face node
+                const int j = (-2 - code[f]) * n + k;
+                double x[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) x[v] = A.bext[(size_t)j * 4 + v];
+                NodeP b;
+                boundary_ghost(A.bkind[j], x, o, f, g, b.u);
+                make_node(b, g);
+                o = b;
+            }
+            lo[f] = wave_speed(o, f >> 1);
+        }
+        auto large = [&](int f) { return code[f] >= 0 && !fm_small(code[f]); };
+        if (large(0) || large(1) || large(2) || large(3)) {
+            // (the state's registers are free again: all four faces' loads first)
+#pragma unroll
+            for (int f = 0; f < 4; ++f)
+                if (large(f)) load_u<N>(A.u, A.fnbr2[e * 4 + f], face_q<N>(f ^ 1, k), fu[f]);
+#pragma unroll
+            for (int f = 0; f < 4; ++f) {
+                if (!large(f)) continue;
+                NodeP o;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) o.u[v] = fu[f][v];
+                make_node(o, g);
+                lo2[f] = wave_speed(o, f >> 1);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            if (!inside(f)) continue;
+            const int w = nb[f] / G::WE, q = face_q<N>(f ^ 1, k);
+            lo[f] = sL[w][f >> 1][(nb[f] - w * G::WE) * G::ES + (q / n) * G::RS + q % n];
+        }
+    }
+    __syncthreads();  // the rows are summed in place
+    // edges across face f at position k: 2 |c_ij| lambda_ij, lm the wave speed of this side
+    auto face = [&](int f, double lm) {
+        const double hf = f < 2 ? hy : hx;
+        double sum = 0.5 * wk * hf * fmax(lm, lo[f]);
+        if (__any(code[f] >= 0)) {
+            // mortar: the wave speeds of the other side by position (large side:
+            // of both small elements; small side: of the large one)
+            sM[wv][0][lane] = lo[f];
+            sM[wv][1][lane] = lo2[f];
+            wave_sync();
+            if (code[f] >= 0) {
+                const bool small = fm_small(code[f]);
+                sum = 0.0;
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh) {
+                    if (small && hh != fm_half(code[f])) continue;
+#pragma unroll
+                    for (int l = 0; l < n; ++l) {
+                        const double wt = small ? 2.0 * sWt[l][hh * n + k] : sWt[k][hh * n + l];
+                        if (wt == 0.0) continue;
+                        sum += 2.0 * wt * hf * 0.25 * fmax(lm, sM[wv][small ? 0 : hh][el * n + l]);
+                    }
+                }
+            }
+            wave_sync();
+        }
+        return sum;
+    };
+    double y[n], s = 0.0;
+    if (idp) {
+        // edges along x carry 2 |c| = w_b h_y / 2, along y w_a h_x / 2
+        double* row = lx + t * G::RS;
+#pragma unroll
+        for (int i = 0; i < n; ++i) y[i] = row[i];
+        double prev = face(0, y[0]);
+        const double last = face(1, y[N]), cx = 0.5 * wk * hy;
+#pragma unroll
+        for (int i = 0; i < n; ++i) {
+            const double next = i < N ? cx * fmax(y[i], y[i + 1 < n ? i + 1 : N]) : last;
+            row[i] = prev + next;
+            prev = next;
+        }
+        wave_sync();
+    }
+    const double* colx = lx + el * G::ES + k;
+    const double* coly = ly + el * G::ES + k;
+#pragma unroll
+    for (int j = 0; j < n; ++j) y[j] = coly[j * G::RS];
+    if (idp) {
+        double prev = face(2, y[0]);
+        const double last = face(3, y[N]), cy = 0.5 * wk * hx;
+#pragma unroll
+        for (int j = 0; j < n; ++j) {
+            const double next = j < N ? cy * fmax(y[j], y[j + 1 < n ? j + 1 : N]) : last;
+            s = fmax(s, (colx[j * G::RS] + (prev + next)) * tb.winv[j]);
+            prev = next;
+        }
+        s *= 4.0 * frcp(hx * hy) * tb.winv[k];
+    } else {
+#pragma unroll
+        for (int j = 0; j < n; ++j)
+            s = fmax(s, (N + 1) * (colx[j * G::RS] * frcp(hx) + y[j] * frcp(hy)));
+    }
+    s = wave_max(s);
+    if (lane == 0) sRed[wv] = s;
+    __syncthreads();
+    dt_merge<G::kWaves>(A, sRed);
 }
 
 // ---------------------------------------------------------------------------
@@ -2161,34 +2364,13 @@ __global__ __launch_bounds__(kDtBlock) void k_dt(DtArgs A)
 // whole reduction against this one: modal indicator 51 -> 30 us, features 50 -> 33,
 // learned indicator 62 -> 43.
 // ---------------------------------------------------------------------------
-template <int N>
-struct ModalGeo {
-    static constexpr int n = N + 1, NN = n * n;
-    static constexpr int WE = 64 / n;                     // elements per wave: 16 at N = 3, 12 at N = 4
-    static constexpr int L = WE * n;                      // lanes with a row or column
-    static constexpr int PER = (WE * NN + 63) / 64;       // nodes per lane when loading
-    // LDS strides: rows 5 doubles apart and elements 20 (N = 3) or 25 apart: the 16
-    // lanes of an access differ modulo 16 (but for two pairs at N = 4 by columns)
-    static constexpr int RS = 5, ES = RS * n;
-    static constexpr int kWaves = 4;                      // per block
-};
-
-// orders the LDS accesses of one wave (which the hardware keeps in order) for the
-// compiler; no wave waits for another
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // density and pressure of the wave's nodes lane + 64 i of elements e0 .. e0 + WE - 1
 // (elements past the last repeat it)
 template <int N>
 __device__ __forceinline__ void modal_load(const double* __restrict__ u, int e0, int E, double gamma, int lane,
-                                           double (&r)[ModalGeo<N>::PER], double (&p)[ModalGeo<N>::PER])
+                                           double (&r)[RowGeo<N>::PER], double (&p)[RowGeo<N>::PER])
 {
-    using G = ModalGeo<N>;
+    using G = RowGeo<N>;
     double w[G::PER][4];
 #pragma unroll
     for (int i = 0; i < G::PER; ++i) {
@@ -2209,10 +2391,10 @@ __device__ __forceinline__ void modal_load(const double* __restrict__ u, int e0,
 // WE * ES doubles.  Q's column c of the element may be overwritten by its lane
 // afterwards.
 template <int N>
-__device__ __forceinline__ void modal_modes(const Tab<N>& tb, double* Q, const double (&x)[ModalGeo<N>::PER],
+__device__ __forceinline__ void modal_modes(const Tab<N>& tb, double* Q, const double (&x)[RowGeo<N>::PER],
                                             int lane, int t, double (&m)[N + 1])
 {
-    using G = ModalGeo<N>;
+    using G = RowGeo<N>;
     constexpr int n = G::n;
 #pragma unroll
     for (int i = 0; i < G::PER; ++i) {
@@ -2251,7 +2433,7 @@ __global__ __launch_bounds__(256) void k_indicator(const double* __restrict__ u,
                                                    const int* __restrict__ perm, double gamma, double thresh,
                                                    double sharp, OUT* __restrict__ alpha)
 {
-    using G = ModalGeo<N>;
+    using G = RowGeo<N>;
     constexpr int n = G::n;
     __shared__ double sQ[G::kWaves][G::WE * G::ES];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -2292,7 +2474,7 @@ __global__ __launch_bounds__(256) void k_indicator(const double* __restrict__ u,
 template <int N, bool SHOCK, typename OUT>
 static void launch_modal(int E, const double* u, const int* perm, double gamma, OUT* alpha, hipStream_t s)
 {
-    using G = ModalGeo<N>;
+    using G = RowGeo<N>;
     const double thresh = 0.5 * std::pow(10.0, -1.8 * std::pow((double)(N + 1), 0.25));
     const double sharp = std::log((1.0 - 1e-4) / 1e-4);
     hipLaunchKernelGGL((k_indicator<N, SHOCK, OUT>), dim3((E - 1) / (G::kWaves * G::WE) + 1), dim3(256), 0, s, u, E,
@@ -2308,7 +2490,7 @@ __global__ __launch_bounds__(256) void k_features(const double* __restrict__ u, 
                                                   const int* __restrict__ perm, double gamma,
                                                   const uint16_t* __restrict__ wb, float* __restrict__ out)
 {
-    using G = ModalGeo<N>;
+    using G = RowGeo<N>;
     constexpr int n = G::n, NT = NET ? 2 : 1;
     static_assert(NT * G::WE <= 32 && N >= 3, "one network pass per wave; shells N-3 .. N");
     static_assert(G::WE * 16 % 64 == 0, "whole waves of features");
@@ -2378,7 +2560,7 @@ template <int N, bool NET>
 static void launch_features(int E, const double* u, const int* perm, double gamma, const uint16_t* wb, float* out,
                             hipStream_t s)
 {
-    constexpr int per = ModalGeo<N>::kWaves * ModalGeo<N>::WE * (NET ? 2 : 1);
+    constexpr int per = RowGeo<N>::kWaves * RowGeo<N>::WE * (NET ? 2 : 1);
     hipLaunchKernelGGL((k_features<N, NET>), dim3((E - 1) / per + 1), dim3(256), 0, s, u, E, perm, gamma, wb, out);
 }
 
@@ -2866,11 +3048,22 @@ int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, 
     A.mode = mode;
     A.acc = acc;
     A.other = other;
-    if (N == 3)
-        hipLaunchKernelGGL(k_dt<3>, dim3((m.E + DtGeo<3>::EPB - 1) / DtGeo<3>::EPB), dim3(kDtBlock), 0, s, A);
-    else if (N == 4)
-        hipLaunchKernelGGL(k_dt<4>, dim3((m.E + DtGeo<4>::EPB - 1) / DtGeo<4>::EPB), dim3(kDtBlock), 0, s, A);
-    else return -1;
+    // rows and columns per lane from kRowsMin elements on: its chain is longer, and
+    // below, fewer waves than fill the chip are left.  Of a blast with one refined
+    // level, one thread per node against rows: N = 3, 19,864 elements 6.9 and 8.6 us,
+    // 31,012 8.2 and 8.8, 44,688 9.8 and 9.7, 60,856 12.8 and 11.6; N = 4, 31,012 11.2 and
+    // 11.7, 44,688 14.9 and 13.5, 79,420 21.6 and 18.9.
+    constexpr int kRowsMin = 40960;
+    if (N != 3 && N != 4) return -1;
+    if (m.E >= kRowsMin) {
+        if (N == 3) hipLaunchKernelGGL(k_dt_rows<3>, dim3((m.E - 1) / (4 * RowGeo<3>::WE) + 1), dim3(256), 0, s, A);
+        else hipLaunchKernelGGL(k_dt_rows<4>, dim3((m.E - 1) / (4 * RowGeo<4>::WE) + 1), dim3(256), 0, s, A);
+    } else {
+        if (N == 3)
+            hipLaunchKernelGGL(k_dt<3>, dim3((m.E + DtGeo<3>::EPB - 1) / DtGeo<3>::EPB), dim3(kDtBlock), 0, s, A);
+        else
+            hipLaunchKernelGGL(k_dt<4>, dim3((m.E + DtGeo<4>::EPB - 1) / DtGeo<4>::EPB), dim3(kDtBlock), 0, s, A);
+    }
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
