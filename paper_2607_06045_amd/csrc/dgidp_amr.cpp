@@ -66,7 +66,7 @@ int across(const LeafLookup& L, const int8_t* lev, const int32_t* ix, const int3
 }  // namespace
 
 int adapt_leaves(int64_t E, const int8_t* lev, const int32_t* ix, const int32_t* iy, int nx0,
-                 int ny0, const int8_t* flags, AdaptPlan& plan, std::string& err)
+                 int ny0, const int8_t* flags, AdaptPlan& plan, std::string& err, const LeafLookup* leaves)
 {
     if (E <= 0 || !lev || !ix || !iy || !flags || nx0 <= 0 || ny0 <= 0) {
         err = "invalid adaptation arguments";
@@ -77,8 +77,9 @@ int adapt_leaves(int64_t E, const int8_t* lev, const int32_t* ix, const int32_t*
             err = "refinement beyond level 20";
             return DGIDP_E_INVALID_ARG;
         }
-    LeafLookup L;
-    L.build(E, lev, ix, iy, nx0, ny0);
+    LeafLookup own;
+    if (!leaves) own.build(E, lev, ix, iy, nx0, ny0);
+    const LeafLookup& L = leaves ? *leaves : own;
     // rules 1-2
     std::vector<char> ref((size_t)E, 0);
     std::vector<int64_t> work;

@@ -6,6 +6,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <string>
 #include <unordered_map>
 #include <vector>
@@ -27,14 +28,16 @@ using namespace dgidp;
 // every array each time.  The state alternates between two slots so that an
 // adaptation can read the old state while it writes the new one.
 enum PoolSlot {
-    P_FNBR, P_FNBR2, P_FMORT, P_MORT, P_H, P_SNODE, P_SPART, P_PERM, P_BKIND, P_BEXT, P_SLOT, P_BLIST,
-    P_SHOCK, P_LSV, P_U0, P_U1, P_W1, P_W2, P_TKIND, P_TSRC, P_TGRP, P_TCOUNT,
+    P_MESH, P_SLOT, P_SHOCK, P_LSV, P_U0, P_U1, P_W1, P_W2, P_TKIND, P_TSRC, P_TGRP, P_TCOUNT,
     P_COUNT
 };
 struct PoolBuf {
     void* p = nullptr;
     size_t cap = 0;
 };
+
+constexpr size_t kStageMax = size_t(32) << 20;
+constexpr size_t kResultBytes = std::max(sizeof(DevStats) * kStatSpread, sizeof(unsigned long long) * kDtWords);
 
 struct dgidp_ctx {
     dgidp_params p{};
@@ -49,6 +52,14 @@ struct dgidp_ctx {
     double x0 = 0, y0 = 0, Lx = 1, Ly = 1;
     int nx0 = 1, ny0 = 1;
     std::vector<double> hh;  // internal [E*2]
+    std::unique_ptr<LeafLookup> leaves;  // of the current mesh (dense tables only)
+    // page-locked host memory: results (kResultBytes, see fetch), and an adapted mesh's
+    // arrays on their way to the device (kept from one adaptation to the next, at
+    // most kStageMax)
+    char* result = nullptr;
+    int fetches = 0;
+    char* stage_buf = nullptr;
+    size_t stage_cap = 0;
     // device
     DevMesh dm;
     double *U = nullptr, *W1 = nullptr, *W2 = nullptr;
@@ -147,15 +158,53 @@ void free_mesh(dgidp_ctx* c)
     c->E = c->M = 0;
     c->NB = 0;
     c->bface_elem.clear();
+    c->leaves.reset();
     c->has_state = false;
 }
 
-template <typename T>
-int upload(dgidp_ctx* ctx, int slot, T*& dst, const std::vector<T>& src)
+// Arrays for one device buffer, at offsets that are multiples of 256 bytes.
+struct MeshPack {
+    struct Item {
+        void** dst;
+        const void* src;
+        size_t bytes, at;
+    };
+    std::vector<Item> items;
+    size_t total = 0;
+    template <typename T>
+    void add(T*& dst, const std::vector<T>& src)
+    {
+        items.push_back({(void**)&dst, src.data(), src.size() * sizeof(T), total});
+        total += (std::max<size_t>(1, src.size()) * sizeof(T) + 255) & ~size_t(255);
+    }
+};
+
+// Place and copy the arrays.  staged (adaptations, which repeat): through page-locked
+// memory in one copy; on the 22,156-leaf mesh 137 us, and 208 in 11 copies of pageable
+// memory.  The first upload of a mesh would pay more for allocating that memory than it
+// saves.  The copies are complete on return.
+int upload(dgidp_ctx* ctx, int slot, const MeshPack& pack, bool staged)
 {
-    const size_t bytes = std::max<size_t>(1, src.size()) * sizeof(T);
-    if (int rc = pool_get(ctx, slot, bytes, dst)) return rc;
-    if (!src.empty()) HIPCHK(hipMemcpy(dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice));
+    char* base = nullptr;
+    if (int rc = pool_get(ctx, slot, pack.total, base)) return rc;
+    for (const auto& it : pack.items) *it.dst = base + it.at;
+    if (staged && pack.total > ctx->stage_cap && pack.total <= kStageMax) {
+        if (ctx->stage_buf) (void)hipHostFree(ctx->stage_buf);
+        ctx->stage_buf = nullptr;
+        ctx->stage_cap = 0;
+        const size_t want = std::min(kStageMax, pack.total + pack.total / 2);
+        if (hipHostMalloc((void**)&ctx->stage_buf, want, hipHostMallocDefault) == hipSuccess) ctx->stage_cap = want;
+        else ctx->stage_buf = nullptr, (void)hipGetLastError();
+    }
+    if (staged && pack.total <= ctx->stage_cap) {
+        for (const auto& it : pack.items)
+            if (it.bytes) std::memcpy(ctx->stage_buf + it.at, it.src, it.bytes);
+        HIPCHK(hipMemcpyAsync(base, ctx->stage_buf, pack.total, hipMemcpyHostToDevice, ctx->stream));
+        HIPCHK(hipStreamSynchronize(ctx->stream));
+        return 0;
+    }
+    for (const auto& it : pack.items)
+        if (it.bytes) HIPCHK(hipMemcpy(*it.dst, it.src, it.bytes, hipMemcpyHostToDevice));
     return 0;
 }
 
@@ -184,11 +233,30 @@ double host_pressure(const double* u, double g)
     return (g - 1.0) * (u[3] - 0.5 * (u[1] * u[1] + u[2] * u[2]) / u[0]);
 }
 
+// Copy bytes (at most kResultBytes) from the device after the queued work and wait.
+// From the kFetchMin-th time on through page-locked memory: a copy of 8 KB into
+// pageable memory takes some 13 us longer, allocating page-locked memory once some
+// 130.  Three steps of the 22,732-leaf jet, which fetch dt and the statistics, took
+// 645 us before and 563 with it and with dt and statistics in one copy where a step
+// returns both.
+int fetch(dgidp_ctx* ctx, void* dst, const void* src, size_t bytes)
+{
+    constexpr int kFetchMin = 10;
+    if (!ctx->result && ctx->fetches < kFetchMin && ++ctx->fetches == kFetchMin &&
+        hipHostMalloc((void**)&ctx->result, kResultBytes, hipHostMallocDefault) != hipSuccess) {
+        ctx->result = nullptr;
+        (void)hipGetLastError();
+    }
+    HIPCHK(hipMemcpyAsync(ctx->result ? ctx->result : dst, src, bytes, hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    if (ctx->result) std::memcpy(dst, ctx->result, bytes);
+    return 0;
+}
+
 int sync_stats(dgidp_ctx* ctx, dgidp_stats* s, int nstages)
 {
     std::array<DevStats, kStatSpread> h;
-    HIPCHK(hipMemcpyAsync(h.data(), ctx->stats, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(hipStreamSynchronize(ctx->stream));
+    if (int rc = fetch(ctx, h.data(), ctx->stats, sizeof(h))) return rc;
     *s = dgidp_stats();
     s->theta_vol_min = s->theta_mort_min = 1.0;
     double av = 0.0, am = 0.0;
@@ -225,6 +293,7 @@ struct HostMesh {
     std::vector<int> fnbr2;         // [E*4] second small element of a large face, else -1
     std::vector<int> mort;          // [M*4] large, face, small0, small1
     std::vector<int> snode, spart;  // [M*3n]
+    LeafLookup find;
 };
 
 int build_host_mesh(int N, int64_t E, const int8_t* level, const int32_t* ix, const int32_t* iy,
@@ -269,7 +338,7 @@ int build_host_mesh(int N, int64_t E, const int8_t* level, const int32_t* ix, co
         err = "leaf " + std::to_string(bad) + " outside the root grid";
         return DGIDP_E_MESH_GAP_OR_OVERLAP;
     }
-    LeafLookup find;
+    LeafLookup& find = hm.find;
     const int64_t dup = find.build(E, level, ix, iy, nx0, ny0);
     if (dup >= 0) {
         err = "duplicate leaf " + std::to_string(dup);
@@ -354,8 +423,7 @@ int build_host_mesh(int N, int64_t E, const int8_t* level, const int32_t* ix, co
             ord[e] = {morton((uint64_t)ix[e] << s, (uint64_t)iy[e] << s), (int)e};
         }
     });
-    // (the keys are distinct: chunk sorts merged give the serial order)
-    par_sort(ord);
+    radix_sort(ord);
     {
         const int64_t epb = stage_block_elems(N);
         const int64_t nb = (E + epb - 1) / epb, q = nb >> 3, r = nb & 7;
@@ -441,7 +509,7 @@ int build_host_mesh(int N, int64_t E, const int8_t* level, const int32_t* ix, co
         par_for(nc, [&](int64_t c0, int64_t c1) {
             for (int64_t c = c0; c < c1; ++c)
                 for (int64_t k = nk * c / nc; k < nk * (c + 1) / nc; ++k) at[c + 1] += large[k];
-        }, 1);
+        }, 16);
         for (int64_t c = 0; c < nc; ++c) at[c + 1] += at[c];
         M = (int)at[nc];
         hm.mort.resize((size_t)M * 4);
@@ -459,7 +527,7 @@ int build_host_mesh(int N, int64_t E, const int8_t* level, const int32_t* ix, co
                         ++S;
                     }
             }
-        }, 1);
+        }, 16);
     }
     // pass 2: small sides point at the large element and carry their half
     par_for(M, [&](int64_t lo, int64_t hi) {
@@ -629,6 +697,8 @@ void dgidp_destroy(dgidp_ctx* ctx)
     if (ctx->cap) (void)hipStreamDestroy(ctx->cap);
     dfree(ctx->stats);
     dfree(ctx->bad);
+    if (ctx->result) (void)hipHostFree(ctx->result);
+    if (ctx->stage_buf) (void)hipHostFree(ctx->stage_buf);
     delete ctx;
 }
 
@@ -646,9 +716,10 @@ int dgidp_synchronize(dgidp_ctx* ctx)
     return 0;
 }
 
-int dgidp_mesh_upload(dgidp_ctx* ctx, int64_t E, const int8_t* level, const int32_t* ix,
-                      const int32_t* iy, double x0, double y0, double Lx, double Ly, int nx0,
-                      int ny0)
+// again: the mesh follows another by adaptation
+static int mesh_upload(dgidp_ctx* ctx, int64_t E, const int8_t* level, const int32_t* ix,
+                       const int32_t* iy, double x0, double y0, double Lx, double Ly, int nx0,
+                       int ny0, bool again)
 {
     if (!ctx) return DGIDP_E_INVALID_ARG;
     if (!(Lx > 0) || !(Ly > 0)) return fail(ctx, DGIDP_E_INVALID_ARG, "invalid domain size");
@@ -702,14 +773,19 @@ int dgidp_mesh_upload(dgidp_ctx* ctx, int64_t E, const int8_t* level, const int3
             if (pass == 0 && mort) ++nbm;
         }
     int rc = 0;
-    if ((rc = upload(ctx, P_FNBR, ctx->dm.fnbr, hm.fnbr)) || (rc = upload(ctx, P_FNBR2, ctx->dm.fnbr2, hm.fnbr2)) ||
-        (rc = upload(ctx, P_BLIST, ctx->dm.blist, blist)) ||
-        (rc = upload(ctx, P_FMORT, ctx->dm.fmort, hm.fmort)) ||
-        (rc = upload(ctx, P_MORT, ctx->dm.mort, hm.mort)) || (rc = upload(ctx, P_H, ctx->dm.h, hh)) ||
-        (rc = upload(ctx, P_SNODE, ctx->dm.slot_node, hm.snode)) ||
-        (rc = upload(ctx, P_SPART, ctx->dm.slot_partner, hm.spart)) ||
-        (rc = upload(ctx, P_PERM, ctx->dm.perm, hm.perm)) ||
-        (rc = upload(ctx, P_BKIND, ctx->dm.bkind, bkind)) || (rc = upload(ctx, P_BEXT, ctx->dm.bext, bext))) {
+    MeshPack pack;
+    pack.add(ctx->dm.fnbr, hm.fnbr);
+    pack.add(ctx->dm.fnbr2, hm.fnbr2);
+    pack.add(ctx->dm.fmort, hm.fmort);
+    pack.add(ctx->dm.mort, hm.mort);
+    pack.add(ctx->dm.h, hh);
+    pack.add(ctx->dm.slot_node, hm.snode);
+    pack.add(ctx->dm.slot_partner, hm.spart);
+    pack.add(ctx->dm.perm, hm.perm);
+    pack.add(ctx->dm.blist, blist);
+    pack.add(ctx->dm.bkind, bkind);
+    pack.add(ctx->dm.bext, bext);
+    if ((rc = upload(ctx, P_MESH, pack, again))) {
         free_mesh(ctx);  // no half-built mesh: the context has none
         return rc;
     }
@@ -731,7 +807,15 @@ int dgidp_mesh_upload(dgidp_ctx* ctx, int64_t E, const int8_t* level, const int3
     ctx->dm.E = (int)E;
     ctx->dm.M = M;
     ctx->dm.nbm = nbm;
+    if (hm.find.dense()) ctx->leaves.reset(new LeafLookup(std::move(hm.find)));
     return 0;
+}
+
+int dgidp_mesh_upload(dgidp_ctx* ctx, int64_t E, const int8_t* level, const int32_t* ix,
+                      const int32_t* iy, double x0, double y0, double Lx, double Ly, int nx0,
+                      int ny0)
+{
+    return mesh_upload(ctx, E, level, ix, iy, x0, y0, Lx, Ly, nx0, ny0, false);
 }
 
 int dgidp_mesh_validate(int N, int64_t n_leaves, const int8_t* level, const int32_t* ix,
@@ -983,10 +1067,8 @@ static int host_dt(dgidp_ctx* ctx, double cfl, int mode, double* dt)
     DtSource src;
     int rc = enqueue_dt(ctx, cfl, mode, &src);
     if (rc) return rc;
-    std::vector<unsigned long long> bits(kDtWords);
-    HIPCHK(hipMemcpyAsync(bits.data(), src.dtmax, kDtWords * sizeof(unsigned long long),
-                          hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(hipStreamSynchronize(ctx->stream));
+    std::array<unsigned long long, kDtWords> bits;
+    if ((rc = fetch(ctx, bits.data(), src.dtmax, sizeof(bits)))) return rc;
     double m = 0.0;
     for (int i = 0; i < kDtSpread; ++i) {
         double v;
@@ -1107,11 +1189,12 @@ int dgidp_step(dgidp_ctx* ctx, double cfl, double* dt_used, dgidp_stats* s)
     int rc = enqueue_dt(ctx, cfl, ctx->p.dt_mode, &src);
     if (rc) return rc;
     if ((rc = ssprk3(ctx, s, src))) return rc;
-    if (dt_used) {
-        HIPCHK(hipMemcpyAsync(dt_used, ctx->dt_dev, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-        HIPCHK(hipStreamSynchronize(ctx->stream));
+    if (s) {  // (the statistics hold dt)
+        if ((rc = sync_stats(ctx, s, 3))) return rc;
+        if (dt_used) *dt_used = s->dt;
+    } else if (dt_used) {
+        return fetch(ctx, dt_used, ctx->dt_dev, sizeof(double));
     }
-    if (s) return sync_stats(ctx, s, 3);
     return 0;
 }
 
@@ -1264,7 +1347,7 @@ int dgidp_refine_coarsen(dgidp_ctx* ctx, const int8_t* flags, double zs_eps, int
     AdaptPlan plan;
     std::string err;
     int rc = adapt_leaves(ctx->E, ctx->level.data(), ctx->ix.data(), ctx->iy.data(), ctx->nx0,
-                          ctx->ny0, flags, plan, err);
+                          ctx->ny0, flags, plan, err, ctx->leaves.get());
     if (rc) return fail(ctx, rc, err);
     const int64_t En = (int64_t)plan.level.size();
     // the new mesh must fit the index range of the kernels (the limit that
@@ -1280,8 +1363,8 @@ int dgidp_refine_coarsen(dgidp_ctx* ctx, const int8_t* flags, double zs_eps, int
     double* uold = ctx->U;
     ctx->u_slot ^= 1;
     const double x0 = ctx->x0, y0 = ctx->y0, Lx = ctx->Lx, Ly = ctx->Ly;
-    rc = dgidp_mesh_upload(ctx, En, plan.level.data(), plan.ix.data(), plan.iy.data(), x0, y0, Lx,
-                           Ly, ctx->nx0, ctx->ny0);
+    rc = mesh_upload(ctx, En, plan.level.data(), plan.ix.data(), plan.iy.data(), x0, y0, Lx, Ly,
+                     ctx->nx0, ctx->ny0, true);
     if (rc) return rc;
     // new external -> new internal
     std::vector<int> inv_new((size_t)En);

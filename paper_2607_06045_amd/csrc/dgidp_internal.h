@@ -111,8 +111,11 @@ struct AdaptPlan {
     std::vector<int64_t> src;  // [4 * new leaves]
     int64_t n_refined = 0, n_balance = 0, n_coarsened = 0;
 };
+// leaves: the lookup of these leaves, if the caller has it
+class LeafLookup;
 int adapt_leaves(int64_t E, const int8_t* lev, const int32_t* ix, const int32_t* iy, int nx0,
-                 int ny0, const int8_t* flags, AdaptPlan& plan, std::string& err);
+                 int ny0, const int8_t* flags, AdaptPlan& plan, std::string& err,
+                 const LeafLookup* leaves = nullptr);
 
 // transfer onto a new mesh, new internal element order: tkind[e] 0 copy,
 // 1 child, 2 parent; tsrc[e][4] old internal elements (child: parent, child

@@ -77,6 +77,7 @@ class LeafLookup {
     }
 
     int max_level() const { return lmax_; }
+    bool dense() const { return dense_; }
 
   private:
     static uint64_t key(int l, int64_t i, int64_t j)
