@@ -1,6 +1,6 @@
 // HIP kernels of dgidp for gfx950 (MI355X).
 //
-// One SSP-RK3 stage (Sec. 2.3 and Sec. 3 intro of the paper) is two kernels:
+// One SSP-RK3 stage (Sec. 2.3 and Sec. 3 intro of the paper) is two parts:
 //   k_stage   one thread per LGL node; a block holds 4 elements in one wave
 //             (N = 3) or 5 elements in two waves (N = 4).  It stages the element in LDS,
 //             evaluates the surface fluxes with one lane per face node
@@ -15,9 +15,10 @@
 //             antidiffusive increment and their own admissible fraction of it.
 //   k_mortar  one thread per mortar slot: the mortar's factor is the minimum
 //             over its slots (one factor per mortar keeps the flux conservative,
-//             Sec. 2.3); corrections are added in ascending mortar order.
-// The time step (eq. timestep_restriction) is a per-block max (k_dt) merged by
-// one 64-bit atomic max per block into one of kDtSpread accumulators; the first
+//             Sec. 2.3); corrections are added in ascending mortar order.  On large
+//             meshes the first blocks of k_stage's second launch do this.
+// The time step (eq. timestep_restriction) is a per-block max (k_dt, on large meshes
+// k_dt_rows) merged by one 64-bit atomic max per block into one of kDtSpread accumulators; the first
 // stage kernel of the step reduces those and takes dt = cfl / max.
 #include <hip/hip_runtime.h>
 
@@ -68,12 +69,12 @@ __device__ __forceinline__ int xcd_batch_rev(int bid, int nb)
 
 // launch geometry per degree: one-wave blocks of 4 elements at N = 3 (the
 // phase barriers stay inside a wave and a late block holds less work),
-// two-wave blocks of 5 elements at N = 4 (125 of 128 lanes busy; a block
-// needs 19.6 KB of LDS, so eight blocks, sixteen waves, fill a compute unit
-// to the four waves per SIMD that the conforming variant's registers allow).
-// Three-wave blocks of 7 elements (175 of 192 lanes, 40 KB of LDS with all
-// pairs stored at once, four blocks per CU) took 410.9 against 385.4 us per
-// launch on the 246,736-leaf workload.
+// two-wave blocks of 5 elements at N = 4 (125 of 128 lanes busy; a block of the
+// conforming variant takes 18.3 KB of LDS, so eight blocks, sixteen waves, fill a
+// compute unit to the four waves per SIMD that its 128 registers allow).  An earlier
+// form of the kernel took 410.9 us per launch on the 246,736-leaf workload in
+// three-wave blocks of 7 elements (175 of 192 lanes, four blocks per unit), and
+// 385.4 in two-wave blocks.
 template <int N>
 struct Geo {
     static constexpr int n = N + 1, NN = n * n;
@@ -985,8 +986,8 @@ __device__ __forceinline__ void load_node(const double* u, int e, int q, NodeP& 
 // low-order solution (eq. Bounds_LowOrder), read from A.lsv
 // MORT: the launch over the element batches that hold a mortar element (the
 // surface phase with Kopriva's mortar and the sparse low-order mortar flux,
-// mortar slot records); the batches without one run the MORT = false variant,
-// which has no mortar code, fewer registers and four waves per SIMD.
+// mortar slot records), or over all; the other batches of a stage of two launches
+// run the MORT = false variant, which has no mortar code.
 // Bound: vector instructions and LDS accesses, each busy for about two thirds of
 // the time (the HBM floor is a third), so every phase is written for few of both:
 // pairs on their series or polynomial without logarithms, fluxes in their
@@ -996,14 +997,14 @@ __device__ __forceinline__ void load_node(const double* u, int e, int q, NodeP& 
 // its share of the face sums in registers, and strides without bank conflicts.
 // Conforming launch of the 246,736-leaf N = 4 mesh, per wave: 799 vector and 92
 // LDS instructions (748 LDS cycles, 186 of them conflicts), from 1,119 and 112
-// (1,121, 393); five steps of that mesh take 3.80 ms, from 4.51.  More waves do not
-// help: at 92 registers and 16.3 KB of LDS per block, five per SIMD
-// instead of four, the same instructions took the same time.
+// (1,121, 393); 182 us of the stage, from 229.  More waves do not help: at 92
+// registers and 16.3 KB of LDS per block, five per SIMD instead of four, the same
+// instructions took the same time.
 template <int N, int MODE, bool MIXED, int LIMK, bool MORT>
-// at least three waves per SIMD: the local-limiting variant would otherwise
-// take 172 registers and run two (63.3 against 67.7 us on the 22,156-leaf
-// blast with a few spilled registers; the other variants fit anyway); the
-// conforming positivity variant fits 128 registers, four waves
+// waves per SIMD: four (128 registers) with positivity limiting, but for the FP64
+// N = 3 variant with mortars (148 registers, see LATE: 353 against 346 us with four);
+// three with local bounds, which without the cap would take more than 168 registers
+// and run two (an earlier form 67.7 against 63.3 us)
 __global__ __launch_bounds__(Geo<N>::BS) __attribute__((amdgpu_waves_per_eu((LIMK == 0 && (!MORT || N == 4 || MIXED)) ? 4 : 3)))
 void k_stage(StageArgs A)
 {
