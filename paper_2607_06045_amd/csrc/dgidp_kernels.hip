@@ -1538,25 +1538,28 @@ void k_stage(StageArgs A)
                 const float L7 = unpack2(sRe[(7) * NN + q]).x, R7 = unpack2(sRe[(7) * NN + qo]).x;
                 const float rL = L5.x, rR = R5.x, zL = L6.y, zR = R6.y;
                 const float iz_ln = inv_lnmeanf(zL, zR, L7, R7);
-                // (pressures and velocities in the order of the positions along the line,
-                // so that the single precision result does not depend on who holds the pair)
-                const bool own = (c >> 11) & 1;
-                const float pL = own ? R5.y : L5.y, pR = own ? L5.y : R5.y;
-                const float vnL = (float)(own ? Rn : Ln), vnR = (float)(own ? Ln : Rn);
-                const float vtL = (float)(own ? Rt : Lt), vtR = (float)(own ? Lt : Rt);
+                const float pL = L5.y, pR = R5.y;
+                const float vnL = (float)Ln, vnR = (float)Rn, vtL = (float)Lt, vtR = (float)Rt;
                 const float vna = 0.5f * (vnL + vnR), vta = 0.5f * (vtL + vtR);
                 const float fr = lnmeanf(rL, rR, L6.x, R6.x) * vna;
+                // (sums of products in the order of the positions along the line, so that
+                // the single precision result does not depend on who holds the pair; the
+                // other terms do not change with the order)
+                const bool own = (c >> 11) & 1;
+                const float vn0 = own ? vnR : vnL, vn1 = own ? vnL : vnR;
                 float fn, ft, f3;
                 if (A.vflux == DGIDP_FLUX_CHANDRASHEKAR) {
+                    const float vt0 = own ? vtR : vtL, vt1 = own ? vtL : vtR;
                     const float pt = (rL + rR) / (zL + zR);
                     fn = fr * vna + pt;
                     ft = fr * vta;
-                    f3 = fr * ((float)ig1 * iz_ln - 0.25f * (vnL * vnL + vtL * vtL + vnR * vnR + vtR * vtR)) +
+                    f3 = fr * ((float)ig1 * iz_ln - 0.25f * (vn0 * vn0 + vt0 * vt0 + vn1 * vn1 + vt1 * vt1)) +
                          vna * fn + vta * ft;
                 } else {
+                    const float p0 = own ? pR : pL, p1 = own ? pL : pR;
                     fn = fr * vna + 0.5f * (pL + pR);
                     ft = fr * vta;
-                    f3 = fr * (0.5f * (vnL * vnR + vtL * vtR) + (float)ig1 * iz_ln) + 0.5f * (pL * vnR + pR * vnL);
+                    f3 = fr * (0.5f * (vnL * vnR + vtL * vtR) + (float)ig1 * iz_ln) + 0.5f * (p0 * vn1 + p1 * vn0);
                 }
                 f[0] = hS * fr;
                 f[1] = scale * fn;
