@@ -28,7 +28,7 @@ using namespace dgidp;
 // every array each time.  The state alternates between two slots so that an
 // adaptation can read the old state while it writes the new one.
 enum PoolSlot {
-    P_MESH, P_SLOT, P_SHOCK, P_LSV, P_U0, P_U1, P_W1, P_W2, P_TKIND, P_TSRC, P_TGRP, P_TCOUNT,
+    P_MESH, P_SLOT, P_SHOCK, P_DLO, P_LOB, P_LSV, P_U0, P_U1, P_W1, P_W2, P_TKIND, P_TSRC, P_TGRP, P_TCOUNT,
     P_COUNT
 };
 struct PoolBuf {
@@ -614,22 +614,15 @@ DtSource stored_dt(const dgidp_ctx* c)
 // one limited forward-Euler stage: uout = a un + b FE(uin), with the mesh
 // arrays and per-stage buffers of dm
 int stage_on(dgidp_ctx* ctx, const DevMesh& dm, const double* uin, const double* un, double* uout,
-             double a, double b, DevStats* st, DtSource dt, bool rev = false)
+             double a, double b, DevStats* st, const DtSource& dt, bool rev = false)
 {
     const KernelParams kp = kparams(ctx);
     // combined limiting weighs its factors with the indicator of the stage's input
-    if (kp.limiter == DGIDP_LIMIT_COMBINED && launch_shock_indicator(ctx->p.N, dm, uin, kp.gamma, ctx->stream))
+    if (kp.limiter == DGIDP_LIMIT_COMBINED && launch_shock_indicator(ctx->p.N, dm, kp, uin, ctx->stream))
         return fail(ctx, DGIDP_E_DEVICE, "indicator kernel launch failed");
-    // bounds from the low-order solution: first that solution, which also
-    // stores the step's dt if it takes it from the accumulators
-    if (kp.limiter == DGIDP_LIMIT_LOCAL_LOWORDER) {
-        if (launch_lowsol(ctx->p.N, dm, kp, uin, dt, st, ctx->stream))
-            return fail(ctx, DGIDP_E_DEVICE, "low-order solution launch failed");
-        if (dt.dtmax) {
-            dt.dt = dt.dt_out;
-            dt.dtmax = nullptr;
-        }
-    }
+    // bounds from the low-order solution: R_LO / m of the input, then the bounds
+    if (kp.limiter == DGIDP_LIMIT_LOCAL_LOWORDER && local::launch_lowsol(ctx->p.N, dm, kp, uin, dt, ctx->stream))
+        return fail(ctx, DGIDP_E_DEVICE, "low-order bounds launch failed");
     if (launch_stage(ctx->p.N, dm, kp, uin, un, uout, a, b, dt, st, ctx->stream, rev, true))
         return fail(ctx, DGIDP_E_DEVICE, "stage kernel launch failed");
     return 0;
@@ -793,7 +786,9 @@ static int mesh_upload(dgidp_ctx* ctx, int64_t E, const int8_t* level, const int
     if ((rc = pool_get(ctx, P_SLOT, (size_t)M * 3 * n * kSlotW * sizeof(double), ctx->dm.slot)) ||
         (rc = pool_get(ctx, P_SHOCK, (size_t)E * sizeof(double), ctx->dm.shock_ind)) ||
         (ctx->p.limiter == DGIDP_LIMIT_LOCAL_LOWORDER &&
-         (rc = pool_get(ctx, P_LSV, (size_t)E * 2 * NN * sizeof(double), ctx->dm.lsv))) ||
+         ((rc = pool_get(ctx, P_DLO, sz, ctx->dm.dlo)) ||
+          (rc = pool_get(ctx, P_LOB, (size_t)E * 3 * NN * sizeof(double), ctx->dm.lob)) ||
+          (rc = pool_get(ctx, P_LSV, (size_t)E * 2 * NN * sizeof(double), ctx->dm.lsv)))) ||
         (rc = pool_get(ctx, P_U0 + ctx->u_slot, sz, ctx->U)) || (rc = pool_get(ctx, P_W1, sz, ctx->W1)) ||
         (rc = pool_get(ctx, P_W2, sz, ctx->W2))) {
         free_mesh(ctx);
@@ -1238,13 +1233,11 @@ int dgidp_step_noalloc(dgidp_ctx* ctx, double cfl)
     const size_t o_w1 = take(state), o_w2 = take(state);
     const size_t o_slot = take(M * 3 * n * kSlotW * sizeof(double));
     const size_t o_ind = take(E * sizeof(double));
-    size_t o_lsv = 0;
+    size_t o_dlo = 0, o_lob = 0, o_lsv = 0;
     if (ctx->p.limiter == DGIDP_LIMIT_LOCAL_LOWORDER) {
-        // (16 B per node are used; the mode's documented 72 B per node decide
-        // which meshes fit)
-        o_lsv = take(state);
-        take(E * 3 * NN * sizeof(double));
-        take(E * 2 * NN * sizeof(double));
+        o_dlo = take(state);
+        o_lob = take(E * 3 * NN * sizeof(double));
+        o_lsv = take(E * 2 * NN * sizeof(double));
     }
     if (off > cap)
         return fail(ctx, DGIDP_E_INVALID_ARG,
@@ -1254,6 +1247,8 @@ int dgidp_step_noalloc(dgidp_ctx* ctx, double cfl)
     dm.slot = (double*)(base + o_slot);
     dm.shock_ind = (double*)(base + o_ind);
     if (ctx->p.limiter == DGIDP_LIMIT_LOCAL_LOWORDER) {
+        dm.dlo = (double*)(base + o_dlo);
+        dm.lob = (double*)(base + o_lob);
         dm.lsv = (double*)(base + o_lsv);
     }
     unsigned long long* acc = (unsigned long long*)(base + o_acc);
@@ -1292,12 +1287,12 @@ int dgidp_time_kernels(dgidp_ctx* ctx, int reps, double* ms)
     if (rc) return rc;
     if (launch_set_double(ctx->dt_dev, dt, ctx->stream)) return fail(ctx, DGIDP_E_DEVICE, "launch failed");
     if (kp.limiter == DGIDP_LIMIT_COMBINED &&
-        launch_shock_indicator(ctx->p.N, ctx->dm, ctx->U, kp.gamma, ctx->stream))
+        launch_shock_indicator(ctx->p.N, ctx->dm, kp, ctx->U, ctx->stream))
         return fail(ctx, DGIDP_E_DEVICE, "indicator kernel launch failed");
     // (the low-order solution is formed once, outside the timed stages)
     if (kp.limiter == DGIDP_LIMIT_LOCAL_LOWORDER &&
-        launch_lowsol(ctx->p.N, ctx->dm, kp, ctx->U, stored_dt(ctx), nullptr, ctx->stream))
-        return fail(ctx, DGIDP_E_DEVICE, "low-order solution launch failed");
+        local::launch_lowsol(ctx->p.N, ctx->dm, kp, ctx->U, stored_dt(ctx), ctx->stream))
+        return fail(ctx, DGIDP_E_DEVICE, "low-order bounds launch failed");
     HIPCHK(hipEventRecord(ev[0], ctx->stream));
     for (int r = 0; r < reps; ++r)
         if (launch_stage(ctx->p.N, ctx->dm, kp, ctx->U, nullptr, ctx->W1, 0.0, 1.0, stored_dt(ctx), nullptr,

@@ -68,7 +68,9 @@ struct DevMesh {
     double* slot = nullptr;     // [M*3n*kSlotW]
     int* perm = nullptr;        // [E] external index of internal element e
     double* shock_ind = nullptr;  // [E] shock indicator of combined limiting (internal order)
-    double* lsv = nullptr;      // [E*2*NN] density and ln s of the low-order solution (its bounds)
+    double* dlo = nullptr;      // [E*4*NN] R_LO / m of a stage's input (low-order-solution bounds)
+    double* lob = nullptr;      // [E*3*NN] rho min, rho max, ln s min from the low-order solution
+    double* lsv = nullptr;      // [E*2*NN] low-order density and ln s per node
     // [ceil(E / stage_block_elems(N))] stage-kernel element batches: the nbm
     // batches holding an element with a mortar face first, then the others,
     // each part in ascending order
@@ -163,15 +165,29 @@ int launch_rhs(int N, const DevMesh& m, const KernelParams& kp, const double* u,
 int launch_mortar(int N, const DevMesh& m, double* uout, double b, DevStats* st, hipStream_t s,
                   double gamma, int limiter);
 // per-element shock indicator on the pressure of u into m.shock_ind (combined limiting)
-int launch_shock_indicator(int N, const DevMesh& m, const double* u, double gamma, hipStream_t s);
-// density and log entropy of the low-order solution u + dt R_LO / m into m.lsv
-// (bounds of eq. Bounds_LowOrder); st only receives the dt it takes from dtmax
-int launch_lowsol(int N, const DevMesh& m, const KernelParams& kp, const double* u, const DtSource& dt,
-                  DevStats* st, hipStream_t s);
+int launch_shock_indicator(int N, const DevMesh& m, const KernelParams& kp, const double* u, hipStream_t s);
 // max over nodes of the dt denominator, atomically merged into the accumulator
 // set acc (all zero on entry); the set other is cleared for the next step
 int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, int mode,
               unsigned long long* acc, unsigned long long* other, hipStream_t s);
+// the modes with an arithmetic of their own (dgidp_local.hip); launch_stage, launch_dt
+// and launch_shock_indicator go there by themselves
+inline bool local_arithmetic(const KernelParams& kp)
+{
+    return kp.limiter == DGIDP_LIMIT_LOCAL || kp.limiter == DGIDP_LIMIT_LOCAL_LOWORDER ||
+           (kp.limiter == DGIDP_LIMIT_COMBINED && kp.precision == DGIDP_MIXED);
+}
+namespace local {
+int upload_tables(int N, const void* host_tab, size_t bytes);
+int launch_stage(int N, const DevMesh& m, const KernelParams& kp, const double* uin, const double* un, double* uout,
+                 double a, double b, const DtSource& dt, DevStats* st, hipStream_t s, bool rev);
+int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, int mode, unsigned long long* acc,
+              unsigned long long* other, hipStream_t s);
+int launch_shock_indicator(int N, const DevMesh& m, const double* u, double gamma, hipStream_t s);
+// local bounds from the low-order solution u + dt R_LO / m into m.lob (eq. Bounds_LowOrder);
+// m.dlo and m.lsv hold the residual and the solution's density and log entropy
+int launch_lowsol(int N, const DevMesh& m, const KernelParams& kp, const double* u, const DtSource& dt, hipStream_t s);
+}  // namespace local
 int launch_permute(int N, int E, const int* perm, const double* src, double* dst, int to_internal,
                    hipStream_t s);
 int launch_stats_reset(DevStats* st, hipStream_t s);

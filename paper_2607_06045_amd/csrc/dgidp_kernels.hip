@@ -42,6 +42,7 @@ __device__ __forceinline__ const Tab<4>& T<4>() { return c_tab4; }
 
 int upload_tables(int N, const void* host_tab, size_t bytes)
 {
+    if (local::upload_tables(N, host_tab, bytes)) return -1;
     hipError_t e = hipErrorInvalidValue;
     if (N == 3 && bytes == sizeof(Tab<3>)) e = hipMemcpyToSymbol(HIP_SYMBOL(c_tab3), host_tab, bytes);
     if (N == 4 && bytes == sizeof(Tab<4>)) e = hipMemcpyToSymbol(HIP_SYMBOL(c_tab4), host_tab, bytes);
@@ -427,13 +428,12 @@ __device__ __forceinline__ double fexp(double x)
 }
 
 // logarithm of the specific entropy, ln p - gamma ln rho (rho, p > 0, else NaN).
-// The local-limiting stages are bound by vector instructions, of which the run-time
+// Stages with local factors are bound by vector instructions, of which the run-time
 // library's two logarithms per bar state (some 160), the exponential and logarithm
-// per evaluation of the entropy root and the IEEE divisions and roots took
-// the larger part; with these forms (errors at most 0.9 ulp against its 0.6,
-// exponential, reciprocal and root alike) five steps went from 928 to 726 us with
-// bar states and 1,310 to 1,125 us with the low-order solution on the 22,156-leaf
-// blast, three of the N = 4 double Mach reflection from 838 to 674 us.
+// per evaluation of the entropy root and the IEEE divisions and roots took a large
+// part; with these forms (errors at most 0.9 ulp against its 0.6, exponential,
+// reciprocal and root alike) three steps of the blended 22,732-leaf jet went from 804
+// to 706 us.
 __device__ __forceinline__ double log_entropy(double rho, double p, double g)
 {
     double lr, lp;
@@ -888,13 +888,8 @@ __global__ __launch_bounds__(256) void k_mortar(MortarArgs A)
 // ---------------------------------------------------------------------------
 // element kernel
 // ---------------------------------------------------------------------------
-// MODE_LOWSOL: the low-order solution u + dt R_LO / m of every node, its density
-// and log entropy (+inf where density or pressure is not positive), for the
-// bounds of eq. Bounds_LowOrder, which the stage itself gathers through LDS and
-// its face lanes.  The low-order modes skip the pair fluxes.  On the 22,156-leaf
-// blast a stage's bounds cost a residual with pair fluxes (15.9 us), a pass over
-// it (6.4 us) and a gather (11.7 us) before, 10.8 us now; five steps 1,124 and 825 us.
-enum { MODE_STAGE = 0, MODE_RHS_HIGH = 1, MODE_RHS_LOW = 2, MODE_LOWSOL = 3 };
+// The low-order residual skips the pair fluxes.
+enum { MODE_STAGE = 0, MODE_RHS_HIGH = 1, MODE_RHS_LOW = 2 };
 
 struct StageArgs {
     const double* uin;
@@ -903,7 +898,6 @@ struct StageArgs {
     double a, b;
     const double* dt;
     const double* ind;  // combined limiting: shock indicator per element, in [0, 1]
-    const double* lsv;  // bounds from the low-order solution: [E][2][NN] its density and log entropy
     // when set, dt = cfl / max over the accumulator set dtmax (bits of
     // non-negative doubles); block 0 stores it in dt_out
     const unsigned long long* dtmax;
@@ -980,10 +974,10 @@ __device__ __forceinline__ void load_node(const double* u, int e, int q, NodeP& 
         X.u[3] = MIXED ? fma(X.p, ig1, 0.5 * (X.u[1] * X.v1 + X.u[2] * X.v2)) : sRe[5 * NN + (qq)]; \
     } while (0)
 
-// LIMK: 0 positivity (or none, at run time), 1 local bounds from bar states,
-// 2 the blend of positivity and bar-state local factors by the per-element
-// shock indicator A.ind (eq. combination_posLim_local), 3 local bounds from the
-// low-order solution (eq. Bounds_LowOrder), read from A.lsv
+// LIMK: 0 positivity (or none, at run time), 2 the blend of positivity and
+// bar-state local factors by the per-element shock indicator A.ind
+// (eq. combination_posLim_local); 1 and 3, local bounds alone, and the mixed
+// blend have a kernel of their own (dgidp_local.hip, which says why)
 // MORT: the launch over the element batches that hold a mortar element (the
 // surface phase with Kopriva's mortar and the sparse low-order mortar flux,
 // mortar slot records), or over all; the other batches of a stage of two launches
@@ -1003,18 +997,15 @@ __device__ __forceinline__ void load_node(const double* u, int e, int q, NodeP& 
 template <int N, int MODE, bool MIXED, int LIMK, bool MORT>
 // waves per SIMD: four (128 registers) with positivity limiting, but for the FP64
 // N = 3 variant with mortars (148 registers, see LATE: 353 against 346 us with four);
-// three with local bounds, which without the cap would take more than 168 registers
-// and run two (an earlier form 67.7 against 63.3 us)
+// three with the blend
 __global__ __launch_bounds__(Geo<N>::BS) __attribute__((amdgpu_waves_per_eu((LIMK == 0 && (!MORT || N == 4 || MIXED)) ? 4 : 3)))
 void k_stage(StageArgs A)
 {
     using G = Geo<N>;
-    // LOC: local bounds enforced; COMB: blended with positivity; BAR: the bounds
-    // come from bar states (computed here), otherwise from the low-order
-    // solution (read from A.lsv); PURE: local factors only
-    // PAIRS: the pair fluxes and antidiffusive fluxes are needed
-    constexpr bool LOC = LIMK >= 1, COMB = LIMK == 2, BAR = LIMK == 1 || LIMK == 2;
-    constexpr bool PURE = LIMK == 1 || LIMK == 3;
+    // COMB: local bounds from bar states, blended with positivity; PAIRS: the pair
+    // fluxes and antidiffusive fluxes are needed
+    static_assert(LIMK == 0 || (LIMK == 2 && !MIXED), "the other local modes have their own kernel");
+    constexpr bool COMB = LIMK == 2;
     constexpr bool PAIRS = MODE == MODE_STAGE || MODE == MODE_RHS_HIGH;
     constexpr int n = G::n, NN = G::NN, EPB = G::EPB, NT = G::NT;
     constexpr int PP = G::pp(MORT);
@@ -1034,12 +1025,10 @@ void k_stage(StageArgs A)
     // per node: rho, v1, v2, p, c, E, z = rho / p (mixed: FP32 pairs in rows 5-7)
     __shared__ double sR[EPB * G::ES];
     __shared__ double sPair[EPB * G::es(MORT)];  // pair fluxes, then antidiffusive fluxes and corner terms
-    // local bounds from the low-order solution: rows 0 and 1 its density and log
-    // entropy per node; from bar states: rows 0-3 the subcell faces owned by a node
-    // (x: density, log entropy; y: the same), rows 4-6 the face lanes' range
-    // (face f, position k at f n + k) across the element face; row 0 later the
-    // local node factors of the blend
-    __shared__ double sB[LOC ? EPB : 1][7][LOC ? NN : 1];
+    // local bounds: rows 0-3 the subcell faces owned by a node (x: density, log
+    // entropy; y: the same), rows 4-6 the face lanes' range (face f, position k at
+    // f n + k) across the element face; row 0 later the local node factors
+    __shared__ double sB[COMB ? EPB : 1][7][COMB ? NN : 1];
     __shared__ double sTw[2][n];              // LGL weights and their reciprocals, read per lane
     __shared__ double sS[n][n];               // Sbar / 2, read per pair
     // After phase 5b the primitive rows of sR are read no more: they take the
@@ -1094,7 +1083,7 @@ void k_stage(StageArgs A)
     const int fcode_f = A.fmort[e * 4 + ff];
     const int fnb = A.fnbr[e * 4 + ff];
     int fcode[4];  // the element's face codes (local bounds and mortar slots)
-    if (LOC || MORT)
+    if (COMB || MORT)
 #pragma unroll
         for (int f = 0; f < 4; ++f) fcode[f] = A.fmort[e * 4 + f];
     const int fnb2 = MORT ? A.fnbr2[e * 4 + ff] : -1;
@@ -1139,43 +1128,12 @@ void k_stage(StageArgs A)
         }
         // the blend needs local factors only where the indicator fires, and at
         // mortar nodes (their mortar may blend with another element's weight)
-        need_loc = LOC && (!COMB || w_e > 0.0 || fcode[0] >= 0 || fcode[1] >= 0 || fcode[2] >= 0 ||
+        need_loc = COMB && (w_e > 0.0 || fcode[0] >= 0 || fcode[1] >= 0 || fcode[2] >= 0 ||
                            fcode[3] >= 0);
         // ln(p rho^-gamma) of the node itself, the bar state (i, i)
         if (need_loc) ls_own = log_entropy(me.r, me.p, g);
     }
     const double hx = A.h[2 * e], hy = A.h[2 * e + 1];
-    if (LIMK == 3) {
-        // the low-order solution at the node and across this lane's face node (the
-        // matching node of a conforming face, the nodes with a nonzero sparse
-        // weight across a mortar, none across a boundary)
-        const double* own = A.lsv + ((unsigned)e * 2u * NN + (unsigned)q);
-        sB[le][0][q] = own[0];
-        sB[le][1][q] = own[NN];
-        auto gather = [&](int el, int node) {
-            const double* o = A.lsv + ((unsigned)el * 2u * NN + (unsigned)node);
-            fb_lo = fmin(fb_lo, o[0]);
-            fb_hi = fmax(fb_hi, o[0]);
-            fb_ls = fmin(fb_ls, o[NN]);
-        };
-        if (fcode_f == -1) {
-            gather(fnb, qfn);
-        } else if (MORT && fcode_f >= 0) {
-            const bool small = fm_small(fcode_f);
-            const int hh = fm_half(fcode_f);
-            const int nz = small ? tb.snc[hh][fk] : tb.lnc[fk];
-#pragma unroll 1
-            for (int i = 0; i < nz; ++i) {
-                const int col = small ? tb.snz[hh][fk][i] : tb.lnz[fk][i];  // large side: h n + l
-                gather(small || col < n ? fnb : fnb2, face_q<N>(ff ^ 1, col < n ? col : col - n));
-            }
-        }
-        if (fown || fcor) {
-            sB[le][4][ff * n + fk] = fb_lo;
-            sB[le][5][ff * n + fk] = fb_hi;
-            sB[le][6][ff * n + fk] = fb_ls;
-        }
-    }
     if (MORT && fcode_f >= 0) {
         if (!fm_small(fcode_f)) {
             // large side: stage both small traces at position fk
@@ -1253,7 +1211,7 @@ void k_stage(StageArgs A)
     double fterm[4];
     {
         NodeP own;  // the face node's state (mortars; boundaries; bar states)
-        if (MORT || BAR) LDS_NODE(own, qfo);
+        if (MORT || COMB) LDS_NODE(own, qfo);
         if (fcode_f < 0) {
             if (fcode_f < -1) {
                 NodeP me;
@@ -1286,7 +1244,7 @@ void k_stage(StageArgs A)
             F[3] = fma(K, onb[3] - E, fma(onb[3], wb, E * wa));
             F[1] = fma(Ws, p + op, F[1]);
             F[3] += fma(op, wb, p * wa);
-            if (BAR && need_loc) {
+            if (COMB && need_loc) {
                 NodeP o;
                 o.u[0] = o.r = onb[0];
                 o.u[1] = dff == 0 ? onb[1] : onb[2];
@@ -1324,7 +1282,7 @@ void k_stage(StageArgs A)
                 make_node(us, g);
                 double Gf[4];
                 llf_face(dff, lowf, own, us, Gf);
-                if (BAR && need_loc) {
+                if (COMB && need_loc) {
                     double rb, lb;
                     bar_bounds(dff, lowf, own, us, g, rb, lb);
                     fb_lo = fmin(fb_lo, rb);
@@ -1371,7 +1329,7 @@ void k_stage(StageArgs A)
                 make_node(uj, g);
                 double Gf[4];
                 llf_face(dff, lowf, own, uj, Gf);
-                if (BAR && need_loc) {
+                if (COMB && need_loc) {
                     double rb, lb;
                     bar_bounds(dff, lowf, own, uj, g, rb, lb);
                     fb_lo = fmin(fb_lo, rb);
@@ -1624,7 +1582,7 @@ void k_stage(StageArgs A)
                 FVo[d][v] = fma(-hl, o.u[v] - me.u[v], fma(o.u[v], wb, me.u[v] * wa));
             FVo[d][1 + d] = fma(hw, me.p + o.p, FVo[d][1 + d]);
             FVo[d][3] += fma(o.p, wb, me.p * wa);
-            if (BAR && need_loc) bar_bounds(d, true, me, o, g, brb[d], bls[d]);
+            if (COMB && need_loc) bar_bounds(d, true, me, o, g, brb[d], bls[d]);
         }
     }
     // the node's low-order residual so far: its surface term and the faces it owns
@@ -1684,7 +1642,7 @@ void k_stage(StageArgs A)
 #pragma unroll
         for (int v = 0; v < 4; ++v) sPe[v * PP + cs] = fterm[v];
     }
-    if (BAR && need_loc) {
+    if (COMB && need_loc) {
         if (a < N) {
             sB[le][0][q] = brb[0];
             sB[le][1][q] = bls[0];
@@ -1749,18 +1707,6 @@ void k_stage(StageArgs A)
             nmf = (cx >= 0) + (cy >= 0);
         }
     }
-    if (MODE == MODE_LOWSOL) {
-        double w[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) w[v] = u0[v] + dt * (RLO[v] * im);
-        const double p = pressure(w, g);
-        if (act) {
-            double* o = A.uout + ((unsigned)e * 2u * NN + (unsigned)q);
-            o[0] = w[0];
-            o[NN] = w[0] > 0.0 && p > 0.0 ? log_entropy(w[0], p, g) : __builtin_inf();
-        }
-        return;
-    }
     if (MODE == MODE_RHS_LOW || MODE == MODE_RHS_HIGH) {
         if (act) {
 #pragma unroll
@@ -1792,33 +1738,7 @@ void k_stage(StageArgs A)
         if (act && (!(uFV[0] > 0.0) || !(pFV > 0.0))) inad = 1;
         rmin = A.beta * uFV[0];
         pmin = A.beta * pFV;
-        if (need_loc && !BAR) {
-            // bounds from the low-order solution over the node and its low-order
-            // neighbours; the node's own low-order state, as computed here, is inside
-            // them by definition (its stored copy may differ in the last bit)
-            double rlo = uFV[0];
-            rhi = uFV[0];
-            lsi = uFV[0] > 0.0 && pFV > 0.0 ? log_entropy(uFV[0], pFV, g) : -__builtin_inf();
-            lsm = lsi;
-            auto take = [&](double lo, double hi, double ls) {
-                rlo = fmin(rlo, lo);
-                rhi = fmax(rhi, hi);
-                lsm = fmin(lsm, ls);
-            };
-            // (at the element's edge the node itself once more, and its faces)
-            const int nq[5] = {q, a > 0 ? q - 1 : q, a < N ? q + 1 : q, b > 0 ? q - n : q, b < N ? q + n : q};
-#pragma unroll
-            for (int j = 0; j < 5; ++j) take(sB[le][0][nq[j]], sB[le][0][nq[j]], sB[le][1][nq[j]]);
-            if (onf[0] || onf[1]) {
-                const int i = (onf[0] ? 0 : n) + b;
-                take(sB[le][4][i], sB[le][5][i], sB[le][6][i]);
-            }
-            if (onf[2] || onf[3]) {
-                const int i = (onf[2] ? 2 * n : 3 * n) + a;
-                take(sB[le][4][i], sB[le][5][i], sB[le][6][i]);
-            }
-            rlf = fmax(rmin, rlo);
-        } else if (need_loc) {
+        if (need_loc) {
             // bounds over the node and the bar states of its low-order neighbours
             // (the node's own bar state is its input state: no cap)
             lsi = __builtin_inf();
@@ -1867,12 +1787,8 @@ void k_stage(StageArgs A)
             cf[3][v] = -dtm * ADo[1][v];
         }
         if (A.limiter != DGIDP_LIMIT_NONE) {
-            if (PURE) {
-                th = volume_factor<true>(uFV, cf, rlf, pmin, rhi, lsm, lsi, g, ig1);
-            } else {
-                th = volume_factor<false>(uFV, cf, rmin, pmin, 0.0, 0.0, 0.0, g, ig1);
-                if (COMB && need_loc) thl = volume_factor<true>(uFV, cf, rlf, pmin, rhi, lsm, lsi, g, ig1);
-            }
+            th = volume_factor<false>(uFV, cf, rmin, pmin, 0.0, 0.0, 0.0, g, ig1);
+            if (COMB && need_loc) thl = volume_factor<true>(uFV, cf, rlf, pmin, rhi, lsm, lsi, g, ig1);
         }
     }
     if (LATE && A.a != 0.0) load_u<N>(A.un, e, q, un4);
@@ -1915,12 +1831,7 @@ void k_stage(StageArgs A)
             po[v * NN] = fma(A.a, un4[v], A.b * uvol[v]);
         }
         if (nmf == 0) {
-            if (PURE) {
-                if (A.st && (!(uvol[0] >= rlf * (1.0 - kLocalTol)) || uvol[0] > rhi * (1.0 + kLocalTol) ||
-                             pressure(uvol, g) < pmin ||
-                             !(log_entropy(uvol[0], pressure(uvol, g), g) >= lsm - kLocalTol)))
-                    viol = 1;
-            } else if (A.limiter != DGIDP_LIMIT_NONE) {
+            if (A.limiter != DGIDP_LIMIT_NONE) {
                 // p(uvol) >= pmin as 2 rho (E - pmin / (gamma - 1)) >= |m|^2 (rho >= rmin > 0)
                 const double gp = 2.0 * uvol[0] * (uvol[3] - pmin * ig1) - (uvol[1] * uvol[1] + uvol[2] * uvol[2]);
                 if (!(uvol[0] >= rmin) || !(gp >= 0.0)) viol = 1;
@@ -1944,8 +1855,6 @@ void k_stage(StageArgs A)
                     // an undefined high-order mortar flux keeps the low-order flux
                     if (!fin) {
                         ts = tsl = 0.0;
-                    } else if (PURE) {
-                        ts = mortar_factor<true>(uvol, dc, rlf, pmin, rhi, lsm, lsi, g, ig1);
                     } else {
                         ts = mortar_factor<false>(uvol, dc, rmin, pmin, 0.0, 0.0, 0.0, g, ig1);
                         if (COMB) tsl = mortar_factor<true>(uvol, dc, rlf, pmin, rhi, lsm, lsi, g, ig1);
@@ -1957,12 +1866,8 @@ void k_stage(StageArgs A)
                     S[4 + v] = c[v];
                 }
                 S[8] = ts;
-                S[9] = PURE ? rlf : rmin;
+                S[9] = rmin;
                 S[10] = pmin;
-                if (PURE) {
-                    S[11] = rhi;
-                    S[12] = lsm;
-                }
                 if (COMB) {
                     S[13] = tsl;
                     S[14] = w_e;
@@ -2594,9 +2499,11 @@ int launch_learned_indicator(int N, int E, const double* u, const int* perm, dou
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_shock_indicator(int N, const DevMesh& m, const double* u, double gamma, hipStream_t s)
+int launch_shock_indicator(int N, const DevMesh& m, const KernelParams& kp, const double* u, hipStream_t s)
 {
     if (m.E <= 0) return 0;
+    const double gamma = kp.gamma;
+    if (local_arithmetic(kp)) return local::launch_shock_indicator(N, m, u, gamma, s);
     if (N == 3) launch_modal<3, true>(m.E, u, nullptr, gamma, m.shock_ind, s);
     else if (N == 4) launch_modal<4, true>(m.E, u, nullptr, gamma, m.shock_ind, s);
     else return -1;
@@ -2892,7 +2799,6 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     A.b = b;
     A.dt = dt.dt;
     A.ind = m.shock_ind;
-    A.lsv = m.lsv;
     A.dtmax = dt.dtmax;
     A.cfl = dt.cfl;
     A.dt_out = dt.dt_out;
@@ -2915,9 +2821,7 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     A.st = st;
     const int nb = (m.E + G::EPB - 1) / G::EPB;
     const bool mixed = kp.precision == DGIDP_MIXED;
-    const int lk = kp.limiter == DGIDP_LIMIT_LOCAL ? 1
-                   : kp.limiter == DGIDP_LIMIT_COMBINED ? 2
-                   : kp.limiter == DGIDP_LIMIT_LOCAL_LOWORDER ? 3 : 0;
+    const int lk = mode == MODE_STAGE && kp.limiter == DGIDP_LIMIT_COMBINED ? 2 : 0;
     // Positivity limiting on a large mesh: the batches with a mortar element
     // (the first m.nbm entries of the batch list) in one launch, the others in
     // a second one without mortar code, in which the first launch's mortars are
@@ -2925,9 +2829,8 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     // kSplitMin batches, or with a larger mortar share, runs as one launch of the
     // mortar variant: five steps of the 22,156-leaf blast (5,539 batches, N = 3) take
     // 348 us in one launch and 478 in two, of the 246,736-leaf quadrants (49,348,
-    // N = 4) 3,851 and 3,748.  So do the local-limiting modes (three steps of the
-    // 22,156-leaf blast 714 and 979).  A mesh without mortars runs the conforming
-    // variant alone.
+    // N = 4) 3,851 and 3,748.  So does the blend (three steps of the 22,732-leaf jet
+    // 658 and 854).  A mesh without mortars runs the conforming variant alone.
     constexpr int kSplitMin = 16384;
     const bool split = m.nbm == 0 || (lk == 0 && nb >= kSplitMin && 8LL * m.nbm <= nb);
     const bool two = split && m.nbm > 0;
@@ -2979,15 +2882,8 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     using BF = std::false_type;
     if (mode == MODE_STAGE) {
         using MS = std::integral_constant<int, MODE_STAGE>;
-        if (lk == 3) {
-            if (mixed) go(MS(), BT(), std::integral_constant<int, 3>());
-            else go(MS(), BF(), std::integral_constant<int, 3>());
-        } else if (lk == 1) {
-            if (mixed) go(MS(), BT(), std::integral_constant<int, 1>());
-            else go(MS(), BF(), std::integral_constant<int, 1>());
-        } else if (lk == 2) {
-            if (mixed) go(MS(), BT(), std::integral_constant<int, 2>());
-            else go(MS(), BF(), std::integral_constant<int, 2>());
+        if (lk == 2) {
+            go(MS(), BF(), std::integral_constant<int, 2>());
         } else {
             if (mixed) go(MS(), BT(), I0());
             else go(MS(), BF(), I0());
@@ -2996,10 +2892,8 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
         using MH = std::integral_constant<int, MODE_RHS_HIGH>;
         if (mixed) go(MH(), BT(), I0());
         else go(MH(), BF(), I0());
-    } else if (mode == MODE_RHS_LOW) {
-        go(std::integral_constant<int, MODE_RHS_LOW>(), BF(), I0());
     } else {
-        go(std::integral_constant<int, MODE_LOWSOL>(), BF(), I0());
+        go(std::integral_constant<int, MODE_RHS_LOW>(), BF(), I0());
     }
     if (A.mo.M > 0 && !two)
         hipLaunchKernelGGL(k_mortar<N>, dim3((A.mo.M * 3 * (N + 1) + 255) / 256), dim3(256), 0, s, A.mo);
@@ -3011,17 +2905,12 @@ int launch_stage(int N, const DevMesh& m, const KernelParams& kp, const double* 
                  DevStats* st, hipStream_t s, bool rev, bool mortars)
 {
     if (m.E == 0) return 0;
+    if (local_arithmetic(kp)) {
+        if (local::launch_stage(N, m, kp, uin, un, uout, a, b, dt, st, s, rev)) return -1;
+        return mortars ? launch_mortar(N, m, uout, b, st, s, kp.gamma, kp.limiter) : 0;
+    }
     if (N == 3) return stage_N<3>(m, kp, uin, un, uout, a, b, dt, st, MODE_STAGE, s, rev, mortars);
     if (N == 4) return stage_N<4>(m, kp, uin, un, uout, a, b, dt, st, MODE_STAGE, s, rev, mortars);
-    return -1;
-}
-
-int launch_lowsol(int N, const DevMesh& m, const KernelParams& kp, const double* u, const DtSource& dt,
-                  DevStats* st, hipStream_t s)
-{
-    if (m.E == 0) return 0;
-    if (N == 3) return stage_N<3>(m, kp, u, nullptr, m.lsv, 0.0, 1.0, dt, st, MODE_LOWSOL, s);
-    if (N == 4) return stage_N<4>(m, kp, u, nullptr, m.lsv, 0.0, 1.0, dt, st, MODE_LOWSOL, s);
     return -1;
 }
 
@@ -3051,6 +2940,7 @@ int launch_mortar(int N, const DevMesh& m, double* uout, double b, DevStats* st,
 int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, int mode,
               unsigned long long* acc, unsigned long long* other, hipStream_t s)
 {
+    if (local_arithmetic(kp)) return local::launch_dt(N, m, kp, u, mode, acc, other, s);
     DtArgs A;
     A.u = u;
     A.fnbr = m.fnbr;
