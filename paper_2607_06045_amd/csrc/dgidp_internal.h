@@ -68,7 +68,6 @@ struct DevMesh {
     double* slot = nullptr;     // [M*3n*kSlotW]
     int* perm = nullptr;        // [E] external index of internal element e
     double* shock_ind = nullptr;  // [E] shock indicator of combined limiting (internal order)
-    double* dlo = nullptr;      // [E*4*NN] R_LO / m of a stage's input (low-order-solution bounds)
     double* lob = nullptr;      // [E*3*NN] rho min, rho max, ln s min from the low-order solution
     double* lsv = nullptr;      // [E*2*NN] low-order density and ln s per node
     // [ceil(E / stage_block_elems(N))] stage-kernel element batches: the nbm
@@ -185,7 +184,7 @@ int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, 
               unsigned long long* other, hipStream_t s);
 int launch_shock_indicator(int N, const DevMesh& m, const double* u, double gamma, hipStream_t s);
 // local bounds from the low-order solution u + dt R_LO / m into m.lob (eq. Bounds_LowOrder);
-// m.dlo and m.lsv hold the residual and the solution's density and log entropy
+// m.lsv holds that solution's density and log entropy
 int launch_lowsol(int N, const DevMesh& m, const KernelParams& kp, const double* u, const DtSource& dt, hipStream_t s);
 }  // namespace local
 int launch_permute(int N, int E, const int* perm, const double* src, double* dst, int to_internal,

