@@ -28,7 +28,7 @@ using namespace dgidp;
 // every array each time.  The state alternates between two slots so that an
 // adaptation can read the old state while it writes the new one.
 enum PoolSlot {
-    P_MESH, P_SLOT, P_SHOCK, P_LOB, P_LSV, P_U0, P_U1, P_W1, P_W2, P_TKIND, P_TSRC, P_TGRP, P_TCOUNT,
+    P_MESH, P_SLOT, P_SHOCK, P_LSV, P_U0, P_U1, P_W1, P_W2, P_TKIND, P_TSRC, P_TGRP, P_TCOUNT,
     P_COUNT
 };
 struct PoolBuf {
@@ -620,7 +620,7 @@ int stage_on(dgidp_ctx* ctx, const DevMesh& dm, const double* uin, const double*
     // combined limiting weighs its factors with the indicator of the stage's input
     if (kp.limiter == DGIDP_LIMIT_COMBINED && launch_shock_indicator(ctx->p.N, dm, kp, uin, ctx->stream))
         return fail(ctx, DGIDP_E_DEVICE, "indicator kernel launch failed");
-    // bounds from the low-order solution: that solution of the input, then the bounds
+    // bounds from the low-order solution: first that solution of the input
     if (kp.limiter == DGIDP_LIMIT_LOCAL_LOWORDER && local::launch_lowsol(ctx->p.N, dm, kp, uin, dt, ctx->stream))
         return fail(ctx, DGIDP_E_DEVICE, "low-order bounds launch failed");
     if (launch_stage(ctx->p.N, dm, kp, uin, un, uout, a, b, dt, st, ctx->stream, rev, true))
@@ -786,8 +786,7 @@ static int mesh_upload(dgidp_ctx* ctx, int64_t E, const int8_t* level, const int
     if ((rc = pool_get(ctx, P_SLOT, (size_t)M * 3 * n * kSlotW * sizeof(double), ctx->dm.slot)) ||
         (rc = pool_get(ctx, P_SHOCK, (size_t)E * sizeof(double), ctx->dm.shock_ind)) ||
         (ctx->p.limiter == DGIDP_LIMIT_LOCAL_LOWORDER &&
-         ((rc = pool_get(ctx, P_LOB, (size_t)E * 3 * NN * sizeof(double), ctx->dm.lob)) ||
-          (rc = pool_get(ctx, P_LSV, (size_t)E * 2 * NN * sizeof(double), ctx->dm.lsv)))) ||
+         (rc = pool_get(ctx, P_LSV, (size_t)E * 2 * NN * sizeof(double), ctx->dm.lsv))) ||
         (rc = pool_get(ctx, P_U0 + ctx->u_slot, sz, ctx->U)) || (rc = pool_get(ctx, P_W1, sz, ctx->W1)) ||
         (rc = pool_get(ctx, P_W2, sz, ctx->W2))) {
         free_mesh(ctx);
@@ -1232,11 +1231,13 @@ int dgidp_step_noalloc(dgidp_ctx* ctx, double cfl)
     const size_t o_w1 = take(state), o_w2 = take(state);
     const size_t o_slot = take(M * 3 * n * kSlotW * sizeof(double));
     const size_t o_ind = take(E * sizeof(double));
-    size_t o_lob = 0, o_lsv = 0;
+    size_t o_lsv = 0;
     if (ctx->p.limiter == DGIDP_LIMIT_LOCAL_LOWORDER) {
-        take(state);  // (not used; the mode's documented 72 B per node decide which meshes fit)
-        o_lob = take(E * 3 * NN * sizeof(double));
+        // (16 B per node are used; the mode's documented 72 B per node decide
+        // which meshes fit)
         o_lsv = take(E * 2 * NN * sizeof(double));
+        take(state);
+        take(E * 3 * NN * sizeof(double));
     }
     if (off > cap)
         return fail(ctx, DGIDP_E_INVALID_ARG,
@@ -1246,7 +1247,6 @@ int dgidp_step_noalloc(dgidp_ctx* ctx, double cfl)
     dm.slot = (double*)(base + o_slot);
     dm.shock_ind = (double*)(base + o_ind);
     if (ctx->p.limiter == DGIDP_LIMIT_LOCAL_LOWORDER) {
-        dm.lob = (double*)(base + o_lob);
         dm.lsv = (double*)(base + o_lsv);
     }
     unsigned long long* acc = (unsigned long long*)(base + o_acc);

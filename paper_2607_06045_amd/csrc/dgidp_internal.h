@@ -68,8 +68,7 @@ struct DevMesh {
     double* slot = nullptr;     // [M*3n*kSlotW]
     int* perm = nullptr;        // [E] external index of internal element e
     double* shock_ind = nullptr;  // [E] shock indicator of combined limiting (internal order)
-    double* lob = nullptr;      // [E*3*NN] rho min, rho max, ln s min from the low-order solution
-    double* lsv = nullptr;      // [E*2*NN] low-order density and ln s per node
+    double* lsv = nullptr;      // [E*2*NN] density and ln s of the low-order solution (its bounds)
     // [ceil(E / stage_block_elems(N))] stage-kernel element batches: the nbm
     // batches holding an element with a mortar face first, then the others,
     // each part in ascending order
@@ -183,8 +182,8 @@ int launch_stage(int N, const DevMesh& m, const KernelParams& kp, const double* 
 int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, int mode, unsigned long long* acc,
               unsigned long long* other, hipStream_t s);
 int launch_shock_indicator(int N, const DevMesh& m, const double* u, double gamma, hipStream_t s);
-// local bounds from the low-order solution u + dt R_LO / m into m.lob (eq. Bounds_LowOrder);
-// m.lsv holds that solution's density and log entropy
+// density and log entropy of the low-order solution u + dt R_LO / m into m.lsv (bounds of
+// eq. Bounds_LowOrder)
 int launch_lowsol(int N, const DevMesh& m, const KernelParams& kp, const double* u, const DtSource& dt, hipStream_t s);
 }  // namespace local
 int launch_permute(int N, int E, const int* perm, const double* src, double* dst, int to_internal,

@@ -676,9 +676,16 @@ __device__ __forceinline__ void push_stats(DevStats* st, unsigned long long inad
 // ---------------------------------------------------------------------------
 // element kernel
 // ---------------------------------------------------------------------------
-// MODE_LOWSOL: each node's low-order density and log entropy, for the bounds from the
-// low-order solution, without the pair fluxes: 10 us of a stage on the 22,156-leaf
-// blast, a residual with pair fluxes and a pass over it 22 us; results are the same bits.
+// Local bounds from the low-order solution (eq. Bounds_LowOrder): per node the density
+// range over u^FV = u + dt R_LO / m of the node and its low-order neighbours (subcell
+// neighbours; the matching node across a conforming face; the nodes with a nonzero
+// sparse weight across a mortar; none across a boundary), and the smallest
+// ln(p rho^-gamma) among those with rho, p > 0.
+// MODE_LOWSOL: each node's low-order density and log entropy (+inf where rho or p <= 0),
+// without the pair fluxes; the stage gathers them through LDS and its face lanes.  On the
+// 22,156-leaf blast the bounds took a residual with pair fluxes (15.9 us of a stage), a
+// pass over it (6.4) and a gather (11.7); five steps 1,494 us, without the pair fluxes and
+// the pass 1,366, without the gather's kernel 1,245; results are the same bits.
 enum { MODE_STAGE = 0, MODE_LOWSOL = 1 };
 
 struct StageArgs {
@@ -688,7 +695,7 @@ struct StageArgs {
     double a, b;
     const double* dt;
     const double* ind;  // combined limiting: shock indicator per element, in [0, 1]
-    const double* lob;  // bounds from the low-order solution: [E][3][NN] rho min, rho max, ln s min
+    const double* lsv;  // bounds from the low-order solution: [E][2][NN] its density and log entropy
     // when set, dt = cfl / max over the accumulator set dtmax (bits of
     // non-negative doubles); block 0 stores it in dt_out
     const unsigned long long* dtmax;
@@ -777,7 +784,7 @@ __device__ __forceinline__ void pair_lk(int i, int& l, int& k)
 // LIMK: 0 positivity (or none, at run time), 1 local bounds from bar states,
 // 2 the blend of positivity and bar-state local factors by the per-element
 // shock indicator A.ind (eq. combination_posLim_local), 3 local bounds from the
-// low-order solution (eq. Bounds_LowOrder), read from A.lob
+// low-order solution (eq. Bounds_LowOrder), read from A.lsv
 // MORT: the launch over the element batches that hold a mortar element (the
 // surface phase with Kopriva's mortar and the sparse low-order mortar flux,
 // mortar slot records); the batches without one run the MORT = false variant,
@@ -793,7 +800,7 @@ void k_stage(StageArgs A)
     using G = Geo<N>;
     // LOC: local bounds enforced; COMB: blended with positivity; BAR: the bounds
     // come from bar states (computed here), otherwise from the low-order
-    // solution (read from A.lob); PURE: local factors only
+    // solution (read from A.lsv); PURE: local factors only
     constexpr bool LOC = LIMK >= 1, COMB = LIMK == 2, BAR = LIMK == 1 || LIMK == 2;
     constexpr bool PURE = LIMK == 1 || LIMK == 3;
     constexpr bool PAIRS = MODE == MODE_STAGE;
@@ -813,7 +820,8 @@ void k_stage(StageArgs A)
     // bar states of local limiting: rows 0-3 the subcell faces owned by a node
     // (x: density, log entropy; y: the same), rows 4-6 the face lanes' range
     // across the element face; row 0 later the local node factors of the blend
-    __shared__ double sB[BAR ? EPB : 1][7][BAR ? NN : 1];
+    // (from the low-order solution: rows 0 and 1 its density and log entropy per node)
+    __shared__ double sB[LOC ? EPB : 1][7][LOC ? NN : 1];
     __shared__ double sTw[2][n];              // LGL weights and their reciprocals, read per lane
     __shared__ double sS[n][n];               // Sbar, read per pair
     // After phase 5b the primitive rows of sR are read no more: they take the
@@ -937,6 +945,37 @@ void k_stage(StageArgs A)
                 load_u<N>(A.uin, fnb, qfn, w);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) sPair[le][v][ff * n + fk] = w[v];
+            }
+        }
+        if (LIMK == 3) {
+            // the low-order solution at the node and across this lane's face node (the
+            // matching node of a conforming face, the nodes with a nonzero sparse
+            // weight across a mortar, none across a boundary)
+            const double* own = A.lsv + ((unsigned)e * 2u * NN + (unsigned)q);
+            sB[le][0][q] = own[0];
+            sB[le][1][q] = own[NN];
+            auto gather = [&](int el, int node) {
+                const double* o = A.lsv + ((unsigned)el * 2u * NN + (unsigned)node);
+                fb_lo = fmin(fb_lo, o[0]);
+                fb_hi = fmax(fb_hi, o[0]);
+                fb_ls = fmin(fb_ls, o[NN]);
+            };
+            if (fnode) {
+                if (fcode_f == -1) {
+                    gather(fnb, qfn);
+                } else if (MORT && fcode_f >= 0) {
+                    const bool small = fm_small(fcode_f);
+                    const int hh = fm_half(fcode_f);
+                    const int nz = small ? tb.snc[hh][fk] : tb.lnc[fk];
+#pragma unroll 1
+                    for (int i = 0; i < nz; ++i) {
+                        const int col = small ? tb.snz[hh][fk][i] : tb.lnz[fk][i];  // large side: h n + l
+                        gather(small || col < n ? fnb : fnb2, face_q<N>(ff ^ 1, col < n ? col : col - n));
+                    }
+                }
+                sB[le][4][q] = fb_lo;
+                sB[le][5][q] = fb_hi;
+                sB[le][6][q] = fb_ls;
             }
         }
     }
@@ -1420,15 +1459,30 @@ void k_stage(StageArgs A)
         rmin = A.beta * uFV[0];
         pmin = A.beta * pFV;
         if (need_loc && !BAR) {
-            // bounds from the low-order solution; the node's own low-order
-            // state, as computed here, is inside them by definition (the
-            // bounds kernel's copy of it may differ in the last bit)
-            const size_t bi = (size_t)e * 3 * NN + q;
-            double rlo = fmin(A.lob[bi], uFV[0]);
-            rhi = fmax(A.lob[bi + NN], uFV[0]);
-            lsm = A.lob[bi + 2 * NN];
+            // bounds from the low-order solution over the node and its low-order
+            // neighbours; the node's own low-order state, as computed here, is inside
+            // them by definition (its stored copy may differ in the last bit)
+            double rlo = uFV[0];
+            rhi = uFV[0];
             lsi = uFV[0] > 0.0 && pFV > 0.0 ? log(pFV) - g * log(uFV[0]) : -__builtin_inf();
-            lsm = fmin(lsm, lsi);
+            lsm = lsi;
+            auto take = [&](double lo, double hi, double ls) {
+                rlo = fmin(rlo, lo);
+                rhi = fmax(rhi, hi);
+                lsm = fmin(lsm, ls);
+            };
+            // (at the element's edge the node itself once more, and its faces)
+            const int nq[5] = {q, a > 0 ? q - 1 : q, a < N ? q + 1 : q, b > 0 ? q - n : q, b < N ? q + n : q};
+#pragma unroll
+            for (int j = 0; j < 5; ++j) take(sB[le][0][nq[j]], sB[le][0][nq[j]], sB[le][1][nq[j]]);
+            if (onf[0] || onf[1]) {
+                const int i = (onf[0] ? 0 : n) + b;
+                take(sB[le][4][i], sB[le][5][i], sB[le][6][i]);
+            }
+            if (onf[2] || onf[3]) {
+                const int i = (onf[2] ? 2 * n : 3 * n) + a;
+                take(sB[le][4][i], sB[le][5][i], sB[le][6][i]);
+            }
             rlf = fmax(rmin, rlo);
         } else if (need_loc) {
             // bounds over the node and the bar states of its low-order neighbours
@@ -1581,93 +1635,6 @@ void k_stage(StageArgs A)
         }
     }
     if (A.st) push_stats(A.st, inad, viol, thmin, asum, false);
-}
-
-// ---------------------------------------------------------------------------
-// local bounds from the low-order solution (eq. Bounds_LowOrder): per node the
-// density range over u^FV = u + dt R_LO / m of the node and its low-order
-// neighbours (subcell neighbours; the matching node across a conforming face;
-// the nodes with a nonzero sparse weight across a mortar; none across a
-// boundary), and the smallest ln(p rho^-gamma) among those with rho, p > 0.
-// k_stage (MODE_LOWSOL) forms each node's low-order density and log entropy once,
-// k_lowbounds gathers them.
-// ---------------------------------------------------------------------------
-struct LoBoundsArgs {
-    const int* fnbr;
-    const int* fnbr2;
-    const int* fmort;
-    int E;
-    const double* lsv;  // [E][2][NN] low-order density, ln s (+inf where rho or p <= 0)
-    double* lob;  // [E][3][NN] rho min, rho max, ln s min
-};
-
-template <int N>
-__device__ __forceinline__ void lo_gather(const double* __restrict__ lsv, int e, int q, double& lo,
-                                          double& hi, double& ls)
-{
-    constexpr int NN = (N + 1) * (N + 1);
-    const double r = lsv[(size_t)e * 2 * NN + q];
-    lo = fmin(lo, r);
-    hi = fmax(hi, r);
-    ls = fmin(ls, lsv[(size_t)e * 2 * NN + NN + q]);
-}
-
-// one thread per node
-template <int N>
-__global__ __launch_bounds__(256) void k_lowbounds(LoBoundsArgs A)
-{
-    constexpr int n = N + 1, NN = n * n;
-    const Tab<N>& tb = T<N>();
-    // (contiguous node ranges per XCD: the neighbours' values mostly in the same L2)
-    const size_t i = (size_t)xcd_batch(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    if (i >= (size_t)A.E * NN) return;
-    const int e = (int)(i / NN), q = (int)(i - (size_t)e * NN), a = q % n, b = q / n;
-    double lo = __builtin_inf(), hi = -__builtin_inf(), ls = __builtin_inf();
-    lo_gather<N>(A.lsv, e, q, lo, hi, ls);
-    if (a > 0) lo_gather<N>(A.lsv, e, q - 1, lo, hi, ls);
-    if (a < N) lo_gather<N>(A.lsv, e, q + 1, lo, hi, ls);
-    if (b > 0) lo_gather<N>(A.lsv, e, q - n, lo, hi, ls);
-    if (b < N) lo_gather<N>(A.lsv, e, q + n, lo, hi, ls);
-    const bool on[4] = {a == 0, a == N, b == 0, b == N};
-#pragma unroll
-    for (int f = 0; f < 4; ++f) {
-        if (!on[f]) continue;
-        const int code = A.fmort[e * 4 + f];
-        if (code < -1) continue;  // boundary
-        const int k = f < 2 ? b : a;
-        const int nb = A.fnbr[e * 4 + f];
-        if (code == -1) {
-            lo_gather<N>(A.lsv, nb, face_q<N>(f ^ 1, k), lo, hi, ls);
-        } else if (!fm_small(code)) {
-            const int nb2 = A.fnbr2[e * 4 + f];
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int l = 0; l < n; ++l)
-                    if (tb.Wt[k][hh * n + l] != 0.0)
-                        lo_gather<N>(A.lsv, hh == 0 ? nb : nb2, face_q<N>(f ^ 1, l), lo, hi, ls);
-        } else {
-            const int hh = fm_half(code);
-#pragma unroll
-            for (int kk = 0; kk < n; ++kk)
-                if (tb.Wt[kk][hh * n + k] != 0.0) lo_gather<N>(A.lsv, nb, face_q<N>(f ^ 1, kk), lo, hi, ls);
-        }
-    }
-    const size_t bi = (size_t)e * 3 * NN + q;
-    A.lob[bi] = lo;
-    A.lob[bi + NN] = hi;
-    A.lob[bi + 2 * NN] = ls;
-}
-
-static int launch_lowbounds(int N, const DevMesh& m, hipStream_t s)
-{
-    const LoBoundsArgs A = {m.fnbr, m.fnbr2, m.fmort, m.E, m.lsv, m.lob};
-    const size_t nodes = (size_t)m.E * (N + 1) * (N + 1);
-    const dim3 grid((unsigned)((nodes + 255) / 256));
-    if (N == 3) hipLaunchKernelGGL(k_lowbounds<3>, grid, dim3(256), 0, s, A);
-    else if (N == 4) hipLaunchKernelGGL(k_lowbounds<4>, grid, dim3(256), 0, s, A);
-    else return -1;
-    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 // ---------------------------------------------------------------------------
@@ -1946,7 +1913,7 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     A.b = b;
     A.dt = dt.dt;
     A.ind = m.shock_ind;
-    A.lob = m.lob;
+    A.lsv = m.lsv;
     A.dtmax = dt.dtmax;
     A.cfl = dt.cfl;
     A.dt_out = dt.dt_out;
@@ -2026,14 +1993,12 @@ int launch_stage(int N, const DevMesh& m, const KernelParams& kp, const double* 
     return -1;
 }
 
-// the low-order solution of u, then the bounds
 int launch_lowsol(int N, const DevMesh& m, const KernelParams& kp, const double* u, const DtSource& dt, hipStream_t s)
 {
     if (m.E == 0) return 0;
-    int rc = -1;
-    if (N == 3) rc = stage_N<3>(m, kp, u, nullptr, m.lsv, 0.0, 1.0, dt, nullptr, MODE_LOWSOL, s);
-    if (N == 4) rc = stage_N<4>(m, kp, u, nullptr, m.lsv, 0.0, 1.0, dt, nullptr, MODE_LOWSOL, s);
-    return rc ? rc : launch_lowbounds(N, m, s);
+    if (N == 3) return stage_N<3>(m, kp, u, nullptr, m.lsv, 0.0, 1.0, dt, nullptr, MODE_LOWSOL, s);
+    if (N == 4) return stage_N<4>(m, kp, u, nullptr, m.lsv, 0.0, 1.0, dt, nullptr, MODE_LOWSOL, s);
+    return -1;
 }
 
 int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, int mode,
