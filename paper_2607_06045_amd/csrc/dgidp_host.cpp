@@ -16,7 +16,7 @@
 #include "dgidp_par.h"
 
 namespace dgidp {
-int build_and_upload_tables(int N, std::vector<double>* nodes);
+int build_and_upload_tables(int N, std::vector<double>* nodes, bool local_modes);
 int host_tables(int N, double* out);
 }  // namespace dgidp
 
@@ -656,7 +656,7 @@ int dgidp_create(const dgidp_params* p, void* stream, dgidp_ctx** out)
     dgidp_ctx* ctx = new dgidp_ctx();
     ctx->p = *p;
     ctx->stream = (hipStream_t)stream;
-    if (build_and_upload_tables(p->N, &ctx->xi)) {
+    if (build_and_upload_tables(p->N, &ctx->xi, local_arithmetic(kparams(ctx)))) {
         delete ctx;
         return DGIDP_E_DEVICE;
     }

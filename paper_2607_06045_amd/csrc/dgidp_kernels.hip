@@ -42,7 +42,6 @@ __device__ __forceinline__ const Tab<4>& T<4>() { return c_tab4; }
 
 int upload_tables(int N, const void* host_tab, size_t bytes)
 {
-    if (local::upload_tables(N, host_tab, bytes)) return -1;
     hipError_t e = hipErrorInvalidValue;
     if (N == 3 && bytes == sizeof(Tab<3>)) e = hipMemcpyToSymbol(HIP_SYMBOL(c_tab3), host_tab, bytes);
     if (N == 4 && bytes == sizeof(Tab<4>)) e = hipMemcpyToSymbol(HIP_SYMBOL(c_tab4), host_tab, bytes);

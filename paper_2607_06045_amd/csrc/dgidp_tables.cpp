@@ -303,7 +303,8 @@ void build(Tab<N>& t)
 
 }  // namespace
 
-int build_and_upload_tables(int N, std::vector<double>* nodes)
+// local_modes: also for the kernels of the local limiting modes
+int build_and_upload_tables(int N, std::vector<double>* nodes, bool local_modes)
 {
     if (N == 3) {
         Tab<3> t;
@@ -313,6 +314,7 @@ int build_and_upload_tables(int N, std::vector<double>* nodes)
             lgl(3, x, w);
             nodes->assign(x.begin(), x.end());
         }
+        if (local_modes && local::upload_tables(3, &t, sizeof(t))) return -1;
         return upload_tables(3, &t, sizeof(t));
     }
     if (N == 4) {
@@ -323,6 +325,7 @@ int build_and_upload_tables(int N, std::vector<double>* nodes)
             lgl(4, x, w);
             nodes->assign(x.begin(), x.end());
         }
+        if (local_modes && local::upload_tables(4, &t, sizeof(t))) return -1;
         return upload_tables(4, &t, sizeof(t));
     }
     return -1;
