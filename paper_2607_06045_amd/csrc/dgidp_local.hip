@@ -10,7 +10,7 @@
 // dgidp_kernels.hip a shear layer's transverse momentum changed by up to 5e-3 of
 // its largest value in five steps, the FP32 fluxes' rounding by 1e-7 in a jet.  The
 // faster forms were left out for that: on the 22,156-leaf blast, five steps, 715 against
-// 928 us with bar states and 812 against 1,310 with the low-order solution.  The blend
+// 942 us with bar states and 812 against 1,065 with the low-order solution.  The blend
 // in FP64 (weights below one only at shocks) holds its results to 1e-13 with them and
 // runs there.
 //
