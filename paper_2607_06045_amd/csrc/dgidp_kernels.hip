@@ -183,7 +183,9 @@ __device__ __forceinline__ unsigned pair_entry<4>(int q, int i) { return c_pm4.c
 // ---------------------------------------------------------------------------
 // 1/y from the hardware estimate r (relative error e = 1 - y r of about 2^-23)
 // and the third-order step r (1 + e + e^2), whose own error is e^3 (about 1 ulp
-// after rounding); used on the paths every node takes, where y > 0
+// after rounding); used on the paths every node takes, where y > 0.  For 2^-1022 <=
+// |y| <= 2^1022 only: below, r is infinite and e NaN, so a quotient by an increment,
+// which may be subnormal, is a division instead
 __device__ __forceinline__ double frcp(double y)
 {
     const double r = __builtin_amdgcn_rcp(y);
@@ -708,8 +710,8 @@ __device__ __forceinline__ double mortar_factor(const double* uvol, const double
     const double rt = rfl * kMarginMortar, pt = pfl * kMarginMortar;
     double ts = 1.0;
     const bool negl = LOCB && fabs(dc[0]) <= kLocalNegl * uvol[0];
-    if (dc[0] < 0.0 && !negl) ts = fmin(ts, fmax((rt - uvol[0]) * frcp(dc[0]), 0.0));
-    if (LOCB && dc[0] > 0.0 && !negl) ts = fmin(ts, fmax((rce * kMarginMortarHi - uvol[0]) * frcp(dc[0]), 0.0));
+    if (dc[0] < 0.0 && !negl) ts = fmin(ts, fmax((rt - uvol[0]) / dc[0], 0.0));
+    if (LOCB && dc[0] > 0.0 && !negl) ts = fmin(ts, fmax((rce * kMarginMortarHi - uvol[0]) / dc[0], 0.0));
     ts = fmin(ts, theta_p(uvol, dc, pt, ig1));
     if (LOCB) ts = theta_s(uvol, dc, fmin(lsm + 0x1p-41, lsi - 0x1p-40), g, ts);
     return ts;
