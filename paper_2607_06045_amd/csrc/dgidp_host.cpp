@@ -618,7 +618,7 @@ int stage_on(dgidp_ctx* ctx, const DevMesh& dm, const double* uin, const double*
 {
     const KernelParams kp = kparams(ctx);
     // combined limiting weighs its factors with the indicator of the stage's input
-    if (kp.limiter == DGIDP_LIMIT_COMBINED && launch_shock_indicator(ctx->p.N, dm, kp, uin, ctx->stream))
+    if (kp.limiter == DGIDP_LIMIT_COMBINED && local::launch_shock_indicator(ctx->p.N, dm, uin, kp.gamma, ctx->stream))
         return fail(ctx, DGIDP_E_DEVICE, "indicator kernel launch failed");
     // bounds from the low-order solution: first that solution of the input
     if (kp.limiter == DGIDP_LIMIT_LOCAL_LOWORDER && local::launch_lowsol(ctx->p.N, dm, kp, uin, dt, ctx->stream))
@@ -656,7 +656,7 @@ int dgidp_create(const dgidp_params* p, void* stream, dgidp_ctx** out)
     dgidp_ctx* ctx = new dgidp_ctx();
     ctx->p = *p;
     ctx->stream = (hipStream_t)stream;
-    if (build_and_upload_tables(p->N, &ctx->xi, local_arithmetic(kparams(ctx)))) {
+    if (build_and_upload_tables(p->N, &ctx->xi, local_bounds(kparams(ctx)))) {
         delete ctx;
         return DGIDP_E_DEVICE;
     }
@@ -1285,7 +1285,7 @@ int dgidp_time_kernels(dgidp_ctx* ctx, int reps, double* ms)
     if (rc) return rc;
     if (launch_set_double(ctx->dt_dev, dt, ctx->stream)) return fail(ctx, DGIDP_E_DEVICE, "launch failed");
     if (kp.limiter == DGIDP_LIMIT_COMBINED &&
-        launch_shock_indicator(ctx->p.N, ctx->dm, kp, ctx->U, ctx->stream))
+        local::launch_shock_indicator(ctx->p.N, ctx->dm, ctx->U, kp.gamma, ctx->stream))
         return fail(ctx, DGIDP_E_DEVICE, "indicator kernel launch failed");
     // (the low-order solution is formed once, outside the timed stages)
     if (kp.limiter == DGIDP_LIMIT_LOCAL_LOWORDER &&

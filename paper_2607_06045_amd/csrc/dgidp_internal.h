@@ -162,18 +162,16 @@ int launch_rhs(int N, const DevMesh& m, const KernelParams& kp, const double* u,
                double* du, hipStream_t s);
 int launch_mortar(int N, const DevMesh& m, double* uout, double b, DevStats* st, hipStream_t s,
                   double gamma, int limiter);
-// per-element shock indicator on the pressure of u into m.shock_ind (combined limiting)
-int launch_shock_indicator(int N, const DevMesh& m, const KernelParams& kp, const double* u, hipStream_t s);
 // max over nodes of the dt denominator, atomically merged into the accumulator
 // set acc (all zero on entry); the set other is cleared for the next step
 int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, int mode,
               unsigned long long* acc, unsigned long long* other, hipStream_t s);
-// the modes with an arithmetic of their own (dgidp_local.hip); launch_stage, launch_dt
-// and launch_shock_indicator go there by themselves
-inline bool local_arithmetic(const KernelParams& kp)
+// the modes with local bounds, which have an arithmetic of their own (dgidp_local.hip);
+// launch_stage and launch_dt go there by themselves
+inline bool local_bounds(const KernelParams& kp)
 {
     return kp.limiter == DGIDP_LIMIT_LOCAL || kp.limiter == DGIDP_LIMIT_LOCAL_LOWORDER ||
-           (kp.limiter == DGIDP_LIMIT_COMBINED && kp.precision == DGIDP_MIXED);
+           kp.limiter == DGIDP_LIMIT_COMBINED;
 }
 namespace local {
 int upload_tables(int N, const void* host_tab, size_t bytes);
@@ -181,6 +179,7 @@ int launch_stage(int N, const DevMesh& m, const KernelParams& kp, const double* 
                  double a, double b, const DtSource& dt, DevStats* st, hipStream_t s, bool rev);
 int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, int mode, unsigned long long* acc,
               unsigned long long* other, hipStream_t s);
+// per-element shock indicator on the pressure of u into m.shock_ind (combined limiting)
 int launch_shock_indicator(int N, const DevMesh& m, const double* u, double gamma, hipStream_t s);
 // density and log entropy of the low-order solution u + dt R_LO / m into m.lsv (bounds of
 // eq. Bounds_LowOrder)

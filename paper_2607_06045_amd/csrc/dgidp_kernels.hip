@@ -391,11 +391,6 @@ __device__ __forceinline__ double log_join(const LogParts& p, double r, double x
     const double l = fma(p.k, 0x1.62e42fefp-1, fma(p.k, 0x1.473de6af278edp-34, lm));
     return x > 0.0 ? l : __builtin_nan("");
 }
-__device__ __forceinline__ double flog(double x)
-{
-    const LogParts p = log_split(x);
-    return log_join(p, frcp(2.0 + p.f), x);
-}
 __device__ __forceinline__ void flog2(double x, double y, double& lx, double& ly)
 {
     const LogParts px = log_split(x), py = log_split(y);
@@ -405,36 +400,7 @@ __device__ __forceinline__ void flog2(double x, double y, double& lx, double& ly
     ly = log_join(py, dx * r, y);
 }
 
-// exp(x): x = k ln 2 + r, |r| <= ln 2 / 2, k ln 2 in two parts as above, e^r by
-// its series to r^13 (the rest is below 2^-58), scaled by 2^k; 0 below -745 and
-// inf above 710, as far as the double range goes.  About 1 ulp; NaN gives 0.
-__device__ __forceinline__ double fexp(double x)
-{
-    x = fmin(fmax(x, -800.0), 800.0);
-    const double k = rint(x * 0x1.71547652b82fep+0);
-    const double r = fma(k, -0x1.473de6af278edp-34, fma(k, -0x1.62e42fefp-1, x));
-    double t = fma(r, 1.0 / 6227020800.0, 1.0 / 479001600.0);
-    t = fma(r, t, 1.0 / 39916800.0);
-    t = fma(r, t, 1.0 / 3628800.0);
-    t = fma(r, t, 1.0 / 362880.0);
-    t = fma(r, t, 1.0 / 40320.0);
-    t = fma(r, t, 1.0 / 5040.0);
-    t = fma(r, t, 1.0 / 720.0);
-    t = fma(r, t, 1.0 / 120.0);
-    t = fma(r, t, 1.0 / 24.0);
-    t = fma(r, t, 1.0 / 6.0);
-    t = fma(r, t, 0.5);
-    t = fma(r, t, 1.0);
-    return ldexp(fma(r, t, 1.0), (int)k);
-}
-
-// logarithm of the specific entropy, ln p - gamma ln rho (rho, p > 0, else NaN).
-// Stages with local factors are bound by vector instructions, of which the run-time
-// library's two logarithms per bar state (some 160), the exponential and logarithm
-// per evaluation of the entropy root and the IEEE divisions and roots took a large
-// part; with these forms (errors at most 0.9 ulp against its 0.6, exponential,
-// reciprocal and root alike) three steps of the blended 22,732-leaf jet went from 804
-// to 706 us.
+// logarithm of the specific entropy, ln p - gamma ln rho (rho, p > 0, else NaN)
 __device__ __forceinline__ double log_entropy(double rho, double p, double g)
 {
     double lr, lp;
@@ -509,159 +475,29 @@ __device__ __forceinline__ double theta_p(const double* u0, const double* c, dou
 // the limiter aims at the bounds raised by this relative margin so that the
 // rounding of the final sums cannot cross the bounds themselves
 constexpr double kMargin = 1.0 + 0x1p-40;
-constexpr double kMarginHi = 1.0 - 0x1p-40;  // the same for upper bounds
 // the mortar correction aims at half that margin: a node that the volume
 // limiter left on its target keeps 2^-41 of room, instead of a zero or one
 // mortar factor decided by the sign of a rounding error
 constexpr double kMarginMortar = 1.0 + 0x1p-41;
-constexpr double kMarginMortarHi = 1.0 - 0x1p-41;
 // the local bounds hold for the low-order state only up to rounding (it is a
 // convex combination of bar states in exact arithmetic): the bound check allows
 // this relative slack for them
 constexpr double kLocalTol = 1e-12;
-// density increments (per node and step) this small relative to the density are
-// not limited against the local density bounds
-constexpr double kLocalNegl = 1e-14;
-
-// ---------------------------------------------------------------------------
-// local bounds (eq. Bounds_Barstates)
-// ---------------------------------------------------------------------------
-// Density and log specific entropy ln(p rho^-gamma) of the bar state of the
-// low-order graph edge between this element's node `own` and the node `o`
-// across a face of direction d (own_low: `own` on the low side).  The bar state
-// (u_i + u_j)/2 - c_ij . (f_j - f_i) / (2 d_ij) with d_ij = |c_ij| lambda_ij is
-// (u_L + u_R)/2 - (f(u_R) - f(u_L)) / (2 lambda), lambda as in llf_face.  A bar
-// state outside the admissible set (only by rounding) gives -inf: no entropy
-// bound from it.
-__device__ __forceinline__ void bar_bounds(int d, bool own_low, const NodeP& own, const NodeP& o,
-                                           double g, double& rb, double& lsb)
-{
-    const bool dx = d == 0;
-    const double va = dx ? own.v1 : own.v2, vb = dx ? o.v1 : o.v2;
-    const double lam = fmax(fabs(va) + own.c, fabs(vb) + o.c);
-    const double k = (own_low ? 0.5 : -0.5) * frcp(lam);
-    double fa[4], fb[4];
-    fa[0] = own.r * va;
-    fa[1] = own.u[1] * va + (dx ? own.p : 0.0);
-    fa[2] = own.u[2] * va + (dx ? 0.0 : own.p);
-    fa[3] = (own.u[3] + own.p) * va;
-    fb[0] = o.r * vb;
-    fb[1] = o.u[1] * vb + (dx ? o.p : 0.0);
-    fb[2] = o.u[2] * vb + (dx ? 0.0 : o.p);
-    fb[3] = (o.u[3] + o.p) * vb;
-    double ub[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) ub[v] = 0.5 * (own.u[v] + o.u[v]) - k * (fb[v] - fa[v]);
-    rb = ub[0];
-    const double pb = (g - 1.0) * (ub[3] - 0.5 * (ub[1] * ub[1] + ub[2] * ub[2]) * frcp(ub[0]));
-    const double ls = log_entropy(rb, pb, g);
-    lsb = (rb > 0.0 && pb > 0.0) ? ls : -__builtin_inf();
-}
-
-// psi(theta) = p(u0 + theta dc) - exp(lst + gamma ln rho(theta)) and its
-// derivative: psi >= 0 with rho > 0 is p rho^-gamma >= exp(lst).  p is concave
-// in the conserved variables and rho^gamma convex, so psi is concave on the ray.
-__device__ __forceinline__ double psi_s(const double* u0, const double* dc, double th, double lst,
-                                        double g, double& dpsi)
-{
-    const double q0 = u0[0] + th * dc[0], q1 = u0[1] + th * dc[1];
-    const double q2 = u0[2] + th * dc[2], q3 = u0[3] + th * dc[3];
-    if (!(q0 > 0.0)) {
-        dpsi = 0.0;
-        return -__builtin_inf();
-    }
-    const double ir = frcp(q0);
-    const double v1 = q1 * ir, v2 = q2 * ir;
-    const double p = (g - 1.0) * (q3 - 0.5 * (q1 * v1 + q2 * v2));
-    const double rg = fexp(fma(g, flog(q0), lst));
-    const double dp = (g - 1.0) * (dc[3] - v1 * dc[1] - v2 * dc[2] + 0.5 * (v1 * v1 + v2 * v2) * dc[0]);
-    dpsi = dp - g * rg * ir * dc[0];
-    return p - rg;
-}
-
-// Largest theta in [0, thi] with p rho^-gamma >= exp(lst) at u0 + theta dc, on
-// a ray where rho stays positive up to thi.  The admissible set of the concave
-// psi is an interval [0, theta*] when psi(0) >= 0.  The root is bracketed from
-// both sides: the chord through the feasible and the infeasible end cuts the
-// axis at or below theta* (concavity), the Newton step from the infeasible end
-// at or above it (the tangent lies above psi); the two-sided iteration of
-// convex limiting (Guermond, Nazarov, Popov and Tomas, SIAM J. Sci. Comput.
-// 2018).  When the two estimates are within 1e-14 (or cross by rounding) it
-// returns the chord point, theta* up to rounding; otherwise it stops when the
-// bracket is that narrow, at most 16 rounds, and returns the feasible end;
-// psi(0) <= 0 returns 0.
-__device__ double theta_s(const double* u0, const double* dc, double lst, double g, double thi)
-{
-    if (!(thi > 0.0)) return 0.0;
-    double dh, dl, dx;
-    double ph = psi_s(u0, dc, thi, lst, g, dh);
-    if (ph >= 0.0) return thi;
-    double pl = psi_s(u0, dc, 0.0, lst, g, dl);
-    if (!(pl > 0.0)) return 0.0;
-    double lo = 0.0, hi = thi;
-#pragma unroll 1
-    for (int it = 0; it < 16; ++it) {
-        double c = lo + pl * (hi - lo) * frcp(pl - ph);
-        double nw = dh < 0.0 ? hi - ph * frcp(dh) : hi;
-        if (!(c > lo)) c = lo;
-        if (!(c < hi)) c = hi;
-        if (!(nw < hi)) nw = hi;
-        if (nw < c) nw = c;
-        const double pc = psi_s(u0, dc, c, lst, g, dx);
-        if (pc >= 0.0) {
-            lo = c;
-            pl = pc;
-        } else {
-            hi = c;
-            ph = pc;
-            dh = dx;
-        }
-        // the estimates meet: c is theta* up to rounding
-        if (nw - c <= 1e-14) return c;
-        const double pn = psi_s(u0, dc, nw, lst, g, dx);
-        if (pn >= 0.0) {
-            if (nw > lo) {
-                lo = nw;
-                pl = pn;
-            }
-        } else if (nw < hi) {
-            hi = nw;
-            ph = pn;
-            dh = dx;
-        }
-        if (hi - lo <= 1e-14) break;
-    }
-    return lo;
-}
 
 // Node factor of the volume limiter from the node's four face increments cf
-// (dt/m_i-scaled, zero for missing faces): Zalesak factors for the density
-// floor rfl (and, with local bounds, the ceiling rce), the pressure root per
-// face and, with local bounds, the entropy root per face on [0, theta] (log
-// entropy floor lsm); the last two on Gamma = 4-scaled increments.
-template <bool LOCB>
+// (dt/m_i-scaled, zero for missing faces): the Zalesak factor for the density
+// floor rfl and the pressure root per face, this on Gamma = 4-scaled increments.
 __device__ __forceinline__ double volume_factor(const double* uFV, const double (&cf)[4][4], double rfl,
-                                                double pfl, double rce, double lsm, double lsi, double g,
-                                                double ig1)
+                                                double pfl, double ig1)
 {
     const double rt = rfl * kMargin, pt = pfl * kMargin;
-    // Zalesak: the sum of the negative (positive) density increments may use at
-    // most the distance to the floor (ceiling)
-    double P = 0.0, Pp = 0.0;
+    // Zalesak: the sum of the negative density increments may use at most the
+    // distance to the floor
+    double P = 0.0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        P += fmin(cf[j][0], 0.0);
-        if (LOCB) Pp += fmax(cf[j][0], 0.0);
-    }
-    // local bounds: increments below kLocalNegl of the density are rounding
-    // noise and are not limited (a node whose density interval has zero width
-    // would otherwise switch between theta = 0 and 1 on the sign of a rounding
-    // error)
-    if (LOCB && P > -kLocalNegl * uFV[0]) P = 0.0;
-    if (LOCB && Pp < kLocalNegl * uFV[0]) Pp = 0.0;
+    for (int j = 0; j < 4; ++j) P += fmin(cf[j][0], 0.0);
     double th = 1.0;
     if (P < 0.0) th = fmax(fmin((rt - uFV[0]) * frcp(P), 1.0), 0.0);
-    if (LOCB && Pp > 0.0) th = fmin(th, fmax((rce * kMarginHi - uFV[0]) * frcp(Pp), 0.0));
     // pressure: each face's increment scaled by Gamma = 2d = 4 (a zero
     // increment, as on a missing face, admits theta = 1 at an admissible uFV).
     // All four full steps are tested first, without a branch; only a wave with a
@@ -683,38 +519,18 @@ __device__ __forceinline__ double volume_factor(const double* uFV, const double 
 #pragma unroll
         for (int j = 0; j < 4; ++j) th = fmin(th, theta_p<4>(uFV, cf[j], pt, ig1));
     }
-    // specific entropy: per face on [0, th].  The target ln(s_min (1 + 2^-40))
-    // is capped at lsi lowered by 2^-41: with bounds from the low-order solution
-    // lsi is the node's own low-order log entropy (where the node itself is the
-    // minimum of its neighbourhood, the raised bound would lie above the state
-    // the limiter starts from); with bar states lsi = +inf (no cap)
-    if (LOCB) {
-        const double lst = fmin(lsm + 0x1p-40, lsi - 0x1p-41);
-#pragma unroll 1
-        for (int j = 0; j < 4; ++j) {
-            const double dc[4] = {4.0 * cf[j][0], 4.0 * cf[j][1], 4.0 * cf[j][2], 4.0 * cf[j][3]};
-            if (dc[0] == 0.0 && dc[1] == 0.0 && dc[2] == 0.0 && dc[3] == 0.0) continue;
-            th = theta_s(uFV, dc, lst, g, th);
-        }
-    }
     return th;
 }
 
 // Factor of one mortar node for its n_i-scaled increment dc on top of u^vol:
-// density floor (and ceiling), pressure root, entropy root, all against half
-// the volume margin.
-template <bool LOCB>
+// density floor and pressure root, both against half the volume margin.
 __device__ __forceinline__ double mortar_factor(const double* uvol, const double* dc, double rfl, double pfl,
-                                                double rce, double lsm, double lsi, double g, double ig1)
+                                                double ig1)
 {
     const double rt = rfl * kMarginMortar, pt = pfl * kMarginMortar;
     double ts = 1.0;
-    const bool negl = LOCB && fabs(dc[0]) <= kLocalNegl * uvol[0];
-    if (dc[0] < 0.0 && !negl) ts = fmin(ts, fmax((rt - uvol[0]) / dc[0], 0.0));
-    if (LOCB && dc[0] > 0.0 && !negl) ts = fmin(ts, fmax((rce * kMarginMortarHi - uvol[0]) / dc[0], 0.0));
-    ts = fmin(ts, theta_p(uvol, dc, pt, ig1));
-    if (LOCB) ts = theta_s(uvol, dc, fmin(lsm + 0x1p-41, lsi - 0x1p-40), g, ts);
-    return ts;
+    if (dc[0] < 0.0) ts = fmin(ts, fmax((rt - uvol[0]) / dc[0], 0.0));
+    return fmin(ts, theta_p(uvol, dc, pt, ig1));
 }
 
 // ---------------------------------------------------------------------------
@@ -898,7 +714,6 @@ struct StageArgs {
     double* uout;
     double a, b;
     const double* dt;
-    const double* ind;  // combined limiting: shock indicator per element, in [0, 1]
     // when set, dt = cfl / max over the accumulator set dtmax (bits of
     // non-negative doubles); block 0 stores it in dt_out
     const unsigned long long* dtmax;
@@ -975,10 +790,8 @@ __device__ __forceinline__ void load_node(const double* u, int e, int q, NodeP& 
         X.u[3] = MIXED ? fma(X.p, ig1, 0.5 * (X.u[1] * X.v1 + X.u[2] * X.v2)) : sRe[5 * NN + (qq)]; \
     } while (0)
 
-// LIMK: 0 positivity (or none, at run time), 2 the blend of positivity and
-// bar-state local factors by the per-element shock indicator A.ind
-// (eq. combination_posLim_local); 1 and 3, local bounds alone, and the mixed
-// blend have a kernel of their own (dgidp_local.hip, which says why)
+// The positivity bounds (or none, at run time); the modes with local bounds have a
+// kernel of their own (dgidp_local.hip, which says why).
 // MORT: the launch over the element batches that hold a mortar element (the
 // surface phase with Kopriva's mortar and the sparse low-order mortar flux,
 // mortar slot records), or over all; the other batches of a stage of two launches
@@ -995,18 +808,14 @@ __device__ __forceinline__ void load_node(const double* u, int e, int q, NodeP& 
 // (1,121, 393); 182 us of the stage, from 229.  More waves do not help: at 92
 // registers and 16.3 KB of LDS per block, five per SIMD instead of four, the same
 // instructions took the same time.
-template <int N, int MODE, bool MIXED, int LIMK, bool MORT>
-// waves per SIMD: four (128 registers) with positivity limiting, but for the FP64
-// N = 3 variant with mortars (148 registers, see LATE: 353 against 346 us with four);
-// three with the blend
-__global__ __launch_bounds__(Geo<N>::BS) __attribute__((amdgpu_waves_per_eu((LIMK == 0 && (!MORT || N == 4 || MIXED)) ? 4 : 3)))
+template <int N, int MODE, bool MIXED, bool MORT>
+// waves per SIMD: four (128 registers), but for the FP64 N = 3 variant with mortars (148
+// registers, three waves, see LATE: 353 against 346 us with four)
+__global__ __launch_bounds__(Geo<N>::BS) __attribute__((amdgpu_waves_per_eu((!MORT || N == 4 || MIXED) ? 4 : 3)))
 void k_stage(StageArgs A)
 {
     using G = Geo<N>;
-    // COMB: local bounds from bar states, blended with positivity; PAIRS: the pair
-    // fluxes and antidiffusive fluxes are needed
-    static_assert(LIMK == 0 || (LIMK == 2 && !MIXED), "the other local modes have their own kernel");
-    constexpr bool COMB = LIMK == 2;
+    // PAIRS: the pair fluxes and antidiffusive fluxes are needed
     constexpr bool PAIRS = MODE == MODE_STAGE || MODE == MODE_RHS_HIGH;
     constexpr int n = G::n, NN = G::NN, EPB = G::EPB, NT = G::NT;
     constexpr int PP = G::pp(MORT);
@@ -1015,21 +824,16 @@ void k_stage(StageArgs A)
     // LATE: the large sides form their high-order mortar fluxes after every lane
     // has read the staged traces, in place of them, and u^n, the state and the mortar
     // increments are read where they are used: 128 registers instead of 148,
-    // four waves per SIMD, with positivity limiting, no spills with local bounds.  The
-    // FP64 N = 3 variant runs on the small meshes, where a block's chain counts
+    // four waves per SIMD.  The FP64 N = 3 variant runs on the small meshes, where a block's chain counts
     // more than waves: it forms those fluxes beside the low-order pairs and holds
     // them over the barrier.  Five steps of the 14,871-leaf N = 4 blast took 402 us late and
-    // 414 early, of the mixed shear layer 659 and 670, three of the blended jet 669 and
-    // 711; but of the 22,156-leaf N = 3 blast 353 late and 346 early.
-    constexpr bool LATE = MORT && (N == 4 || LIMK != 0 || MIXED);
+    // 414 early, of the mixed shear layer 659 and 670; but of the 22,156-leaf N = 3 blast
+    // 353 late and 346 early.
+    constexpr bool LATE = MORT && (N == 4 || MIXED);
 
     // per node: rho, v1, v2, p, c, E, z = rho / p (mixed: FP32 pairs in rows 5-7)
     __shared__ double sR[EPB * G::ES];
     __shared__ double sPair[EPB * G::es(MORT)];  // pair fluxes, then antidiffusive fluxes and corner terms
-    // local bounds: rows 0-3 the subcell faces owned by a node (x: density, log
-    // entropy; y: the same), rows 4-6 the face lanes' range (face f, position k at
-    // f n + k) across the element face; row 0 later the local node factors
-    __shared__ double sB[COMB ? EPB : 1][7][COMB ? NN : 1];
     __shared__ double sTw[2][n];              // LGL weights and their reciprocals, read per lane
     __shared__ double sS[n][n];               // Sbar / 2, read per pair
     // After phase 5b the primitive rows of sR are read no more: they take the
@@ -1047,7 +851,7 @@ void k_stage(StageArgs A)
                   "the last lanes repeat nodes of their own wave");
     const int tid = threadIdx.x;
     int bid = blockIdx.x, nblk = gridDim.x;
-    if constexpr (!MORT && LIMK == 0 && MODE == MODE_STAGE) {
+    if constexpr (!MORT && MODE == MODE_STAGE) {
         if (bid < A.mblocks) {
             mortar_slot<N>(A.mo, bid * G::BS + tid);
             return;
@@ -1083,8 +887,8 @@ void k_stage(StageArgs A)
     // issue the independent global loads first
     const int fcode_f = A.fmort[e * 4 + ff];
     const int fnb = A.fnbr[e * 4 + ff];
-    int fcode[4];  // the element's face codes (local bounds and mortar slots)
-    if (COMB || MORT)
+    int fcode[4];  // the element's face codes (mortar slots)
+    if (MORT)
 #pragma unroll
         for (int f = 0; f < 4; ++f) fcode[f] = A.fmort[e * 4 + f];
     const int fnb2 = MORT ? A.fnbr2[e * 4 + ff] : -1;
@@ -1094,19 +898,12 @@ void k_stage(StageArgs A)
     double onb[4];
     double us1[4];  // large side: the second small element's trace at position fk
     int bk = 0;
-    // local bounds: own log entropy; for face lanes the density range and the
-    // smallest log entropy of the bar states across this lane's face node
-    double ls_own = 0.0;
-    double w_e = 0.0;  // combined limiting: weight of the local factors
-    bool need_loc = false;  // this element computes bounds and local factors (uniform per element)
-    double fb_lo = __builtin_inf(), fb_hi = -__builtin_inf(), fb_ls = __builtin_inf();
     const double dtpart =
         A.dtmax ? __longlong_as_double((long long)A.dtmax[(tid & 63) * kDtStride]) : 0.0;
     double u0[4];  // this node's state
     {
         NodeP me;
         load_node<N>(A.uin, e, q, me, g);
-        if (COMB) w_e = A.ind[e];
 #pragma unroll
         for (int v = 0; v < 4; ++v) u0[v] = me.u[v];
         // mixed mode: rows 5-7 hold the FP32 operands of the two-point volume
@@ -1127,12 +924,6 @@ void k_stage(StageArgs A)
             // its pair fluxes undefined)
             if (PAIRS) sRe[6 * NN + q] = me.r > 0.0 ? z : __builtin_nan("");
         }
-        // the blend needs local factors only where the indicator fires, and at
-        // mortar nodes (their mortar may blend with another element's weight)
-        need_loc = COMB && (w_e > 0.0 || fcode[0] >= 0 || fcode[1] >= 0 || fcode[2] >= 0 ||
-                           fcode[3] >= 0);
-        // ln(p rho^-gamma) of the node itself, the bar state (i, i)
-        if (need_loc) ls_own = log_entropy(me.r, me.p, g);
     }
     const double hx = A.h[2 * e], hy = A.h[2 * e + 1];
     if (MORT && fcode_f >= 0) {
@@ -1211,8 +1002,8 @@ void k_stage(StageArgs A)
     const double hff = ff < 2 ? hy : hx;
     double fterm[4];
     {
-        NodeP own;  // the face node's state (mortars; boundaries; bar states)
-        if (MORT || COMB) LDS_NODE(own, qfo);
+        NodeP own;  // the face node's state (mortars)
+        if (MORT) LDS_NODE(own, qfo);
         if (fcode_f < 0) {
             if (fcode_f < -1) {
                 NodeP me;
@@ -1245,19 +1036,6 @@ void k_stage(StageArgs A)
             F[3] = fma(K, onb[3] - E, fma(onb[3], wb, E * wa));
             F[1] = fma(Ws, p + op, F[1]);
             F[3] += fma(op, wb, p * wa);
-            if (COMB && need_loc) {
-                NodeP o;
-                o.u[0] = o.r = onb[0];
-                o.u[1] = dff == 0 ? onb[1] : onb[2];
-                o.u[2] = dff == 0 ? onb[2] : onb[1];
-                o.u[3] = onb[3];
-                o.v1 = dff == 0 ? on : ot;
-                o.v2 = dff == 0 ? ot : on;
-                o.p = op;
-                o.c = oc;
-                bar_bounds(dff, lowf, own, o, g, fb_lo, fb_ls);
-                fb_hi = fb_lo;
-            }
             fterm[0] = F[0];
             fterm[1] = dff == 0 ? F[1] : F[2];
             fterm[2] = dff == 0 ? F[2] : F[1];
@@ -1283,13 +1061,6 @@ void k_stage(StageArgs A)
                 make_node(us, g);
                 double Gf[4];
                 llf_face(dff, lowf, own, us, Gf);
-                if (COMB && need_loc) {
-                    double rb, lb;
-                    bar_bounds(dff, lowf, own, us, g, rb, lb);
-                    fb_lo = fmin(fb_lo, rb);
-                    fb_hi = fmax(fb_hi, rb);
-                    fb_ls = fmin(fb_ls, lb);
-                }
                 const double W = sgf * wt * hff * 0.5;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) lo[v] += W * Gf[v];
@@ -1330,13 +1101,6 @@ void k_stage(StageArgs A)
                 make_node(uj, g);
                 double Gf[4];
                 llf_face(dff, lowf, own, uj, Gf);
-                if (COMB && need_loc) {
-                    double rb, lb;
-                    bar_bounds(dff, lowf, own, uj, g, rb, lb);
-                    fb_lo = fmin(fb_lo, rb);
-                    fb_hi = fmax(fb_hi, rb);
-                    fb_ls = fmin(fb_ls, lb);
-                }
                 const double W = sgf * wt * hff;  // wt * h_L / 2 with h_L = 2 h
 #pragma unroll
                 for (int v = 0; v < 4; ++v) lo[v] += W * Gf[v];
@@ -1565,7 +1329,6 @@ void k_stage(StageArgs A)
     // takes itself as the neighbour with weight 0)
     const double whx = a < N ? 0.5 * hy * sTw[0][b] : 0.0, why = b < N ? 0.5 * hx * sTw[0][a] : 0.0;
     double FVo[2][4];
-    double brb[2] = {0.0, 0.0}, bls[2] = {0.0, 0.0};  // bar state of each owned subcell face
     {
         NodeP me;
         LDS_NODE(me, q);
@@ -1583,7 +1346,6 @@ void k_stage(StageArgs A)
                 FVo[d][v] = fma(-hl, o.u[v] - me.u[v], fma(o.u[v], wb, me.u[v] * wa));
             FVo[d][1 + d] = fma(hw, me.p + o.p, FVo[d][1 + d]);
             FVo[d][3] += fma(o.p, wb, me.p * wa);
-            if (COMB && need_loc) bar_bounds(d, true, me, o, g, brb[d], bls[d]);
         }
     }
     // the node's low-order residual so far: its surface term and the faces it owns
@@ -1642,21 +1404,6 @@ void k_stage(StageArgs A)
         const int cs = N + n * ((fk ? 1 : 0) + (ff & 1 ? 2 : 0));
 #pragma unroll
         for (int v = 0; v < 4; ++v) sPe[v * PP + cs] = fterm[v];
-    }
-    if (COMB && need_loc) {
-        if (a < N) {
-            sB[le][0][q] = brb[0];
-            sB[le][1][q] = bls[0];
-        }
-        if (b < N) {
-            sB[le][2][q] = brb[1];
-            sB[le][3][q] = bls[1];
-        }
-        if (fown || fcor) {
-            sB[le][4][ff * n + fk] = fb_lo;
-            sB[le][5][ff * n + fk] = fb_hi;
-            sB[le][6][ff * n + fk] = fb_ls;
-        }
     }
     __syncthreads();
 
@@ -1727,10 +1474,6 @@ void k_stage(StageArgs A)
     const double dtm = dt * im;
     double uFV[4], cf[4][4];
     double rmin = 0.0, pmin = 0.0, th = 1.0;
-    // local bounds: density floor (the larger of the local and the positivity
-    // floor), ceiling, log entropy floor; thl the local node factor of the blend
-    double rlf = 0.0, rhi = 0.0, lsm = 0.0, thl = 1.0;
-    double lsi = 0.0;  // local bounds: the node's own low-order log entropy (cap of the entropy target)
     unsigned long long inad = 0;
     {
 #pragma unroll
@@ -1739,44 +1482,6 @@ void k_stage(StageArgs A)
         if (act && (!(uFV[0] > 0.0) || !(pFV > 0.0))) inad = 1;
         rmin = A.beta * uFV[0];
         pmin = A.beta * pFV;
-        if (need_loc) {
-            // bounds over the node and the bar states of its low-order neighbours
-            // (the node's own bar state is its input state: no cap)
-            lsi = __builtin_inf();
-            double rlo = u0[0];
-            rhi = u0[0];
-            lsm = ls_own;
-            if (a > 0) {
-                rlo = fmin(rlo, sB[le][0][q - 1]);
-                rhi = fmax(rhi, sB[le][0][q - 1]);
-                lsm = fmin(lsm, sB[le][1][q - 1]);
-            }
-            if (a < N) {
-                rlo = fmin(rlo, sB[le][0][q]);
-                rhi = fmax(rhi, sB[le][0][q]);
-                lsm = fmin(lsm, sB[le][1][q]);
-            }
-            if (b > 0) {
-                rlo = fmin(rlo, sB[le][2][q - n]);
-                rhi = fmax(rhi, sB[le][2][q - n]);
-                lsm = fmin(lsm, sB[le][3][q - n]);
-            }
-            if (b < N) {
-                rlo = fmin(rlo, sB[le][2][q]);
-                rhi = fmax(rhi, sB[le][2][q]);
-                lsm = fmin(lsm, sB[le][3][q]);
-            }
-            const int fnq[4] = {0 * n + b, 1 * n + b, 2 * n + a, 3 * n + a};
-#pragma unroll
-            for (int f = 0; f < 4; ++f) {
-                if (!onf[f]) continue;
-                rlo = fmin(rlo, sB[le][4][fnq[f]]);
-                rhi = fmax(rhi, sB[le][5][fnq[f]]);
-                lsm = fmin(lsm, sB[le][6][fnq[f]]);
-            }
-            // the positivity floor stays: the density floor is the larger one
-            rlf = fmax(rmin, rlo);
-        }
         // the faces' increments dt / m_i w (f^HO - f^FV) (left, right, below,
         // above), signed (zero for missing faces)
         const double dl = dtm * hasl, db = dtm * hasb;
@@ -1787,17 +1492,10 @@ void k_stage(StageArgs A)
             cf[2][v] = db * ADb[v];
             cf[3][v] = -dtm * ADo[1][v];
         }
-        if (A.limiter != DGIDP_LIMIT_NONE) {
-            th = volume_factor<false>(uFV, cf, rmin, pmin, 0.0, 0.0, 0.0, g, ig1);
-            if (COMB && need_loc) thl = volume_factor<true>(uFV, cf, rlf, pmin, rhi, lsm, lsi, g, ig1);
-        }
+        if (A.limiter != DGIDP_LIMIT_NONE) th = volume_factor(uFV, cf, rmin, pmin, ig1);
     }
     if (LATE && A.a != 0.0) load_u<N>(A.un, e, q, un4);
-    // the blend keeps its local node factors in the first bar-state row, read
-    // above for the bounds
-    if (COMB) __syncthreads();
     sT[q] = th;
-    if (COMB) sB[le][0][q] = thl;
     __syncthreads();
 
     // ---- phase 7: limited volume update, SSP combination, mortar slots ----
@@ -1806,14 +1504,11 @@ void k_stage(StageArgs A)
     if (act) {
         double uvol[4];
         double tf[4];
-        // face factor: the smaller of its two node factors; blended:
-        // (1 - w) theta_pos + w theta_local
+        // face factor: the smaller of its two node factors
         // (a missing face reads the node itself; its increment is zero)
         const int qn4[4] = {a > 0 ? q - 1 : q, a < N ? q + 1 : q, b > 0 ? q - n : q, b < N ? q + n : q};
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            tf[j] = COMB ? (1.0 - w_e) * fmin(th, sT[qn4[j]]) + w_e * fmin(thl, sB[le][0][qn4[j]])
-                         : fmin(th, sT[qn4[j]]);
+        for (int j = 0; j < 4; ++j) tf[j] = fmin(th, sT[qn4[j]]);
 #pragma unroll
         for (int v = 0; v < 4; ++v)
             uvol[v] = uFV[v] + tf[0] * cf[0][v] + tf[1] * cf[1][v] + tf[2] * cf[2][v] + tf[3] * cf[3][v];
@@ -1851,16 +1546,9 @@ void k_stage(StageArgs A)
                     dc[v] = nmf * c[v];
                     fin = fin && isfinite(dc[v]);
                 }
-                double ts = 1.0, tsl = 1.0;
-                if (A.limiter != DGIDP_LIMIT_NONE) {
-                    // an undefined high-order mortar flux keeps the low-order flux
-                    if (!fin) {
-                        ts = tsl = 0.0;
-                    } else {
-                        ts = mortar_factor<false>(uvol, dc, rmin, pmin, 0.0, 0.0, 0.0, g, ig1);
-                        if (COMB) tsl = mortar_factor<true>(uvol, dc, rlf, pmin, rhi, lsm, lsi, g, ig1);
-                    }
-                }
+                double ts = 1.0;
+                // an undefined high-order mortar flux keeps the low-order flux
+                if (A.limiter != DGIDP_LIMIT_NONE) ts = fin ? mortar_factor(uvol, dc, rmin, pmin, ig1) : 0.0;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     S[v] = uvol[v];
@@ -1869,10 +1557,6 @@ void k_stage(StageArgs A)
                 S[8] = ts;
                 S[9] = rmin;
                 S[10] = pmin;
-                if (COMB) {
-                    S[13] = tsl;
-                    S[14] = w_e;
-                }
             }
         }
     }
@@ -2257,9 +1941,8 @@ __global__ __launch_bounds__(256) void k_dt_rows(DtArgs A)
 //   r[b'][i] = sum_a' Vinv[i][a'] q[b'][a'],   m[j][i] = sum_b' Vinv[j][b'] r[b'][i]
 //  Hennemann indicator: energy = max of the energy fractions of the highest and
 //  the second-highest mode shells, alpha = logistic with threshold
-//  T = 0.5 10^(-1.8 (N+1)^(1/4)) and sharpness ln(9999), zero below 1e-3.  On rho p,
-//  capped at 0.5 (FP32, external element order); or, for combined limiting
-//  (Sec. 3.5), on p and not capped (FP64, internal order).
+//  T = 0.5 10^(-1.8 (N+1)^(1/4)) and sharpness ln(9999), zero below 1e-3, on rho p,
+//  capped at 0.5 (FP32, external element order).
 //  Features: x- and y-shell energy fractions of rho and of p for the shells
 //  N-3 .. N (16 values; FP32, external order).
 //
@@ -2337,11 +2020,10 @@ __device__ __forceinline__ void modal_modes(const Tab<N>& tb, double* Q, const d
     }
 }
 
-// SHOCK: the pressure, FP64 result in internal order
-template <int N, bool SHOCK, typename OUT>
+template <int N>
 __global__ __launch_bounds__(256) void k_indicator(const double* __restrict__ u, int E,
                                                    const int* __restrict__ perm, double gamma, double thresh,
-                                                   double sharp, OUT* __restrict__ alpha)
+                                                   double sharp, float* __restrict__ alpha)
 {
     using G = RowGeo<N>;
     constexpr int n = G::n;
@@ -2352,10 +2034,8 @@ __global__ __launch_bounds__(256) void k_indicator(const double* __restrict__ u,
     double* Q = sQ[wv];
     double r[G::PER], p[G::PER], m[n];
     modal_load<N>(u, e0, E, gamma, lane, r, p);
-    if (!SHOCK) {
 #pragma unroll
-        for (int i = 0; i < G::PER; ++i) p[i] *= r[i];
-    }
+    for (int i = 0; i < G::PER; ++i) p[i] *= r[i];
     const int t = min(lane, G::L - 1), c = t % n;
     modal_modes<N>(T<N>(), Q, p, lane, t, m);
     // this column's part of the highest shell, the second-highest and the rest
@@ -2377,17 +2057,16 @@ __global__ __launch_bounds__(256) void k_indicator(const double* __restrict__ u,
     }
     const double low1 = low2 + top2, en = fmax(top1 / (low1 + top1), top2 / low1);
     const double al = 1.0 / (1.0 + exp(-(sharp / thresh) * (en - thresh)));
-    if (SHOCK) alpha[e0 + lane] = al < 1e-3 ? 0.0 : al;
-    else alpha[perm[e0 + lane]] = al < 1e-3 ? 0.0f : (OUT)fmin(al, 0.5);
+    alpha[perm[e0 + lane]] = al < 1e-3 ? 0.0f : (float)fmin(al, 0.5);
 }
 
-template <int N, bool SHOCK, typename OUT>
-static void launch_modal(int E, const double* u, const int* perm, double gamma, OUT* alpha, hipStream_t s)
+template <int N>
+static void launch_modal(int E, const double* u, const int* perm, double gamma, float* alpha, hipStream_t s)
 {
     using G = RowGeo<N>;
     const double thresh = 0.5 * std::pow(10.0, -1.8 * std::pow((double)(N + 1), 0.25));
     const double sharp = std::log((1.0 - 1e-4) / 1e-4);
-    hipLaunchKernelGGL((k_indicator<N, SHOCK, OUT>), dim3((E - 1) / (G::kWaves * G::WE) + 1), dim3(256), 0, s, u, E,
+    hipLaunchKernelGGL(k_indicator<N>, dim3((E - 1) / (G::kWaves * G::WE) + 1), dim3(256), 0, s, u, E,
                        perm, gamma, thresh, sharp, alpha);
 }
 
@@ -2480,8 +2159,8 @@ int launch_indicator(int N, int E, const double* u, const int* perm, double gamm
     if (E <= 0) return 0;
     if (N != 3 && N != 4) return -1;
     if (alpha) {
-        if (N == 3) launch_modal<3, false>(E, u, perm, gamma, alpha, s);
-        else launch_modal<4, false>(E, u, perm, gamma, alpha, s);
+        if (N == 3) launch_modal<3>(E, u, perm, gamma, alpha, s);
+        else launch_modal<4>(E, u, perm, gamma, alpha, s);
     }
     if (feat) {
         if (N == 3) launch_features<3, false>(E, u, perm, gamma, nullptr, feat, s);
@@ -2496,17 +2175,6 @@ int launch_learned_indicator(int N, int E, const double* u, const int* perm, dou
     if (E <= 0) return 0;
     if (N == 3) launch_features<3, true>(E, u, perm, gamma, wb, alpha, s);
     else if (N == 4) launch_features<4, true>(E, u, perm, gamma, wb, alpha, s);
-    else return -1;
-    return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
-int launch_shock_indicator(int N, const DevMesh& m, const KernelParams& kp, const double* u, hipStream_t s)
-{
-    if (m.E <= 0) return 0;
-    const double gamma = kp.gamma;
-    if (local_arithmetic(kp)) return local::launch_shock_indicator(N, m, u, gamma, s);
-    if (N == 3) launch_modal<3, true>(m.E, u, nullptr, gamma, m.shock_ind, s);
-    else if (N == 4) launch_modal<4, true>(m.E, u, nullptr, gamma, m.shock_ind, s);
     else return -1;
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -2799,7 +2467,6 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     A.a = a;
     A.b = b;
     A.dt = dt.dt;
-    A.ind = m.shock_ind;
     A.dtmax = dt.dtmax;
     A.cfl = dt.cfl;
     A.dt_out = dt.dt_out;
@@ -2822,18 +2489,16 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     A.st = st;
     const int nb = (m.E + G::EPB - 1) / G::EPB;
     const bool mixed = kp.precision == DGIDP_MIXED;
-    const int lk = mode == MODE_STAGE && kp.limiter == DGIDP_LIMIT_COMBINED ? 2 : 0;
-    // Positivity limiting on a large mesh: the batches with a mortar element
+    // A large mesh: the batches with a mortar element
     // (the first m.nbm entries of the batch list) in one launch, the others in
     // a second one without mortar code, in which the first launch's mortars are
     // corrected.  The first ends with a partly idle GPU, so a mesh of fewer than
     // kSplitMin batches, or with a larger mortar share, runs as one launch of the
     // mortar variant: five steps of the 22,156-leaf blast (5,539 batches, N = 3) take
     // 348 us in one launch and 478 in two, of the 246,736-leaf quadrants (49,348,
-    // N = 4) 3,851 and 3,748.  So does the blend (three steps of the 22,732-leaf jet
-    // 658 and 854).  A mesh without mortars runs the conforming variant alone.
+    // N = 4) 3,851 and 3,748.  A mesh without mortars runs the conforming variant alone.
     constexpr int kSplitMin = 16384;
-    const bool split = m.nbm == 0 || (lk == 0 && nb >= kSplitMin && 8LL * m.nbm <= nb);
+    const bool split = m.nbm == 0 || (nb >= kSplitMin && 8LL * m.nbm <= nb);
     const bool two = split && m.nbm > 0;
     // dt from the accumulators: in a stage of two launches the first reduces them
     // per wave, stores dt, and the second reads it.  In one launch over a large mesh
@@ -2849,19 +2514,19 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     // the mortar corrections of this stage
     A.mo = {m.slot, m.slot_node, m.slot_partner, mortars ? m.M : 0, uout, b, kp.gamma, kp.limiter, st};
     A.mblocks = 0;
-    auto go = [&](auto modec, auto mixc, auto lkc) {
-        constexpr int MD = decltype(modec)::value, LK = decltype(lkc)::value;
+    auto go = [&](auto modec, auto mixc) {
+        constexpr int MD = decltype(modec)::value;
         constexpr bool MX = decltype(mixc)::value;
         if (!split) {
             A.blist = nullptr;  // element batches in mesh order
             A.boff = 0;
-            hipLaunchKernelGGL((k_stage<N, MD, MX, LK, true>), dim3(nb), dim3(G::BS), 0, s, A);
+            hipLaunchKernelGGL((k_stage<N, MD, MX, true>), dim3(nb), dim3(G::BS), 0, s, A);
             return;
         }
         A.blist = m.nbm > 0 ? m.blist : nullptr;
         if (m.nbm > 0) {
             A.boff = 0;
-            hipLaunchKernelGGL((k_stage<N, MD, MX, LK, true>), dim3(m.nbm), dim3(G::BS), 0, s, A);
+            hipLaunchKernelGGL((k_stage<N, MD, MX, true>), dim3(m.nbm), dim3(G::BS), 0, s, A);
             if (A.dtmax) {
                 A.dt = dt.dt_out;
                 A.dtmax = nullptr;
@@ -2875,26 +2540,21 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
             // costlier mortar batches first on purpose)
             A.boff = m.nbm;
             A.rev = rev ? 1 : 0;
-            hipLaunchKernelGGL((k_stage<N, MD, MX, LK, false>), dim3(A.mblocks + nb - m.nbm), dim3(G::BS), 0, s, A);
+            hipLaunchKernelGGL((k_stage<N, MD, MX, false>), dim3(A.mblocks + nb - m.nbm), dim3(G::BS), 0, s, A);
         }
     };
-    using I0 = std::integral_constant<int, 0>;
     using BT = std::true_type;
     using BF = std::false_type;
     if (mode == MODE_STAGE) {
         using MS = std::integral_constant<int, MODE_STAGE>;
-        if (lk == 2) {
-            go(MS(), BF(), std::integral_constant<int, 2>());
-        } else {
-            if (mixed) go(MS(), BT(), I0());
-            else go(MS(), BF(), I0());
-        }
+        if (mixed) go(MS(), BT());
+        else go(MS(), BF());
     } else if (mode == MODE_RHS_HIGH) {
         using MH = std::integral_constant<int, MODE_RHS_HIGH>;
-        if (mixed) go(MH(), BT(), I0());
-        else go(MH(), BF(), I0());
+        if (mixed) go(MH(), BT());
+        else go(MH(), BF());
     } else {
-        go(std::integral_constant<int, MODE_RHS_LOW>(), BF(), I0());
+        go(std::integral_constant<int, MODE_RHS_LOW>(), BF());
     }
     if (A.mo.M > 0 && !two)
         hipLaunchKernelGGL(k_mortar<N>, dim3((A.mo.M * 3 * (N + 1) + 255) / 256), dim3(256), 0, s, A.mo);
@@ -2906,7 +2566,7 @@ int launch_stage(int N, const DevMesh& m, const KernelParams& kp, const double* 
                  DevStats* st, hipStream_t s, bool rev, bool mortars)
 {
     if (m.E == 0) return 0;
-    if (local_arithmetic(kp)) {
+    if (local_bounds(kp)) {
         if (local::launch_stage(N, m, kp, uin, un, uout, a, b, dt, st, s, rev)) return -1;
         return mortars ? launch_mortar(N, m, uout, b, st, s, kp.gamma, kp.limiter) : 0;
     }
@@ -2941,7 +2601,7 @@ int launch_mortar(int N, const DevMesh& m, double* uout, double b, DevStats* st,
 int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, int mode,
               unsigned long long* acc, unsigned long long* other, hipStream_t s)
 {
-    if (local_arithmetic(kp)) return local::launch_dt(N, m, kp, u, mode, acc, other, s);
+    if (local_bounds(kp)) return local::launch_dt(N, m, kp, u, mode, acc, other, s);
     DtArgs A;
     A.u = u;
     A.fnbr = m.fnbr;

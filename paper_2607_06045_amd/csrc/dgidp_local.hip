@@ -1,5 +1,5 @@
-// HIP kernels of the local limiting modes (bounds from bar states or from the low-order
-// solution, and the blend in mixed precision).
+// HIP kernels of the limiting modes with local bounds (from bar states or from the low-order
+// solution, alone or blended with positivity).
 //
 // These modes keep an arithmetic of their own, operation by operation, apart from
 // dgidp_kernels.hip's.  Where the density or the entropy is constant along a
@@ -8,11 +8,13 @@
 // factor also multiplies the node's increments in the other direction.  So any other order
 // of the operations, though as accurate, gives other solutions: with the forms of
 // dgidp_kernels.hip a shear layer's transverse momentum changed by up to 5e-3 of
-// its largest value in five steps, the FP32 fluxes' rounding by 1e-7 in a jet.  The
-// faster forms were left out for that: on the 22,156-leaf blast, five steps, 715 against
-// 942 us with bar states and 812 against 1,065 with the low-order solution.  The blend
-// in FP64 (weights below one only at shocks) holds its results to 1e-13 with them and
-// runs there.
+// its largest value in five steps with local bounds alone; with the blend, whose weights
+// are above zero at shocks only, a top-hat blast in gas of constant density by up to 4e-5
+// and a pressure jump beside a shear by 8e-8, though blasts, quadrants and the jet only by
+// 1e-13; the FP32 fluxes' rounding by 1e-7 in the jet.  The faster forms were left out for
+// that: on the 22,156-leaf blast, five steps, 715 against 942 us with bar states and
+// 812 against 1,065 with the low-order solution; three of the blended 22,732-leaf jet
+// 570 against 680.
 //
 // k_stage is as described in dgidp_kernels.hip, with these differences: logarithms of
 // density and rho / p per node, the pair fluxes telescoped through LDS, the library's
@@ -1975,8 +1977,9 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     } else if (lk == 1) {
         if (mixed) go(MS(), BT(), std::integral_constant<int, 1>());
         else go(MS(), BF(), std::integral_constant<int, 1>());
-    } else if (lk == 2 && mixed) {
-        go(MS(), BT(), std::integral_constant<int, 2>());
+    } else if (lk == 2) {
+        if (mixed) go(MS(), BT(), std::integral_constant<int, 2>());
+        else go(MS(), BF(), std::integral_constant<int, 2>());
     } else {
         return -1;
     }
