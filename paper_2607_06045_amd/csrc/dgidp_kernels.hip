@@ -457,18 +457,18 @@ __device__ __forceinline__ double theta_p(const double* u0, const double* c, dou
     const double g2 = dc[0] * dc[3] - 0.5 * (dc[1] * dc[1] + dc[2] * dc[2]);
     double root = 1.0;
     if (g2 == 0.0) {
-        if (g1 < 0.0) root = fmin(root, -g0 * frcp(g1));
+        if (g1 < 0.0) root = fmin(root, -g0 / g1);
     } else {
         const double disc = g1 * g1 - 4.0 * g2 * g0;
         if (disc >= 0.0) {
-            const double sq = fsqrt(disc);
+            const double sq = sqrt(disc);
             const double qq = -0.5 * (g1 + (g1 >= 0.0 ? sq : -sq));
-            const double ra = qq * frcp(g2), rb = g0 * frcp(qq);
+            const double ra = qq / g2, rb = g0 / qq;
             if (ra > 0.0) root = fmin(root, ra);
             if (rb > 0.0) root = fmin(root, rb);
         }
     }
-    if (dc[0] < 0.0) root = fmin(root, -u0[0] * frcp(dc[0]));
+    if (dc[0] < 0.0) root = fmin(root, -u0[0] / dc[0]);
     return root;
 }
 
