@@ -126,27 +126,56 @@ inline void par_for(int64_t n, const std::function<void(int64_t, int64_t)>& fn, 
     HostPool::get().run(n, fn, grain);
 }
 
-// sort v by its distinct keys (first): digit by digit from the lowest, up to the highest
-// bit set in any key.  22,156 leaves (18 bits, two passes) take 100 us, in two chunks
-// sorted by comparison on two threads and merged 231.
+// sort v by its distinct keys (first): digit by digit from the lowest, the digits that no
+// key uses left out.  A pass counts the digits per chunk, turns the counts into
+// places digit by digit and chunk by chunk, and moves every chunk's entries to its
+// own places in order, so the result does not depend on the number of chunks.  Below
+// kChunked entries one chunk: two threads take longer to start than they save (40,000
+// entries 0.66 ms in one chunk, 0.93 in two).  Row-major leaves by Morton key, ms on
+// eight cores, against chunks sorted by comparison and merged, and against one chunk:
+// 22,201 leaves 0.19, 0.72 and 0.20; 65,536 1.2, 1.6 and 1.3; 247,009 2.3, 4.0 and 6.1;
+// 1,048,576 12, 16 and 69; 4,194,304 78, 81 and 325.
 template <class V>
 void radix_sort(std::vector<std::pair<uint64_t, V>>& v)
 {
-    constexpr int kBits = 11;
+    constexpr int kBits = 11, kBins = 1 << kBits;
+    constexpr int64_t kChunked = 65536, kChunkMin = 16384;
+    const int64_t n = (int64_t)v.size();
+    const int64_t nch = n < kChunked ? 1 : std::min<int64_t>(HostPool::get().threads(), n / kChunkMin);
+    // fn(chunk, first, one past the last)
+    auto chunks = [&](auto&& fn) {
+        par_for(nch, [&](int64_t c0, int64_t c1) {
+            for (int64_t c = c0; c < c1; ++c) fn(c, n * c / nch, n * (c + 1) / nch);
+        }, 1);
+    };
+    std::vector<uint64_t> bits((size_t)nch, 0);
+    chunks([&](int64_t c, int64_t lo, int64_t hi) {
+        uint64_t all = 0;
+        for (int64_t i = lo; i < hi; ++i) all |= v[i].first;
+        bits[c] = all;
+    });
     uint64_t all = 0;
-    for (const auto& x : v) all |= x.first;
+    for (uint64_t b : bits) all |= b;
     std::vector<std::pair<uint64_t, V>> w(v.size());
-    std::vector<size_t> at((size_t)1 << kBits);
-    for (int sh = 0; sh < 64 && (all >> sh) != 0; sh += kBits) {
-        std::fill(at.begin(), at.end(), 0);
-        for (const auto& x : v) ++at[(x.first >> sh) & (at.size() - 1)];
-        size_t sum = 0;
-        for (size_t& c : at) {
-            const size_t k = c;
-            c = sum;
-            sum += k;
-        }
-        for (const auto& x : v) w[at[(x.first >> sh) & (at.size() - 1)]++] = x;
+    std::vector<int64_t> at((size_t)nch * kBins);
+    for (int sh = 0; sh < 64; sh += kBits) {
+        if (((all >> sh) & (kBins - 1)) == 0) continue;
+        chunks([&](int64_t c, int64_t lo, int64_t hi) {
+            int64_t* to = &at[c * kBins];
+            std::fill(to, to + kBins, 0);
+            for (int64_t i = lo; i < hi; ++i) ++to[(v[i].first >> sh) & (kBins - 1)];
+        });
+        int64_t sum = 0;
+        for (int b = 0; b < kBins; ++b)
+            for (int64_t c = 0; c < nch; ++c) {
+                const int64_t k = at[c * kBins + b];
+                at[c * kBins + b] = sum;
+                sum += k;
+            }
+        chunks([&](int64_t c, int64_t lo, int64_t hi) {
+            int64_t* to = &at[c * kBins];
+            for (int64_t i = lo; i < hi; ++i) w[to[(v[i].first >> sh) & (kBins - 1)]++] = v[i];
+        });
         v.swap(w);
     }
 }
