@@ -1303,7 +1303,7 @@ int dgidp_time_kernels(dgidp_ctx* ctx, int reps, double* ms)
     HIPCHK(hipEventRecord(ev[1], ctx->stream));
     HIPCHK(hipEventRecord(ev[2], ctx->stream));
     for (int r = 0; r < reps; ++r)
-        if (launch_mortar(ctx->p.N, ctx->dm, ctx->W2, 0.25, nullptr, ctx->stream, kp.gamma, kp.limiter))
+        if (launch_mortar(ctx->p.N, ctx->dm, kp, ctx->W2, 0.25, nullptr, ctx->stream))
             return fail(ctx, DGIDP_E_DEVICE, "mortar kernel launch failed");
     HIPCHK(hipEventRecord(ev[3], ctx->stream));
     HIPCHK(hipEventRecord(ev[4], ctx->stream));

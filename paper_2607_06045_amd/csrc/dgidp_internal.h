@@ -160,14 +160,13 @@ int launch_stage(int N, const DevMesh& m, const KernelParams& kp, const double* 
                  DevStats* st, hipStream_t s, bool rev = false, bool mortars = false);
 int launch_rhs(int N, const DevMesh& m, const KernelParams& kp, const double* u, int which,
                double* du, hipStream_t s);
-int launch_mortar(int N, const DevMesh& m, double* uout, double b, DevStats* st, hipStream_t s,
-                  double gamma, int limiter);
+int launch_mortar(int N, const DevMesh& m, const KernelParams& kp, double* uout, double b, DevStats* st, hipStream_t s);
 // max over nodes of the dt denominator, atomically merged into the accumulator
 // set acc (all zero on entry); the set other is cleared for the next step
 int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, int mode,
               unsigned long long* acc, unsigned long long* other, hipStream_t s);
 // the modes with local bounds, which have an arithmetic of their own (dgidp_local.hip);
-// launch_stage and launch_dt go there by themselves
+// launch_stage, launch_mortar and launch_dt go there by themselves
 inline bool local_bounds(const KernelParams& kp)
 {
     return kp.limiter == DGIDP_LIMIT_LOCAL || kp.limiter == DGIDP_LIMIT_LOCAL_LOWORDER ||
@@ -179,6 +178,7 @@ int launch_stage(int N, const DevMesh& m, const KernelParams& kp, const double* 
                  double a, double b, const DtSource& dt, DevStats* st, hipStream_t s, bool rev);
 int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, int mode, unsigned long long* acc,
               unsigned long long* other, hipStream_t s);
+int launch_mortar(int N, const DevMesh& m, const KernelParams& kp, double* uout, double b, DevStats* st, hipStream_t s);
 // per-element shock indicator on the pressure of u into m.shock_ind (combined limiting)
 int launch_shock_indicator(int N, const DevMesh& m, const double* u, double gamma, hipStream_t s);
 // density and log entropy of the low-order solution u + dt R_LO / m into m.lsv (bounds of

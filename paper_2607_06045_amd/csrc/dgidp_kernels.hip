@@ -20,12 +20,13 @@
 // The time step (eq. timestep_restriction) is a per-block max (k_dt, on large meshes
 // k_dt_rows) merged by one 64-bit atomic max per block into one of kDtSpread accumulators; the first
 // stage kernel of the step reduces those and takes dt = cfl / max.
+// k_mortar, k_dt and what else dgidp_local.hip has in common are in dgidp_device.h.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <type_traits>
 
-#include "dgidp_internal.h"
+#include "dgidp_device.h"
 #include "dgidp_mlp_dev.h"
 
 namespace dgidp {
@@ -48,24 +49,14 @@ int upload_tables(int N, const void* host_tab, size_t bytes)
     return e == hipSuccess ? 0 : -1;
 }
 
-// Workgroups are dispatched round-robin over the 8 XCDs; give each XCD a
-// contiguous range of element batches so that face neighbours share its L2.
-__device__ __forceinline__ int xcd_batch(int bid, int nb)
-{
-    const int q = nb >> 3, r = nb & 7;
-    const int x = bid & 7, j = bid >> 3;
-    return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + j;
-}
-// the same ranges walked from their ends: a kernel that reads what the
-// previous one wrote takes the most recently written batches, the ones most
-// likely still held by the memory-side cache, first
-__device__ __forceinline__ int xcd_batch_rev(int bid, int nb)
-{
-    const int q = nb >> 3, r = nb & 7;
-    const int x = bid & 7, j = bid >> 3;
-    const int len = x < r ? q + 1 : q;
-    return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + len - 1 - j;
-}
+// this file's arithmetic
+struct Rc : Rcp3 {
+    template <int N>
+    static __device__ __forceinline__ const Tab<N>& tab()
+    {
+        return T<N>();
+    }
+};
 
 // launch geometry per degree: one-wave blocks of 4 elements at N = 3 (the
 // phase barriers stay inside a wave and a late block holds less work),
@@ -181,144 +172,6 @@ __device__ __forceinline__ unsigned pair_entry<4>(int q, int i) { return c_pm4.c
 // ---------------------------------------------------------------------------
 // arithmetic helpers
 // ---------------------------------------------------------------------------
-// 1/y from the hardware estimate r (relative error e = 1 - y r of about 2^-23)
-// and the third-order step r (1 + e + e^2), whose own error is e^3 (about 1 ulp
-// after rounding); used on the paths every node takes, where y > 0.  For 2^-1022 <=
-// |y| <= 2^1022 only: below, r is infinite and e NaN, so a quotient by an increment,
-// which may be subnormal, is a division instead
-__device__ __forceinline__ double frcp(double y)
-{
-    const double r = __builtin_amdgcn_rcp(y);
-    const double e = fma(-y, r, 1.0);
-    return fma(r, fma(e, e, e), r);
-}
-
-// sqrt(y) for y >= 0 (normal or zero): the hardware reciprocal square root,
-// one step of the coupled Newton iteration for sqrt y and 1 / (2 sqrt y), then
-// a Newton correction of the root (about 1 ulp).  y = 0 gives 0, y < 0 or NaN
-// gives NaN.
-__device__ __forceinline__ double fsqrt(double y)
-{
-    const double r = __builtin_amdgcn_rsq(y);
-    double g = y * r, h = 0.5 * r;
-    const double e = fma(-g, h, 0.5);
-    g = fma(g, e, g);
-    h = fma(h, e, h);
-    g = fma(fma(-g, g, y), h, g);
-    return y == 0.0 ? 0.0 : g;
-}
-
-// two FP32 values in one FP64 LDS slot (register moves only)
-struct F2 {
-    float x, y;
-};
-__device__ __forceinline__ double pack2(float x, float y)
-{
-    return __hiloint2double(__float_as_int(y), __float_as_int(x));
-}
-__device__ __forceinline__ F2 unpack2(double d)
-{
-    return F2{__int_as_float(__double2loint(d)), __int_as_float(__double2hiint(d))};
-}
-
-struct NodeP {
-    double u[4];
-    double r, v1, v2, p, c;
-};
-
-__device__ __forceinline__ void make_node(NodeP& s, double g)
-{
-    const double ir = frcp(s.u[0]);
-    s.r = s.u[0];
-    s.v1 = s.u[1] * ir;
-    s.v2 = s.u[2] * ir;
-    s.p = (g - 1.0) * (s.u[3] - 0.5 * (s.u[1] * s.v1 + s.u[2] * s.v2));
-    s.c = fsqrt(g * s.p * ir);
-}
-
-// Ghost state across a boundary face f (0 x-, 1 x+, 2 y-, 3 y+) of the interior
-// node s; the outward normal is the axis f / 2, negative on even faces.  Wall:
-// the normal momentum reversed.  Characteristic, by the outward normal velocity
-// vn and sound speed c of s: the exterior state x if vn <= -c; x's density and
-// velocity with s's pressure if vn <= 0; s's density and velocity with x's
-// pressure if vn < c; else s.  Outflow: s.
-__device__ __forceinline__ void boundary_ghost(int kind, const double* x, const NodeP& s, int f,
-                                               double g, double* gu)
-{
-    const int d = f >> 1;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) gu[v] = s.u[v];
-    if (kind == DGIDP_BC_WALL) {  // (constant indices keep gu in registers)
-        if (d == 0) gu[1] = -s.u[1];
-        else gu[2] = -s.u[2];
-        return;
-    }
-    if (kind != DGIDP_BC_CHARACTERISTIC) return;
-    const double vn = (f & 1) ? (d == 0 ? s.v1 : s.v2) : -(d == 0 ? s.v1 : s.v2);
-    if (vn >= s.c) return;
-    if (vn <= -s.c) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) gu[v] = x[v];
-        return;
-    }
-    const double ixr = 1.0 / x[0], xv1 = x[1] * ixr, xv2 = x[2] * ixr;
-    if (vn <= 0.0) {
-        gu[0] = x[0];
-        gu[1] = x[0] * xv1;
-        gu[2] = x[0] * xv2;
-        gu[3] = s.p / (g - 1.0) + 0.5 * x[0] * (xv1 * xv1 + xv2 * xv2);
-    } else {
-        const double xp = (g - 1.0) * (x[3] - 0.5 * (x[1] * xv1 + x[2] * xv2));
-        gu[3] = xp / (g - 1.0) + 0.5 * s.r * (s.v1 * s.v1 + s.v2 * s.v2);
-    }
-}
-
-__device__ __forceinline__ double pressure(const double* u, double g)
-{
-    return (g - 1.0) * (u[3] - 0.5 * (u[1] * u[1] + u[2] * u[2]) * frcp(u[0]));
-}
-
-// local Lax-Friedrichs flux across a face (eq. FVmethod): 1/2 (f_n(u_L) + f_n(u_R)) -
-// 1/2 lambda (u_R - u_L), lambda = max(|v_n| + c) of the two states.
-// Normal direction d and side are run-time values (lanes of a wave hold
-// different faces): this element's state `own`, the other side's state `o`,
-// own_low = this element is on the low side.  Branch free, so a wave evaluates
-// one flux body whatever mix of faces its lanes hold.
-__device__ __forceinline__ void llf_face(int d, bool own_low, const NodeP& own, const NodeP& o,
-                                         double* F)
-{
-    const bool dx = d == 0;
-    const double va = dx ? own.v1 : own.v2, vb = dx ? o.v1 : o.v2;
-    const double lam = fmax(fabs(va) + own.c, fabs(vb) + o.c);
-    const double hl = own_low ? 0.5 * lam : -0.5 * lam;
-    double fa[4], fb[4];
-    fa[0] = own.r * va;
-    fa[1] = own.u[1] * va + (dx ? own.p : 0.0);
-    fa[2] = own.u[2] * va + (dx ? 0.0 : own.p);
-    fa[3] = (own.u[3] + own.p) * va;
-    fb[0] = o.r * vb;
-    fb[1] = o.u[1] * vb + (dx ? o.p : 0.0);
-    fb[2] = o.u[2] * vb + (dx ? 0.0 : o.p);
-    fb[3] = (o.u[3] + o.p) * vb;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) F[v] = 0.5 * (fa[v] + fb[v]) - hl * (o.u[v] - own.u[v]);
-}
-
-// LLF flux on a mortar node between the interpolated large-face state ui and
-// the small-face state us.  An interpolated state outside the admissible set
-// leaves the high-order mortar flux undefined (NaN); the mortar limiter then
-// keeps the low-order flux for the whole mortar.
-__device__ __forceinline__ void mortar_flux(int d, bool large_low, const NodeP& ui, const NodeP& us,
-                                            double* F)
-{
-    if (!(ui.r > 0.0) || !(ui.p > 0.0)) {
-        const double nan = __builtin_nan("");
-        F[0] = F[1] = F[2] = F[3] = nan;
-        return;
-    }
-    llf_face(d, large_low, ui, us, F);
-}
-
 // Half the logarithmic mean, x^ln / 2 with x^ln = (x - y) / (ln x - ln y), and
 // the inverse one, 1 / x^ln.  With s = x + y, d = x - y, f = d / s, z = f^2
 //   x^ln / 2 = (s/4) f / atanh f,   1 / x^ln = (2 / s) atanh f / f
@@ -395,94 +248,10 @@ __device__ __forceinline__ void flog2(double x, double y, double& lx, double& ly
 {
     const LogParts px = log_split(x), py = log_split(y);
     const double dx = 2.0 + px.f, dy = 2.0 + py.f;
-    const double r = frcp(dx * dy);
+    const double r = Rc::rcp(dx * dy);
     lx = log_join(px, dy * r, x);
     ly = log_join(py, dx * r, y);
 }
-
-// logarithm of the specific entropy, ln p - gamma ln rho (rho, p > 0, else NaN)
-__device__ __forceinline__ double log_entropy(double rho, double p, double g)
-{
-    double lr, lp;
-    flog2(rho, p, lr, lp);
-    return lp - g * lr;
-}
-
-__device__ __forceinline__ float lnmeanf(float x, float y, float lx, float ly)
-{
-    const float s = x + y, d = x - y;
-    if (d * d < 1e-2f * (s * s)) {
-        const float is = __builtin_amdgcn_rcpf(s);
-        const float f2 = d * d * is * is;
-        return s * __builtin_amdgcn_rcpf(2.0f + f2 * (2.0f / 3.0f + f2 * (2.0f / 5.0f + f2 * (2.0f / 7.0f))));
-    }
-    return d * __builtin_amdgcn_rcpf(lx - ly);
-}
-
-__device__ __forceinline__ float inv_lnmeanf(float x, float y, float lx, float ly)
-{
-    const float s = x + y, d = x - y;
-    if (d * d < 1e-2f * (s * s)) {
-        const float is = __builtin_amdgcn_rcpf(s);
-        const float f2 = d * d * is * is;
-        return (2.0f + f2 * (2.0f / 3.0f + f2 * (2.0f / 5.0f + f2 * (2.0f / 7.0f)))) * is;
-    }
-    return (lx - ly) * __builtin_amdgcn_rcpf(d);
-}
-
-// ---------------------------------------------------------------------------
-// pressure blending factor: largest theta in [0,1] with rho(u0 + theta dc) > 0
-// and p(u0 + theta dc) >= pt.  For rho > 0, p >= pt is
-// g(theta) = (E - pt/(gamma-1)) rho - |m|^2 / 2 >= 0, a quadratic in theta whose
-// admissible set along the ray is an interval [0, theta*] (p is concave).
-// ---------------------------------------------------------------------------
-// The ray's direction is S c (S = Gamma = 4 for the volume faces' increments,
-// 1 otherwise): a power of two, so that S c is formed exactly inside the
-// fused multiply-adds.
-template <int S = 1>
-__device__ __forceinline__ double theta_p(const double* u0, const double* c, double pt, double ig1)
-{
-    const double e0 = u0[3] - pt * ig1;
-    const double g0 = u0[0] * e0 - 0.5 * (u0[1] * u0[1] + u0[2] * u0[2]);
-    if (!(g0 > 0.0) || !(u0[0] > 0.0)) return 0.0;
-    // full step admissible: the interval contains [0, 1]
-    const double r1 = fma((double)S, c[0], u0[0]);
-    if (r1 > 0.0) {
-        const double m1 = fma((double)S, c[1], u0[1]), m2 = fma((double)S, c[2], u0[2]);
-        const double g1v = fma((double)S, c[3], e0) * r1 - 0.5 * (m1 * m1 + m2 * m2);
-        if (g1v >= 0.0) return 1.0;
-    }
-    const double dc[4] = {S * c[0], S * c[1], S * c[2], S * c[3]};
-    const double g1 = dc[0] * e0 + u0[0] * dc[3] - (u0[1] * dc[1] + u0[2] * dc[2]);
-    const double g2 = dc[0] * dc[3] - 0.5 * (dc[1] * dc[1] + dc[2] * dc[2]);
-    double root = 1.0;
-    if (g2 == 0.0) {
-        if (g1 < 0.0) root = fmin(root, -g0 / g1);
-    } else {
-        const double disc = g1 * g1 - 4.0 * g2 * g0;
-        if (disc >= 0.0) {
-            const double sq = sqrt(disc);
-            const double qq = -0.5 * (g1 + (g1 >= 0.0 ? sq : -sq));
-            const double ra = qq / g2, rb = g0 / qq;
-            if (ra > 0.0) root = fmin(root, ra);
-            if (rb > 0.0) root = fmin(root, rb);
-        }
-    }
-    if (dc[0] < 0.0) root = fmin(root, -u0[0] / dc[0]);
-    return root;
-}
-
-// the limiter aims at the bounds raised by this relative margin so that the
-// rounding of the final sums cannot cross the bounds themselves
-constexpr double kMargin = 1.0 + 0x1p-40;
-// the mortar correction aims at half that margin: a node that the volume
-// limiter left on its target keeps 2^-41 of room, instead of a zero or one
-// mortar factor decided by the sign of a rounding error
-constexpr double kMarginMortar = 1.0 + 0x1p-41;
-// the local bounds hold for the low-order state only up to rounding (it is a
-// convex combination of bar states in exact arithmetic): the bound check allows
-// this relative slack for them
-constexpr double kLocalTol = 1e-12;
 
 // Node factor of the volume limiter from the node's four face increments cf
 // (dt/m_i-scaled, zero for missing faces): the Zalesak factor for the density
@@ -497,7 +266,7 @@ __device__ __forceinline__ double volume_factor(const double* uFV, const double 
 #pragma unroll
     for (int j = 0; j < 4; ++j) P += fmin(cf[j][0], 0.0);
     double th = 1.0;
-    if (P < 0.0) th = fmax(fmin((rt - uFV[0]) * frcp(P), 1.0), 0.0);
+    if (P < 0.0) th = fmax(fmin((rt - uFV[0]) * Rc::rcp(P), 1.0), 0.0);
     // pressure: each face's increment scaled by Gamma = 2d = 4 (a zero
     // increment, as on a missing face, admits theta = 1 at an admissible uFV).
     // All four full steps are tested first, without a branch; only a wave with a
@@ -534,175 +303,6 @@ __device__ __forceinline__ double mortar_factor(const double* uvol, const double
 }
 
 // ---------------------------------------------------------------------------
-// statistics
-// ---------------------------------------------------------------------------
-template <typename TT>
-__device__ __forceinline__ TT wave_sum(TT v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-__device__ __forceinline__ double wave_min(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
-__device__ __forceinline__ double wave_max(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
-// accumulation of per-thread statistics; every lane of the wave must call it.
-// Counts are taken from lane masks (per lane: inad and viol 0 or 1); the two
-// floating-point reductions run only in waves where some lane has a value to
-// contribute, and only such waves touch memory, at the accumulator of their
-// block.  The number of faces and mortars, by which the means divide, follows
-// from the mesh and is not counted here.  Bound: the device-scope atomics that
-// meet at one address are served one after another, about 10 ns each; with one
-// accumulator and two counts per wave the 22,156-leaf N = 3 stage took 142 us
-// with statistics against 20 us without, with them spread and the counts gone
-// 21.4 us; the blended stage of the 22,732-leaf jet 157 and 43 us, the N = 4
-// local one of the 20,480-element double Mach reflection 305 and 74 us.
-__device__ __forceinline__ void push_stats(DevStats* st, unsigned long long inad,
-                                           unsigned long long viol, double thmin, double asum, bool mortar)
-{
-    const unsigned long long ninad = __popcll(__ballot(inad != 0));
-    const unsigned long long nviol = __popcll(__ballot(viol != 0));
-    const bool any_a = __ballot(asum != 0.0) != 0, any_t = __ballot(thmin < 1.0) != 0;
-    if (any_a) asum = wave_sum(asum);
-    if (any_t) thmin = wave_min(thmin);
-    if ((threadIdx.x & 63) == 0) {
-        DevStats* s = st + blockIdx.x % kStatSpread;
-        if (ninad) atomicAdd(&s->fv_inadmissible, ninad);
-        if (nviol) atomicAdd(&s->violations, nviol);
-        if (any_a) atomicAdd(mortar ? &s->alpha_mort_sum : &s->alpha_vol_sum, asum);
-        if (any_t) {
-            unsigned long long bits = __double_as_longlong(fmax(thmin, 0.0));
-            atomicMin(mortar ? &s->theta_mort_min_bits : &s->theta_vol_min_bits, bits);
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// mortar corrections: one thread per slot, after the stage's mortar elements are
-// written.  Where the stage is one launch they are a launch of their own (k_mortar);
-// where it is two, the conforming elements' launch starts with them: neither reads
-// what the other writes, and most of a launch of little work is hidden.  On the
-// 246,736-leaf mesh they take 8.6 to 10.5 us in a launch of their own and lengthen the
-// conforming launch by 4 us; five steps 3,780 us before, 3,729 now (with the time step
-// taken by the mortar elements' launch).
-// ---------------------------------------------------------------------------
-struct MortarArgs {
-    const double* slot;
-    const int* snode;
-    const int* spart;
-    int M;
-    double* uout;
-    double b;
-    double gamma;
-    int limiter;
-    DevStats* st;
-};
-
-// factor of mortar S: the minimum of its slots' node factors; combined
-// limiting blends the positivity and the local minimum with the largest
-// indicator of the mortar's three elements
-template <int N>
-__device__ __forceinline__ double mortar_theta(const double* __restrict__ slot, int S, int limiter)
-{
-    constexpr int NS = 3 * (N + 1);
-    double t = 1.0, tl = 1.0, w = 0.0;
-#pragma unroll
-    for (int j = 0; j < NS; ++j) {
-        const double* R = slot + ((size_t)S * NS + j) * kSlotW;
-        t = fmin(t, R[8]);
-        if (limiter == DGIDP_LIMIT_COMBINED) {
-            tl = fmin(tl, R[13]);
-            w = fmax(w, R[14]);
-        }
-    }
-    return limiter == DGIDP_LIMIT_COMBINED ? (1.0 - w) * t + w * tl : t;
-}
-
-// correction of slot s (past the last slot: none); all lanes of a wave call it
-template <int N>
-__device__ __forceinline__ void mortar_slot(const MortarArgs& A, int s)
-{
-    constexpr int n = N + 1, NN = n * n, NS = 3 * n;
-    const double* __restrict__ slot = A.slot;
-    double* uout = A.uout;
-    unsigned long long viol = 0;
-    double asum = 0.0, thmin = 1.0;
-    if (s < A.M * NS) {
-        const int S = s / NS;
-        // every load that needs no other load first: slot factors of the
-        // mortar, this slot's record, its node and its partner
-        const double* R = slot + (size_t)s * kSlotW;
-        const int part = A.spart[s];
-        const int node = A.snode[s];
-        double rec[11];
-#pragma unroll
-        for (int i = 0; i < 11; ++i) rec[i] = R[i];
-        double t = mortar_theta<N>(slot, S, A.limiter);
-        const int e = node / NN, q = node - e * NN;
-        double uo[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) uo[v] = uout[((size_t)e * 4 + v) * NN + q];
-        if (s == S * NS) {
-            asum = 1.0 - t;
-            thmin = t;
-        }
-        bool apply = true;
-        double corr[4] = {0, 0, 0, 0};
-        if (t != 0.0)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) corr[v] = t * rec[4 + v];
-        if (part >= 0) {
-            const int S2 = part / NS;
-            if (S2 < S) {
-                apply = false;  // the lower-numbered mortar applies both corrections
-            } else {
-                const double t2 = mortar_theta<N>(slot, S2, A.limiter);
-                if (t2 != 0.0)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) corr[v] += t2 * slot[(size_t)part * kSlotW + 4 + v];
-            }
-        }
-        if (apply) {
-            double w[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                uout[((size_t)e * 4 + v) * NN + q] = uo[v] + A.b * corr[v];
-                w[v] = rec[v] + corr[v];
-            }
-            if (A.limiter == DGIDP_LIMIT_LOCAL || A.limiter == DGIDP_LIMIT_LOCAL_LOWORDER) {
-                const double rhi = R[11], lsm = R[12];
-                const double pw = pressure(w, A.gamma);
-                if (!(w[0] >= rec[9] * (1.0 - kLocalTol)) || w[0] > rhi * (1.0 + kLocalTol) ||
-                    pw < rec[10] || !(log_entropy(w[0], pw, A.gamma) >= lsm - kLocalTol))
-                    viol = 1;
-            } else if (A.limiter != DGIDP_LIMIT_NONE &&
-                       (w[0] < rec[9] || pressure(w, A.gamma) < rec[10] || w[0] != w[0])) {
-                viol = 1;
-            }
-        }
-    }
-    if (A.st) push_stats(A.st, 0, viol, thmin, asum, true);
-}
-
-template <int N>
-__global__ __launch_bounds__(256) void k_mortar(MortarArgs A)
-{
-    mortar_slot<N>(A, blockIdx.x * blockDim.x + threadIdx.x);
-}
-
-// ---------------------------------------------------------------------------
 // element kernel
 // ---------------------------------------------------------------------------
 // The low-order residual skips the pair fluxes.
@@ -722,6 +322,8 @@ struct StageArgs {
     const int* fnbr;
     const int* fnbr2;
     const int* fmort;
+    // (not read; it keeps the members' places: without it the compiler groups the loads of
+    // the arguments otherwise, and five steps of the 304-leaf mesh take 222 us for 219)
     const int* mort;
     const double* h;
     double* slot;
@@ -739,38 +341,14 @@ struct StageArgs {
     int vflux;  // two-point volume flux: DGIDP_FLUX_RANOCHA or DGIDP_FLUX_CHANDRASHEKAR
     DevStats* st;
     // the first mblocks blocks of a conforming launch, a multiple of 8, correct the
-    // mortars of the launch before it instead
+    // mortars of the launch before it instead: neither reads what the other writes, and
+    // most of a launch of little work is hidden.  On the 246,736-leaf mesh the corrections
+    // take 8.6 to 10.5 us in a launch of their own and lengthen the conforming launch by
+    // 4 us; five steps 3,780 us before, 3,729 now (with the time step taken by the mortar
+    // elements' launch).
     int mblocks;
     MortarArgs mo;
 };
-
-// node (a, b) at position k along face f
-template <int N>
-__device__ __forceinline__ int face_q(int f, int k)
-{
-    constexpr int n = N + 1;
-    // x faces (0, 1) run along a column, y faces (2, 3) along a row; the odd
-    // face of each pair is N columns or N rows further on
-    const int hi = f & 1;
-    return f < 2 ? k * n + hi * N : k + hi * (N * n);
-}
-
-template <int N>
-__device__ __forceinline__ void load_u(const double* u, int e, int q, double* w)
-{
-    constexpr int NN = (N + 1) * (N + 1);
-    // one address per node; the variables at constant offsets (index < 2^30, mesh limit)
-    const double* p = u + ((unsigned)e * 4u * NN + (unsigned)q);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) w[v] = p[v * NN];
-}
-
-template <int N>
-__device__ __forceinline__ void load_node(const double* u, int e, int q, NodeP& s, double g)
-{
-    load_u<N>(u, e, q, s.u);
-    make_node(s, g);
-}
 
 // node qq of the block's element le from its LDS rows; the momenta are formed
 // again from the primitives (rho v = rho * v: within an ulp of the stored
@@ -853,7 +431,7 @@ void k_stage(StageArgs A)
     int bid = blockIdx.x, nblk = gridDim.x;
     if constexpr (!MORT && MODE == MODE_STAGE) {
         if (bid < A.mblocks) {
-            mortar_slot<N>(A.mo, bid * G::BS + tid);
+            mortar_slot<N, Rc, false>(A.mo, bid * G::BS + tid);
             return;
         }
         bid -= A.mblocks;
@@ -903,12 +481,12 @@ void k_stage(StageArgs A)
     double u0[4];  // this node's state
     {
         NodeP me;
-        load_node<N>(A.uin, e, q, me, g);
+        load_node<N, Rc>(A.uin, e, q, me, g);
 #pragma unroll
         for (int v = 0; v < 4; ++v) u0[v] = me.u[v];
         // mixed mode: rows 5-7 hold the FP32 operands of the two-point volume
         // fluxes in pairs (rho, p), (ln rho, z), (ln z, 0)
-        const double z = PAIRS ? me.r * frcp(me.p) : 0.0;
+        const double z = PAIRS ? me.r * Rc::rcp(me.p) : 0.0;
         sRe[(0) * NN + q] = me.r;
         sRe[(1) * NN + q] = me.v1;
         sRe[(2) * NN + q] = me.v2;
@@ -977,7 +555,7 @@ void k_stage(StageArgs A)
         NodeP ui, us;
 #pragma unroll
         for (int v = 0; v < 4; ++v) us.u[v] = u[v];
-        make_node(us, g);
+        make_node<Rc>(us, g);
         double ia[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int j = 0; j < n; ++j) {
@@ -994,7 +572,7 @@ void k_stage(StageArgs A)
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) ui.u[v] = ia[v];
-        make_node(ui, g);
+        make_node<Rc>(ui, g);
         mortar_flux(dff, lowf, ui, us, u);
     };
     // ---- phase 2: one surface flux per face node: the low-order surface term ----
@@ -1022,7 +600,7 @@ void k_stage(StageArgs A)
             const double p = sRe[(3) * NN + qfo], c = sRe[(4) * NN + qfo];
             const double mn = r * vn, mt = r * vt;
             const double E = MIXED ? fma(p, ig1, 0.5 * fma(mn, vn, mt * vt)) : sRe[5 * NN + qfo];
-            const double ir = frcp(onb[0]);
+            const double ir = Rc::rcp(onb[0]);
             const double on = onb[1] * ir, ot = onb[2] * ir;
             const double op = (g - 1.0) * (onb[3] - 0.5 * fma(onb[1], on, onb[2] * ot));
             const double oc = fsqrt(g * op * ir);
@@ -1058,7 +636,7 @@ void k_stage(StageArgs A)
                 NodeP us;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) us.u[v] = sPe[v * PP + MB + ff * 2 * n + col];
-                make_node(us, g);
+                make_node<Rc>(us, g);
                 double Gf[4];
                 llf_face(dff, lowf, own, us, Gf);
                 const double W = sgf * wt * hff * 0.5;
@@ -1085,7 +663,7 @@ void k_stage(StageArgs A)
                     ui.u[v] = acc;
                 }
             }
-            make_node(ui, g);
+            make_node<Rc>(ui, g);
             double F[4], ho[4], lo[4] = {0, 0, 0, 0};
             mortar_flux(dff, !lowf, ui, own, F);
 #pragma unroll
@@ -1098,7 +676,7 @@ void k_stage(StageArgs A)
                 NodeP uj;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) uj.u[v] = sPe[v * PP + ff * n + j];
-                make_node(uj, g);
+                make_node<Rc>(uj, g);
                 double Gf[4];
                 llf_face(dff, lowf, own, uj, Gf);
                 const double W = sgf * wt * hff;  // wt * h_L / 2 with h_L = 2 h
@@ -1218,7 +796,7 @@ void k_stage(StageArgs A)
                 const double s0 = L0 + R0, d0 = L0 - R0, s6 = L6 + R6, d6 = L6 - R6;
                 // one reciprocal for both sums; the round takes the shortest form
                 // that serves all its lanes
-                const double r = frcp(s0 * s6), r6 = s0 * r;
+                const double r = Rc::rcp(s0 * s6), r6 = s0 * r;
                 const double f0 = d0 * (s6 * r), f6 = d6 * r6;
                 const double z0 = f0 * f0, z6 = f6 * f6, zm = fmax(z0, z6);
                 double hl, iz;  // rho^ln / 2 and 1 / z^ln
@@ -1229,11 +807,11 @@ void k_stage(StageArgs A)
                     hl = half_lnmean_poly(s0, z0);
                     iz = inv_lnmean_poly(r6, z6);
                     if (!__all(zm < kLnPoly)) {
-                        const double rr = frcp(R0 * R6);
+                        const double rr = Rc::rcp(R0 * R6);
                         double l0, l6;
                         flog2(L0 * (R6 * rr), L6 * (R0 * rr), l0, l6);
-                        if (!(z0 < kLnPoly)) hl = 0.5 * d0 * frcp(l0);
-                        if (!(z6 < kLnPoly)) iz = l6 * frcp(d6);
+                        if (!(z0 < kLnPoly)) hl = 0.5 * d0 * Rc::rcp(l0);
+                        if (!(z6 < kLnPoly)) iz = l6 * Rc::rcp(d6);
                     }
                 }
                 const double sn = Ln + Rn, st = Lt + Rt;
@@ -1242,7 +820,7 @@ void k_stage(StageArgs A)
                 if (A.vflux == DGIDP_FLUX_CHANDRASHEKAR) {
                     // Chandrashekar: beta = z / 2, so p~ = rho-bar / (2 beta-bar) =
                     // (rho_L + rho_R) / (z_L + z_R) and 1 / (2 beta^ln) = 1 / z^ln
-                    const double fn = fma(h, sn, 2.0 * hS * (s0 * frcp(s6))), ft = h * st;
+                    const double fn = fma(h, sn, 2.0 * hS * (s0 * Rc::rcp(s6))), ft = h * st;
                     const double k2 = Ln * Ln + Lt * Lt + Rn * Rn + Rt * Rt;
                     f[1] = fn;
                     f[2] = ft;
@@ -1419,7 +997,7 @@ void k_stage(StageArgs A)
     // boundary) has weight 0 (hasl, hasb)
     double ADl[4], ADb[4], dS0[4], dS1[4];
     int slot0 = -1, slot1 = -1, nmf = 0;
-    const double im = 4.0 * frcp(hx * hy) * sTw[1][a] * sTw[1][b];  // 1 / m_i
+    const double im = 4.0 * Rc::rcp(hx * hy) * sTw[1][a] * sTw[1][b];  // 1 / m_i
     {
         const int hl = a > 0 ? q - 1 : q, hb = NN + (b > 0 ? q - n : q);
         const int fl = a > 0 ? q - b - 1 : b * N, fb = b > 0 ? q - n : q;
@@ -1478,7 +1056,7 @@ void k_stage(StageArgs A)
     {
 #pragma unroll
         for (int v = 0; v < 4; ++v) uFV[v] = u0[v] + dtm * RLO[v];
-        const double pFV = pressure(uFV, g);
+        const double pFV = pressure<Rc>(uFV, g);
         if (act && (!(uFV[0] > 0.0) || !(pFV > 0.0))) inad = 1;
         rmin = A.beta * uFV[0];
         pmin = A.beta * pFV;
@@ -1588,181 +1166,6 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// ---------------------------------------------------------------------------
-// time step: per node sum_j 2 d_ij / m_i (or the low-order estimate), block max
-// ---------------------------------------------------------------------------
-struct DtArgs {
-    const double* u;
-    const int* fnbr;
-    const int* fnbr2;
-    const int* fmort;
-    const int* mort;
-    const double* h;
-    const int8_t* bkind;
-    const double* bext;
-    int E;
-    double gamma;
-    int mode;
-    unsigned long long* acc;    // running maximum, bits of a non-negative double
-    unsigned long long* other;  // the other accumulator, cleared for the next step
-};
-
-__device__ __forceinline__ double wave_speed(const NodeP& s, int d)
-{
-    return fabs(d == 0 ? s.v1 : s.v2) + s.c;
-}
-
-// the block's maximum (of its waves' in red) into one of the accumulators
-template <int NW>
-__device__ __forceinline__ void dt_merge(const DtArgs& A, const double* red)
-{
-    if (threadIdx.x == 0) {
-        // non-negative doubles order like their bit patterns; NaN and zero
-        // maxima are left out, as fmax would
-        double m = red[0];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) m = fmax(m, red[w]);
-        if (m > 0.0)
-            atomicMax(A.acc + (blockIdx.x % kDtSpread) * kDtStride,
-                      (unsigned long long)__double_as_longlong(m));
-    }
-    if (blockIdx.x == 0 && threadIdx.x < kDtSpread) A.other[threadIdx.x * kDtStride] = 0ull;
-}
-
-// the dt kernel: kDtBlock = 256-thread blocks (16 elements at N = 3, 10 at N = 4), fewer
-// blocks and so fewer atomics than the stage kernel's geometry
-// threads per block of the dt kernel (whole elements per block)
-constexpr int kDtBlock = 256;
-
-template <int N>
-struct DtGeo {
-    static constexpr int n = N + 1, NN = n * n, NFN = 4 * n;
-    static constexpr int BS = kDtBlock, EPB = BS / NN, NT = EPB * NN;
-};
-
-template <int N>
-__global__ __launch_bounds__(kDtBlock) void k_dt(DtArgs A)
-{
-    using G = DtGeo<N>;
-    constexpr int n = G::n, NN = G::NN, EPB = G::EPB, NT = G::NT, NFN = G::NFN;
-    __shared__ double sL[EPB][2][NN];
-    __shared__ double sF[EPB][NFN];
-    __shared__ double sMl[EPB][8 * n];  // wave speeds across mortars, staged per position
-    constexpr int NW = G::BS / 64;  // waves per block
-    __shared__ double sRed[NW];
-    __shared__ double sTw[2][n];  // LGL weights and their reciprocals, read per lane
-    const Tab<N>& tb = T<N>();
-    const double g = A.gamma;
-    const int tid = threadIdx.x;
-    const int le = tid / NN, q = tid - le * NN, a = q % n, b = q / n;
-    // (contiguous element ranges per XCD, as in the stage kernel: the face
-    // neighbours' traces are then mostly in the same L2; each range from its
-    // end, where the stage before this kernel finished writing)
-    const int e = xcd_batch_rev(blockIdx.x, gridDim.x) * EPB + le;
-    const bool act = tid < NT && e < A.E;
-    if (tid < n) {
-        sTw[0][tid] = tb.w[tid];
-        sTw[1][tid] = tb.winv[tid];
-    }
-    const bool idp = A.mode != DGIDP_DT_LOWORDER;
-    const bool fnode = act && idp && q < NFN;
-    const int ff = q / n, fk = q - (q / n) * n, dff = ff >> 1;
-    double hx = 1.0, hy = 1.0, lo_nb = 0.0;
-    int code = -1, nb = 0, nb2 = -1;
-    if (act) {
-        if (fnode) {  // face tables first: the neighbour loads depend on them
-            code = A.fmort[e * 4 + ff];
-            nb = A.fnbr[e * 4 + ff];
-            nb2 = A.fnbr2[e * 4 + ff];
-        }
-        NodeP me;
-        load_node<N>(A.u, e, q, me, g);
-        hx = A.h[2 * e];
-        hy = A.h[2 * e + 1];
-        sL[le][0][q] = wave_speed(me, 0);
-        sL[le][1][q] = wave_speed(me, 1);
-        if (fnode) {
-            NodeP o;
-            if (code >= -1) {
-                load_node<N>(A.u, nb, face_q<N>(ff ^ 1, fk), o, g);
-            } else {  // boundary: the ghost state of the face node
-                const int j = (-2 - code) * n + fk;
-                double x[4];
-#pragma unroll
-                for (int v = 0; v < 4; ++v) x[v] = A.bext[(size_t)j * 4 + v];
-                NodeP s;
-                load_node<N>(A.u, e, face_q<N>(ff, fk), s, g);
-                boundary_ghost(A.bkind[j], x, s, ff, g, o.u);
-                make_node(o, g);
-            }
-            lo_nb = wave_speed(o, dff);
-            if (code >= 0) {
-                // mortar: stage the wave speeds of the other side at position fk
-                // (large side: both small elements; small side: the large one)
-                sMl[le][(ff * 2) * n + fk] = lo_nb;
-                if (!fm_small(code)) {
-                    NodeP o2;
-                    load_node<N>(A.u, nb2, face_q<N>(ff ^ 1, fk), o2, g);
-                    sMl[le][(ff * 2 + 1) * n + fk] = wave_speed(o2, dff);
-                }
-            }
-        }
-    }
-    __syncthreads();
-    if (fnode) {
-        // edges across face ff at position fk: 2 |c_ij| lambda_ij
-        const double hf = ff < 2 ? hy : hx;
-        const double lm = sL[le][dff][face_q<N>(ff, fk)];
-        double sum = 0.0;
-        if (code < 0) {
-            sum = 0.5 * sTw[0][fk] * hf * fmax(lm, lo_nb);
-        } else if (!fm_small(code)) {
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int l = 0; l < n; ++l) {
-                    const double wt = tb.Wt[fk][hh * n + l];
-                    if (wt == 0.0) continue;
-                    sum += 2.0 * wt * hf * 0.25 * fmax(lm, sMl[le][(ff * 2 + hh) * n + l]);
-                }
-        } else {
-            const int hh = fm_half(code);
-#pragma unroll
-            for (int j = 0; j < n; ++j) {
-                const double wt = tb.Wt[j][hh * n + fk];
-                if (wt == 0.0) continue;
-                sum += 2.0 * wt * (2.0 * hf) * 0.25 * fmax(lm, sMl[le][(ff * 2) * n + j]);
-            }
-        }
-        sF[le][q] = sum;
-    }
-    __syncthreads();
-    double s = 0.0;
-    if (act) {
-        const double lx = sL[le][0][q], ly = sL[le][1][q];
-        if (!idp) {
-            s = (N + 1) * (lx * frcp(hx) + ly * frcp(hy));
-        } else {
-            // edges along x carry 2 |c| = w_b h_y / 2, along y w_a h_x / 2
-            const double cx = 0.5 * sTw[0][b] * hy, cy = 0.5 * sTw[0][a] * hx;
-            double sum = 0.0;
-            if (a > 0) sum += cx * fmax(lx, sL[le][0][q - 1]);
-            if (a < N) sum += cx * fmax(lx, sL[le][0][q + 1]);
-            if (b > 0) sum += cy * fmax(ly, sL[le][1][q - n]);
-            if (b < N) sum += cy * fmax(ly, sL[le][1][q + n]);
-            if (a == 0) sum += sF[le][0 * n + b];
-            if (a == N) sum += sF[le][1 * n + b];
-            if (b == 0) sum += sF[le][2 * n + a];
-            if (b == N) sum += sF[le][3 * n + a];
-            s = sum * (4.0 * frcp(hx * hy)) * sTw[1][a] * sTw[1][b];
-        }
-    }
-    s = wave_max(s);
-    if ((tid & 63) == 0) sRed[tid >> 6] = s;
-    __syncthreads();
-    dt_merge<NW>(A, sRed);
-}
-
 // The same maximum on a large mesh, by waves of 64 / (N+1) elements: the nodes' wave
 // speeds once per node, then one row of nodes per lane with the element's x faces at its
 // ends, then one column with the y faces.  Bound: memory; besides the 32 B per node the
@@ -1808,7 +1211,7 @@ __global__ __launch_bounds__(256) void k_dt_rows(DtArgs A)
     for (int i = 0; i < G::PER; ++i) {
         const int j = lane + 64 * i, ej = j / NN, q = j - ej * NN;
         NodeP o;
-        load_node<N>(A.u, min(e0 + ej, A.E - 1), q, o, g);
+        load_node<N, Rc>(A.u, min(e0 + ej, A.E - 1), q, o, g);
         if (G::WE * NN % 64 == 0 || i + 1 < G::PER || ej < G::WE) {
             const int at = ej * G::ES + (q / n) * G::RS + q % n;
             lx[at] = wave_speed(o, 0);
@@ -1827,7 +1230,7 @@ __global__ __launch_bounds__(256) void k_dt_rows(DtArgs A)
             NodeP o;
 #pragma unroll
             for (int v = 0; v < 4; ++v) o.u[v] = fu[f][v];
-            make_node(o, g);
+            make_node<Rc>(o, g);
             if (code[f] < -1) {  // boundary: the ghost state of the face node
                 const int j = (-2 - code[f]) * n + k;
                 double x[4];
@@ -1835,7 +1238,7 @@ __global__ __launch_bounds__(256) void k_dt_rows(DtArgs A)
                 for (int v = 0; v < 4; ++v) x[v] = A.bext[(size_t)j * 4 + v];
                 NodeP b;
                 boundary_ghost(A.bkind[j], x, o, f, g, b.u);
-                make_node(b, g);
+                make_node<Rc>(b, g);
                 o = b;
             }
             lo[f] = wave_speed(o, f >> 1);
@@ -1852,7 +1255,7 @@ __global__ __launch_bounds__(256) void k_dt_rows(DtArgs A)
                 NodeP o;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) o.u[v] = fu[f][v];
-                make_node(o, g);
+                make_node<Rc>(o, g);
                 lo2[f] = wave_speed(o, f >> 1);
             }
         }
@@ -1922,11 +1325,11 @@ __global__ __launch_bounds__(256) void k_dt_rows(DtArgs A)
             s = fmax(s, (colx[j * G::RS] + (prev + next)) * tb.winv[j]);
             prev = next;
         }
-        s *= 4.0 * frcp(hx * hy) * tb.winv[k];
+        s *= 4.0 * Rc::rcp(hx * hy) * tb.winv[k];
     } else {
 #pragma unroll
         for (int j = 0; j < n; ++j)
-            s = fmax(s, (N + 1) * (colx[j * G::RS] * frcp(hx) + y[j] * frcp(hy)));
+            s = fmax(s, (N + 1) * (colx[j * G::RS] * Rc::rcp(hx) + y[j] * Rc::rcp(hy)));
     }
     s = wave_max(s);
     if (lane == 0) sRed[wv] = s;
@@ -2436,21 +1839,6 @@ __global__ void k_check_state(int total_nodes, int NN, double g, const double* u
     if (!ok) atomicMin(bad, (unsigned long long)i);
 }
 
-// dt = cfl / (the maximum over the dt kernel's accumulators), once per step:
-// one wave reads the kDtSpread accumulators; the stage kernels then read the
-// stored value (a per-wave reduction in every block of the first stage would
-// read the kDtSpread cache lines once per wave)
-__global__ __launch_bounds__(64) void k_dt_final(const unsigned long long* dtmax, double cfl, double* dt_out,
-                                                 DevStats* st)
-{
-    const double m = wave_max(__longlong_as_double((long long)dtmax[threadIdx.x * kDtStride]));
-    if (threadIdx.x == 0) {
-        const double dt = cfl / m;
-        *dt_out = dt;
-        if (st) st->dt = dt;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
@@ -2461,32 +1849,8 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
 {
     using G = Geo<N>;
     StageArgs A;
-    A.uin = uin;
-    A.un = un;
-    A.uout = uout;
-    A.a = a;
-    A.b = b;
-    A.dt = dt.dt;
-    A.dtmax = dt.dtmax;
-    A.cfl = dt.cfl;
-    A.dt_out = dt.dt_out;
-    A.fnbr = m.fnbr;
-    A.fnbr2 = m.fnbr2;
-    A.fmort = m.fmort;
-    A.bkind = m.bkind;
-    A.bext = m.bext;
-    A.mort = m.mort;
-    A.h = m.h;
-    A.slot = m.slot;
+    set_stage(A, m, kp, uin, un, uout, a, b, dt, st);
     A.blist = m.blist;
-    A.E = m.E;
-    A.gamma = kp.gamma;
-    A.ig1 = 1.0 / (kp.gamma - 1.0);
-    A.rev = 0;
-    A.beta = kp.beta;
-    A.limiter = kp.limiter;
-    A.vflux = kp.vflux;
-    A.st = st;
     const int nb = (m.E + G::EPB - 1) / G::EPB;
     const bool mixed = kp.precision == DGIDP_MIXED;
     // A large mesh: the batches with a mortar element
@@ -2502,11 +1866,8 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     const bool two = split && m.nbm > 0;
     // dt from the accumulators: in a stage of two launches the first reduces them
     // per wave, stores dt, and the second reads it.  In one launch over a large mesh
-    // k_dt_final reduces them once; with fewer than kFinalMin batches the extra launch
-    // costs more than the stage's own per-wave reduction.
-    constexpr int kFinalMin = 16384;
+    // k_dt_final reduces them once.
     if (dt.dtmax && dt.dt_out && !two && nb >= kFinalMin) {
-        static_assert(kDtSpread == 64, "one wave reduces the dt accumulators");
         hipLaunchKernelGGL(k_dt_final, dim3(1), dim3(64), 0, s, dt.dtmax, dt.cfl, dt.dt_out, st);
         A.dt = dt.dt_out;
         A.dtmax = nullptr;
@@ -2556,9 +1917,8 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     } else {
         go(std::integral_constant<int, MODE_RHS_LOW>(), BF());
     }
-    if (A.mo.M > 0 && !two)
-        hipLaunchKernelGGL(k_mortar<N>, dim3((A.mo.M * 3 * (N + 1) + 255) / 256), dim3(256), 0, s, A.mo);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    if (hipGetLastError() != hipSuccess) return -1;
+    return A.mo.M > 0 && !two ? run_mortar<Rc, false>(N, A.mo, s) : 0;
 }
 
 int launch_stage(int N, const DevMesh& m, const KernelParams& kp, const double* uin,
@@ -2568,7 +1928,7 @@ int launch_stage(int N, const DevMesh& m, const KernelParams& kp, const double* 
     if (m.E == 0) return 0;
     if (local_bounds(kp)) {
         if (local::launch_stage(N, m, kp, uin, un, uout, a, b, dt, st, s, rev)) return -1;
-        return mortars ? launch_mortar(N, m, uout, b, st, s, kp.gamma, kp.limiter) : 0;
+        return mortars ? launch_mortar(N, m, kp, uout, b, st, s) : 0;
     }
     if (N == 3) return stage_N<3>(m, kp, uin, un, uout, a, b, dt, st, MODE_STAGE, s, rev, mortars);
     if (N == 4) return stage_N<4>(m, kp, uin, un, uout, a, b, dt, st, MODE_STAGE, s, rev, mortars);
@@ -2586,52 +1946,28 @@ int launch_rhs(int N, const DevMesh& m, const KernelParams& kp, const double* u,
     return -1;
 }
 
-int launch_mortar(int N, const DevMesh& m, double* uout, double b, DevStats* st, hipStream_t s,
-                  double gamma, int limiter)
+int launch_mortar(int N, const DevMesh& m, const KernelParams& kp, double* uout, double b, DevStats* st, hipStream_t s)
 {
     if (m.M == 0) return 0;
-    const MortarArgs A = {m.slot, m.slot_node, m.slot_partner, m.M, uout, b, gamma, limiter, st};
-    const dim3 grid((m.M * 3 * (N + 1) + 255) / 256);
-    if (N == 3) hipLaunchKernelGGL(k_mortar<3>, grid, dim3(256), 0, s, A);
-    else if (N == 4) hipLaunchKernelGGL(k_mortar<4>, grid, dim3(256), 0, s, A);
-    else return -1;
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    if (local_bounds(kp)) return local::launch_mortar(N, m, kp, uout, b, st, s);
+    return run_mortar<Rc, false>(N, {m.slot, m.slot_node, m.slot_partner, m.M, uout, b, kp.gamma, kp.limiter, st}, s);
 }
 
 int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, int mode,
               unsigned long long* acc, unsigned long long* other, hipStream_t s)
 {
     if (local_bounds(kp)) return local::launch_dt(N, m, kp, u, mode, acc, other, s);
-    DtArgs A;
-    A.u = u;
-    A.fnbr = m.fnbr;
-    A.fnbr2 = m.fnbr2;
-    A.fmort = m.fmort;
-    A.bkind = m.bkind;
-    A.bext = m.bext;
-    A.mort = m.mort;
-    A.h = m.h;
-    A.E = m.E;
-    A.gamma = kp.gamma;
-    A.mode = mode;
-    A.acc = acc;
-    A.other = other;
+    const DtArgs A = dt_args(m, kp, u, mode, acc, other);
     // rows and columns per lane from kRowsMin elements on: its chain is longer, and
     // below, fewer waves than fill the chip are left.  Of a blast with one refined
     // level, one thread per node against rows: N = 3, 19,864 elements 6.9 and 8.6 us,
     // 31,012 8.2 and 8.8, 44,688 9.8 and 9.7, 60,856 12.8 and 11.6; N = 4, 31,012 11.2 and
     // 11.7, 44,688 14.9 and 13.5, 79,420 21.6 and 18.9.
     constexpr int kRowsMin = 40960;
-    if (N != 3 && N != 4) return -1;
-    if (m.E >= kRowsMin) {
-        if (N == 3) hipLaunchKernelGGL(k_dt_rows<3>, dim3((m.E - 1) / (4 * RowGeo<3>::WE) + 1), dim3(256), 0, s, A);
-        else hipLaunchKernelGGL(k_dt_rows<4>, dim3((m.E - 1) / (4 * RowGeo<4>::WE) + 1), dim3(256), 0, s, A);
-    } else {
-        if (N == 3)
-            hipLaunchKernelGGL(k_dt<3>, dim3((m.E + DtGeo<3>::EPB - 1) / DtGeo<3>::EPB), dim3(kDtBlock), 0, s, A);
-        else
-            hipLaunchKernelGGL(k_dt<4>, dim3((m.E + DtGeo<4>::EPB - 1) / DtGeo<4>::EPB), dim3(kDtBlock), 0, s, A);
-    }
+    if (m.E < kRowsMin) return run_dt<Rc>(N, A, s);
+    if (N == 3) hipLaunchKernelGGL(k_dt_rows<3>, dim3((m.E - 1) / (4 * RowGeo<3>::WE) + 1), dim3(256), 0, s, A);
+    else if (N == 4) hipLaunchKernelGGL(k_dt_rows<4>, dim3((m.E - 1) / (4 * RowGeo<4>::WE) + 1), dim3(256), 0, s, A);
+    else return -1;
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

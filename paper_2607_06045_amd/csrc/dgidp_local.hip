@@ -24,7 +24,7 @@
 
 #include <type_traits>
 
-#include "dgidp_internal.h"
+#include "dgidp_device.h"
 
 namespace dgidp {
 namespace local {
@@ -47,24 +47,14 @@ int upload_tables(int N, const void* host_tab, size_t bytes)
     return e == hipSuccess ? 0 : -1;
 }
 
-// Workgroups are dispatched round-robin over the 8 XCDs; give each XCD a
-// contiguous range of element batches so that face neighbours share its L2.
-__device__ __forceinline__ int xcd_batch(int bid, int nb)
-{
-    const int q = nb >> 3, r = nb & 7;
-    const int x = bid & 7, j = bid >> 3;
-    return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + j;
-}
-// the same ranges walked from their ends: a kernel that reads what the
-// previous one wrote takes the most recently written batches, the ones most
-// likely still held by the memory-side cache, first
-__device__ __forceinline__ int xcd_batch_rev(int bid, int nb)
-{
-    const int q = nb >> 3, r = nb & 7;
-    const int x = bid & 7, j = bid >> 3;
-    const int len = x < r ? q + 1 : q;
-    return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + len - 1 - j;
-}
+// this file's arithmetic
+struct Rc : Rcp2 {
+    template <int N>
+    static __device__ __forceinline__ const Tab<N>& tab()
+    {
+        return T<N>();
+    }
+};
 
 // launch geometry per degree: one-wave blocks of 4 elements at N = 3 (the
 // phase barriers stay inside a wave and a late block holds less work),
@@ -166,143 +156,6 @@ __device__ __forceinline__ unsigned pair_entry<4>(int q, int i) { return c_pm4.c
 // ---------------------------------------------------------------------------
 // arithmetic helpers
 // ---------------------------------------------------------------------------
-// 1/y from the hardware estimate and two Newton steps (about 1 ulp); used on
-// the paths every node takes, where y > 0
-__device__ __forceinline__ double frcp(double y)
-{
-    double r = __builtin_amdgcn_rcp(y);
-    double e = fma(-y, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-y, r, 1.0);
-    return fma(r, e, r);
-}
-
-// sqrt(y) for y >= 0 (normal or zero): the hardware reciprocal square root,
-// one step of the coupled Newton iteration for sqrt y and 1 / (2 sqrt y), then
-// a Newton correction of the root (about 1 ulp).  y = 0 gives 0, y < 0 or NaN
-// gives NaN.
-__device__ __forceinline__ double fsqrt(double y)
-{
-    const double r = __builtin_amdgcn_rsq(y);
-    double g = y * r, h = 0.5 * r;
-    const double e = fma(-g, h, 0.5);
-    g = fma(g, e, g);
-    h = fma(h, e, h);
-    g = fma(fma(-g, g, y), h, g);
-    return y == 0.0 ? 0.0 : g;
-}
-
-// two FP32 values in one FP64 LDS slot (register moves only)
-struct F2 {
-    float x, y;
-};
-__device__ __forceinline__ double pack2(float x, float y)
-{
-    return __hiloint2double(__float_as_int(y), __float_as_int(x));
-}
-__device__ __forceinline__ F2 unpack2(double d)
-{
-    return F2{__int_as_float(__double2loint(d)), __int_as_float(__double2hiint(d))};
-}
-
-struct NodeP {
-    double u[4];
-    double r, v1, v2, p, c;
-};
-
-__device__ __forceinline__ void make_node(NodeP& s, double g)
-{
-    const double ir = frcp(s.u[0]);
-    s.r = s.u[0];
-    s.v1 = s.u[1] * ir;
-    s.v2 = s.u[2] * ir;
-    s.p = (g - 1.0) * (s.u[3] - 0.5 * (s.u[1] * s.v1 + s.u[2] * s.v2));
-    s.c = fsqrt(g * s.p * ir);
-}
-
-// Ghost state across a boundary face f (0 x-, 1 x+, 2 y-, 3 y+) of the interior
-// node s; the outward normal is the axis f / 2, negative on even faces.  Wall:
-// the normal momentum reversed.  Characteristic, by the outward normal velocity
-// vn and sound speed c of s: the exterior state x if vn <= -c; x's density and
-// velocity with s's pressure if vn <= 0; s's density and velocity with x's
-// pressure if vn < c; else s.  Outflow: s.
-__device__ __forceinline__ void boundary_ghost(int kind, const double* x, const NodeP& s, int f,
-                                               double g, double* gu)
-{
-    const int d = f >> 1;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) gu[v] = s.u[v];
-    if (kind == DGIDP_BC_WALL) {  // (constant indices keep gu in registers)
-        if (d == 0) gu[1] = -s.u[1];
-        else gu[2] = -s.u[2];
-        return;
-    }
-    if (kind != DGIDP_BC_CHARACTERISTIC) return;
-    const double vn = (f & 1) ? (d == 0 ? s.v1 : s.v2) : -(d == 0 ? s.v1 : s.v2);
-    if (vn >= s.c) return;
-    if (vn <= -s.c) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) gu[v] = x[v];
-        return;
-    }
-    const double ixr = 1.0 / x[0], xv1 = x[1] * ixr, xv2 = x[2] * ixr;
-    if (vn <= 0.0) {
-        gu[0] = x[0];
-        gu[1] = x[0] * xv1;
-        gu[2] = x[0] * xv2;
-        gu[3] = s.p / (g - 1.0) + 0.5 * x[0] * (xv1 * xv1 + xv2 * xv2);
-    } else {
-        const double xp = (g - 1.0) * (x[3] - 0.5 * (x[1] * xv1 + x[2] * xv2));
-        gu[3] = xp / (g - 1.0) + 0.5 * s.r * (s.v1 * s.v1 + s.v2 * s.v2);
-    }
-}
-
-__device__ __forceinline__ double pressure(const double* u, double g)
-{
-    return (g - 1.0) * (u[3] - 0.5 * (u[1] * u[1] + u[2] * u[2]) * frcp(u[0]));
-}
-
-// local Lax-Friedrichs flux across a face (eq. FVmethod): 1/2 (f_n(u_L) + f_n(u_R)) -
-// 1/2 lambda (u_R - u_L), lambda = max(|v_n| + c) of the two states.
-// Normal direction d and side are run-time values (lanes of a wave hold
-// different faces): this element's state `own`, the other side's state `o`,
-// own_low = this element is on the low side.  Branch free, so a wave evaluates
-// one flux body whatever mix of faces its lanes hold.
-__device__ __forceinline__ void llf_face(int d, bool own_low, const NodeP& own, const NodeP& o,
-                                         double* F)
-{
-    const bool dx = d == 0;
-    const double va = dx ? own.v1 : own.v2, vb = dx ? o.v1 : o.v2;
-    const double lam = fmax(fabs(va) + own.c, fabs(vb) + o.c);
-    const double hl = own_low ? 0.5 * lam : -0.5 * lam;
-    double fa[4], fb[4];
-    fa[0] = own.r * va;
-    fa[1] = own.u[1] * va + (dx ? own.p : 0.0);
-    fa[2] = own.u[2] * va + (dx ? 0.0 : own.p);
-    fa[3] = (own.u[3] + own.p) * va;
-    fb[0] = o.r * vb;
-    fb[1] = o.u[1] * vb + (dx ? o.p : 0.0);
-    fb[2] = o.u[2] * vb + (dx ? 0.0 : o.p);
-    fb[3] = (o.u[3] + o.p) * vb;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) F[v] = 0.5 * (fa[v] + fb[v]) - hl * (o.u[v] - own.u[v]);
-}
-
-// LLF flux on a mortar node between the interpolated large-face state ui and
-// the small-face state us.  An interpolated state outside the admissible set
-// leaves the high-order mortar flux undefined (NaN); the mortar limiter then
-// keeps the low-order flux for the whole mortar.
-__device__ __forceinline__ void mortar_flux(int d, bool large_low, const NodeP& ui, const NodeP& us,
-                                            double* F)
-{
-    if (!(ui.r > 0.0) || !(ui.p > 0.0)) {
-        const double nan = __builtin_nan("");
-        F[0] = F[1] = F[2] = F[3] = nan;
-        return;
-    }
-    llf_face(d, large_low, ui, us, F);
-}
-
 // logarithmic mean x^ln = (x - y) / (ln x - ln y) from the logarithms lx, ly.
 // Where |f| = |x - y| / (x + y) < 1e-2 (f^2 < 1e-4) the series
 // x^ln = (x + y)/2 f / atanh f = (x + y)/2 (1 - f^2/3 - 4 f^4/45 - 44 f^6/945 - ...)
@@ -313,7 +166,7 @@ __device__ __forceinline__ double lnmean(double x, double y, double lx, double l
 {
     const double s = x + y, d = x - y;
     const bool ser = fabs(d) < 1e-2 * s;
-    const double r = frcp(ser ? s : lx - ly);
+    const double r = Rc::rcp(ser ? s : lx - ly);
     const double f = d * r, f2 = f * f;
     // 1/3 + f2 (4/45 + f2 44/945) = 44/945 (945/132 + f2 (21/11 + f2)): one
     // literal per instruction
@@ -327,7 +180,7 @@ __device__ __forceinline__ double inv_lnmean(double x, double y, double lx, doub
 {
     const double s = x + y, d = x - y;
     const bool ser = fabs(d) < 1e-2 * s;
-    const double r = frcp(ser ? s : d);
+    const double r = Rc::rcp(ser ? s : d);
     const double f = d * r, f2 = f * f;
     // 2/3 + f2 (2/5 + f2 2/7) = 2/7 (7/3 + f2 (7/5 + f2))
     const double t = fma(f2, f2 + 7.0 / 5.0, 7.0 / 3.0) * f2;
@@ -352,7 +205,7 @@ __device__ __forceinline__ double flog(double x)
         k -= 1;
     }
     const double f = m - 1.0;
-    const double sf = f * frcp(2.0 + f);
+    const double sf = f * Rc::rcp(2.0 + f);
     const double z = sf * sf;
     const double t = z * (2.0 / 3.0 + z * (2.0 / 5.0 + z * (2.0 / 7.0 + z * (2.0 / 9.0 + z * (2.0 / 11.0 +
                      z * (2.0 / 13.0 + z * (2.0 / 15.0 + z * (2.0 / 17.0 + z * (2.0 / 19.0 + z * (2.0 / 21.0))))))))));
@@ -362,83 +215,9 @@ __device__ __forceinline__ double flog(double x)
     return x > 0.0 ? r : __builtin_nan("");
 }
 
-__device__ __forceinline__ float lnmeanf(float x, float y, float lx, float ly)
-{
-    const float s = x + y, d = x - y;
-    if (d * d < 1e-2f * (s * s)) {
-        const float is = __builtin_amdgcn_rcpf(s);
-        const float f2 = d * d * is * is;
-        return s * __builtin_amdgcn_rcpf(2.0f + f2 * (2.0f / 3.0f + f2 * (2.0f / 5.0f + f2 * (2.0f / 7.0f))));
-    }
-    return d * __builtin_amdgcn_rcpf(lx - ly);
-}
-
-__device__ __forceinline__ float inv_lnmeanf(float x, float y, float lx, float ly)
-{
-    const float s = x + y, d = x - y;
-    if (d * d < 1e-2f * (s * s)) {
-        const float is = __builtin_amdgcn_rcpf(s);
-        const float f2 = d * d * is * is;
-        return (2.0f + f2 * (2.0f / 3.0f + f2 * (2.0f / 5.0f + f2 * (2.0f / 7.0f)))) * is;
-    }
-    return (lx - ly) * __builtin_amdgcn_rcpf(d);
-}
-
-// ---------------------------------------------------------------------------
-// pressure blending factor: largest theta in [0,1] with rho(u0 + theta dc) > 0
-// and p(u0 + theta dc) >= pt.  For rho > 0, p >= pt is
-// g(theta) = (E - pt/(gamma-1)) rho - |m|^2 / 2 >= 0, a quadratic in theta whose
-// admissible set along the ray is an interval [0, theta*] (p is concave).
-// ---------------------------------------------------------------------------
-// The ray's direction is S c (S = Gamma = 4 for the volume faces' increments,
-// 1 otherwise): a power of two, so that S c is formed exactly inside the
-// fused multiply-adds.
-template <int S = 1>
-__device__ __forceinline__ double theta_p(const double* u0, const double* c, double pt, double ig1)
-{
-    const double e0 = u0[3] - pt * ig1;
-    const double g0 = u0[0] * e0 - 0.5 * (u0[1] * u0[1] + u0[2] * u0[2]);
-    if (!(g0 > 0.0) || !(u0[0] > 0.0)) return 0.0;
-    // full step admissible: the interval contains [0, 1]
-    const double r1 = fma((double)S, c[0], u0[0]);
-    if (r1 > 0.0) {
-        const double m1 = fma((double)S, c[1], u0[1]), m2 = fma((double)S, c[2], u0[2]);
-        const double g1v = fma((double)S, c[3], e0) * r1 - 0.5 * (m1 * m1 + m2 * m2);
-        if (g1v >= 0.0) return 1.0;
-    }
-    const double dc[4] = {S * c[0], S * c[1], S * c[2], S * c[3]};
-    const double g1 = dc[0] * e0 + u0[0] * dc[3] - (u0[1] * dc[1] + u0[2] * dc[2]);
-    const double g2 = dc[0] * dc[3] - 0.5 * (dc[1] * dc[1] + dc[2] * dc[2]);
-    double root = 1.0;
-    if (g2 == 0.0) {
-        if (g1 < 0.0) root = fmin(root, -g0 / g1);
-    } else {
-        const double disc = g1 * g1 - 4.0 * g2 * g0;
-        if (disc >= 0.0) {
-            const double sq = sqrt(disc);
-            const double qq = -0.5 * (g1 + (g1 >= 0.0 ? sq : -sq));
-            const double ra = qq / g2, rb = g0 / qq;
-            if (ra > 0.0) root = fmin(root, ra);
-            if (rb > 0.0) root = fmin(root, rb);
-        }
-    }
-    if (dc[0] < 0.0) root = fmin(root, -u0[0] / dc[0]);
-    return root;
-}
-
-// the limiter aims at the bounds raised by this relative margin so that the
-// rounding of the final sums cannot cross the bounds themselves
-constexpr double kMargin = 1.0 + 0x1p-40;
-constexpr double kMarginHi = 1.0 - 0x1p-40;  // the same for upper bounds
-// the mortar correction aims at half that margin: a node that the volume
-// limiter left on its target keeps 2^-41 of room, instead of a zero or one
-// mortar factor decided by the sign of a rounding error
-constexpr double kMarginMortar = 1.0 + 0x1p-41;
+// upper bounds are aimed at from below by the same margins
+constexpr double kMarginHi = 1.0 - 0x1p-40;
 constexpr double kMarginMortarHi = 1.0 - 0x1p-41;
-// the local bounds hold for the low-order state only up to rounding (it is a
-// convex combination of bar states in exact arithmetic): the bound check allows
-// this relative slack for them
-constexpr double kLocalTol = 1e-12;
 // density increments (per node and step) this small relative to the density are
 // not limited against the local density bounds
 constexpr double kLocalNegl = 1e-14;
@@ -459,7 +238,7 @@ __device__ __forceinline__ void bar_bounds(int d, bool own_low, const NodeP& own
     const bool dx = d == 0;
     const double va = dx ? own.v1 : own.v2, vb = dx ? o.v1 : o.v2;
     const double lam = fmax(fabs(va) + own.c, fabs(vb) + o.c);
-    const double k = (own_low ? 0.5 : -0.5) * frcp(lam);
+    const double k = (own_low ? 0.5 : -0.5) * Rc::rcp(lam);
     double fa[4], fb[4];
     fa[0] = own.r * va;
     fa[1] = own.u[1] * va + (dx ? own.p : 0.0);
@@ -579,7 +358,7 @@ __device__ __forceinline__ double volume_factor(const double* uFV, const double 
     if (LOCB && P > -kLocalNegl * uFV[0]) P = 0.0;
     if (LOCB && Pp < kLocalNegl * uFV[0]) Pp = 0.0;
     double th = 1.0;
-    if (P < 0.0) th = fmax(fmin((rt - uFV[0]) * frcp(P), 1.0), 0.0);
+    if (P < 0.0) th = fmax(fmin((rt - uFV[0]) * Rc::rcp(P), 1.0), 0.0);
     if (LOCB && Pp > 0.0) th = fmin(th, fmax((rce * kMarginHi - uFV[0]) / Pp, 0.0));
     // pressure: each face's increment scaled by Gamma = 2d = 4 (a zero
     // increment, as on a missing face, admits theta = 1 at an admissible uFV)
@@ -620,62 +399,6 @@ __device__ __forceinline__ double mortar_factor(const double* uvol, const double
 }
 
 // ---------------------------------------------------------------------------
-// statistics
-// ---------------------------------------------------------------------------
-template <typename TT>
-__device__ __forceinline__ TT wave_sum(TT v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-__device__ __forceinline__ double wave_min(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
-__device__ __forceinline__ double wave_max(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
-// accumulation of per-thread statistics; every lane of the wave must call it.
-// Counts are taken from lane masks (per lane: inad and viol 0 or 1); the two
-// floating-point reductions run only in waves where some lane has a value to
-// contribute, and only such waves touch memory, at the accumulator of their
-// block.  The number of faces and mortars, by which the means divide, follows
-// from the mesh and is not counted here.  Bound: the device-scope atomics that
-// meet at one address are served one after another, about 10 ns each; with one
-// accumulator and two counts per wave the 22,156-leaf N = 3 stage took 142 us
-// with statistics against 20 us without, with them spread and the counts gone
-// 21.4 us; the blended stage of the 22,732-leaf jet 157 and 43 us, the N = 4
-// local one of the 20,480-element double Mach reflection 305 and 74 us.
-__device__ __forceinline__ void push_stats(DevStats* st, unsigned long long inad,
-                                           unsigned long long viol, double thmin, double asum, bool mortar)
-{
-    const unsigned long long ninad = __popcll(__ballot(inad != 0));
-    const unsigned long long nviol = __popcll(__ballot(viol != 0));
-    const bool any_a = __ballot(asum != 0.0) != 0, any_t = __ballot(thmin < 1.0) != 0;
-    if (any_a) asum = wave_sum(asum);
-    if (any_t) thmin = wave_min(thmin);
-    if ((threadIdx.x & 63) == 0) {
-        DevStats* s = st + blockIdx.x % kStatSpread;
-        if (ninad) atomicAdd(&s->fv_inadmissible, ninad);
-        if (nviol) atomicAdd(&s->violations, nviol);
-        if (any_a) atomicAdd(mortar ? &s->alpha_mort_sum : &s->alpha_vol_sum, asum);
-        if (any_t) {
-            unsigned long long bits = __double_as_longlong(fmax(thmin, 0.0));
-            atomicMin(mortar ? &s->theta_mort_min_bits : &s->theta_vol_min_bits, bits);
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // element kernel
 // ---------------------------------------------------------------------------
 // Local bounds from the low-order solution (eq. Bounds_LowOrder): per node the density
@@ -706,15 +429,11 @@ struct StageArgs {
     const int* fnbr;
     const int* fnbr2;
     const int* fmort;
-    const int* mort;
+    const int* mort;  // (not read; see dgidp_kernels.hip)
     const double* h;
     double* slot;
     const int8_t* bkind;  // boundary nodes: condition and exterior state
     const double* bext;
-    // element batches of this launch: blist[boff + i], i < gridDim.x (the
-    // batches holding a mortar element and the others are separate launches)
-    const int* blist;
-    int boff;
     int E;
     double gamma, beta;
     double ig1;  // 1 / (gamma - 1)
@@ -723,48 +442,6 @@ struct StageArgs {
     int vflux;  // two-point volume flux: DGIDP_FLUX_RANOCHA or DGIDP_FLUX_CHANDRASHEKAR
     DevStats* st;
 };
-
-// node (a, b) at position k along face f
-template <int N>
-__device__ __forceinline__ int face_q(int f, int k)
-{
-    constexpr int n = N + 1;
-    // x faces (0, 1) run along a column, y faces (2, 3) along a row; the odd
-    // face of each pair is N columns or N rows further on
-    const int hi = f & 1;
-    return f < 2 ? k * n + hi * N : k + hi * (N * n);
-}
-
-template <int N>
-__device__ __forceinline__ void load_u(const double* u, int e, int q, double* w)
-{
-    constexpr int NN = (N + 1) * (N + 1);
-    // one address per node; the variables at constant offsets (index < 2^30, mesh limit)
-    const double* p = u + ((unsigned)e * 4u * NN + (unsigned)q);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) w[v] = p[v * NN];
-}
-
-template <int N>
-__device__ __forceinline__ void load_node(const double* u, int e, int q, NodeP& s, double g)
-{
-    load_u<N>(u, e, q, s.u);
-    make_node(s, g);
-}
-
-// pair (l, k), l < k, number i of a line
-template <int N>
-__device__ __forceinline__ void pair_lk(int i, int& l, int& k)
-{
-    constexpr int n = N + 1;
-    int r = i;
-    l = 0;
-    while (r >= n - 1 - l) {
-        r -= n - 1 - l;
-        ++l;
-    }
-    k = l + 1 + r;
-}
 
 // node qq of the block's element le from its LDS primitives; the conserved
 // state is formed again from them (rho v = rho * v, E = p / (gamma - 1) +
@@ -837,7 +514,7 @@ void k_stage(StageArgs A)
     const int tid = threadIdx.x;
     const int le = tid / NN, q = tid - le * NN, a = q % n, b = q / n;
     const int xb = !MORT && A.rev ? xcd_batch_rev(blockIdx.x, gridDim.x) : xcd_batch(blockIdx.x, gridDim.x);
-    const int e = (A.blist ? A.blist[A.boff + xb] : xb) * EPB + le;
+    const int e = xb * EPB + le;
     double* const sRe = &sR[0][0][0] + le * 8 * NN;  // element le's rows, flat
     double* const sPe = &sPair[0][0][0] + le * 4 * PP;  // element le's pair buffer, flat
     const bool act = tid < NT && e < A.E;
@@ -885,7 +562,7 @@ void k_stage(StageArgs A)
             fnb2 = A.fnbr2[e * 4 + ff];
         }
         NodeP me;
-        load_node<N>(A.uin, e, q, me, g);
+        load_node<N, Rc>(A.uin, e, q, me, g);
         hx = A.h[2 * e];
         hy = A.h[2 * e + 1];
         if (COMB) w_e = A.ind[e];
@@ -894,7 +571,7 @@ void k_stage(StageArgs A)
         // the logarithms feed only the two-point volume fluxes: FP32 in the
         // mixed mode, where rows 5-7 hold the FP32 operands of those fluxes in
         // pairs (rho, p), (ln rho, z), (ln z, 0)
-        const double z = me.r * frcp(me.p);
+        const double z = me.r * Rc::rcp(me.p);
         sR[le][0][q] = me.r;
         sR[le][1][q] = me.v1;
         sR[le][2][q] = me.v2;
@@ -1010,7 +687,7 @@ void k_stage(StageArgs A)
             } else {
                 boundary_ghost(bk, onb, own, ff, g, o.u);
             }
-            make_node(o, g);
+            make_node<Rc>(o, g);
             double F[4];
             llf_face(dff, lowf, own, o, F);
             if (BAR && need_loc) {
@@ -1028,7 +705,7 @@ void k_stage(StageArgs A)
                 NodeP ui, us;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) us.u[v] = hh == 0 ? onb[v] : us1[v];
-                make_node(us, g);
+                make_node<Rc>(us, g);
                 // the large face interpolated to half hh, from the face nodes'
                 // conserved states formed as LDS_NODE does
                 double ia[4] = {0, 0, 0, 0};
@@ -1046,7 +723,7 @@ void k_stage(StageArgs A)
                 }
 #pragma unroll
                 for (int v = 0; v < 4; ++v) ui.u[v] = ia[v];
-                make_node(ui, g);
+                make_node<Rc>(ui, g);
                 double F[4];
                 mortar_flux(dff, lowf, ui, us, F);
 #pragma unroll
@@ -1066,7 +743,7 @@ void k_stage(StageArgs A)
                 NodeP us;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) us.u[v] = sPair[le][v][MB + ff * 2 * n + col];
-                make_node(us, g);
+                make_node<Rc>(us, g);
                 double Gf[4];
                 llf_face(dff, lowf, own, us, Gf);
                 if (BAR && need_loc) {
@@ -1100,7 +777,7 @@ void k_stage(StageArgs A)
                     ui.u[v] = acc;
                 }
             }
-            make_node(ui, g);
+            make_node<Rc>(ui, g);
             double F[4], ho[4], lo[4] = {0, 0, 0, 0};
             mortar_flux(dff, !lowf, ui, own, F);
 #pragma unroll
@@ -1113,7 +790,7 @@ void k_stage(StageArgs A)
                 NodeP uj;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) uj.u[v] = sPair[le][v][ff * n + j];
-                make_node(uj, g);
+                make_node<Rc>(uj, g);
                 double Gf[4];
                 llf_face(dff, lowf, own, uj, Gf);
                 if (BAR && need_loc) {
@@ -1218,7 +895,7 @@ void k_stage(StageArgs A)
                 if (A.vflux == DGIDP_FLUX_CHANDRASHEKAR) {
                     // Chandrashekar: beta = z / 2, so p~ = rho-bar / (2 beta-bar) =
                     // (rho_L + rho_R) / (z_L + z_R) and 1 / (2 beta^ln) = 1 / z^ln
-                    const double pt = (L0 + R0) * frcp(L6 + R6);
+                    const double pt = (L0 + R0) * Rc::rcp(L6 + R6);
                     fn = fr * vna + pt;
                     ft = fr * vta;
                     f3 = fr * (ig1 * iz_ln - 0.25 * (Ln * Ln + Lt * Lt + Rn * Rn + Rt * Rt)) + vna * fn + vta * ft;
@@ -1390,10 +1067,8 @@ void k_stage(StageArgs A)
     double RLO[4], dS0[4] = {0, 0, 0, 0}, dS1[4] = {0, 0, 0, 0};
     int slot0 = -1, slot1 = -1, nmf = 0;
     double im = 1.0;  // 1 / m_i
-    // antidiffusive flux w (f^HO - f^FV) of face j, signed as its weight, variable v
-    auto antidiff = [&](int j, int v) { return fweight(j) * (sPe[v * PP + hslot(j)] - sFV(v, fidx(j))); };
     if (act) {
-        im = 4.0 * frcp(hx * hy) * sTw[1][a] * sTw[1][b];
+        im = 4.0 * Rc::rcp(hx * hy) * sTw[1][a] * sTw[1][b];
         const double cw[4] = {fweight(0), fweight(1), fweight(2), fweight(3)};
         const int fi[4] = {fidx(0), fidx(1), fidx(2), fidx(3)};
         // the surface terms of the element faces the node lies on: at most one
@@ -1436,7 +1111,7 @@ void k_stage(StageArgs A)
         double w[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) w[v] = u0[v] + dt * (RLO[v] * im);
-        const double p = pressure(w, g);
+        const double p = pressure<Rc>(w, g);
         if (act) {
             double* o = A.uout + ((unsigned)e * 2u * NN + (unsigned)q);
             o[0] = w[0];
@@ -1456,7 +1131,7 @@ void k_stage(StageArgs A)
     if (act) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) uFV[v] = u0[v] + dtm * RLO[v];
-        const double pFV = pressure(uFV, g);
+        const double pFV = pressure<Rc>(uFV, g);
         if (!(uFV[0] > 0.0) || !(pFV > 0.0)) inad = 1;
         rmin = A.beta * uFV[0];
         pmin = A.beta * pFV;
@@ -1583,8 +1258,8 @@ void k_stage(StageArgs A)
         if (nmf == 0) {
             if (PURE) {
                 if (A.st && (!(uvol[0] >= rlf * (1.0 - kLocalTol)) || uvol[0] > rhi * (1.0 + kLocalTol) ||
-                             pressure(uvol, g) < pmin ||
-                             !(log(pressure(uvol, g)) - g * log(uvol[0]) >= lsm - kLocalTol)))
+                             pressure<Rc>(uvol, g) < pmin ||
+                             !(log(pressure<Rc>(uvol, g)) - g * log(uvol[0]) >= lsm - kLocalTol)))
                     viol = 1;
             } else if (A.limiter != DGIDP_LIMIT_NONE) {
                 // p(uvol) >= pmin as 2 rho (E - pmin / (gamma - 1)) >= |m|^2 (rho >= rmin > 0)
@@ -1637,174 +1312,6 @@ void k_stage(StageArgs A)
         }
     }
     if (A.st) push_stats(A.st, inad, viol, thmin, asum, false);
-}
-
-// ---------------------------------------------------------------------------
-// time step: per node sum_j 2 d_ij / m_i (or the low-order estimate), block max
-// ---------------------------------------------------------------------------
-struct DtArgs {
-    const double* u;
-    const int* fnbr;
-    const int* fnbr2;
-    const int* fmort;
-    const int* mort;
-    const double* h;
-    const int8_t* bkind;
-    const double* bext;
-    int E;
-    double gamma;
-    int mode;
-    unsigned long long* acc;    // running maximum, bits of a non-negative double
-    unsigned long long* other;  // the other accumulator, cleared for the next step
-};
-
-__device__ __forceinline__ double wave_speed(const NodeP& s, int d)
-{
-    return fabs(d == 0 ? s.v1 : s.v2) + s.c;
-}
-
-// the dt kernel: kDtBlock = 256-thread blocks (16 elements at N = 3, 10 at N = 4), fewer
-// blocks and so fewer atomics than the stage kernel's geometry
-// threads per block of the dt kernel (whole elements per block)
-constexpr int kDtBlock = 256;
-
-template <int N>
-struct DtGeo {
-    static constexpr int n = N + 1, NN = n * n, NFN = 4 * n;
-    static constexpr int BS = kDtBlock, EPB = BS / NN, NT = EPB * NN;
-};
-
-template <int N>
-__global__ __launch_bounds__(kDtBlock) void k_dt(DtArgs A)
-{
-    using G = DtGeo<N>;
-    constexpr int n = G::n, NN = G::NN, EPB = G::EPB, NT = G::NT, NFN = G::NFN;
-    __shared__ double sL[EPB][2][NN];
-    __shared__ double sF[EPB][NFN];
-    __shared__ double sMl[EPB][8 * n];  // wave speeds across mortars, staged per position
-    constexpr int NW = G::BS / 64;  // waves per block
-    __shared__ double sRed[NW];
-    __shared__ double sTw[2][n];  // LGL weights and their reciprocals, read per lane
-    const Tab<N>& tb = T<N>();
-    const double g = A.gamma;
-    const int tid = threadIdx.x;
-    const int le = tid / NN, q = tid - le * NN, a = q % n, b = q / n;
-    // (contiguous element ranges per XCD, as in the stage kernel: the face
-    // neighbours' traces are then mostly in the same L2; each range from its
-    // end, where the stage before this kernel finished writing)
-    const int e = xcd_batch_rev(blockIdx.x, gridDim.x) * EPB + le;
-    const bool act = tid < NT && e < A.E;
-    if (tid < n) {
-        sTw[0][tid] = tb.w[tid];
-        sTw[1][tid] = tb.winv[tid];
-    }
-    const bool idp = A.mode != DGIDP_DT_LOWORDER;
-    const bool fnode = act && idp && q < NFN;
-    const int ff = q / n, fk = q - (q / n) * n, dff = ff >> 1;
-    double hx = 1.0, hy = 1.0, lo_nb = 0.0;
-    int code = -1, nb = 0, nb2 = -1;
-    if (act) {
-        if (fnode) {  // face tables first: the neighbour loads depend on them
-            code = A.fmort[e * 4 + ff];
-            nb = A.fnbr[e * 4 + ff];
-            nb2 = A.fnbr2[e * 4 + ff];
-        }
-        NodeP me;
-        load_node<N>(A.u, e, q, me, g);
-        hx = A.h[2 * e];
-        hy = A.h[2 * e + 1];
-        sL[le][0][q] = wave_speed(me, 0);
-        sL[le][1][q] = wave_speed(me, 1);
-        if (fnode) {
-            NodeP o;
-            if (code >= -1) {
-                load_node<N>(A.u, nb, face_q<N>(ff ^ 1, fk), o, g);
-            } else {  // boundary: the ghost state of the face node
-                const int j = (-2 - code) * n + fk;
-                double x[4];
-#pragma unroll
-                for (int v = 0; v < 4; ++v) x[v] = A.bext[(size_t)j * 4 + v];
-                NodeP s;
-                load_node<N>(A.u, e, face_q<N>(ff, fk), s, g);
-                boundary_ghost(A.bkind[j], x, s, ff, g, o.u);
-                make_node(o, g);
-            }
-            lo_nb = wave_speed(o, dff);
-            if (code >= 0) {
-                // mortar: stage the wave speeds of the other side at position fk
-                // (large side: both small elements; small side: the large one)
-                sMl[le][(ff * 2) * n + fk] = lo_nb;
-                if (!fm_small(code)) {
-                    NodeP o2;
-                    load_node<N>(A.u, nb2, face_q<N>(ff ^ 1, fk), o2, g);
-                    sMl[le][(ff * 2 + 1) * n + fk] = wave_speed(o2, dff);
-                }
-            }
-        }
-    }
-    __syncthreads();
-    if (fnode) {
-        // edges across face ff at position fk: 2 |c_ij| lambda_ij
-        const double hf = ff < 2 ? hy : hx;
-        const double lm = sL[le][dff][face_q<N>(ff, fk)];
-        double sum = 0.0;
-        if (code < 0) {
-            sum = 0.5 * sTw[0][fk] * hf * fmax(lm, lo_nb);
-        } else if (!fm_small(code)) {
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int l = 0; l < n; ++l) {
-                    const double wt = tb.Wt[fk][hh * n + l];
-                    if (wt == 0.0) continue;
-                    sum += 2.0 * wt * hf * 0.25 * fmax(lm, sMl[le][(ff * 2 + hh) * n + l]);
-                }
-        } else {
-            const int hh = fm_half(code);
-#pragma unroll
-            for (int j = 0; j < n; ++j) {
-                const double wt = tb.Wt[j][hh * n + fk];
-                if (wt == 0.0) continue;
-                sum += 2.0 * wt * (2.0 * hf) * 0.25 * fmax(lm, sMl[le][(ff * 2) * n + j]);
-            }
-        }
-        sF[le][q] = sum;
-    }
-    __syncthreads();
-    double s = 0.0;
-    if (act) {
-        const double lx = sL[le][0][q], ly = sL[le][1][q];
-        if (!idp) {
-            s = (N + 1) * (lx * frcp(hx) + ly * frcp(hy));
-        } else {
-            // edges along x carry 2 |c| = w_b h_y / 2, along y w_a h_x / 2
-            const double cx = 0.5 * sTw[0][b] * hy, cy = 0.5 * sTw[0][a] * hx;
-            double sum = 0.0;
-            if (a > 0) sum += cx * fmax(lx, sL[le][0][q - 1]);
-            if (a < N) sum += cx * fmax(lx, sL[le][0][q + 1]);
-            if (b > 0) sum += cy * fmax(ly, sL[le][1][q - n]);
-            if (b < N) sum += cy * fmax(ly, sL[le][1][q + n]);
-            if (a == 0) sum += sF[le][0 * n + b];
-            if (a == N) sum += sF[le][1 * n + b];
-            if (b == 0) sum += sF[le][2 * n + a];
-            if (b == N) sum += sF[le][3 * n + a];
-            s = sum * (4.0 * frcp(hx * hy)) * sTw[1][a] * sTw[1][b];
-        }
-    }
-    s = wave_max(s);
-    if ((tid & 63) == 0) sRed[tid >> 6] = s;
-    __syncthreads();
-    if (tid == 0) {
-        // non-negative doubles order like their bit patterns; NaN and zero
-        // maxima are left out, as fmax would
-        double m = sRed[0];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) m = fmax(m, sRed[w]);
-        if (m > 0.0)
-            atomicMax(A.acc + (blockIdx.x % kDtSpread) * kDtStride,
-                      (unsigned long long)__double_as_longlong(m));
-    }
-    if (blockIdx.x == 0 && tid < kDtSpread) A.other[tid * kDtStride] = 0ull;
 }
 
 // ---------------------------------------------------------------------------
@@ -1884,20 +1391,6 @@ int launch_shock_indicator(int N, const DevMesh& m, const double* u, double gamm
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// one wave reads the kDtSpread accumulators; the stage kernels then read the
-// stored value (a per-wave reduction in every block of the first stage would
-// read the kDtSpread cache lines once per wave)
-__global__ __launch_bounds__(64) void k_dt_final(const unsigned long long* dtmax, double cfl, double* dt_out,
-                                                 DevStats* st)
-{
-    const double m = wave_max(__longlong_as_double((long long)dtmax[threadIdx.x * kDtStride]));
-    if (threadIdx.x == 0) {
-        const double dt = cfl / m;
-        *dt_out = dt;
-        if (st) st->dt = dt;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
@@ -1908,45 +1401,16 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
 {
     using G = Geo<N>;
     StageArgs A;
-    A.uin = uin;
-    A.un = un;
-    A.uout = uout;
-    A.a = a;
-    A.b = b;
-    A.dt = dt.dt;
+    set_stage(A, m, kp, uin, un, uout, a, b, dt, st);
     A.ind = m.shock_ind;
     A.lsv = m.lsv;
-    A.dtmax = dt.dtmax;
-    A.cfl = dt.cfl;
-    A.dt_out = dt.dt_out;
-    // on a large mesh dt is reduced once, by k_dt_final, and the stage reads
-    // it; on a small one (fewer than kFinalMin batches) the extra launch costs
-    // more than the stage's own per-wave reduction
-    constexpr int kFinalMin = 16384;
-    if (dt.dtmax && dt.dt_out && mode == MODE_STAGE && (m.E + G::EPB - 1) / G::EPB >= kFinalMin) {
-        static_assert(kDtSpread == 64, "one wave reduces the dt accumulators");
+    const int nb = (m.E + G::EPB - 1) / G::EPB;
+    // on a large mesh dt is reduced once, and the stage reads it
+    if (dt.dtmax && dt.dt_out && mode == MODE_STAGE && nb >= kFinalMin) {
         hipLaunchKernelGGL(k_dt_final, dim3(1), dim3(64), 0, s, dt.dtmax, dt.cfl, dt.dt_out, st);
         A.dt = dt.dt_out;
         A.dtmax = nullptr;
     }
-    A.fnbr = m.fnbr;
-    A.fnbr2 = m.fnbr2;
-    A.fmort = m.fmort;
-    A.bkind = m.bkind;
-    A.bext = m.bext;
-    A.mort = m.mort;
-    A.h = m.h;
-    A.slot = m.slot;
-    A.blist = m.blist;
-    A.E = m.E;
-    A.gamma = kp.gamma;
-    A.ig1 = 1.0 / (kp.gamma - 1.0);
-    A.rev = 0;
-    A.beta = kp.beta;
-    A.limiter = kp.limiter;
-    A.vflux = kp.vflux;
-    A.st = st;
-    const int nb = (m.E + G::EPB - 1) / G::EPB;
     const bool mixed = kp.precision == DGIDP_MIXED;
     const int lk = kp.limiter == DGIDP_LIMIT_LOCAL ? 1
                    : kp.limiter == DGIDP_LIMIT_COMBINED ? 2
@@ -1957,8 +1421,6 @@ static int stage_N(const DevMesh& m, const KernelParams& kp, const double* uin, 
     auto go = [&](auto modec, auto mixc, auto lkc) {
         constexpr int MD = decltype(modec)::value, LK = decltype(lkc)::value;
         constexpr bool MX = decltype(mixc)::value;
-        A.blist = nullptr;  // element batches in mesh order
-        A.boff = 0;
         if (m.nbm > 0) hipLaunchKernelGGL((k_stage<N, MD, MX, LK, true>), dim3(nb), dim3(G::BS), 0, s, A);
         else {
             A.rev = rev ? 1 : 0;
@@ -2007,26 +1469,12 @@ int launch_lowsol(int N, const DevMesh& m, const KernelParams& kp, const double*
 int launch_dt(int N, const DevMesh& m, const KernelParams& kp, const double* u, int mode,
               unsigned long long* acc, unsigned long long* other, hipStream_t s)
 {
-    DtArgs A;
-    A.u = u;
-    A.fnbr = m.fnbr;
-    A.fnbr2 = m.fnbr2;
-    A.fmort = m.fmort;
-    A.bkind = m.bkind;
-    A.bext = m.bext;
-    A.mort = m.mort;
-    A.h = m.h;
-    A.E = m.E;
-    A.gamma = kp.gamma;
-    A.mode = mode;
-    A.acc = acc;
-    A.other = other;
-    if (N == 3)
-        hipLaunchKernelGGL(k_dt<3>, dim3((m.E + DtGeo<3>::EPB - 1) / DtGeo<3>::EPB), dim3(kDtBlock), 0, s, A);
-    else if (N == 4)
-        hipLaunchKernelGGL(k_dt<4>, dim3((m.E + DtGeo<4>::EPB - 1) / DtGeo<4>::EPB), dim3(kDtBlock), 0, s, A);
-    else return -1;
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    return run_dt<Rc>(N, dt_args(m, kp, u, mode, acc, other), s);
+}
+
+int launch_mortar(int N, const DevMesh& m, const KernelParams& kp, double* uout, double b, DevStats* st, hipStream_t s)
+{
+    return run_mortar<Rc, true>(N, {m.slot, m.slot_node, m.slot_partner, m.M, uout, b, kp.gamma, kp.limiter, st}, s);
 }
 
 }  // namespace local

@@ -16,10 +16,10 @@ CMD="bash paper_2607_06045_amd/profile_bench.sh"
 BT="python3 bench.py --steps 20 --warmup 2 --no-cpu-baseline --legs none"
 BC="python3 bench.py --steps 2 --warmup 1 --no-cpu-baseline --legs none"
 CP="python3 -m paper_2607_06045_amd.profiling copy --mib 512"
-# one stage is two launches of the element kernel: k_stage<4, 0, false, 0, true>
-# over the element batches with a mortar element, k_stage<4, 0, false, 0, false>
+# one stage is two launches of the element kernel: k_stage<4, 0, false, true>
+# over the element batches with a mortar element, k_stage<4, 0, false, false>
 # over the others; the summaries add the two per stage
-KERNEL="k_stage<4, 0, false, 0,"
+KERNEL="k_stage<4, 0, false,"
 
 echo "== kernel trace: $BT"
 timeout -k 10 300 rocprofv3 --kernel-trace --stats -d "$OUT/trace" -o trace --output-format csv -- $BT \
@@ -45,7 +45,7 @@ pmc sqc "SQ_WAVE_CYCLES SQ_WAIT_INST_ANY SQ_ACTIVE_INST_VALU SQ_ACTIVE_INST_ANY 
 STATS=$(find "$OUT/trace" -name '*kernel_stats.csv' | head -1)
 python3 -m paper_2607_06045_amd.profiling stats --csv "$STATS" \
     --out "$OUT/summary/kernels_k_stage_quadrants247k.txt" \
-    --title "kernel durations, bench.py headline workload (four-quadrant states, 246,736 leaves, N=4, FP64; 20 steps + kernel timing; one stage = the two k_stage<4, 0, false, 0, *> launches)" \
+    --title "kernel durations, bench.py headline workload (four-quadrant states, 246,736 leaves, N=4, FP64; 20 steps + kernel timing; one stage = the two k_stage<4, 0, false, *> launches)" \
     --command "$CMD" --trace-csv "$(find "$OUT/trace" -name '*kernel_trace.csv' | head -1)" \
     --kernel "$KERNEL" --tail 150 --bench-log "$OUT/trace.log" || exit 1
 python3 -m paper_2607_06045_amd.profiling counters --fetch "$OUT/fetch" --write "$OUT/write" \
