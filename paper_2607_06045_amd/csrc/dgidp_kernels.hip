@@ -794,8 +794,9 @@ void k_stage(StageArgs A)
                 const double L0 = sRe[(0) * NN + q], L3 = sRe[(3) * NN + q], L6 = sRe[(6) * NN + q];
                 const double R0 = sRe[(0) * NN + qo], R3 = sRe[(3) * NN + qo], R6 = sRe[(6) * NN + qo];
                 const double s0 = L0 + R0, d0 = L0 - R0, s6 = L6 + R6, d6 = L6 - R6;
-                // one reciprocal for both sums; the round takes the shortest form
-                // that serves all its lanes
+                // one reciprocal for both sums (rho^2 / p, their product's size, within the
+                // range of Rcp3::rcp; NaN beyond); the round takes the shortest form that
+                // serves all its lanes
                 const double r = Rc::rcp(s0 * s6), r6 = s0 * r;
                 const double f0 = d0 * (s6 * r), f6 = d6 * r6;
                 const double z0 = f0 * f0, z6 = f6 * f6, zm = fmax(z0, z6);
@@ -807,11 +808,15 @@ void k_stage(StageArgs A)
                     hl = half_lnmean_poly(s0, z0);
                     iz = inv_lnmean_poly(r6, z6);
                     if (!__all(zm < kLnPoly)) {
-                        const double rr = Rc::rcp(R0 * R6);
                         double l0, l6;
-                        flog2(L0 * (R6 * rr), L6 * (R0 * rr), l0, l6);
+                        flog2(L0 * Rc::rcp(R0), L6 * Rc::rcp(R6), l0, l6);
                         if (!(z0 < kLnPoly)) hl = 0.5 * d0 * Rc::rcp(l0);
                         if (!(z6 < kLnPoly)) iz = l6 * Rc::rcp(d6);
+                        if (__any(zm != zm)) {  // a reciprocal for each sum
+                            const double q6 = Rc::rcp(s6), g0 = d0 * Rc::rcp(s0), g6 = d6 * q6;
+                            if (g0 * g0 < kLnPoly) hl = half_lnmean_poly(s0, g0 * g0);
+                            if (g6 * g6 < kLnPoly) iz = inv_lnmean_poly(q6, g6 * g6);
+                        }
                     }
                 }
                 const double sn = Ln + Rn, st = Lt + Rt;
