@@ -178,11 +178,11 @@ __device__ __forceinline__ unsigned pair_entry<4>(int q, int i) { return c_pm4.c
 // (ln x - ln y = 2 atanh f, as in Ismail & Roe 2009), both analytic in z:
 //   z < 1e-4: the series
 //     s (1/4 - (11/945) z (945/132 + z (21/11 + z))) and (2 + (2/7) z (7/3 + z (7/5 + z))) / s
-//     (the next terms are below 4e-18 relative there; monic, so that an
+//     (the next terms are at most 3.1e-18 and 1.2e-17 relative there; monic, so that an
 //     instruction has one literal at most)
 //   z < kLnPoly, x / y between 0.71 and 1.41: polynomials of seven coefficients with the least
-//     largest error (2.4e-19 and 1.3e-18 relative), so that a pair needs no logarithms of its
-//     nodes
+//     largest error (4.2e-19 and 1.8e-18 relative as rounded to doubles), so that a pair
+//     needs no logarithms of its nodes
 //   beyond: the logarithm of the ratio.
 constexpr double kLnSeries = 1e-4;
 constexpr double kLnPoly = 0.0294;
@@ -222,7 +222,7 @@ __device__ __forceinline__ double inv_lnmean_poly(double r, double z) { return f
 // x = m 2^k with m in [sqrt(1/2), sqrt(2)), f = m - 1 (exact), s = f / (2 + f), so
 // that ln m = 2 atanh s = 2 s + T, T = 2 s^3/3 + 2 s^5/5 + ..., and 2 s = f - s f
 // gives ln m = f - s (f - T / s) with T / s = z (2/3 + 2 z/5 + ...) in z = s^2 < 0.0295
-// (here the polynomial of seven coefficients with the least largest error, 2^-59
+// (here the polynomial of seven coefficients with the least largest error, 2.2e-18
 // of ln m); ln x = k ln 2 + ln m with ln 2 split into a head whose product
 // with k is exact and a tail.  About 1 ulp; the two share one reciprocal, of
 // (2 + f_x)(2 + f_y) between 2.9 and 5.9.
@@ -388,7 +388,7 @@ struct StageArgs {
 // instructions took the same time.
 template <int N, int MODE, bool MIXED, bool MORT>
 // waves per SIMD: four (128 registers), but for the FP64 N = 3 variant with mortars (148
-// registers, three waves, see LATE: 353 against 346 us with four)
+// registers, three waves, see LATE)
 __global__ __launch_bounds__(Geo<N>::BS) __attribute__((amdgpu_waves_per_eu((!MORT || N == 4 || MIXED) ? 4 : 3)))
 void k_stage(StageArgs A)
 {
@@ -402,11 +402,13 @@ void k_stage(StageArgs A)
     // LATE: the large sides form their high-order mortar fluxes after every lane
     // has read the staged traces, in place of them, and u^n, the state and the mortar
     // increments are read where they are used: 128 registers instead of 148,
-    // four waves per SIMD.  The FP64 N = 3 variant runs on the small meshes, where a block's chain counts
-    // more than waves: it forms those fluxes beside the low-order pairs and holds
-    // them over the barrier.  Five steps of the 14,871-leaf N = 4 blast took 402 us late and
-    // 414 early, of the mixed shear layer 659 and 670; but of the 22,156-leaf N = 3 blast
-    // 353 late and 346 early.
+    // four waves per SIMD.  Early, they are formed beside the low-order pairs and held
+    // over the barrier, at three: a shorter chain, which counts where a mesh does not fill
+    // those waves.  At N = 4 the 14,871-leaf blast took 414 us early and 402 late, five
+    // steps.  At N = 3 the line lies at some 40,000 leaves, but a variant is early or
+    // late for all sizes, FP64 early and mixed late.  FP64, early and late: 304
+    // leaves 219 and 222, 22,156 352 and 353, 44,788 556 and 554, 50,160 585 and 564, 59,392
+    // 664 and 650; mixed: 304 220 and 224, 22,156 341 and 347, 59,392 662 and 647.
     constexpr bool LATE = MORT && (N == 4 || MIXED);
 
     // per node: rho, v1, v2, p, c, E, z = rho / p (mixed: FP32 pairs in rows 5-7)

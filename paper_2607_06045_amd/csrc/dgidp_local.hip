@@ -12,9 +12,9 @@
 // are above zero at shocks only, a top-hat blast in gas of constant density by up to 4e-5
 // and a pressure jump beside a shear by 8e-8, though blasts, quadrants and the jet only by
 // 1e-13; the FP32 fluxes' rounding by 1e-7 in the jet.  The faster forms were left out for
-// that: on the 22,156-leaf blast, five steps, 715 against 942 us with bar states and
-// 812 against 1,065 with the low-order solution; three of the blended 22,732-leaf jet
-// 570 against 680.
+// that.  Timed in turn: five steps of the 22,156-leaf blast 715 us with them and 940 here
+// with bar states, 812 and 1,350 with the low-order solution (1,222 since, see MODE_LOWSOL);
+// three of the blended 22,732-leaf jet 570 and 680.
 //
 // k_stage is as described in dgidp_kernels.hip, with these differences: logarithms of
 // density and rho / p per node, the pair fluxes telescoped through LDS, the library's

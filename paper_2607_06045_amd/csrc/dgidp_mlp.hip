@@ -36,7 +36,7 @@ using namespace mlp;
 
 constexpr int kRow = kNP + 1;   // partial row: gradient, then the loss sum
 constexpr int kGS = 64;         // samples per pass of the gradient kernel
-constexpr int kMaxGradBlocks = 256;  // one per compute unit (119 KB of LDS each)
+constexpr int kMaxGradBlocks = 256;  // one per compute unit (107 of its 160 KB of LDS each)
 
 __global__ __launch_bounds__(256) void k_mlp_round(const float* __restrict__ master,
                                                    uint16_t* __restrict__ wb)
