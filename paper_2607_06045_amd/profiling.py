@@ -174,7 +174,7 @@ def stats(a):
     lines = [f"# {a.title}", f"# command: {a.command}", "",
              f"{'kernel':60s} {'calls':>6s} {'mean_us':>9s} {'min_us':>8s} {'max_us':>8s} {'pct':>6s}"]
     for r in rows:
-        name = r["Name"].split("(")[0][:60]
+        name = r["Name"].replace("(anonymous namespace)::", "").split("(")[0][:60]
         lines.append(f"{name:60s} {int(r['Calls']):6d} {float(r['AverageNs']) / 1e3:9.2f} "
                      f"{float(r['MinNs']) / 1e3:8.2f} {float(r['MaxNs']) / 1e3:8.2f} "
                      f"{float(r['Percentage']):6.2f}")
